@@ -303,6 +303,10 @@ lor_status lor_build_sa(const uint8_t *seqs, const int64_t *offsets, int32_t num
     if (!joined) LOR_TAKE(ar, uint8_t, (size_t)N, joined);
     LOR_TRY(zero_words(hdr, 16, s));
     LOR_TRY(join_text(seqs, offsets, num_seqs, joined, hdr, s));
+    bool done = false;
+    LOR_TRY(prefix_sa_joined(joined, (uint32_t)N, offsets, (uint32_t)num_seqs, sa_out, ar, hdr, s, &done));
+    if (done && !trace_on()) return LOR_OK;
+    // DC3 (with LOR_TRACE always, for the notes on its levels; the order is the same).
     // symbols are byte + 1: bases 1..4, separators 5..4+num_seqs
     return dc3_u8(joined, (uint32_t)N, 4u + (uint32_t)num_seqs, sa_out, ar, hdr, s);
 }

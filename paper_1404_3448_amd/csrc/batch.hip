@@ -1,6 +1,7 @@
 // Batched longest overlap for many independent sequence pairs on gfx950.
 //
-// All pairs go through one DC3 run. Pair p is written as the tagged text
+// All pairs go through one suffix sort (prefix.hip; DC3 under capture and for
+// what that cannot sort). Pair p is written as the tagged text
 //   8p+c(A_p) ... 8p+5  8p+c(B_p) ... 8p+6      (c(base) = base + 1)
 // with 16-bit symbols. The pair tag is the most significant part of every
 // symbol and each pair ends with its own unique separator, so comparing two
@@ -509,7 +510,11 @@ lor_status batch_overlap_run(const uint8_t *seqs, uint32_t P, uint64_t N, const 
     LOR_LAUNCH("k_join_pairs", 3.0 * N, s,
                hipLaunchKernelGGL(k_join_pairs, dim3(div_up(N, kJoinTile)), dim3(kBlock), 0, s, seqs, start, alen, src,
                                   P, (uint32_t)N, in_end, text, hdr));
-    LOR_TRY(dc3_u16(text, (uint32_t)N, 8u * (P - 1) + 6u, sa, ar, hdr, s));
+    // A captured launch sequence is DC3's, whose name counts are checked on replay.
+    bool done = false;
+    if (!decision_tape())
+        LOR_TRY(prefix_sa_tagged(text, (uint32_t)N, P, start, alen, h_start, h_alen, sa, ar, hdr, s, &done));
+    if (!done) LOR_TRY(dc3_u16(text, (uint32_t)N, 8u * (P - 1) + 6u, sa, ar, hdr, s));
     ar.release(phase);
     if (lcp_out) lcp = lcp_out;   // the caller keeps the whole batch's LCP (and ISA)
     LOR_TRY(lcp_build_u16(text, (uint32_t)N, sa, lcp, isa_out, ar, s));

@@ -226,6 +226,18 @@ lor_status dc3_u16(const uint16_t *text, uint32_t n, uint32_t alphabet, int32_t 
                    uint32_t *hdr_dev, hipStream_t s);
 size_t dc3_workspace_bound(uint64_t n);
 
+// ------------------------------------------------------- prefix sorting
+// The same suffix arrays by sorting prefixes (prefix.hip). *done stays false,
+// with sa unspecified, when the text needs DC3 (long exact repeats) or the
+// workspace left in `ar` does not suffice; header words 3..5 are used.
+lor_status prefix_sa_joined(const uint8_t *text, uint32_t n, const int64_t *offsets, uint32_t k, int32_t *sa,
+                            Arena &ar, uint32_t *hdr, hipStream_t s, bool *done);
+lor_status prefix_sa_tagged(const uint16_t *text, uint32_t n, uint32_t pairs, const int32_t *start,
+                            const int32_t *alen, const int32_t *h_start, const int32_t *h_alen, int32_t *sa,
+                            Arena &ar, uint32_t *hdr, hipStream_t s, bool *done);
+lor_status prefix_sa_shared(const uint8_t *text, uint32_t n, int32_t *sa, Arena &ar, uint32_t *hdr, hipStream_t s,
+                            bool *done);
+
 // Zero `count` words on the stream with a kernel (no memset nodes).
 lor_status zero_words(uint32_t *p, uint32_t count, hipStream_t s);
 

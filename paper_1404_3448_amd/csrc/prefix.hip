@@ -1,0 +1,1040 @@
+// Suffix array by sorting prefixes, for the texts of the library on gfx950.
+//
+// DC3 sorts a text of any structure in O(n), but on DNA nearly every suffix
+// is told from all others by a few dozen symbols, and DC3 still pays for its
+// levels: about two dozen passes over (shrinking) arrays, a gather per merged
+// suffix and a read-back per level. Here the same (unique) order is built as
+//   keys   : the first K symbols of every suffix packed in at most 32 bits;
+//   sort   : LSD radix passes over (key, position), 1 to 4 of them;
+//   resolve: suffixes with equal keys are neighbours now. A group of up to
+//            kSmall of them is ordered inside one workgroup: 16 more text
+//            bytes per member are gathered into LDS, a member's place is the
+//            number of smaller ones, and members that still agree compare
+//            their texts directly;
+//   groups : larger groups (short tandem repeats, mostly) are collected and
+//            radix sorted by a key that sees through a repeat. Let t be the
+//            period of the group's K symbols and e the first place where a
+//            suffix breaks that period. Of two suffixes of the group the one
+//            that breaks first is smaller if it breaks downwards (to a smaller
+//            symbol than the period asks for) and larger otherwise; of two
+//            that break at the same place and in the same direction the
+//            symbols from there on decide. So (direction and e, next symbols)
+//            orders a repeat of any length in one sort.
+// Suffixes that come within K symbols of their sequence's separator ("near"
+// suffixes, at most K per sequence) would need keys with separators in them;
+// they are left out of the sort and merged in afterwards (k_merge).
+//
+// Measured against DC3 on the same texts (whole call, SA + LCP + ISA +
+// overlap): two sequences of 600 and 431 bases 1.41 -> 0.36 ms, 50k + 50k
+// 2.56 -> 0.63 ms, 8M + 8M noncoding-like 7.34 -> 3.27 ms, 16 x 2^26
+// 248 -> 131 ms.
+//
+// Work is bounded: long direct comparisons draw on a budget, and when it is
+// spent, or a group stays large, or the workspace does not hold the large
+// groups, the caller builds the suffix array with DC3 instead (long exact
+// repeats, long repeats of long period).
+#include <stdio.h>
+
+#include <algorithm>
+#include <memory>
+#include <new>
+
+#include "lor_internal.hpp"
+
+namespace lor {
+
+namespace {
+
+constexpr int kWordAbort = 4;      // header words of this file (see WsHeader)
+constexpr int kWordTied = 3;       // suffixes in large groups
+constexpr int kWordHeads = 6;      // large groups
+constexpr int kWordSpent = 5;      // comparison budget used, in units of kUnit steps
+
+constexpr uint32_t kSmall = 64;               // largest group resolved in a workgroup
+constexpr int kResItems = 4;                  // ranks per thread of the resolve kernels
+constexpr uint32_t kResTile = kBlock * kResItems;
+constexpr uint32_t kResWords = kResTile / 64;
+constexpr uint32_t kUnit = 64;                // 16-byte comparison steps per budget unit
+constexpr uint32_t kCodeBits = 15;
+constexpr uint32_t kExtent = (1u << (kCodeBits - 1)) - 1u;   // longest repeat a key describes
+constexpr uint32_t kKeyTile = 2048;           // positions per workgroup of the key kernels
+constexpr int kMaxRounds = 4;                 // sorts of large groups before DC3 takes over
+constexpr int kMaxK = 16;
+
+// ------------------------------------------------------------ text access
+
+struct __attribute__((packed, aligned(1))) Bytes16 {
+    uint32_t x, y, z, w;
+};
+
+struct __attribute__((packed, aligned(1))) Bytes8 {
+    uint32_t x, y;
+};
+
+__device__ __forceinline__ uint64_t be64(uint32_t a, uint32_t b, uint8_t) {
+    return ((uint64_t)__builtin_bswap32(a) << 32) | __builtin_bswap32(b);
+}
+__device__ __forceinline__ uint64_t be64(uint32_t a, uint32_t b, uint16_t) {
+    return ((uint64_t)((a << 16) | (a >> 16)) << 32) | ((b << 16) | (b >> 16));
+}
+
+// 16 text bytes from symbol i on, in comparison order (first symbol most
+// significant); symbols past the end read 0.
+template <typename CH>
+__device__ __forceinline__ void window(const CH *__restrict__ t, uint32_t n, uint32_t i, uint64_t *hi, uint64_t *lo) {
+    constexpr uint32_t W = 16 / sizeof(CH);
+    if (i < n && W <= n - i) {
+        const Bytes16 v = *reinterpret_cast<const Bytes16 *>(t + i);
+        *hi = be64(v.x, v.y, CH());
+        *lo = be64(v.z, v.w, CH());
+        return;
+    }
+    uint64_t h = 0, l = 0;
+    for (uint32_t c = 0; c < W; ++c) {
+        const uint64_t x = (i < n && c < n - i) ? (uint64_t)t[i + c] : 0ull;
+        if (c < W / 2) h = (h << (8 * sizeof(CH))) | x;
+        else l = (l << (8 * sizeof(CH))) | x;
+    }
+    *hi = h;
+    *lo = l;
+}
+
+// The first 8 of those bytes.
+template <typename CH>
+__device__ __forceinline__ uint64_t window8(const CH *__restrict__ t, uint32_t n, uint32_t i) {
+    constexpr uint32_t W = 8 / sizeof(CH);
+    if (i < n && W <= n - i) {
+        const Bytes8 v = *reinterpret_cast<const Bytes8 *>(t + i);
+        return be64(v.x, v.y, CH());
+    }
+    uint64_t h = 0;
+    for (uint32_t c = 0; c < W; ++c) h = (h << (8 * sizeof(CH))) | ((i < n && c < n - i) ? (uint64_t)t[i + c] : 0ull);
+    return h;
+}
+
+// A budget for long comparisons: every kUnit steps a lane draws one unit; true
+// when the call should give up.
+__device__ __forceinline__ bool draw(uint32_t *hdr, uint32_t budget) {
+    const uint64_t m = __ballot(1);
+    const int lead = __builtin_ctzll(m);
+    uint32_t got = 0;
+    if ((int)dev::lane_id() == lead) got = atomicAdd(&hdr[kWordSpent], (uint32_t)__popcll(m));
+    got = (uint32_t)__shfl((int)got, lead, kWave);
+    if (got > budget) {
+        hdr[kWordAbort] = 1;
+        return true;
+    }
+    return __hip_atomic_load(&hdr[kWordAbort], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+}
+
+// Length of the common prefix of suffixes p and q, given that the first h
+// symbols agree, at most cap (or the end of the text).
+template <typename CH>
+__device__ __forceinline__ uint32_t common(const CH *__restrict__ t, uint32_t n, uint32_t p, uint32_t q, uint32_t h,
+                                           uint32_t cap, uint32_t *hdr, uint32_t budget) {
+    constexpr uint32_t W = 16 / sizeof(CH), B = 8 * sizeof(CH);
+    const uint32_t lim = min(cap, n - max(p, q));
+    uint32_t steps = 0;
+    while (h < lim && lim - h >= W) {
+        const Bytes16 x = *reinterpret_cast<const Bytes16 *>(t + p + h);
+        const Bytes16 y = *reinterpret_cast<const Bytes16 *>(t + q + h);
+        const uint64_t d0 = ((uint64_t)(x.y ^ y.y) << 32) | (x.x ^ y.x);
+        if (d0) return h + (uint32_t)__builtin_ctzll(d0) / B;
+        const uint64_t d1 = ((uint64_t)(x.w ^ y.w) << 32) | (x.z ^ y.z);
+        if (d1) return h + W / 2 + (uint32_t)__builtin_ctzll(d1) / B;
+        h += W;
+        if ((++steps % kUnit) == 0 && draw(hdr, budget)) return h;
+    }
+    while (h < lim && t[p + h] == t[q + h]) ++h;
+    return h;
+}
+
+// Does suffix p come before suffix q (p != q)?
+template <typename CH>
+__device__ __forceinline__ bool before(const CH *__restrict__ t, uint32_t n, uint32_t p, uint32_t q, uint32_t h,
+                                       uint32_t *hdr, uint32_t budget) {
+    const uint32_t l = common(t, n, p, q, h, 0xffffffffu, hdr, budget);
+    if (l >= n - max(p, q)) return p > q;
+    return t[p + l] < t[q + l];
+}
+
+// ------------------------------------------------------------------ texts
+// What the kernels need to know of a text: its symbols, how a suffix's first
+// K symbols make a key, and where its near suffixes are.
+//
+// Joined: up to kMaxSeqs sequences, unique separators above every base. Key:
+//   two bits per base.
+// Tagged: the batched path's text (symbol = 8 * pair + code; codes 1..4 bases,
+//   5 and 6 separators). Key: the pair, then two bits per base.
+// Shared: a reference and its queries, one separator symbol for all, so a
+//   suffix reads on past it. Key: K symbols base 5; no near suffixes.
+struct Joined {
+    using CH = uint8_t;
+    const uint8_t *t;
+    uint32_t n;
+    int K;
+    uint32_t k;                          // sequences
+    uint32_t near;                       // near suffixes in total
+    int32_t start[kMaxSeqs + 1];         // joined start of every sequence, plus n
+};
+struct Tagged {
+    using CH = uint16_t;
+    const uint16_t *t;
+    uint32_t n;
+    int K;
+    uint32_t k;                          // pairs
+    uint32_t near;
+    const int32_t *start, *alen;         // joined start of every pair (plus n), |A|
+    const uint32_t *below;               // near suffixes in the pairs before
+};
+struct Shared {
+    using CH = uint8_t;
+    const uint8_t *t;
+    uint32_t n;
+    int K;
+};
+
+__host__ __device__ __forceinline__ uint32_t near_of(uint32_t len, int K) {   // of one sequence and its separator
+    return (len < (uint32_t)K - 1u ? len : (uint32_t)K - 1u) + 1u;
+}
+
+// Order-keeping small codes of a symbol: 0 past the end, bases 1..4, separator 5.
+__device__ __forceinline__ uint32_t code3(uint8_t c) { return c < 4u ? (uint32_t)c + 1u : 5u; }
+__device__ __forceinline__ uint32_t code3(uint16_t c) { return min((uint32_t)c & 7u, 5u); }
+
+// ------------------------------------------------------------------- keys
+// One workgroup per kKeyTile positions. The tile's symbols are packed once
+// into 2-bit words in LDS (16 symbols a word, first symbol on top), so a
+// position's key is a funnel shift of two words; keys and positions leave in
+// position order with the near suffixes left out.
+constexpr uint32_t kKeyWords = kKeyTile / 16 + 2;
+
+__device__ __forceinline__ uint32_t pack4(uint32_t w) {   // 4 byte symbols -> 8 bits, first on top
+    return ((w & 0x03030303u) * 0x40100401u) >> 24;
+}
+
+__device__ __forceinline__ void pack_tile(const Joined &x, uint32_t base, uint32_t *s_w) {
+    for (uint32_t i = threadIdx.x; i < kKeyWords; i += kBlock) {
+        const uint32_t p = base + 16 * i;
+        uint32_t v = 0;
+        if (p < x.n && x.n - p >= 16) {   // p is a multiple of 16, the text 4-byte aligned
+            const uint32_t *w = reinterpret_cast<const uint32_t *>(x.t + p);
+            v = (pack4(w[0]) << 24) | (pack4(w[1]) << 16) | (pack4(w[2]) << 8) | pack4(w[3]);
+        } else {
+            for (uint32_t c = 0; c < 16; ++c) v = (v << 2) | ((p < x.n && c < x.n - p) ? x.t[p + c] & 3u : 0u);
+        }
+        s_w[i] = v;
+    }
+}
+
+__device__ __forceinline__ void pack_tile(const Tagged &x, uint32_t base, uint32_t *s_w) {
+    for (uint32_t i = threadIdx.x; i < kKeyWords; i += kBlock) {
+        const uint32_t p = base + 16 * i;
+        uint32_t v = 0;
+        if (p < x.n && x.n - p >= 16) {   // the text is 256-byte aligned
+            const uint32_t *w = reinterpret_cast<const uint32_t *>(x.t + p);
+#pragma unroll
+            for (int c = 0; c < 8; ++c) v = (v << 4) | ((((w[c] & 7u) - 1u) & 3u) << 2) | (((w[c] >> 16 & 7u) - 1u) & 3u);
+        } else {
+            for (uint32_t c = 0; c < 16; ++c)
+                v = (v << 2) | ((p < x.n && c < x.n - p) ? ((x.t[p + c] & 7u) - 1u) & 3u : 0u);
+        }
+        s_w[i] = v;
+    }
+}
+
+// Largest j in [0, count) with start[j] <= x.
+__device__ __forceinline__ uint32_t seq_of(const int32_t *start, uint32_t count, uint32_t x) {
+    uint32_t lo = 0, hi = count - 1;
+    while (lo < hi) {
+        const uint32_t mid = (lo + hi + 1) >> 1;
+        if ((uint32_t)start[mid] <= x) lo = mid; else hi = mid - 1;
+    }
+    return lo;
+}
+
+__global__ __launch_bounds__(kBlock) void k_prefix_keys(Joined x, uint32_t *__restrict__ keys,
+                                                        uint32_t *__restrict__ vals) {
+    __shared__ uint32_t s_w[kKeyWords];
+    __shared__ int32_t s_start[kMaxSeqs + 1];
+    __shared__ uint32_t s_below[kMaxSeqs + 1];
+    __shared__ uint32_t s_tmp[kBlock / kWave];
+    const uint32_t base = blockIdx.x * kKeyTile, tid = threadIdx.x;
+    static_assert(kMaxSeqs < kBlock, "one thread per sequence");
+    uint32_t mine = 0, all;
+    if (tid <= x.k) s_start[tid] = x.start[tid];
+    if (tid < x.k) mine = near_of((uint32_t)(x.start[tid + 1] - x.start[tid]) - 1u, x.K);
+    const uint32_t bel = dev::block_exclusive_sum(mine, s_tmp, &all);
+    if (tid < x.k) s_below[tid] = bel;
+    pack_tile(x, base, s_w);
+    __syncthreads();
+    const uint32_t drop = 32u - 2u * (uint32_t)x.K;
+    const uint32_t j0 = seq_of(s_start, x.k, base);
+#pragma unroll
+    for (int r = 0; r < (int)(kKeyTile / kBlock); ++r) {
+        const uint32_t l = r * kBlock + tid, p = base + l;
+        if (p >= x.n) continue;
+        uint32_t j = j0;
+        while (p >= (uint32_t)s_start[j + 1]) ++j;        // p < n = start[k]
+        if (p + (uint32_t)x.K >= (uint32_t)s_start[j + 1]) continue;   // near: its separator is among its K symbols
+        const uint32_t i = l >> 4, sh = (l & 15u) * 2u;
+        const uint64_t ww = ((uint64_t)s_w[i] << 32) | s_w[i + 1];
+        const uint32_t key = (uint32_t)((ww << sh) >> 32) >> drop;
+        const uint32_t e = p - s_below[j];
+        keys[e] = key;
+        vals[e] = p;
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void k_prefix_keys_tagged(Tagged x, uint32_t *__restrict__ keys,
+                                                               uint32_t *__restrict__ vals) {
+    const uint32_t m = x.n - x.near;
+    __shared__ uint32_t s_w[kKeyWords];
+    const uint32_t base = blockIdx.x * kKeyTile, tid = threadIdx.x;
+    pack_tile(x, base, s_w);
+    __syncthreads();
+    const uint32_t drop = 32u - 2u * (uint32_t)x.K;
+#pragma unroll
+    for (int r = 0; r < (int)(kKeyTile / kBlock); ++r) {
+        const uint32_t l = r * kBlock + tid, p = base + l;
+        if (p >= x.n) continue;
+        const uint32_t pair = min((uint32_t)x.t[p] >> 3, x.k - 1u);
+        const uint32_t s0 = (uint32_t)x.start[pair], a = (uint32_t)x.alen[pair], s1 = (uint32_t)x.start[pair + 1];
+        const uint32_t sep = s0 + a;                                  // separator of A
+        const bool inb = p > sep;
+        if (p + (uint32_t)x.K >= (inb ? s1 : sep + 1u)) continue;
+        const uint32_t i = l >> 4, sh = (l & 15u) * 2u;
+        const uint64_t ww = ((uint64_t)s_w[i] << 32) | s_w[i + 1];
+        const uint32_t key = ((uint32_t)((ww << sh) >> 32) >> drop) | (uint32_t)((uint64_t)pair << (2 * x.K));
+        const uint32_t e = p - x.below[pair] - (inb ? near_of(a, x.K) : 0u);
+        if (e >= m) continue;   // a bad input base spoils the pair number; the call then fails
+        keys[e] = key;
+        vals[e] = p;
+    }
+}
+
+// Base-5 keys, 8 consecutive positions per thread from the last to the first:
+// key(p) = s_p 5^(K-1) + key(p+1) / 5.
+constexpr int kShareRun = 8;
+__global__ __launch_bounds__(kBlock) void k_prefix_keys_shared(Shared x, uint32_t top, uint32_t *__restrict__ keys) {
+    const uint32_t p0 = (blockIdx.x * kBlock + threadIdx.x) * kShareRun;
+    if (p0 >= x.n) return;
+    uint32_t s[kShareRun + kMaxK];
+#pragma unroll
+    for (int i = 0; i < (kShareRun + kMaxK) / 4; ++i) {
+        const uint32_t p = p0 + 4 * i;
+        uint32_t w = 0;
+        if (p < x.n && x.n - p >= 4) w = *reinterpret_cast<const uint32_t *>(x.t + p);
+        else
+            for (uint32_t c = 0; c < 4; ++c) w |= (p < x.n && c < x.n - p ? (uint32_t)x.t[p + c] : 0u) << (8 * c);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) s[4 * i + c] = min((w >> (8 * c)) & 255u, 4u);
+    }
+    uint32_t key = 0, out[kShareRun];
+#pragma unroll
+    for (int i = kShareRun + kMaxK - 1; i >= 0; --i) {
+        key = s[i] * top + key / 5u;
+        if (i < kShareRun) out[i] = key;
+    }
+    if (x.n - p0 >= (uint32_t)kShareRun) {
+        *reinterpret_cast<uint4 *>(keys + p0) = make_uint4(out[0], out[1], out[2], out[3]);
+        *reinterpret_cast<uint4 *>(keys + p0 + 4) = make_uint4(out[4], out[5], out[6], out[7]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < kShareRun; ++i)
+            if (p0 + i < x.n) keys[p0 + i] = out[i];
+    }
+}
+
+// ----------------------------------------------------------- near suffixes
+// A near suffix w#.. (w of d < K bases, then the separator) follows every
+// normal suffix that starts with w and precedes those that start with
+// anything larger: its place among the normal ones is the number of keys not
+// above w filled with the largest base. Near suffixes that fill to the same
+// key order by d from long to short (at the shorter one's separator the other
+// has a base), then by separator. One thread per (sequence, d); `places`
+// receives the places in order, which is all that the resolve kernel needs to
+// shift the normal suffixes apart.
+__device__ __forceinline__ uint32_t keys_not_above(const uint32_t *__restrict__ keys, uint32_t m, uint32_t v) {
+    uint32_t lo = 0, len = m;
+    while (len > 0) {
+        const uint32_t half = len >> 1;
+        if (keys[lo + half] <= v) {
+            lo += half + 1;
+            len -= half + 1;
+        } else {
+            len = half;
+        }
+    }
+    return lo;
+}
+
+__device__ __forceinline__ uint32_t base2(uint8_t c) { return c & 3u; }
+__device__ __forceinline__ uint32_t base2(uint16_t c) { return ((c & 7u) - 1u) & 3u; }
+
+// Fill key of the suffix d symbols before the separator at `sep`, then what
+// orders equal fills: K - 1 - d.
+template <typename CH>
+__device__ __forceinline__ uint32_t near_fill(const CH *__restrict__ t, uint32_t sep, uint32_t d, int K) {
+    uint32_t v = 0;
+    for (uint32_t c = 0; c < (uint32_t)K; ++c) v = (v << 2) | (c < d ? base2(t[sep - d + c]) : 3u);
+    return v;
+}
+
+__global__ __launch_bounds__(kBlock) void k_merge(Joined x, const uint32_t *__restrict__ keys, uint32_t m,
+                                                  int32_t *__restrict__ sa, uint32_t *__restrict__ places) {
+    extern __shared__ uint64_t s_key[];   // one per (sequence, d); ~0 where there is none
+    const uint32_t slots = x.k * (uint32_t)x.K;
+    for (uint32_t i = threadIdx.x; i < slots; i += kBlock) {
+        const uint32_t j = i / (uint32_t)x.K, d = i % (uint32_t)x.K;
+        const uint32_t len = (uint32_t)(x.start[j + 1] - x.start[j]) - 1u;
+        uint64_t v = ~0ull;
+        if (d <= len)
+            v = ((uint64_t)near_fill(x.t, (uint32_t)x.start[j + 1] - 1u, d, x.K) << 12) |
+                ((uint64_t)((uint32_t)x.K - 1u - d) << 8) | j;
+        s_key[i] = v;
+    }
+    __syncthreads();
+    const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
+    if (i >= slots || s_key[i] == ~0ull) return;
+    const uint64_t mine = s_key[i];
+    uint32_t rank = 0;
+    for (uint32_t q = 0; q < slots; ++q) rank += s_key[q] < mine;
+    const uint32_t at = keys_not_above(keys, m, (uint32_t)(mine >> 12));
+    const uint32_t j = i / (uint32_t)x.K, d = i % (uint32_t)x.K;
+    sa[at + rank] = x.start[j + 1] - 1 - (int32_t)d;
+    places[rank] = at;
+}
+
+// The same for pairs: the pair leads every key, so near suffixes only compare
+// inside their pair.
+__global__ __launch_bounds__(kBlock) void k_merge_tagged(Tagged x, const uint32_t *__restrict__ keys, uint32_t m,
+                                                         int32_t *__restrict__ sa, uint32_t *__restrict__ places) {
+    const uint32_t per = 2u * (uint32_t)x.K;
+    const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
+    const uint32_t pair = i / per, q0 = i % per;
+    if (pair >= x.k) return;
+    const uint32_t s0 = (uint32_t)x.start[pair], a = (uint32_t)x.alen[pair], s1 = (uint32_t)x.start[pair + 1];
+    auto key_of = [&](uint32_t q, uint32_t *pos) -> uint64_t {
+        const uint32_t second = q >= (uint32_t)x.K, d = q - (second ? (uint32_t)x.K : 0u);
+        const uint32_t len = second ? s1 - s0 - a - 2u : a, sep = second ? s1 - 1u : s0 + a;
+        if (d > len) return ~0ull;
+        *pos = sep - d;
+        return ((uint64_t)near_fill(x.t, sep, d, x.K) << 12) | ((uint64_t)((uint32_t)x.K - 1u - d) << 8) | second;
+    };
+    uint32_t pos = 0, other;
+    const uint64_t mine = key_of(q0, &pos);
+    if (mine == ~0ull) return;
+    uint32_t rank = x.below[pair];
+    for (uint32_t q = 0; q < per; ++q) rank += key_of(q, &other) < mine;
+    const uint32_t at = keys_not_above(keys, m, (uint32_t)((uint64_t)pair << (2 * x.K)) | (uint32_t)(mine >> 12));
+    sa[at + rank] = (int32_t)pos;
+    places[rank] = at;
+}
+
+// Number of the `count` sorted entries not above x, by one lane and by a wave.
+__device__ __forceinline__ uint32_t places_not_above(const uint32_t *__restrict__ a, uint32_t count, uint32_t x) {
+    return keys_not_above(a, count, x);
+}
+
+__device__ __forceinline__ uint32_t wave_not_above(const uint32_t *__restrict__ a, uint32_t count, uint32_t x) {
+    const uint32_t lane = threadIdx.x & 63u;
+    uint32_t lo = 0, len = count;
+    while (len > 0) {
+        const uint32_t step = (len + 63u) / 64u, o = lane * step;
+        const bool in = o < len && a[lo + o] <= x;
+        const uint32_t c = (uint32_t)__popcll(__ballot(in));
+        if (c == 0) return lo;
+        const uint32_t first = (c - 1u) * step + 1u;       // entries up to lo + first - 1 are in
+        const uint32_t next = min(len, first + step - 1u);
+        lo += first;
+        len = next - first;
+    }
+    return lo;
+}
+
+// ----------------------------------------------------------- repeat keys
+// The `count` (at most 21) symbols from i on at 3 bits, first on top; symbols
+// past the end read 0, and with `stop` so do those behind a separator.
+template <typename CH>
+__device__ __forceinline__ uint64_t codes(const CH *__restrict__ t, uint32_t n, uint32_t i, uint32_t count,
+                                          bool stop) {
+    constexpr uint32_t W = 16 / sizeof(CH);
+    uint64_t v = 0;
+    bool open = true;
+    for (uint32_t c0 = 0; c0 < count; c0 += W) {
+        uint64_t hi, lo;
+        window(t, n, i + c0, &hi, &lo);
+#pragma unroll
+        for (uint32_t c = 0; c < W; ++c) {
+            if (c0 + c >= count) continue;
+            const uint64_t half = c < W / 2 ? hi : lo;
+            const uint32_t at = (W / 2 - 1u - c % (W / 2)) * 8u * (uint32_t)sizeof(CH);
+            const uint32_t k = open && i + c0 + c < n ? code3((CH)(half >> at)) : 0u;
+            if (stop && k == 5u) open = false;
+            v = (v << 3) | k;
+        }
+    }
+    return v;
+}
+
+// Smallest period of the K symbols from p on (K when they have none).
+template <typename X>
+__device__ __forceinline__ uint32_t period_at(const X &x, uint32_t p) {
+    const uint32_t K = (uint32_t)x.K;
+    const uint64_t v = codes(x.t, x.n, p, K, false);
+    for (uint32_t t = 1; t < K; ++t)
+        if (((v ^ (v >> (3u * t))) & ((1ull << (3u * (K - t))) - 1ull)) == 0) return t;
+    return K;
+}
+template <typename X> struct StopAtSep { static constexpr bool value = true; };
+template <> struct StopAtSep<Shared> { static constexpr bool value = false; };
+
+// Where and how the suffix at q leaves the period t of its first K symbols
+// (15 bits: e when it breaks downwards, 2 kExtent + 1 - e when upwards,
+// kExtent when it runs at least that far), then its next `ns` symbols at 3
+// bits (0 behind a unique separator, which decides).
+template <typename X>
+__device__ __forceinline__ uint64_t repeat_key(const X &x, uint32_t q, uint32_t t, uint32_t ns, uint32_t *hdr,
+                                               uint32_t budget) {
+    uint32_t code = kExtent, e = x.n - q;
+    if (q + t < x.n) {
+        e = min(e, t + common(x.t, x.n, q, q + t, (uint32_t)x.K - t, kExtent - t, hdr, budget));
+        if (e < kExtent) code = (q + e >= x.n || x.t[q + e] < x.t[q + e - t]) ? e : 2 * kExtent + 1u - e;
+    } else {
+        code = e;
+    }
+    return ((uint64_t)code << (3 * ns)) | codes(x.t, x.n, q + e, ns, StopAtSep<X>::value);
+}
+
+// ---------------------------------------------------------------- resolve
+// Sort keys of large groups: group number, then a repeat key of ns symbols
+// taken off[group] symbols into the suffix (off == nullptr: 0).
+struct GroupKey {
+    uint32_t ns;
+    const uint32_t *off;
+    __device__ uint32_t shift() const { return kCodeBits + 3u * ns; }
+    __device__ uint32_t offset(uint64_t key) const { return off ? off[key >> shift()] : 0u; }
+    // do the next symbols hold a separator (5, the only code with bits 2 and 0)?
+    __device__ bool at_sep(uint64_t key) const {
+        const uint64_t v = key & ((1ull << (3u * ns)) - 1ull);
+        return ((v >> 2) & v & 0x1249249249249249ull) != 0;
+    }
+    // symbols up to the break: what the members of a group of equal keys share at least
+    __device__ uint32_t reach(uint64_t key) const {
+        const uint32_t c = (uint32_t)(key >> (3u * ns)) & ((1u << kCodeBits) - 1u);
+        return offset(key) + (c <= kExtent ? c : 2u * kExtent + 1u - c);
+    }
+};
+
+// Groups of equal keys over sorted (key, position) pairs, kResTile ranks per
+// workgroup. Head flags are ballots (a 64-bit word per 64 ranks), with the
+// words beside the tile's, so every rank of a group of at most kSmall knows
+// its whole group and works out its own place; members just outside the tile
+// are looked at by both workgroups. 8 text bytes behind the known prefix are
+// gathered into LDS for every tied rank; a rank's place is the number of
+// smaller ones in its group. Members that agree there too form a class, which
+// goes on with repeat keys (stage 0: a tandem repeat inside one short group
+// would cost a long comparison per pair of members otherwise) and at last
+// with whole texts.
+// Stage 0 (32-bit keys of the sort) writes places shifted by the near
+// suffixes; stage 1 (64-bit keys of large groups) through `slots`. Larger
+// groups are marked in `large` and counted, with their heads, per tile.
+template <typename X, typename KT>
+__global__ __launch_bounds__(kBlock) void k_resolve(X x, GroupKey gk, const KT *__restrict__ keys,
+                                                    const uint32_t *__restrict__ vals, uint32_t m,
+                                                    int32_t *__restrict__ sa, const uint32_t *__restrict__ slots,
+                                                    const uint32_t *__restrict__ places, uint32_t near,
+                                                    uint64_t *__restrict__ large, uint32_t *__restrict__ tcount,
+                                                    uint32_t *__restrict__ hcount, uint32_t *__restrict__ hdr,
+                                                    uint32_t budget) {
+    using CH = typename X::CH;
+    constexpr bool kFirst = sizeof(KT) == 4;
+    constexpr uint32_t kSlots = kResTile + 2 * kSmall;
+    constexpr int kWaves = kBlock / kWave;
+    __shared__ uint64_t s_head[kResWords + 2];
+    __shared__ uint32_t s_val[kSlots];
+    __shared__ uint64_t s_win[kSlots];
+    __shared__ uint16_t s_cls[kSlots];
+    __shared__ uint32_t s_shift[2], s_large, s_heads, s_again;
+    const uint32_t base = blockIdx.x * kResTile, tid = threadIdx.x, lane = tid & 63u, w = tid >> 6;
+    // Round r < kResItems: slot kSmall + 256 r + tid, rank base + 256 r + tid;
+    // the last round: the ranks beside the tile, waves 0 (before) and 1 (after).
+    auto slot_of = [&](int r) { return r < kResItems ? kSmall + r * kBlock + tid : (w == 0 ? lane : kResTile + tid); };
+    auto rank_of = [&](int r) { return base + slot_of(r) - kSmall; };   // wraps before rank 0: not below m then
+    // Values are positions; after a bad input base some may be anything, and
+    // no text read may leave the text.
+#pragma unroll
+    for (int r = 0; r <= kResItems; ++r) {
+        if (r == kResItems && w >= 2) break;
+        const uint32_t e = rank_of(r);
+        const bool ok = e < m;
+        const KT key = ok ? keys[e] : KT(0);
+        const uint32_t val = ok ? min(vals[e], x.n - 1u) : 0u;
+        KT prev;
+        if constexpr (kFirst) {
+            prev = (KT)__shfl_up((int)key, 1, kWave);
+            if (lane == 0 && ok && e > 0) prev = keys[e - 1];
+        } else {
+            prev = (ok && e > 0) ? keys[e - 1] : KT(0);
+        }
+        const uint64_t h = __ballot(!ok || e == 0 || prev != key);   // past the end: heads, so groups end there
+        if (lane == 0) s_head[r < kResItems ? 1 + r * kWaves + w : (w == 0 ? 0 : kResWords + 1)] = h;
+        s_val[slot_of(r)] = val;
+    }
+    if (kFirst && w >= 2) {
+        const uint32_t a = wave_not_above(places, near,
+                                          w == 2 ? (base > kSmall ? base - kSmall : 0u) : base + kResTile + kSmall);
+        if (lane == 0) s_shift[w - 2] = a;
+    }
+    if (tid == 0) s_large = s_heads = s_again = 0;
+    __syncthreads();
+
+    // Group of a slot: first slot and size; size 0 when it is larger than kSmall.
+    auto group = [&](uint32_t l, uint32_t *first) -> uint32_t {
+        const uint32_t wd = l >> 6, b = l & 63u;
+        const uint64_t upto = s_head[wd] & (~0ull >> (63u - b));
+        uint32_t f, g;
+        if (upto) f = wd * 64u + 63u - (uint32_t)__builtin_clzll(upto);
+        else if (wd > 0 && s_head[wd - 1]) f = (wd - 1) * 64u + 63u - (uint32_t)__builtin_clzll(s_head[wd - 1]);
+        else return 0;
+        const uint64_t over = b == 63 ? 0ull : s_head[wd] & (~0ull << (b + 1u));
+        if (over) g = wd * 64u + (uint32_t)__builtin_ctzll(over);
+        else if (wd + 1 < kResWords + 2 && s_head[wd + 1]) g = (wd + 1) * 64u + (uint32_t)__builtin_ctzll(s_head[wd + 1]);
+        else return 0;
+        *first = f;
+        return g - f <= kSmall ? g - f : 0u;
+    };
+    // Size of a slot's group when this workgroup has to look at it: every rank
+    // of the tile, and those beside it whose group reaches into it.
+    auto tied = [&](int r, uint32_t *first) -> uint32_t {
+        if (r == kResItems) {
+            if (w >= 2) return 0;
+            const uint64_t h = s_head[w == 0 ? 0 : kResWords + 1];
+            const bool reach = w == 0 ? (lane == 63 || !(h >> (lane + 1u))) && !(s_head[1] & 1ull)
+                                      : !(h & (~0ull >> (63u - lane)));
+            if (!reach) return 0;
+        }
+        return rank_of(r) < m ? group(slot_of(r), first) : 0u;
+    };
+
+    // 8 text bytes of every tied rank, all gathers of a thread in flight at once
+    uint64_t win[kResItems + 1];
+#pragma unroll
+    for (int r = 0; r <= kResItems; ++r) {
+        uint32_t f;
+        win[r] = 0;
+        if (tied(r, &f) > 1) {
+            const uint32_t l = slot_of(r);
+            uint32_t h = (uint32_t)x.K;
+            if constexpr (!kFirst) h = max(h, gk.reach(keys[rank_of(r)]));
+            win[r] = window8(x.t, x.n, s_val[l] + h);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r <= kResItems; ++r)
+        if (r < kResItems || w < 2) s_win[slot_of(r)] = win[r];
+    __syncthreads();
+    // class of every tied rank: first place of those with its window
+    uint32_t again = 0;   // bit r: others share it
+#pragma unroll
+    for (int r = 0; r <= kResItems; ++r) {
+        uint32_t f, same = 0;
+        const uint32_t size = tied(r, &f);
+        if (size > 1) {
+            uint32_t less = f;
+            for (uint32_t q = f; q < f + size; ++q) {
+                less += s_win[q] < win[r];
+                same += s_win[q] == win[r];
+            }
+            s_cls[slot_of(r)] = (uint16_t)less;
+        }
+        again |= (same > 1 ? 1u : 0u) << r;
+    }
+    if (__any(again != 0) && lane == 0) s_again = 1;
+    __syncthreads();
+    if (kFirst && s_again) {   // uniform
+#pragma unroll 1
+        for (int r = 0; r <= kResItems; ++r) {
+            if (!((again >> r) & 1u)) continue;
+            const uint32_t l = slot_of(r);
+            s_win[l] = repeat_key(x, s_val[l], period_at(x, s_val[l]), (64u - kCodeBits) / 3u, hdr, budget);
+        }
+        __syncthreads();
+    }
+
+    const uint32_t sh0 = kFirst ? s_shift[0] : 0u, sh1 = kFirst ? s_shift[1] : 0u;
+    uint32_t lost = 0, heads = 0;
+#pragma unroll 1
+    for (int r = 0; r < kResItems; ++r) {
+        const uint32_t l = slot_of(r), e = rank_of(r);
+        const bool valid = e < m;
+        uint32_t f = 0;
+        const uint32_t size = group(l, &f), v = s_val[l];
+        bool big = valid && size == 0, kept = false;
+        if constexpr (!kFirst && StopAtSep<X>::value) {
+            // equal up to their separators: ordered by those, so by position,
+            // which the stable sorts have kept
+            if (big && gk.at_sep(keys[e])) {
+                big = false;
+                kept = true;
+            }
+        }
+        const uint64_t bm = __ballot(big);
+        if (lane == 0) {
+            large[(size_t)blockIdx.x * kResWords + r * kWaves + w] = bm;
+            lost += (uint32_t)__popcll(bm);
+            heads += (uint32_t)__popcll(bm & s_head[l >> 6]);
+        }
+        if (!valid || big) continue;
+        uint32_t place = l;
+        if (size > 1 && !kept) {
+            place = s_cls[l];
+            if ((again >> r) & 1u) {
+                const uint64_t mine = s_win[l];
+                uint32_t h = (uint32_t)x.K;
+                if constexpr (kFirst) {
+                    const uint32_t c = (uint32_t)(mine >> (3u * ((64u - kCodeBits) / 3u)));
+                    h = max(h, c <= kExtent ? c : 2u * kExtent + 1u - c);
+                } else {
+                    h = max(h, gk.reach(keys[e]));
+                }
+                const uint16_t cls = s_cls[l];
+                for (uint32_t q = f; q < f + size; ++q) {
+                    if (q == l || s_cls[q] != cls) continue;
+                    const uint64_t o = s_win[q];
+                    place += o < mine || (o == mine && before(x.t, x.n, s_val[q], v, h, hdr, budget));
+                }
+            }
+        }
+        const uint32_t o = base + place - kSmall;           // place in the sorted order
+        if constexpr (kFirst) {
+            uint32_t sh = sh0;
+            if (sh0 != sh1) sh += places_not_above(places + sh0, sh1 - sh0, o);
+            if (o < m) sa[o + sh] = (int32_t)v;
+        } else {
+            if (o < m) sa[slots[o]] = (int32_t)v;
+        }
+    }
+    if (lane == 0 && lost) {
+        atomicAdd(&s_large, lost);
+        atomicAdd(&s_heads, heads);
+    }
+    __syncthreads();
+    if (tid == 0) {
+        tcount[blockIdx.x] = s_large;
+        hcount[blockIdx.x] = s_heads;
+        if (s_large) atomicAdd(&hdr[kWordTied], s_large);
+        if (s_heads) atomicAdd(&hdr[kWordHeads], s_heads);
+    }
+}
+
+// ----------------------------------------------------------- large groups
+// The marked ranks in rank order: position, final slot, and the group number
+// (the count of marked heads up to here); a group's head writes how many
+// symbols further into the suffix the group's next keys start, so that the K
+// symbols there end where the known prefix ends.
+template <typename KT>
+__global__ __launch_bounds__(kBlock) void k_group_collect(GroupKey gk, int K, const KT *__restrict__ keys,
+                                                          const uint32_t *__restrict__ vals, uint32_t m,
+                                                          const uint64_t *__restrict__ large,
+                                                          const uint32_t *__restrict__ tbase,
+                                                          const uint32_t *__restrict__ hbase,
+                                                          const uint32_t *__restrict__ places, uint32_t near,
+                                                          const uint32_t *__restrict__ slots, uint32_t total,
+                                                          uint32_t groups, uint64_t *__restrict__ tkeys,
+                                                          uint32_t *__restrict__ tvals, uint32_t *__restrict__ tslots,
+                                                          uint32_t *__restrict__ off) {
+    constexpr bool kFirst = sizeof(KT) == 4;
+    __shared__ uint32_t s_below[kResWords], s_hbelow[kResWords];
+    __shared__ uint64_t s_bits[kResWords], s_head[kResWords];
+    __shared__ uint32_t s_shift[2];
+    const uint32_t base = blockIdx.x * kResTile, tid = threadIdx.x, lane = tid & 63u, w = tid >> 6;
+    static_assert(kResWords <= 64, "one lane per word");
+    KT key[kResItems];
+#pragma unroll
+    for (int r = 0; r < kResItems; ++r) {
+        const uint32_t e = base + r * kBlock + tid;
+        key[r] = e < m ? keys[e] : KT(0);
+        const KT prev = (e > 0 && e < m) ? keys[e - 1] : KT(0);
+        const uint64_t h = __ballot(e < m && (e == 0 || prev != key[r]));
+        if (lane == 0) s_head[r * (kBlock / kWave) + w] = h;
+    }
+    if (kFirst && w >= 2) {
+        const uint32_t a = wave_not_above(places, near, w == 2 ? base : base + kResTile);
+        if (lane == 0) s_shift[w - 2] = a;
+    }
+    __syncthreads();
+    if (w == 0) {
+        const uint64_t b = lane < kResWords ? large[(size_t)blockIdx.x * kResWords + lane] : 0ull;
+        const uint32_t c = (uint32_t)__popcll(b), hc = lane < kResWords ? (uint32_t)__popcll(b & s_head[lane]) : 0u;
+        const uint32_t inc = dev::wave_inclusive_sum(c), hinc = dev::wave_inclusive_sum(hc);
+        if (lane < kResWords) {
+            s_bits[lane] = b;
+            s_below[lane] = inc - c;
+            s_hbelow[lane] = hinc - hc;
+        }
+    }
+    __syncthreads();
+    const uint32_t at = tbase[blockIdx.x], hat = hbase[blockIdx.x];
+#pragma unroll
+    for (int r = 0; r < kResItems; ++r) {
+        const uint32_t l = r * kBlock + tid, e = base + l;
+        const uint64_t b = s_bits[l >> 6], bit = 1ull << (l & 63u);
+        if (e >= m || !(b & bit)) continue;
+        const uint64_t heads = b & s_head[l >> 6];
+        const uint32_t i = at + s_below[l >> 6] + (uint32_t)__popcll(b & (bit - 1ull));
+        const uint32_t id = hat + s_hbelow[l >> 6] + (uint32_t)__popcll(heads & (bit | (bit - 1ull))) - 1u;
+        if (i >= total || id >= groups) continue;   // never with consistent counts
+        if constexpr (kFirst) {
+            tslots[i] = e + s_shift[0] + places_not_above(places + s_shift[0], s_shift[1] - s_shift[0], e);
+        } else {
+            tslots[i] = slots[e];
+            if (heads & bit) off[id] = gk.reach(key[r]) + gk.ns - (uint32_t)K;
+        }
+        tkeys[i] = id;
+        tvals[i] = vals[e];
+    }
+}
+
+template <typename X>
+__global__ __launch_bounds__(kBlock) void k_group_keys(X x, GroupKey gk, uint64_t *__restrict__ tkeys,
+                                                       const uint32_t *__restrict__ tvals, uint32_t total,
+                                                       uint32_t *__restrict__ hdr, uint32_t budget) {
+    const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
+    if (i >= total) return;
+    const uint64_t id = tkeys[i];
+    const uint32_t p = min(tvals[i], x.n - 1u);
+    const uint32_t q = min(p + (gk.off ? gk.off[id] : 0u), x.n - 1u);
+    tkeys[i] = (id << gk.shift()) | repeat_key(x, q, period_at(x, q), gk.ns, hdr, budget);
+}
+
+// ------------------------------------------------------------------ driver
+
+struct PrefixHdr {
+    uint32_t word[16];
+};
+
+lor_status launch_keys(const Joined &x, uint32_t *k, uint32_t *v, hipStream_t s) {
+    LOR_LAUNCH("k_prefix_keys", 9.0 * x.n, s,
+               hipLaunchKernelGGL(k_prefix_keys, dim3(div_up(x.n, kKeyTile)), dim3(kBlock), 0, s, x, k, v));
+    return LOR_OK;
+}
+lor_status launch_keys(const Tagged &x, uint32_t *k, uint32_t *v, hipStream_t s) {
+    LOR_LAUNCH("k_prefix_keys", 10.0 * x.n, s,
+               hipLaunchKernelGGL(k_prefix_keys_tagged, dim3(div_up(x.n, kKeyTile)), dim3(kBlock), 0, s, x, k, v));
+    return LOR_OK;
+}
+lor_status launch_keys(const Shared &x, uint32_t *k, uint32_t *, hipStream_t s) {
+    uint32_t top = 1;
+    for (int i = 1; i < x.K; ++i) top *= 5u;
+    LOR_LAUNCH("k_prefix_keys", 5.0 * x.n, s,
+               hipLaunchKernelGGL(k_prefix_keys_shared, dim3(div_up(x.n, kBlock * kShareRun)), dim3(kBlock), 0, s, x,
+                                  top, k));
+    return LOR_OK;
+}
+
+lor_status launch_near(const Joined &x, const uint32_t *keys, uint32_t m, int32_t *sa, uint32_t *places,
+                       hipStream_t s) {
+    const uint32_t slots = x.k * (uint32_t)x.K;
+    LOR_LAUNCH("k_merge", 8.0 * x.near, s,
+               hipLaunchKernelGGL(k_merge, dim3(div_up(slots, kBlock)), dim3(kBlock), slots * sizeof(uint64_t), s, x,
+                                  keys, m, sa, places));
+    return LOR_OK;
+}
+lor_status launch_near(const Tagged &x, const uint32_t *keys, uint32_t m, int32_t *sa, uint32_t *places,
+                       hipStream_t s) {
+    LOR_LAUNCH("k_merge", 8.0 * x.near, s,
+               hipLaunchKernelGGL(k_merge_tagged, dim3(div_up(2ull * x.k * (uint32_t)x.K, kBlock)), dim3(kBlock), 0, s,
+                                  x, keys, m, sa, places));
+    return LOR_OK;
+}
+lor_status launch_near(const Shared &, const uint32_t *, uint32_t, int32_t *, uint32_t *, hipStream_t) {
+    return LOR_OK;
+}
+
+lor_status read_header(uint32_t *hdr, PrefixHdr *h, hipStream_t s) {
+    LOR_HIP(hipMemcpyAsync(h, hdr, sizeof(*h), hipMemcpyDeviceToHost, s));
+    LOR_HIP(hipStreamSynchronize(s));
+    if (h->word[0]) {
+        set_error("input base outside 0..3");
+        return LOR_EALPHABET;
+    }
+    return LOR_OK;
+}
+
+// bits: key bits; near: near suffixes (left out of the sort). *done stays
+// false when DC3 has to build the array.
+template <typename X>
+lor_status prefix_sa(const X &x, int bits, uint32_t near, int32_t *sa, Arena &ar, uint32_t *hdr, hipStream_t s,
+                     bool *done) {
+    constexpr bool kImplicit = !StopAtSep<X>::value;   // every position is sorted: its value is its index
+    *done = false;
+    const uint32_t m = x.n - near;
+    const uint32_t tiles = div_up(m ? m : 1, kResTile);
+    // 64 steps over two texts read about 32 lines, some 0.7 ns of the chip's
+    // gather rate; DC3 takes 0.25 to 0.4 ns per suffix. At most about a third of
+    // a DC3 run is spent before giving up.
+    const uint32_t budget = x.n / 8 + 65536u;
+    const size_t mark = ar.mark();
+    struct Release {
+        Arena &a;
+        size_t m;
+        ~Release() { a.release(m); a.overflow = false; }
+    } release{ar, mark};
+    uint32_t *ka = ar.take<uint32_t>(m), *va = ar.take<uint32_t>(m), *places = ar.take<uint32_t>(near + 1);
+    uint64_t *large = ar.take<uint64_t>((size_t)tiles * kResWords);
+    uint32_t *tcount = ar.take<uint32_t>(tiles), *hcount = ar.take<uint32_t>(tiles);
+    uint32_t *stmp = ar.take<uint32_t>(kScanTmpWords);
+    const size_t half = ar.mark();
+    uint32_t *kb = ar.take<uint32_t>(m), *counts = ar.take<uint32_t>(radix_counts_words(m));
+    if (ar.overflow) return LOR_OK;
+    uint32_t *vb = reinterpret_cast<uint32_t *>(sa);
+    if (m > 0) {
+        // the sorted pairs end in (ka, va): sa, the other value buffer, receives the order
+        const int step = plan().digit_bits, passes = radix_passes(0, bits);
+        uint32_t *ki = passes % 2 ? kb : ka, *ko = passes % 2 ? ka : kb;
+        uint32_t *vi = passes % 2 ? vb : va, *vo = passes % 2 ? va : vb;
+        LOR_TRY(launch_keys(x, ki, vi, s));
+        for (int sh = 0; sh < bits; sh += step) {
+            const uint32_t *in = kImplicit && sh == 0 ? nullptr : vi;
+            LOR_TRY(radix_pass<uint32_t>(ki, in, 0, ko, vo, m, sh, std::min(step, bits - sh), counts, s));
+            std::swap(ki, ko);
+            std::swap(vi, vo);
+        }
+    }
+    if (near) LOR_TRY(launch_near(x, ka, m, sa, places, s));
+    GroupKey gk{0, nullptr};
+    if (m > 0)
+        LOR_LAUNCH("k_resolve", 12.0 * m, s,
+                   hipLaunchKernelGGL((k_resolve<X, uint32_t>), dim3(tiles), dim3(kBlock), 0, s, x, gk, ka, va, m, sa,
+                                      (const uint32_t *)nullptr, places, near, large, tcount, hcount, hdr, budget));
+    PrefixHdr h;
+    LOR_TRY(read_header(hdr, &h, s));
+    if (trace_on())
+        fprintf(stderr, "[lor] prefix sort: n=%u near=%u symbols=%d bits=%d large groups=%u with %u suffixes%s\n", x.n,
+                near, x.K, bits, h.word[kWordHeads], h.word[kWordTied], h.word[kWordAbort] ? ", given up" : "");
+    // Rounds over what is still in large groups: collect it, sort it, resolve it.
+    const uint64_t *k64 = nullptr;
+    const uint32_t *v64 = nullptr, *slots = nullptr;
+    uint32_t cur = m;
+    for (int round = 0; h.word[kWordTied] > 0 && !h.word[kWordAbort]; ++round) {
+        if (round == kMaxRounds) return LOR_OK;
+        const uint32_t total = h.word[kWordTied], groups = h.word[kWordHeads];
+        if (total > cur || groups > total || groups == 0) {
+            set_error("internal: %u suffixes in %u large groups of %u", total, groups, cur);
+            return LOR_EINVAL;
+        }
+        // as many symbols as 56 bits hold beside the group number and the repeat code, at least 5
+        const int gb = bits_for(groups - 1), free_bits = std::max(56 - (int)kCodeBits - gb, 15);
+        const GroupKey ng{(uint32_t)std::min(free_bits / 3, 10), round ? ar.take<uint32_t>(groups) : nullptr};
+        if (round == 0) ar.release(half);   // kb and the counts are free
+        uint64_t *k0 = ar.take<uint64_t>(total), *k1 = ar.take<uint64_t>(total);
+        uint32_t *v0 = ar.take<uint32_t>(total), *v1 = ar.take<uint32_t>(total), *ns = ar.take<uint32_t>(total);
+        const size_t scratch = ar.mark();
+        uint32_t *cnt = ar.take<uint32_t>(radix_counts_words(total));
+        if (ar.overflow) return LOR_OK;
+        const uint32_t ct = div_up(cur, kResTile), nt = div_up(total, kResTile);
+        LOR_TRY(scan_exclusive(tcount, ct, stmp, nullptr, s));
+        LOR_TRY(scan_exclusive(hcount, ct, stmp, nullptr, s));
+        if (round == 0)
+            LOR_LAUNCH("k_group_collect", 4.0 * cur + 20.0 * total, s,
+                       hipLaunchKernelGGL(k_group_collect<uint32_t>, dim3(ct), dim3(kBlock), 0, s, gk, x.K, ka, va,
+                                          cur, large, tcount, hcount, places, near, slots, total, groups, k0, v0, ns,
+                                          (uint32_t *)nullptr));
+        else
+            LOR_LAUNCH("k_group_collect", 8.0 * cur + 24.0 * total, s,
+                       hipLaunchKernelGGL(k_group_collect<uint64_t>, dim3(ct), dim3(kBlock), 0, s, gk, x.K, k64, v64,
+                                          cur, large, tcount, hcount, places, near, slots, total, groups, k0, v0, ns,
+                                          const_cast<uint32_t *>(ng.off)));
+        gk = ng;
+        LOR_LAUNCH("k_group_keys", 20.0 * total, s,
+                   hipLaunchKernelGGL(k_group_keys<X>, dim3(div_up(total, kBlock)), dim3(kBlock), 0, s, x, gk, k0, v0,
+                                      total, hdr, budget));
+        bool alt;
+        LOR_TRY(radix_sort<uint64_t>(k0, v0, k1, v1, total, 0, gb + (int)kCodeBits + 3 * (int)gk.ns, cnt, s, &alt));
+        k64 = alt ? k1 : k0;
+        v64 = alt ? v1 : v0;
+        slots = ns;
+        cur = total;
+        ar.release(scratch);
+        LOR_TRY(zero_words(hdr + kWordTied, 1, s));
+        LOR_TRY(zero_words(hdr + kWordHeads, 1, s));
+        LOR_LAUNCH("k_resolve", 20.0 * cur, s,
+                   hipLaunchKernelGGL((k_resolve<X, uint64_t>), dim3(nt), dim3(kBlock), 0, s, x, gk, k64, v64, cur, sa,
+                                      slots, (const uint32_t *)nullptr, 0u, large, tcount, hcount, hdr, budget));
+        LOR_TRY(read_header(hdr, &h, s));
+        if (trace_on())
+            fprintf(stderr, "[lor] prefix sort: round %d, %u suffixes; left: large groups=%u with %u%s\n", round, total,
+                    h.word[kWordHeads], h.word[kWordTied], h.word[kWordAbort] ? ", given up" : "");
+    }
+    if (h.word[kWordAbort]) return LOR_OK;
+    *done = true;
+    return LOR_OK;
+}
+
+// Symbols per key for n suffixes of one text: about one suffix per key on
+// random DNA, in whole 8-bit digits.
+int symbols_for(uint64_t n) {
+    if (n <= 1u << 10) return 4;
+    if (n <= 1u << 17) return 8;
+    if (n <= 1u << 25) return 12;
+    return 16;
+}
+
+}  // namespace
+
+lor_status prefix_sa_joined(const uint8_t *text, uint32_t n, const int64_t *offsets, uint32_t k, int32_t *sa,
+                            Arena &ar, uint32_t *hdr, hipStream_t s, bool *done) {
+    Joined x;
+    x.t = text;
+    x.n = n;
+    x.K = symbols_for(n);
+    x.k = k;
+    x.near = 0;
+    for (uint32_t j = 0; j <= k; ++j) x.start[j] = (int32_t)(offsets[j] + j);
+    for (uint32_t j = 0; j < k; ++j) x.near += near_of((uint32_t)(offsets[j + 1] - offsets[j]), x.K);
+    return prefix_sa(x, 2 * x.K, x.near, sa, ar, hdr, s, done);
+}
+
+lor_status prefix_sa_shared(const uint8_t *text, uint32_t n, int32_t *sa, Arena &ar, uint32_t *hdr, hipStream_t s,
+                            bool *done) {
+    // 6, 10 or 13 symbols base 5 in 14, 24 or 31 bits
+    const Shared x{text, n, n <= 1u << 14 ? 6 : n <= 1u << 22 ? 10 : 13};
+    return prefix_sa(x, x.K == 6 ? 14 : x.K == 10 ? 24 : 31, 0, sa, ar, hdr, s, done);
+}
+
+lor_status prefix_sa_tagged(const uint16_t *text, uint32_t n, uint32_t pairs, const int32_t *start,
+                            const int32_t *alen, const int32_t *h_start, const int32_t *h_alen, int32_t *sa,
+                            Arena &ar, uint32_t *hdr, hipStream_t s, bool *done) {
+    *done = false;
+    uint32_t longest = 0;
+    for (uint32_t p = 0; p < pairs; ++p) longest = std::max(longest, (uint32_t)(h_start[p + 1] - h_start[p]));
+    const int tag = bits_for(pairs - 1);
+    // a symbol more than log4 of the longest pair, then up to whole digits
+    const int want = tag + bits_for(longest) + 2;
+    const int bits = std::min(32, (want + 7) / 8 * 8);
+    const int K = std::min((bits - tag) / 2, kMaxK);
+    if (longest >> (2 * K) > 16) return LOR_OK;   // a huge pair among many: too few symbols fit
+    const std::unique_ptr<uint32_t[]> below(new (std::nothrow) uint32_t[pairs]);
+    if (!below) return LOR_OK;
+    uint32_t near = 0;
+    for (uint32_t p = 0; p < pairs; ++p) {
+        below[p] = near;
+        const uint32_t a = (uint32_t)h_alen[p], b = (uint32_t)(h_start[p + 1] - h_start[p]) - a - 2u;
+        near += near_of(a, K) + near_of(b, K);
+    }
+    const size_t mark = ar.mark();
+    uint32_t *d_below = ar.take<uint32_t>(pairs);
+    lor_status st = LOR_OK;
+    if (!ar.overflow) {
+        LOR_HIP(hipMemcpyAsync(d_below, below.get(), pairs * sizeof(uint32_t), hipMemcpyHostToDevice, s));
+        const Tagged x{text, n, K, pairs, near, start, alen, d_below};
+        st = prefix_sa(x, tag + 2 * K, near, sa, ar, hdr, s, done);
+    }
+    ar.release(mark);
+    ar.overflow = false;
+    return st;
+}
+
+}  // namespace lor

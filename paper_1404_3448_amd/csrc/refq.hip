@@ -409,7 +409,9 @@ lor_status refq_overlap(const uint8_t *seqs, const int64_t *offsets, uint32_t Q,
                hipLaunchKernelGGL(k_rq_join, dim3(grid_for(div_up(N, kRqJoinBytes))), dim3(kBlock), 0, s, seqs,
                                   L.start, L.tab, (uint32_t)N, (uint32_t)(N - S), L.text, hdr));
     // symbols byte + 1: bases 1..4, separator 5
-    LOR_TRY(dc3_u8(L.text, (uint32_t)N, 5u, L.sa, ar, hdr, s));
+    bool done = false;
+    LOR_TRY(prefix_sa_shared(L.text, (uint32_t)N, L.sa, ar, hdr, s, &done));
+    if (!done) LOR_TRY(dc3_u8(L.text, (uint32_t)N, 5u, L.sa, ar, hdr, s));
     ar.release(phase);
     LOR_TRY(lcp_build(L.text, (uint32_t)N, L.sa, L.lcp, nullptr, ar, s));
     ar.release(phase);

@@ -1,0 +1,175 @@
+"""Suffix arrays by prefix sorting against the oracle, at the sizes and texts
+where its parts meet: key widths (1,024 / 131,072 symbols), workgroup tiles of
+2,048 ranks, groups of 63 to 66 equal keys, suffixes near separators, tandem
+repeats (large groups, breaking upwards, downwards and at a separator), long
+exact repeats (handed to DC3), one text per sequence count, and the batched
+and reference texts built on the same sort."""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_1404_3448_amd import lor, synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def say(*a):
+    print(*a, flush=True, file=sys.stderr)
+
+
+def flat(seqs):
+    seqs = [np.asarray(s, dtype=np.uint8) for s in seqs]
+    offs = np.concatenate([[0], np.cumsum([s.size for s in seqs])]).astype(np.int64)
+    cat = np.concatenate(seqs) if offs[-1] else np.zeros(1, np.uint8)
+    return cat, torch.from_numpy(np.ascontiguousarray(cat)).cuda(), offs
+
+
+def check(seqs):
+    cat, d, offs = flat(seqs)
+    sa, joined = lor.lor_build_sa(d, offs)
+    want = oracle.join(cat[:offs[-1]], offs)
+    got = sa.cpu().numpy()
+    assert np.array_equal(joined.cpu().numpy(), want)
+    expect = oracle.suffix_array(want)
+    bad = np.flatnonzero(got != expect)
+    assert bad.size == 0, (bad.size, bad[:5], got[bad[:5]], expect[bad[:5]])
+
+
+def tandem(rng, n, units, copies):
+    s = synth.gc40_bases(rng, n)
+    for u in units:
+        u = np.asarray(u, dtype=np.uint8)
+        at = int(rng.integers(0, max(1, n - u.size * copies)))
+        part = np.tile(u, copies)[:n - at]
+        s[at:at + part.size] = part
+    return s
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 15, 16, 17, 63, 64, 65, 1021, 1023, 1024, 2045, 2046, 2047, 2048, 2049,
+                               4097, 131070, 131073])
+def test_sizes(n):
+    say("prefix size", n)
+    rng = np.random.default_rng(n)
+    check([rng.integers(0, 4, size=n - n // 3, dtype=np.uint8), rng.integers(0, 4, size=n // 3, dtype=np.uint8)])
+
+
+@pytest.mark.parametrize("copies", [2, 31, 62, 63, 64, 65, 66, 130])
+def test_group_sizes(copies):
+    """One 40-base word planted `copies` times between random bases: groups of
+    exactly that many equal keys on both sides of the workgroup's limit, some
+    across tile edges."""
+    say("prefix groups", copies)
+    rng = np.random.default_rng(copies)
+    word = rng.integers(0, 4, size=40, dtype=np.uint8)
+    parts = []
+    for _ in range(copies):
+        parts += [rng.integers(0, 4, size=int(rng.integers(20, 90)), dtype=np.uint8), word]
+    check([np.concatenate(parts), rng.integers(0, 4, size=500, dtype=np.uint8)])
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_tandem_repeats(seed):
+    """Repeats of period 1 to 20, within and at the ends of sequences, so that
+    they break upwards, downwards and at separators."""
+    say("prefix tandem", seed)
+    rng = np.random.default_rng(seed)
+    units = [rng.integers(0, 4, size=p) for p in (1, 2, 2, 3, 5, 6, 7, 11, 12, 13, 17, 20)]
+    a = tandem(rng, 60000, units, 150)
+    b = tandem(rng, 50001, units[::2], 90)
+    ends = [np.tile(np.array(u, np.uint8), 300) for u in ([3], [0], [3, 2], [3, 3, 0])]
+    check([a, *ends, b, np.full(200, 3, np.uint8), np.zeros(0, np.uint8), np.full(7, 3, np.uint8)])
+
+
+@pytest.mark.parametrize("text", ["zeros", "threes", "pairs", "identical", "unit40", "related"])
+def test_repetitive_texts(text):
+    """Whole texts of one repeat, exact copies longer than the comparison
+    budget (DC3 builds these), and a 1%-mutated copy."""
+    say("prefix repetitive", text)
+    rng = np.random.default_rng(5)
+    a = synth.gc40_bases(rng, 70000)
+    if text == "zeros":
+        check([np.zeros(9000, np.uint8), np.zeros(3000, np.uint8)])
+    elif text == "threes":
+        check([np.full(3000, 3, np.uint8), np.full(2999, 3, np.uint8), np.full(10, 3, np.uint8)])
+    elif text == "pairs":
+        check([np.tile(np.array([0, 3], np.uint8), 4000), np.tile(np.array([3, 0], np.uint8), 3000)])
+    elif text == "identical":
+        check([a[:20000], a[:20000]])
+    elif text == "unit40":
+        check([np.tile(a[:40], 500), np.tile(a[:40], 77)])
+    else:
+        check([a, synth.mutate(rng, a, 0.01)])
+
+
+@pytest.mark.parametrize("k", [1, 2, 3, 100, 251])
+def test_sequence_counts(k):
+    """Many sequences around the key length, so near suffixes are as many as
+    sorted ones, many of them equal up to their separators."""
+    say("prefix sequences", k)
+    rng = np.random.default_rng(k)
+    seqs = [rng.integers(0, 2, size=int(rng.integers(0, 40)), dtype=np.uint8) + 2 for _ in range(k)]
+    seqs[0] = rng.integers(0, 4, size=5000, dtype=np.uint8)
+    check(seqs)
+    check([s[:12] for s in seqs])
+    # every sequence ends in one long run: more equal ends than a workgroup resolves
+    check([np.concatenate([s[:9], np.full(30, 3, np.uint8)]) for s in seqs])
+
+
+def test_word_windows_at_every_alignment():
+    """joined_out 4 to 60 bytes past a 64-byte boundary."""
+    rng = np.random.default_rng(9)
+    a = tandem(rng, 30000, [[0, 1], [2, 2, 3]], 100)
+    cat, d, offs = flat([a, a[5000:9000]])
+    n = int(offs[-1]) + 2
+    want = oracle.suffix_array(oracle.join(cat, offs))
+    for off in (4, 8, 20, 60):
+        buf = torch.zeros(n + 64, dtype=torch.uint8, device="cuda")
+        sa, _ = lor.lor_build_sa(d, offs, joined_out=buf[off:off + n])
+        assert np.array_equal(sa.cpu().numpy(), want)
+
+
+def oracle_pair(a, b):
+    offs = np.array([0, a.size, a.size + b.size], np.int64)
+    joined = oracle.join(np.concatenate([a, b]) if a.size + b.size else np.zeros(0, np.uint8), offs)
+    sa = oracle.suffix_array(joined)
+    return joined, sa, oracle.lcp(joined, sa), offs
+
+
+@pytest.mark.parametrize("pairs", [1, 2, 40, 300])
+def test_batched_state(pairs):
+    """Every pair's own LCP and ISA, which determine its suffix array."""
+    say("prefix batched", pairs)
+    rng = np.random.default_rng(pairs)
+    seqs = []
+    for p in range(pairs):
+        na, nb = (int(x) for x in rng.integers(0, 3000 if p % 3 else 30, size=2))
+        a, b = synth.noncoding_like(rng, na), synth.noncoding_like(rng, nb)
+        if p % 5 == 0:
+            b[:min(na, nb)] = a[:min(na, nb)]
+        if p % 7 == 0:
+            a[-50:] = 3
+            b[-70:] = 3
+        seqs += [a, b]
+    cat, d, offs = flat(seqs)
+    rec, lcp, isa = lor.lor_longest_overlap_batched_state(d, offs)
+    rec, lcp, isa, s = lor.records_to_tuples(rec), lcp.cpu().numpy(), isa.cpu().numpy(), lor.pair_starts(offs)
+    for p in range(pairs):
+        joined, sa, want, o = oracle_pair(seqs[2 * p], seqs[2 * p + 1])
+        assert np.array_equal(lcp[s[p]:s[p + 1]], want), p
+        assert np.array_equal(isa[s[p]:s[p + 1]] - s[p], oracle.isa(sa)), p
+        assert rec[p] == oracle.overlap(sa, want, o), p
+
+
+def test_bad_bases_leave_every_access_inside():
+    """Bases of every byte value: the call fails with LOR_EALPHABET."""
+    rng = np.random.default_rng(3)
+    seqs = [rng.integers(0, 256, size=n, dtype=np.uint8) for n in (9000, 5000, 100, 0, 7, 3000)]
+    cat, d, offs = flat(seqs)
+    for call in (lor.lor_build_sa, lor.lor_longest_overlap_batched, lor.lor_longest_overlap_ref):
+        with pytest.raises(lor.LorError) as e:
+            call(d, offs)
+        assert e.value.status == lor.LOR_EALPHABET
