@@ -84,10 +84,11 @@ def test_tandem_repeats(seed):
     check([a, *ends, b, np.full(200, 3, np.uint8), np.zeros(0, np.uint8), np.full(7, 3, np.uint8)])
 
 
-@pytest.mark.parametrize("text", ["zeros", "threes", "pairs", "identical", "unit40", "related"])
+@pytest.mark.parametrize("text", ["zeros", "threes", "pairs", "identical", "unit40", "related", "close", "copies"])
 def test_repetitive_texts(text):
-    """Whole texts of one repeat, exact copies longer than the comparison
-    budget (DC3 builds these), and a 1%-mutated copy."""
+    """Whole texts of one repeat (DC3 builds these); an identical, a 1%- and a
+    0.1%-mutated copy, and 2 to 60 exact copies of 300 to 5,000 bases (runs of
+    suffixes that rounds of doubling settle, many across tile edges)."""
     say("prefix repetitive", text)
     rng = np.random.default_rng(5)
     a = synth.gc40_bases(rng, 70000)
@@ -98,7 +99,16 @@ def test_repetitive_texts(text):
     elif text == "pairs":
         check([np.tile(np.array([0, 3], np.uint8), 4000), np.tile(np.array([3, 0], np.uint8), 3000)])
     elif text == "identical":
-        check([a[:20000], a[:20000]])
+        check([a, a])
+    elif text == "close":
+        check([a, synth.mutate(rng, a, 0.001), synth.mutate(rng, a[10000:50000], 0.001)])
+    elif text == "copies":
+        parts = []
+        for count, length in ((2, 5000), (3, 2500), (20, 700), (60, 300), (64, 256), (63, 257)):
+            word = synth.gc40_bases(rng, length)
+            for _ in range(count):
+                parts += [word, synth.gc40_bases(rng, int(rng.integers(1, 60)))]
+        check([np.concatenate(parts), a[:20000]])
     elif text == "unit40":
         check([np.tile(a[:40], 500), np.tile(a[:40], 77)])
     else:
@@ -117,6 +127,17 @@ def test_sequence_counts(k):
     check([s[:12] for s in seqs])
     # every sequence ends in one long run: more equal ends than a workgroup resolves
     check([np.concatenate([s[:9], np.full(30, 3, np.uint8)]) for s in seqs])
+
+
+def test_doubling_above_the_plain_store_limit():
+    """More than 2^24 suffixes with exact copies of 3,000 bases: the ranks of
+    the doubling rounds come from a bucketed scatter."""
+    say("prefix doubling, 17M")
+    rng = np.random.default_rng(17)
+    a, b = synth.gc40_bases(rng, 9_000_000), synth.gc40_bases(rng, 8_000_001)
+    for k in range(40):
+        b[k * 100_000:k * 100_000 + 3000] = a[k * 77_777:k * 77_777 + 3000]
+    check([a, b])
 
 
 def test_word_windows_at_every_alignment():
