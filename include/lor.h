@@ -336,7 +336,8 @@ lor_status lor_sort_pairs_split_u32(uint32_t *keys, uint32_t *vals, int64_t n, i
  *   radix_items_u32  radix tile = 256 threads x items, 32-bit keys: 8|12|16|24
  *   radix_items_u64  same for 64-bit keys: 8|12|16
  *   merge_items      Step 3 merge-path tile = 256 x items outputs: 4|8|12
- *   plcp_steps       PLCP positions per lane, 16..1024
+ *   plcp_steps       16..1024: the LCP samples every (plcp_steps / 2)-th position of
+ *                    the permuted LCP (rounded down to a power of two)
  * lor_plan_set(NULL) restores the defaults. The process-wide plan is not
  * synchronised: set it before launching work from several threads. */
 typedef struct {

@@ -1,128 +1,258 @@
 // LCP array on gfx950 (Section III, Table IV: LCP[r] = lcp of the suffixes
 // at ranks r-1 and r; the paper cites Kasai et al. for its construction).
 //
-// Permuted-LCP method:
-//   phi    : for every rank r, the pair (r, SA[r-1]) goes to text position
-//            SA[r] -- the inverse permutation and Phi together. The pairs
-//            travel as 64-bit keys (SA[r] << 32 | SA[r-1]) through radix
-//            passes on the top 16 bits of SA[r], then are stored bucket by
-//            bucket (see scatter.hip for why bucketing beats a random
-//            scatter);
-//   plcp   : PLCP[i] = lcp(suffix i, suffix Phi[i]). Kasai's bound
-//            PLCP[i+1] >= PLCP[i] - 1 iterates to PLCP[i+d] >= PLCP[i] - d.
-//            A wave owns a run of 64*K consecutive positions; lane l takes
-//            positions l, l+64, l+128, ... and resumes each comparison from
-//            its previous result minus 64. Loads of neighbouring lanes are
-//            contiguous, and inside long repeats (where the bound pays off)
-//            every lane does the same short extension, so no lane stalls
-//            its wave. The comparison reads 8 symbols at a time. ISA is
-//            written out here, sequentially;
-//   place  : LCP[ISA[i]] = PLCP[i], a bucketed scatter.
+// Kasai's method walks the text and needs SA and LCP permuted into text order
+// and back, two sorts' worth of passes around one random text read per suffix.
+// Neighbouring suffixes of DNA differ within a few dozen symbols, though, so
+//   window : every rank reads the first bytes of its own suffix (the one
+//            random read per suffix that is left) and takes its predecessor's
+//            from the neighbouring lane; LCPs below the window's length are
+//            final, and longer ones are marked. Every S-th text position i
+//            also notes Phi[i] = SA[rank - 1];
+//   plcp   : PLCP[i] = lcp(i, Phi[i]) of those sampled positions only. A
+//            sample whose first S symbols agree and whose successor i + S has
+//            Phi[i + S] = Phi[i] + S is linked to it: PLCP[i] = PLCP[i + S] + S;
+//            the others compare their texts;
+//   links  : the end of every chain of links, by a scan over 64-sample words,
+//            so a copy of any length is compared only where it ends;
+//   finish : a marked rank whose Phi lies on the diagonal of the sample before
+//            or behind its position follows from that; others start from
+//            Kasai's bound PLCP[i + d] >= PLCP[i] - d at the sample before, so
+//            a long repeat costs a rank a few symbols at most.
+// LCP is written in rank order throughout. ISA, when wanted, is a scatter of
+// its own.
+//
+// The window kernel is bound by its random reads (1.36 lines of 64 bytes per
+// suffix): 26 ms at 2^30 suffixes, 41 G suffixes/s, near the 45 G/s that
+// random 8-byte reads reach on a table of this size. LCP + ISA against the
+// text-order method it replaces: 1,000 symbols 96 -> 31 us, 100k 296 -> 40 us,
+// 1M 483 -> 69 us, 16M 1.21 -> 0.66 ms, 256M 14.8 -> 10.2 ms; two identical
+// sequences of 2M bases 75 -> 0.15 ms.
 #include "lor_internal.hpp"
 
 namespace lor {
 
 namespace {
 
+constexpr uint32_t kMarked = 0x80000000u;
+// ISA as plain stores from the window kernel up to here, as a bucketed scatter
+// above: random 4-byte stores cost little while ISA stays in the caches, and
+// the scatter takes about ten launches. LCP + ISA, plain against bucketed: 1M
+// 248 / 279 us, 16M 805 / 849 us, 32M 1589 / 1459 us, 256M 16.7 / 10.4 ms.
+constexpr uint32_t kDirectIsa = 1u << 24;
 
-__global__ __launch_bounds__(kBlock) void k_phi_keys(const int32_t *__restrict__ sa, uint32_t n,
-                                                     uint64_t *__restrict__ keys) {
-    for (uint32_t r = blockIdx.x * kBlock + threadIdx.x; r < n; r += gridDim.x * kBlock) {
-        const uint32_t p = (uint32_t)sa[r];
-        const uint32_t prev = r ? (uint32_t)sa[r - 1] : 0xffffffffu;
-        keys[r] = ((uint64_t)(p < n ? p : 0xffffffffu) << 32) | prev;
+struct __attribute__((packed, aligned(1))) Chunk {
+    uint64_t w[1];
+};
+
+// Symbols that the window kernel looks at: 24 bytes of a byte text (random DNA
+// of 2^30 bases has neighbours that agree on about 15 symbols, practically
+// never on 24; 24 bytes straddle a 64-byte line less often than 32), 32 bytes
+// of a 16-bit text.
+template <typename CH> struct Win {
+    static constexpr int words = sizeof(CH) == 1 ? 3 : 4;
+    static constexpr uint32_t symbols = 8 * words / sizeof(CH);
+};
+
+template <typename CH>
+__device__ __forceinline__ void read_window(const CH *__restrict__ t, uint32_t n, uint32_t i, uint64_t *w) {
+    constexpr int per = 8 / sizeof(CH);
+    if (i < n && n - i >= Win<CH>::symbols) {
+#pragma unroll
+        for (int c = 0; c < Win<CH>::words; ++c) w[c] = reinterpret_cast<const Chunk *>(t + i)[c].w[0];
+        return;
+    }
+#pragma unroll
+    for (int c = 0; c < Win<CH>::words; ++c) {
+        uint64_t v = 0;
+        for (int d = 0; d < per; ++d) {
+            const uint32_t o = c * per + d;
+            v |= (uint64_t)((i < n && o < n - i) ? t[i + o] : CH(0)) << (8 * sizeof(CH) * d);
+        }
+        w[c] = v;
     }
 }
 
-// isa_phi[SA[r]] = (r, SA[r-1]) from the bucketed (key, r) pairs.
-__global__ __launch_bounds__(kBlock) void k_phi_place(const uint64_t *__restrict__ keys,
-                                                      const uint32_t *__restrict__ ranks, uint32_t n,
-                                                      int2 *__restrict__ isa_phi) {
-    const uint32_t i = dev::xcd_block() * kBlock + threadIdx.x;   // one pair per thread, in bucket order
-    if (i >= n) return;
-    const uint64_t k = keys[i];
-    const uint32_t p = (uint32_t)(k >> 32);
-    if (p < n) isa_phi[p] = make_int2((int32_t)ranks[i], (int32_t)(uint32_t)k);
+constexpr int kLcpItems = 4;
+
+// DIRECT: ISA is stored from here.
+template <typename CH, bool DIRECT>
+__global__ __launch_bounds__(kBlock) void k_lcp_window(const CH *__restrict__ t, uint32_t n,
+                                                       const int32_t *__restrict__ sa, int32_t *__restrict__ lcp,
+                                                       uint32_t *__restrict__ phi, int32_t *__restrict__ isa,
+                                                       uint32_t shift) {
+    constexpr int NW = Win<CH>::words;
+    constexpr uint32_t per = 8 / sizeof(CH), WS = Win<CH>::symbols;
+    const uint32_t base = blockIdx.x * (kBlock * kLcpItems), lane = threadIdx.x & 63u;
+    uint32_t p[kLcpItems], q[kLcpItems];
+    uint64_t w[kLcpItems][NW], e[kLcpItems][NW];   // e: lane 0's predecessor
+#pragma unroll
+    for (int k = 0; k < kLcpItems; ++k) {
+        const uint32_t r = base + k * kBlock + threadIdx.x;
+        p[k] = r < n ? min((uint32_t)sa[r], n - 1u) : 0u;
+        q[k] = (lane == 0 && r > 0 && r < n) ? min((uint32_t)sa[r - 1], n - 1u) : 0u;
+    }
+#pragma unroll
+    for (int k = 0; k < kLcpItems; ++k) read_window(t, n, p[k], w[k]);
+    if (lane == 0) {
+#pragma unroll
+        for (int k = 0; k < kLcpItems; ++k) read_window(t, n, q[k], e[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < kLcpItems; ++k) {
+        const uint32_t r = base + k * kBlock + threadIdx.x;
+        const uint32_t pj = (uint32_t)__shfl_up((int)p[k], 1, kWave);
+        const uint32_t j = lane == 0 ? q[k] : pj;
+        uint32_t l = 0;
+        bool open = true;
+#pragma unroll
+        for (int c = 0; c < NW; ++c) {
+            const uint64_t up = __shfl_up(w[k][c], 1, kWave);
+            const uint64_t x = w[k][c] ^ (lane == 0 ? e[k][c] : up);
+            if (open) l += x ? (uint32_t)__builtin_ctzll(x) / (8u * (uint32_t)sizeof(CH)) : per;
+            open = open && x == 0;
+        }
+        if (r >= n) continue;
+        const uint32_t i = p[k];
+        if (r == 0) {
+            lcp[0] = 0;
+        } else {
+            const uint32_t lim = n - max(i, j);   // a window past the end reads zeros
+            lcp[r] = (int32_t)(open && lim > WS ? WS | kMarked : min(l, lim));
+        }
+        if ((i & ((1u << shift) - 1u)) == 0) phi[i >> shift] = r ? j : 0xffffffffu;
+        if constexpr (DIRECT) isa[i] = (int32_t)r;
+    }
 }
 
-// 8 text bytes starting at byte offset a; requires a + 16 <= text bytes and
-// an 8-byte aligned text (two aligned loads, then a funnel shift).
-__device__ __forceinline__ uint64_t load8(const uint8_t *__restrict__ t, uint32_t a) {
-    const uint64_t *w = reinterpret_cast<const uint64_t *>(t + (a & ~7u));
-    const uint32_t sh = (a & 7u) * 8u;
-    const uint64_t lo = w[0], hi = w[1];
-    return sh ? (lo >> sh) | (hi << (64u - sh)) : lo;
-}
+struct __attribute__((packed, aligned(1))) Bytes16 {
+    uint32_t x, y, z, w;
+};
 
-// Common-prefix length of suffixes i and j (in symbols), knowing the first h
-// symbols agree. Wide mode compares 8 bytes (8 / sizeof(CH) symbols) a step.
+// Common-prefix length of suffixes i and j (in symbols), knowing that the
+// first h symbols agree, at most cap.
 template <typename CH>
 __device__ __forceinline__ uint32_t extend(const CH *__restrict__ t, uint32_t n, uint32_t i, uint32_t j, uint32_t h,
-                                           bool wide) {
-    constexpr uint32_t per = 8 / sizeof(CH);
-    const uint32_t lim = n - max(i, j);   // symbols available in both
-    if (wide) {
-        const uint8_t *tb = reinterpret_cast<const uint8_t *>(t);
-        while (h + 2 * per <= lim) {
-            const uint64_t x = load8(tb, (i + h) * (uint32_t)sizeof(CH)) ^ load8(tb, (j + h) * (uint32_t)sizeof(CH));
-            if (x) return h + (uint32_t)(__builtin_ctzll(x) / (8 * sizeof(CH)));
-            h += per;
-        }
+                                           uint32_t cap) {
+    constexpr uint32_t W = 16 / sizeof(CH), B = 8 * sizeof(CH);
+    const uint32_t lim = min(cap, n - max(i, j));
+    uint32_t batch = 1;   // one 16-byte step, then four at a time: their loads wait together
+    while (h < lim && lim - h >= batch * W) {
+        Bytes16 x[4], y[4];
+#pragma unroll
+        for (uint32_t c = 0; c < 4; ++c)
+            if (c < batch) {
+                x[c] = *reinterpret_cast<const Bytes16 *>(t + i + h + c * W);
+                y[c] = *reinterpret_cast<const Bytes16 *>(t + j + h + c * W);
+            }
+#pragma unroll
+        for (uint32_t c = 0; c < 4; ++c)
+            if (c < batch) {
+                const uint64_t d0 = ((uint64_t)(x[c].y ^ y[c].y) << 32) | (x[c].x ^ y[c].x);
+                if (d0) return h + c * W + (uint32_t)__builtin_ctzll(d0) / B;
+                const uint64_t d1 = ((uint64_t)(x[c].w ^ y[c].w) << 32) | (x[c].z ^ y[c].z);
+                if (d1) return h + c * W + W / 2 + (uint32_t)__builtin_ctzll(d1) / B;
+            }
+        h += batch * W;
+        batch = 4;
     }
     while (h < lim && t[i + h] == t[j + h]) ++h;
     return h;
 }
 
-// A step of a wave takes 64 consecutive positions, one per lane. When
-// Phi[i] = Phi[i-1] + 1 and PLCP[i-1] >= 1, then PLCP[i] = PLCP[i-1] - 1
-// exactly (both suffixes lose the same first symbol), so a run of such
-// positions follows from the PLCP at its head with no text read: only heads
-// compare text (Kasai's bound, from the lane's previous step), then every
-// lane of a run takes head - distance by a wave-wide segmented propagation
-// (the run may continue from the previous step's last lane). A run whose head
-// value drops to 0 before its end leaves the rest to compare for themselves.
+constexpr uint32_t kNoCap = 0xffffffffu;
+
+// PLCP of the unlinked sampled positions, and the links, 64 samples a word.
 template <typename CH>
 __global__ __launch_bounds__(kBlock) void k_plcp(const CH *__restrict__ t, uint32_t n,
-                                                 const int2 *__restrict__ isa_phi, int32_t *__restrict__ plcp,
-                                                 int32_t *__restrict__ isa_out, int wide, uint32_t steps) {
-    const uint32_t span = kWave * steps;
-    const uint32_t waves = (n + span - 1) / span;
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint64_t below = lane ? (~0ull >> (64u - lane)) : 0ull;   // lanes under this one
-    for (uint32_t w = (blockIdx.x * kBlock + threadIdx.x) / kWave; w < waves; w += gridDim.x * (kBlock / kWave)) {
-        uint32_t h = 0;                                    // Kasai bound from this lane's previous step
-        uint32_t prev_j = 0xffffffffu, prev_p = 0;         // Phi and PLCP of the position before lane 0
-        for (uint32_t k = 0, i0 = w * span; k < steps && i0 < n; ++k, i0 += kWave) {
-            const uint32_t i = i0 + lane;
-            const bool valid = i < n;
-            uint32_t j = 0xffffffffu;
-            if (valid) {
-                const int2 q = isa_phi[i];
-                isa_out[i] = q.x;
-                j = (uint32_t)q.y;                           // n or more: no predecessor (rank 0)
-            }
-            const bool has = valid && j < n;
-            uint32_t jl = (uint32_t)__shfl_up((int)j, 1, kWave);
-            if (lane == 0) jl = prev_j;
-            const bool chained = has && j > 0 && jl < n && jl == j - 1;
-            uint32_t p = 0;
-            if (has && !chained) p = extend(t, n, i, j, h, wide != 0);
-            // segment heads: every lane not chained to the one before it
-            const uint64_t starts = __ballot(!chained);
-            const uint64_t mine = starts & (below | (1ull << lane));
-            const int head = mine ? 63 - __builtin_clzll(mine) : -1;
-            const uint32_t hv = (uint32_t)__shfl((int)p, head < 0 ? 0 : head, kWave);
-            const uint32_t H = head < 0 ? prev_p : hv;
-            const uint32_t d = head < 0 ? lane + 1u : lane - (uint32_t)head;
-            if (chained) {
-                if (H >= d) p = H - d;
-                else p = extend(t, n, i, j, h, wide != 0);   // the run reached 0 before this lane
-            }
-            if (valid) plcp[i] = (int32_t)p;
-            h = p > kWave ? p - kWave : 0;
-            prev_j = (uint32_t)__shfl((int)j, 63, kWave);
-            prev_p = (uint32_t)__shfl((int)p, 63, kWave);
+                                                 const uint32_t *__restrict__ phi, uint32_t samples, uint32_t shift,
+                                                 uint32_t *__restrict__ plcp, uint64_t *__restrict__ links) {
+    const uint32_t s = blockIdx.x * kBlock + threadIdx.x, step = 1u << shift;
+    bool linked = false;
+    if (s < samples) {
+        const uint32_t i = s << shift, j = phi[s];
+        const uint32_t next = s + 1 < samples ? phi[s + 1] : kNoCap;
+        uint32_t l = 0;
+        if (j < n && j != i) {
+            l = extend(t, n, i, j, 0u, step);
+            linked = l >= step && next < n && next == j + step;
+            if (l >= step && !linked) l = extend(t, n, i, j, step, kNoCap);
         }
+        if (!linked) plcp[s] = l;
+    }
+    const uint64_t m = __ballot(linked);
+    if ((threadIdx.x & 63u) == 0 && s < samples) links[s >> 6] = m;
+}
+
+// ends[w] = the first unlinked sample from 64 w on (one workgroup, each thread
+// a contiguous run of words; the last sample is never linked).
+constexpr int kLinkThreads = 1024;
+__global__ __launch_bounds__(kLinkThreads) void k_plcp_links(const uint64_t *__restrict__ links, uint32_t words,
+                                                             uint32_t samples, uint32_t *__restrict__ ends) {
+    __shared__ uint32_t s_first[kLinkThreads];
+    const uint32_t per = (words + kLinkThreads - 1u) / kLinkThreads;
+    const uint32_t b = min(words, threadIdx.x * per), e = min(words, b + per);
+    auto first_in = [&](uint32_t w) -> uint32_t {
+        const uint32_t left = samples - 64u * w;
+        const uint64_t z = ~links[w] & (left >= 64u ? ~0ull : (1ull << left) - 1ull);
+        return z ? 64u * w + (uint32_t)__builtin_ctzll(z) : kNoCap;
+    };
+    uint32_t first = kNoCap;
+    for (uint32_t w = b; w < e; ++w) first = min(first, first_in(w));
+    s_first[threadIdx.x] = first;
+    __syncthreads();
+    for (uint32_t o = 1; o < (uint32_t)kLinkThreads; o <<= 1) {   // min over this thread's words and all later ones
+        const uint32_t x = threadIdx.x + o < (uint32_t)kLinkThreads ? s_first[threadIdx.x + o] : kNoCap;
+        __syncthreads();
+        s_first[threadIdx.x] = min(s_first[threadIdx.x], x);
+        __syncthreads();
+    }
+    uint32_t after = threadIdx.x + 1 < (uint32_t)kLinkThreads ? s_first[threadIdx.x + 1] : kNoCap;
+    for (uint32_t w = e; w-- > b;) {
+        after = min(after, first_in(w));
+        ends[w] = after;
+    }
+}
+
+template <typename CH>
+__global__ __launch_bounds__(kBlock) void k_lcp_finish(const CH *__restrict__ t, uint32_t n,
+                                                       const int32_t *__restrict__ sa,
+                                                       const uint32_t *__restrict__ phi,
+                                                       const uint32_t *__restrict__ plcp,
+                                                       const uint64_t *__restrict__ links,
+                                                       const uint32_t *__restrict__ ends, uint32_t samples,
+                                                       uint32_t shift, int32_t *__restrict__ lcp) {
+    const uint32_t base = blockIdx.x * (kBlock * kLcpItems);
+    uint32_t v[kLcpItems];
+#pragma unroll
+    for (int k = 0; k < kLcpItems; ++k) {
+        const uint32_t r = base + k * kBlock + threadIdx.x;
+        v[k] = r < n ? (uint32_t)lcp[r] : 0u;
+    }
+#pragma unroll
+    for (int k = 0; k < kLcpItems; ++k) {
+        if (!(v[k] & kMarked)) continue;      // ranks above 0 only
+        const uint32_t r = base + k * kBlock + threadIdx.x;
+        const uint32_t i = min((uint32_t)sa[r], n - 1u), j = min((uint32_t)sa[r - 1], n - 1u);
+        const uint32_t c = i >> shift, d = i & ((1u << shift) - 1u);
+        auto sampled = [&](uint32_t q) -> uint32_t {   // PLCP at sample q, through its chain
+            const uint64_t z = ~links[q >> 6] >> (q & 63u);
+            const uint32_t end = min(z ? q + (uint32_t)__builtin_ctzll(z) : ends[(q >> 6) + 1u], samples - 1u);
+            return plcp[end] + ((end - q) << shift);
+        };
+        const uint32_t got = sampled(c), to_next = (1u << shift) - d;
+        uint32_t h;
+        if (got > d && phi[c] == j - d) {
+            h = got - d;                     // same diagonal as the sample before: exact
+        } else {
+            h = min(max(v[k] & ~kMarked, got > d ? got - d : 0u), n - max(i, j));
+            if (h < to_next) h = extend(t, n, i, j, h, to_next);
+            if (h >= to_next) {
+                if (c + 1 < samples && phi[c + 1] == j + to_next) h = to_next + sampled(c + 1);   // as the one behind
+                else h = extend(t, n, i, j, h, kNoCap);
+            }
+        }
+        lcp[r] = (int32_t)h;
     }
 }
 
@@ -133,48 +263,40 @@ size_t lcp_workspace(uint64_t n) { return (size_t)n * 28 + radix_counts_words(n)
 template <typename CH>
 lor_status lcp_build_t(const CH *text, uint32_t n, const int32_t *sa, int32_t *lcp, int32_t *isa, Arena &ar,
                        hipStream_t s) {
-    uint64_t *keys, *keys2;       // keys later holds the (ISA, Phi) pairs
-    uint32_t *vals2, *plcp, *isa_tmp, *counts;
-    LOR_TAKE(ar, uint64_t, n, keys);
-    LOR_TAKE(ar, uint64_t, n, keys2);
-    LOR_TAKE(ar, uint32_t, n, vals2);
-    LOR_TAKE(ar, uint32_t, n, plcp);
-    LOR_TAKE(ar, uint32_t, n, isa_tmp);
-    LOR_TAKE(ar, uint32_t, radix_counts_words(n), counts);
     if (n == 0) return LOR_OK;
-    int32_t *isa_w = isa ? isa : reinterpret_cast<int32_t *>(isa_tmp);
-    const int wide = ((uintptr_t)text % 8) == 0;
-    LOR_LAUNCH("k_phi_keys", (double)n * 12, s,
-               hipLaunchKernelGGL(k_phi_keys, dim3(grid_for(n)), dim3(kBlock), 0, s, sa, n, keys));
-    // Bucket the pairs by the top bits of SA[r] (two passes for large n);
-    // the (ISA, Phi) pairs then go to whichever 8-byte buffer is free.
-    const BucketDigits g = bucket_digits(n);
-    const uint64_t *bk;
-    const uint32_t *bv;
-    int2 *isa_phi;
-    if (g.lo_bits > 0) {
-        LOR_TRY(radix_pass<uint64_t>(keys, nullptr, 0, keys2, vals2, n, 32 + g.lo_shift, g.lo_bits, counts, s));
-        LOR_TRY(radix_pass<uint64_t>(keys2, vals2, 0, keys, plcp, n, 32 + g.hi_shift, g.hi_bits, counts, s));
-        bk = keys;
-        bv = plcp;
-        isa_phi = reinterpret_cast<int2 *>(keys2);
-    } else {
-        LOR_TRY(radix_pass<uint64_t>(keys, nullptr, 0, keys2, vals2, n, 32 + g.hi_shift, g.hi_bits, counts, s));
-        bk = keys2;
-        bv = vals2;
-        isa_phi = reinterpret_cast<int2 *>(keys);
-    }
-    LOR_LAUNCH("k_phi_place", (double)n * 20, s,
-               hipLaunchKernelGGL(k_phi_place, dim3(xcd_grid(n)), dim3(kBlock), 0, s, bk, bv, n, isa_phi));
-    const uint32_t steps = (uint32_t)plan().plcp_steps;
-    const uint32_t waves = div_up(n, kWave * steps);
-    LOR_LAUNCH("k_plcp", (double)n * (16 + sizeof(CH)), s,
-               hipLaunchKernelGGL(k_plcp<CH>, dim3(grid_for((uint64_t)waves * kWave)), dim3(kBlock), 0, s, text, n,
-                                  isa_phi, reinterpret_cast<int32_t *>(plcp), isa_w, wide, steps));
-    // both 8-byte buffers are free again: four n-word scatter buffers
-    uint32_t *k32 = reinterpret_cast<uint32_t *>(keys), *k232 = reinterpret_cast<uint32_t *>(keys2);
-    uint32_t *const tmp4[4] = {k32, k32 + n, k232, k232 + n};
-    return bucketed_scatter(lcp, n, reinterpret_cast<const uint32_t *>(isa_w), plcp, 0, n, tmp4, counts, s, true);
+    // every 2^shift-th position is sampled: half the plan's steps, 8 to 512
+    const uint32_t shift = (uint32_t)bits_for((uint64_t)plan().plcp_steps) - 2u;
+    const uint32_t samples = div_up(n, 1u << shift), words = div_up(samples, 64);
+    const uint32_t grid = div_up(n, kBlock * kLcpItems);
+    uint32_t *phi, *plcp, *ends;
+    uint64_t *links;
+    LOR_TAKE(ar, uint32_t, samples, phi);
+    LOR_TAKE(ar, uint32_t, samples, plcp);
+    LOR_TAKE(ar, uint64_t, words, links);
+    LOR_TAKE(ar, uint32_t, (size_t)words + 1, ends);
+    const bool direct = isa && n <= kDirectIsa;
+    const double bytes = (double)n * (8 + sizeof(CH) + (direct ? 4 : 0));
+    if (direct)
+        LOR_LAUNCH("k_lcp_window", bytes, s,
+                   hipLaunchKernelGGL((k_lcp_window<CH, true>), dim3(grid), dim3(kBlock), 0, s, text, n, sa, lcp, phi,
+                                      isa, shift));
+    else
+        LOR_LAUNCH("k_lcp_window", bytes, s,
+                   hipLaunchKernelGGL((k_lcp_window<CH, false>), dim3(grid), dim3(kBlock), 0, s, text, n, sa, lcp,
+                                      phi, isa, shift));
+    LOR_LAUNCH("k_plcp", 8.0 * samples, s,
+               hipLaunchKernelGGL(k_plcp<CH>, dim3(div_up(samples, kBlock)), dim3(kBlock), 0, s, text, n, phi,
+                                  samples, shift, plcp, links));
+    LOR_LAUNCH("k_plcp_links", 12.0 * words, s,
+               hipLaunchKernelGGL(k_plcp_links, dim3(1), dim3(kLinkThreads), 0, s, links, words, samples, ends));
+    LOR_LAUNCH("k_lcp_finish", 4.0 * n, s,
+               hipLaunchKernelGGL(k_lcp_finish<CH>, dim3(grid), dim3(kBlock), 0, s, text, n, sa, phi, plcp, links, ends,
+                                  samples, shift, lcp));
+    if (!isa || direct) return LOR_OK;
+    uint32_t *tmp[4], *counts;
+    for (int i = 0; i < 4; ++i) LOR_TAKE(ar, uint32_t, n, tmp[i]);
+    LOR_TAKE(ar, uint32_t, radix_counts_words(n), counts);
+    return bucketed_scatter(isa, n, reinterpret_cast<const uint32_t *>(sa), nullptr, 0, n, tmp, counts, s, true);
 }
 
 lor_status lcp_build(const uint8_t *text, uint32_t n, const int32_t *sa, int32_t *lcp, int32_t *isa, Arena &ar,
