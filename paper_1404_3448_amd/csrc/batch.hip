@@ -29,7 +29,15 @@ namespace {
 constexpr uint32_t kChunk = 16;                        // ranks per thread in a tile
 constexpr uint32_t kTileRanks = kChunk * kBlock;
 constexpr uint32_t kTilesPerGroup = 16;
-constexpr uint32_t kGroupRanks = kTileRanks * kTilesPerGroup;
+constexpr uint32_t kMinGroups = 2048;                  // workgroups wanted before one takes several tiles
+
+// Tiles per workgroup of the run pass: one while that leaves compute units
+// idle (16 at a time left 64 small pairs to 5 workgroups: 303 us).
+uint32_t group_tiles(uint64_t n) {
+    const uint64_t t = (n + kTileRanks - 1) / kTileRanks / kMinGroups;
+    return t < 1 ? 1u : t > kTilesPerGroup ? kTilesPerGroup : (uint32_t)t;
+}
+uint32_t group_count(uint64_t n) { return div_up(n, (uint64_t)kTileRanks * group_tiles(n)); }
 
 // Largest j with start[j] <= x over j in [0, count).
 __device__ __forceinline__ uint32_t find_pair(const int32_t *__restrict__ start, uint32_t count, uint32_t x) {
@@ -294,7 +302,7 @@ __device__ void reduce_chunks(ChunkSum *s, ChunkSum mine, const int32_t *start, 
     }
 }
 
-// One workgroup per group of kTilesPerGroup tiles. Rank r starts a run
+// One workgroup per group of `per` tiles. Rank r starts a run
 // unless it shares at least its pair's L symbols with r - 1. Every tile is
 // first checked for a rank that continues a run, with all its loads in
 // flight at once; tiles without one (nearly all) hold only one-suffix runs
@@ -302,7 +310,7 @@ __device__ void reduce_chunks(ChunkSum *s, ChunkSum mine, const int32_t *start, 
 // go through the per-rank path. Tile summaries are combined in rank order.
 __global__ __launch_bounds__(kBlock) void k_seg_runs(const int32_t *__restrict__ sa, const int32_t *__restrict__ lcp,
                                                      uint32_t n, const int32_t *__restrict__ start,
-                                                     const int32_t *__restrict__ alen, uint32_t P,
+                                                     const int32_t *__restrict__ alen, uint32_t P, uint32_t per,
                                                      const uint32_t *__restrict__ lmax,
                                                      unsigned long long *__restrict__ best,
                                                      ChunkSum *__restrict__ out) {
@@ -314,7 +322,7 @@ __global__ __launch_bounds__(kBlock) void k_seg_runs(const int32_t *__restrict__
     __shared__ uint32_t s_L[kPairWin];
     __shared__ uint32_t s_sh[2];
     const uint32_t tiles = (n + kTileRanks - 1) / kTileRanks;
-    const uint32_t t0 = blockIdx.x * kTilesPerGroup, t1 = min(tiles, t0 + kTilesPerGroup);
+    const uint32_t t0 = blockIdx.x * per, t1 = min(tiles, t0 + per);   // per <= kTilesPerGroup
     if (t0 >= t1) return;
     const uint32_t g0 = t0 * kTileRanks, g1 = min(n, t1 * kTileRanks);
     if (threadIdx.x < kTilesPerGroup) s_any[threadIdx.x] = 0;
@@ -455,7 +463,7 @@ size_t batch_workspace(uint64_t total_bases, uint32_t P) {
     ar.take<uint32_t>(P);                       // lmax
     ar.take<unsigned long long>(P);             // best
     const size_t fixed = ar.top;
-    const size_t scan = (N + kGroupRanks - 1) / kGroupRanks * sizeof(ChunkSum) + 4096;
+    const size_t scan = ((size_t)group_count(N) + 1) * sizeof(ChunkSum) + 4096;
     size_t phase = dc3_workspace_bound(N);
     phase = std::max(phase, lcp_workspace(N) + 4096);
     phase = std::max(phase, scan);
@@ -520,7 +528,7 @@ lor_status batch_overlap_run(const uint8_t *seqs, uint32_t P, uint64_t N, const 
     LOR_TRY(lcp_build_u16(text, (uint32_t)N, sa, lcp, isa_out, ar, s));
     ar.release(phase);
 
-    const uint32_t groups = div_up(N, kGroupRanks);
+    const uint32_t groups = group_count(N);
     ChunkSum *sums;
     LOR_TAKE(ar, ChunkSum, (size_t)groups + 1, sums);
     LOR_LAUNCH("k_pair_init", 8.0 * P, s,
@@ -530,7 +538,7 @@ lor_status batch_overlap_run(const uint8_t *seqs, uint32_t P, uint64_t N, const 
                                   start, alen, P, lmax));
     LOR_LAUNCH("k_seg_runs", 4.0 * N, s,
                hipLaunchKernelGGL(k_seg_runs, dim3(groups), dim3(kBlock), 0, s, sa, lcp, (uint32_t)N, start, alen, P,
-                                  lmax, best, sums));
+                                  group_tiles(N), lmax, best, sums));
     LOR_LAUNCH("k_seg_runs_final", (double)groups * sizeof(ChunkSum), s,
                hipLaunchKernelGGL(k_seg_runs_final, dim3(1), dim3(kBlock), 0, s, sums, groups, start, P, best));
     LOR_LAUNCH("k_pair_records", 32.0 * P, s,

@@ -29,7 +29,15 @@ namespace {
 constexpr uint32_t kChunk = 16;                       // ranks per thread in a tile
 constexpr uint32_t kTileRanks = kChunk * kBlock;      // 4096 ranks per tile
 constexpr uint32_t kTilesPerGroup = 16;
-constexpr uint32_t kGroupRanks = kTileRanks * kTilesPerGroup;
+constexpr uint32_t kMinGroups = 2048;                 // workgroups wanted before one takes several tiles
+
+// Tiles per workgroup of the run pass: one while that leaves compute units
+// idle (16 at a time left 100k ranks to 2 workgroups: 80 us against 9).
+uint32_t group_tiles(uint64_t n) {
+    const uint64_t t = (n + kTileRanks - 1) / kTileRanks / kMinGroups;
+    return t < 1 ? 1u : t > kTilesPerGroup ? kTilesPerGroup : (uint32_t)t;
+}
+uint32_t group_count(uint64_t n) { return div_up(n, (uint64_t)kTileRanks * group_tiles(n)); }
 
 struct RunSum {
     int32_t m1, s1, m2, s2;
@@ -111,10 +119,12 @@ __global__ __launch_bounds__(kBlock) void k_init(uint32_t *w, int count) {
 
 // Largest LCP[r] whose two suffixes start in different sequences. A
 // workgroup takes kCrossItems * 256 consecutive ranks; each thread loads its
-// LCP entries for all its items first. SA entries are loaded only for ranks
-// whose LCP exceeds both the maximum already published by earlier
-// workgroups (a lower bound of the result) and the thread's own best, so
-// after the first workgroups almost every rank costs its 4-byte LCP alone.
+// LCP entries for all its items first. Then every round each lane tries its
+// largest LCP that could still raise the wave's maximum (at the start: the one
+// published by earlier workgroups, a lower bound of the result), and the lanes
+// share what they found, so SA is read for a few ranks per wave. Trying every
+// item in turn took 130 us at 16M ranks, where the first workgroups, half the
+// grid, all start from nothing.
 constexpr int kCrossItems = 16;
 
 __global__ __launch_bounds__(kBlock) void k_cross_max(const int32_t *__restrict__ sa, const int32_t *__restrict__ lcp,
@@ -131,15 +141,28 @@ __global__ __launch_bounds__(kBlock) void k_cross_max(const int32_t *__restrict_
         const uint32_t r = r0 + j * kBlock;
         v[j] = r < n ? lcp[r] : 0;
     }
-    int32_t best = 0;
+    int32_t best = known;   // of the wave
+    for (;;) {
+        int32_t top = best;
+        int at = -1;
 #pragma unroll
-    for (int j = 0; j < kCrossItems; ++j) {
-        const uint32_t r = r0 + j * kBlock;
-        if (v[j] > known && v[j] > best &&
-            seq_of(s_start, st.k, sa[r - 1]) != seq_of(s_start, st.k, sa[r]))   // v[j] > 0 implies r < n
-            best = v[j];
+        for (int j = 0; j < kCrossItems; ++j)
+            if (v[j] > top) {
+                top = v[j];
+                at = j;
+            }
+        if (!__any(at >= 0)) break;
+        int32_t found = best;
+        if (at >= 0) {
+            const uint32_t r = r0 + at * kBlock;   // v > 0 implies r < n
+            if (seq_of(s_start, st.k, sa[r - 1]) != seq_of(s_start, st.k, sa[r])) found = top;
+#pragma unroll
+            for (int j = 0; j < kCrossItems; ++j)
+                if (j == at) v[j] = 0;             // tried
+        }
+        for (int o = 32; o > 0; o >>= 1) found = max(found, __shfl_xor(found, o, 64));
+        best = found;
     }
-    for (int o = 32; o > 0; o >>= 1) best = max(best, __shfl_xor(best, o, 64));
     if ((threadIdx.x & 63u) == 0) s_red[threadIdx.x >> 6] = best;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -158,14 +181,14 @@ __device__ void block_reduce_chunks(ChunkSum *s, ChunkSum mine) {
     }
 }
 
-// One workgroup per group of kTilesPerGroup tiles. First every tile is
+// One workgroup per group of `per` tiles. First every tile is
 // checked for an LCP >= L with all its loads in flight at once; tiles
 // without one (nearly all) hold only one-suffix runs and are summarised by
 // one thread each from their last suffix, the others go through the
 // per-rank path. The tile summaries are then combined in rank order.
 __global__ __launch_bounds__(kBlock) void k_runs(const int32_t *__restrict__ sa, const int32_t *__restrict__ lcp,
-                                                 uint32_t n, SeqStarts st, const uint32_t *__restrict__ Lp,
-                                                 ChunkSum *__restrict__ out) {
+                                                 uint32_t n, SeqStarts st, uint32_t per,
+                                                 const uint32_t *__restrict__ Lp, ChunkSum *__restrict__ out) {
     __shared__ int32_t s_start[kMaxSeqs + 1];
     __shared__ ChunkSum s_sum[kBlock];
     __shared__ ChunkSum s_tile[kTilesPerGroup];
@@ -174,8 +197,9 @@ __global__ __launch_bounds__(kBlock) void k_runs(const int32_t *__restrict__ sa,
     if (threadIdx.x < kTilesPerGroup) s_any[threadIdx.x] = 0;
     __syncthreads();
     const int32_t L = (int32_t)*Lp;
+    if (L == 0) return;   // no region is shared; uniform
     const uint32_t tiles = (n + kTileRanks - 1) / kTileRanks;
-    const uint32_t t0 = blockIdx.x * kTilesPerGroup, t1 = min(tiles, t0 + kTilesPerGroup);
+    const uint32_t t0 = blockIdx.x * per, t1 = min(tiles, t0 + per);   // per <= kTilesPerGroup
     for (uint32_t t = t0; t < t1; ++t) {
         const uint32_t base = t * kTileRanks;
         const uint32_t cnt = min(kTileRanks, n - base);
@@ -250,14 +274,14 @@ __global__ __launch_bounds__(kBlock) void k_runs_final(const ChunkSum *__restric
 }  // namespace
 
 size_t overlap_workspace(uint64_t n) {
-    return ((n + kGroupRanks - 1) / kGroupRanks + 1) * sizeof(ChunkSum) + 1024;
+    return ((size_t)group_count(n) + 1) * sizeof(ChunkSum) + 1024;
 }
 
 lor_status overlap_scan(const int32_t *sa, const int32_t *lcp, uint32_t n, const SeqStarts &st, Arena &ar,
                         hipStream_t s, int64_t result[5]) {
     uint32_t *words;
     LOR_TAKE(ar, uint32_t, 64, words);
-    const uint32_t groups = div_up(n, kGroupRanks);
+    const uint32_t groups = group_count(n);
     ChunkSum *sums;
     LOR_TAKE(ar, ChunkSum, (size_t)groups + 1, sums);
     for (int x = 0; x < 5; ++x) result[x] = -1;
@@ -267,18 +291,16 @@ lor_status overlap_scan(const int32_t *sa, const int32_t *lcp, uint32_t n, const
     LOR_LAUNCH("k_cross_max", (double)n * 4, s,   // LCP; SA only for the few ranks above the running maximum
                hipLaunchKernelGGL(k_cross_max, dim3(div_up(n - 1, kBlock * kCrossItems)), dim3(kBlock), 0, s, sa, lcp,
                                   n, st, words));
-    uint32_t L = 0;
-    LOR_HIP(hipMemcpyAsync(&L, words, 4, hipMemcpyDeviceToHost, s));
-    LOR_HIP(hipStreamSynchronize(s));
-    if (L == 0) return LOR_OK;
     LOR_LAUNCH("k_runs", (double)n * 4, s,
-               hipLaunchKernelGGL(k_runs, dim3(groups), dim3(kBlock), 0, s, sa, lcp, n, st, words, sums));
+               hipLaunchKernelGGL(k_runs, dim3(groups), dim3(kBlock), 0, s, sa, lcp, n, st, group_tiles(n), words, sums));
     LOR_LAUNCH("k_runs_final", (double)groups * sizeof(ChunkSum), s,
                hipLaunchKernelGGL(k_runs_final, dim3(1), dim3(kBlock), 0, s, sums, groups, words + 1));
-    uint32_t pq[2];
-    LOR_HIP(hipMemcpyAsync(pq, words + 1, 8, hipMemcpyDeviceToHost, s));
+    uint32_t w[3];   // length, positions
+    LOR_HIP(hipMemcpyAsync(w, words, sizeof(w), hipMemcpyDeviceToHost, s));
     LOR_HIP(hipStreamSynchronize(s));
-    const int32_t p = (int32_t)pq[0], q = (int32_t)pq[1];
+    const uint32_t L = w[0];
+    if (L == 0) return LOR_OK;
+    const int32_t p = (int32_t)w[1], q = (int32_t)w[2];
     if (p == INT_MAX || q == INT_MAX || p < 0 || q < 0) {
         set_error("internal: no position pair for overlap length %u", L);
         return LOR_EINVAL;

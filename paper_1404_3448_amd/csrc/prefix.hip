@@ -61,7 +61,8 @@ constexpr uint32_t kSmall = 64;               // largest group resolved in a wor
 constexpr int kResItems = 4;                  // ranks per thread of the resolve kernels
 constexpr uint32_t kResTile = kBlock * kResItems;
 constexpr uint32_t kResWords = kResTile / 64;
-constexpr uint32_t kDeep = 256;               // symbols compared directly before ranks are
+constexpr uint32_t kDeep = 256;               // symbols that resolve compares
+constexpr uint32_t kSettle = 2048;            // symbols that k_settle compares
 constexpr uint32_t kUnit = 64;                // 16-byte comparison steps per budget unit
 constexpr uint32_t kCodeBits = 15;
 constexpr uint32_t kExtent = (1u << (kCodeBits - 1)) - 1u;   // longest repeat a key describes
@@ -264,8 +265,14 @@ __device__ __forceinline__ uint32_t seq_of(const int32_t *start, uint32_t count,
     return lo;
 }
 
+// The kernels also clear the tile's words of `open` (see Runs).
+__device__ __forceinline__ void clear_open(uint32_t *open, uint32_t n, uint32_t base) {
+    const uint32_t i = base / 32u + threadIdx.x;
+    if (threadIdx.x < kKeyTile / 32u && i < (n + 31u) / 32u) open[i] = 0;
+}
+
 __global__ __launch_bounds__(kBlock) void k_prefix_keys(Joined x, uint32_t *__restrict__ keys,
-                                                        uint32_t *__restrict__ vals) {
+                                                        uint32_t *__restrict__ vals, uint32_t *__restrict__ open) {
     __shared__ uint32_t s_w[kKeyWords];
     __shared__ int32_t s_start[kMaxSeqs + 1];
     __shared__ uint32_t s_below[kMaxSeqs + 1];
@@ -278,6 +285,7 @@ __global__ __launch_bounds__(kBlock) void k_prefix_keys(Joined x, uint32_t *__re
     const uint32_t bel = dev::block_exclusive_sum(mine, s_tmp, &all);
     if (tid < x.k) s_below[tid] = bel;
     pack_tile(x, base, s_w);
+    clear_open(open, x.n, base);
     __syncthreads();
     const uint32_t drop = 32u - 2u * (uint32_t)x.K;
     const uint32_t j0 = seq_of(s_start, x.k, base);
@@ -298,11 +306,13 @@ __global__ __launch_bounds__(kBlock) void k_prefix_keys(Joined x, uint32_t *__re
 }
 
 __global__ __launch_bounds__(kBlock) void k_prefix_keys_tagged(Tagged x, uint32_t *__restrict__ keys,
-                                                               uint32_t *__restrict__ vals) {
+                                                               uint32_t *__restrict__ vals,
+                                                               uint32_t *__restrict__ open) {
     const uint32_t m = x.n - x.near;
     __shared__ uint32_t s_w[kKeyWords];
     const uint32_t base = blockIdx.x * kKeyTile, tid = threadIdx.x;
     pack_tile(x, base, s_w);
+    clear_open(open, x.n, base);
     __syncthreads();
     const uint32_t drop = 32u - 2u * (uint32_t)x.K;
 #pragma unroll
@@ -327,7 +337,10 @@ __global__ __launch_bounds__(kBlock) void k_prefix_keys_tagged(Tagged x, uint32_
 // Base-5 keys, 8 consecutive positions per thread from the last to the first:
 // key(p) = s_p 5^(K-1) + key(p+1) / 5.
 constexpr int kShareRun = 8;
-__global__ __launch_bounds__(kBlock) void k_prefix_keys_shared(Shared x, uint32_t top, uint32_t *__restrict__ keys) {
+__global__ __launch_bounds__(kBlock) void k_prefix_keys_shared(Shared x, uint32_t top, uint32_t *__restrict__ keys,
+                                                               uint32_t *__restrict__ open) {
+    static_assert(kBlock * kShareRun == kKeyTile, "clear_open covers a workgroup's positions");
+    clear_open(open, x.n, blockIdx.x * kKeyTile);
     const uint32_t p0 = (blockIdx.x * kBlock + threadIdx.x) * kShareRun;
     if (p0 >= x.n) return;
     uint32_t s[kShareRun + kMaxK];
@@ -886,44 +899,58 @@ __global__ __launch_bounds__(kBlock) void k_copy_words(const uint32_t *__restric
 
 constexpr uint32_t kRunTile = 1024;
 constexpr uint32_t kRunWords = (kRunTile + 2 * kSmall) / 32;
-__global__ __launch_bounds__(kBlock) void k_double(const uint32_t *__restrict__ was, uint32_t *__restrict__ open,
-                                                   uint32_t n, uint32_t h, const uint32_t *__restrict__ rank,
-                                                   int32_t *__restrict__ sa, uint32_t *__restrict__ left) {
-    __shared__ uint32_t s_bits[kRunWords], s_rank[kRunTile + kSmall], s_any, s_left;
-    const uint32_t base = blockIdx.x * kRunTile, tid = threadIdx.x, words = (n + 31u) / 32u;
-    if (tid == 0) s_any = s_left = 0;
-    __syncthreads();
-    if (tid < kRunWords) {
-        const uint32_t b = base / 32u + tid < words ? was[base / 32u + tid] : 0u;
-        s_bits[tid] = b;
-        if (b) s_any = 1;
-    }
-    __syncthreads();
-    if (!s_any) return;   // uniform
-    // slot l of the tile or of the kSmall after it: first slot and size of its
-    // run, size 0 when the run is one suffix or starts in another tile
-    auto run_of = [&](uint32_t l, uint32_t *first) -> uint32_t {
+constexpr int kRunItems = (kRunTile + kSmall + kBlock - 1) / kBlock;   // slots per thread: the tile's, then kSmall more
+
+// A tile's run bits (and those of the slots after it) in LDS.
+struct RunTile {
+    const uint32_t *bits;   // kRunWords words
+    // Slot l of the tile or of the kSmall after it: first slot and size of its
+    // run, size 0 when the run is one suffix or starts in another tile.
+    __device__ uint32_t run_of(uint32_t l, uint32_t *first) const {
         uint32_t wd = l >> 5;
-        uint32_t z = ~s_bits[wd] & (0xffffffffu >> (31u - (l & 31u)));
-        while (!z && wd > 0) z = ~s_bits[--wd];
+        uint32_t z = ~bits[wd] & (0xffffffffu >> (31u - (l & 31u)));
+        while (!z && wd > 0) z = ~bits[--wd];
         if (!z) return 0;
         const uint32_t f = wd * 32u + 31u - (uint32_t)__builtin_clz(z);
         uint32_t g = l + 1;
         wd = g >> 5;
-        z = wd < kRunWords ? ~s_bits[wd] & (0xffffffffu << (g & 31u)) : 1u;
-        while (!z && ++wd < kRunWords) z = ~s_bits[wd];
+        z = wd < kRunWords ? ~bits[wd] & (0xffffffffu << (g & 31u)) : 1u;
+        while (!z && ++wd < kRunWords) z = ~bits[wd];
         g = wd < kRunWords ? wd * 32u + (uint32_t)__builtin_ctz(z) : kRunTile + 2 * kSmall;
         *first = f;
         return f < kRunTile && g - f > 1 && g - f <= kSmall ? g - f : 0u;
-    };
-    constexpr int R = (kRunTile + kSmall + kBlock - 1) / kBlock;
-    uint32_t val[R];
+    }
+};
+// Loads the bits; false (for the whole workgroup) when no run is near.
+__device__ __forceinline__ bool load_runs(const uint32_t *__restrict__ was, uint32_t n, uint32_t base,
+                                          uint32_t *s_bits, uint32_t *s_any) {
+    const uint32_t words = (n + 31u) / 32u;
+    if (threadIdx.x == 0) *s_any = 0;
+    __syncthreads();
+    if (threadIdx.x < kRunWords) {
+        const uint32_t b = base / 32u + threadIdx.x < words ? was[base / 32u + threadIdx.x] : 0u;
+        s_bits[threadIdx.x] = b;
+        if (b) *s_any = 1;
+    }
+    __syncthreads();
+    return *s_any != 0;
+}
+
+__global__ __launch_bounds__(kBlock) void k_double(const uint32_t *__restrict__ was, uint32_t *__restrict__ open,
+                                                   uint32_t n, uint32_t h, const uint32_t *__restrict__ rank,
+                                                   int32_t *__restrict__ sa, uint32_t *__restrict__ left) {
+    __shared__ uint32_t s_bits[kRunWords], s_rank[kRunTile + kSmall], s_any, s_left;
+    const uint32_t base = blockIdx.x * kRunTile, tid = threadIdx.x;
+    if (tid == 0) s_left = 0;
+    if (!load_runs(was, n, base, s_bits, &s_any)) return;
+    const RunTile runs{s_bits};
+    uint32_t val[kRunItems];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
+    for (int r = 0; r < kRunItems; ++r) {
         const uint32_t l = r * kBlock + tid;
         uint32_t f;
         val[r] = 0xffffffffu;
-        if (l < kRunTile + kSmall && base + l < n && run_of(l, &f)) {
+        if (l < kRunTile + kSmall && base + l < n && runs.run_of(l, &f)) {
             const uint32_t p = (uint32_t)sa[base + l];
             val[r] = p;
             s_rank[l] = p < n && h < n - p ? rank[p + h] + 1u : 0u;   // the end of the text comes first
@@ -932,11 +959,11 @@ __global__ __launch_bounds__(kBlock) void k_double(const uint32_t *__restrict__ 
     __syncthreads();
     uint32_t mine_left = 0;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
+    for (int r = 0; r < kRunItems; ++r) {
         const uint32_t l = r * kBlock + tid;
         if (val[r] == 0xffffffffu) continue;
         uint32_t f;
-        const uint32_t size = run_of(l, &f), mine = s_rank[l];
+        const uint32_t size = runs.run_of(l, &f), mine = s_rank[l];
         uint32_t place = f, same = 0;
         for (uint32_t q = f; q < f + size; ++q) {
             place += s_rank[q] < mine;
@@ -954,28 +981,68 @@ __global__ __launch_bounds__(kBlock) void k_double(const uint32_t *__restrict__ 
     if (tid == 0 && s_left) atomicAdd(left, s_left);
 }
 
+// The same by comparing texts, up to kSettle symbols: when few suffixes are
+// open, ranks of all of them cost more than these comparisons.
+template <typename X>
+__global__ __launch_bounds__(kBlock) void k_settle(X x, const uint32_t *__restrict__ was, uint32_t *__restrict__ open,
+                                                   int32_t *__restrict__ sa, uint32_t *__restrict__ left) {
+    __shared__ uint32_t s_bits[kRunWords], s_val[kRunTile + kSmall], s_any, s_left;
+    const uint32_t base = blockIdx.x * kRunTile, tid = threadIdx.x;
+    if (tid == 0) s_left = 0;
+    if (!load_runs(was, x.n, base, s_bits, &s_any)) return;
+    const RunTile runs{s_bits};
+    for (uint32_t l = tid; l < kRunTile + kSmall; l += kBlock) {
+        uint32_t f;
+        s_val[l] = base + l < x.n && runs.run_of(l, &f) ? min((uint32_t)sa[base + l], x.n - 1u) : 0xffffffffu;
+    }
+    __syncthreads();
+    uint32_t mine_left = 0;
+    for (uint32_t l = tid; l < kRunTile + kSmall; l += kBlock) {
+        const uint32_t v = s_val[l];
+        if (v == 0xffffffffu) continue;
+        uint32_t f;
+        const uint32_t size = runs.run_of(l, &f);
+        uint32_t place = f, same = 0;
+        for (uint32_t q = f; q < f + size; ++q) {
+            if (q == l) continue;
+            const int c = order(x.t, x.n, s_val[q], v, kDeep, kSettle);
+            place += c < 0;
+            same += c == 0 && q < l;
+        }
+        place += same;
+        const uint32_t slot = base + place;
+        if (slot >= x.n) continue;
+        sa[slot] = (int32_t)v;
+        if (same) ++mine_left;
+        else if (place != f) atomicAnd(&open[slot >> 5], ~(1u << (slot & 31u)));
+    }
+    if (mine_left) atomicAdd(&s_left, mine_left);
+    __syncthreads();
+    if (tid == 0 && s_left) atomicAdd(left, s_left);
+}
+
 // ------------------------------------------------------------------ driver
 
 struct PrefixHdr {
     uint32_t word[16];
 };
 
-lor_status launch_keys(const Joined &x, uint32_t *k, uint32_t *v, hipStream_t s) {
+lor_status launch_keys(const Joined &x, uint32_t *k, uint32_t *v, uint32_t *open, hipStream_t s) {
     LOR_LAUNCH("k_prefix_keys", 9.0 * x.n, s,
-               hipLaunchKernelGGL(k_prefix_keys, dim3(div_up(x.n, kKeyTile)), dim3(kBlock), 0, s, x, k, v));
+               hipLaunchKernelGGL(k_prefix_keys, dim3(div_up(x.n, kKeyTile)), dim3(kBlock), 0, s, x, k, v, open));
     return LOR_OK;
 }
-lor_status launch_keys(const Tagged &x, uint32_t *k, uint32_t *v, hipStream_t s) {
+lor_status launch_keys(const Tagged &x, uint32_t *k, uint32_t *v, uint32_t *open, hipStream_t s) {
     LOR_LAUNCH("k_prefix_keys", 10.0 * x.n, s,
-               hipLaunchKernelGGL(k_prefix_keys_tagged, dim3(div_up(x.n, kKeyTile)), dim3(kBlock), 0, s, x, k, v));
+               hipLaunchKernelGGL(k_prefix_keys_tagged, dim3(div_up(x.n, kKeyTile)), dim3(kBlock), 0, s, x, k, v, open));
     return LOR_OK;
 }
-lor_status launch_keys(const Shared &x, uint32_t *k, uint32_t *, hipStream_t s) {
+lor_status launch_keys(const Shared &x, uint32_t *k, uint32_t *, uint32_t *open, hipStream_t s) {
     uint32_t top = 1;
     for (int i = 1; i < x.K; ++i) top *= 5u;
     LOR_LAUNCH("k_prefix_keys", 5.0 * x.n, s,
                hipLaunchKernelGGL(k_prefix_keys_shared, dim3(div_up(x.n, kBlock * kShareRun)), dim3(kBlock), 0, s, x,
-                                  top, k));
+                                  top, k, open));
     return LOR_OK;
 }
 
@@ -1010,9 +1077,33 @@ lor_status read_header(uint32_t *hdr, PrefixHdr *h, hipStream_t s) {
 
 // Rounds of doubling until no run is open. *done stays false when the
 // workspace does not hold the ranks.
-lor_status double_runs(uint32_t n, uint32_t *open, uint32_t owords, int32_t *sa, Arena &ar, uint32_t *hdr,
-                       hipStream_t s, bool *done) {
-    uint32_t *was = ar.take<uint32_t>(owords), *rank = ar.take<uint32_t>(n);
+template <typename X>
+lor_status double_runs(const X &x, uint32_t count, uint32_t *open, uint32_t owords, int32_t *sa, Arena &ar,
+                       uint32_t *hdr, hipStream_t s, bool *done) {
+    const uint32_t n = x.n;
+    uint32_t *was = ar.take<uint32_t>(owords);
+    if (ar.overflow) return LOR_OK;
+    uint32_t from = kDeep;
+    // The ranks of all suffixes (a scatter) and the rounds take about 15 ps per
+    // suffix of the text; comparing an open suffix to its neighbour through
+    // kSettle symbols reads some 60 lines, about 1.5 ns.
+    if (count <= n / 256u + 512u) {
+        LOR_LAUNCH("k_copy_words", 8.0 * owords, s,
+                   hipLaunchKernelGGL(k_copy_words, dim3(grid_for(owords)), dim3(kBlock), 0, s, open, was, owords));
+        LOR_LAUNCH("k_settle", 0.125 * n, s,
+                   hipLaunchKernelGGL(k_settle<X>, dim3(div_up(n, kRunTile)), dim3(kBlock), 0, s, x, was, open, sa,
+                                      hdr + kWordRound + 3));
+        PrefixHdr w;
+        LOR_TRY(read_header(hdr, &w, s));
+        if (trace_on())
+            fprintf(stderr, "[lor] prefix sort: %u open suffixes compared, %u left\n", count, w.word[kWordRound + 3]);
+        if (w.word[kWordRound + 3] == 0) {
+            *done = true;
+            return LOR_OK;
+        }
+        from = kSettle;
+    }
+    uint32_t *rank = ar.take<uint32_t>(n);
     if (ar.overflow) return LOR_OK;
     if (n <= kDirectRanks) {
         LOR_LAUNCH("k_ranks", 8.0 * n, s,
@@ -1028,7 +1119,7 @@ lor_status double_runs(uint32_t n, uint32_t *open, uint32_t owords, int32_t *sa,
                                  0, n, tmp, counts, s, true));
     }
     constexpr int kPer = 4;   // rounds between read-backs; a round with nothing open is three short launches
-    for (uint64_t h = kDeep;;) {
+    for (uint64_t h = from;;) {
         LOR_TRY(zero_words(hdr + kWordRound, kPer, s));
         for (int r = 0; r < kPer; ++r, h *= 2) {
             const uint32_t step = (uint32_t)std::min<uint64_t>(h, n);
@@ -1091,7 +1182,7 @@ lor_status prefix_sa(const X &x, int bits, uint32_t near, int32_t *sa, Arena &ar
         const int step = plan().digit_bits, passes = radix_passes(0, bits);
         uint32_t *ki = passes % 2 ? kb : ka, *ko = passes % 2 ? ka : kb;
         uint32_t *vi = passes % 2 ? vb : va, *vo = passes % 2 ? va : vb;
-        LOR_TRY(launch_keys(x, ki, vi, s));
+        LOR_TRY(launch_keys(x, ki, vi, open, s));
         for (int sh = 0; sh < bits; sh += step) {
             const uint32_t *in = kImplicit && sh == 0 ? nullptr : vi;
             LOR_TRY(radix_pass<uint32_t>(ki, in, 0, ko, vo, m, sh, std::min(step, bits - sh), counts, s));
@@ -1100,7 +1191,6 @@ lor_status prefix_sa(const X &x, int bits, uint32_t near, int32_t *sa, Arena &ar
         }
     }
     if (near) LOR_TRY(launch_near(x, ka, m, sa, places, s));
-    LOR_TRY(zero_words(open, owords, s));
     GroupKey gk{0, nullptr};
     if (m > 0)
         LOR_LAUNCH("k_resolve", 12.0 * m, s,
@@ -1170,7 +1260,7 @@ lor_status prefix_sa(const X &x, int bits, uint32_t near, int32_t *sa, Arena &ar
     if (h.word[kWordAbort]) return LOR_OK;
     if (h.word[kWordOpen] > 0) {
         ar.release(mark_open);
-        LOR_TRY(double_runs(x.n, open, owords, sa, ar, hdr, s, done));
+        LOR_TRY(double_runs(x, h.word[kWordOpen], open, owords, sa, ar, hdr, s, done));
         return LOR_OK;
     }
     *done = true;

@@ -139,7 +139,38 @@ __global__ __launch_bounds__(kBlock) void k_col_down(uint32_t *__restrict__ tabl
     }
 }
 
-// IMPLICIT: the value of input element e is e + voff (vin unused).
+// The same for at most kSmallRows tiles in one workgroup: three dependent
+// launches cost more than the work there (100k keys of 32 bits: 23 -> 14 us a
+// pass). A thread sums and rescans a quarter of one digit's rows.
+constexpr uint32_t kSmallRows = 128;
+__global__ __launch_bounds__(1024) void k_col_small(uint32_t *__restrict__ table, uint32_t rows) {
+    __shared__ uint32_t s_sum[4][kBins];
+    __shared__ uint32_t s_w[4];
+    const uint32_t d = threadIdx.x & (kBins - 1u), q = threadIdx.x / kBins;
+    const uint32_t r0 = rows * q / 4u, r1 = rows * (q + 1u) / 4u;
+    uint32_t acc = 0;
+#pragma unroll 4
+    for (uint32_t r = r0; r < r1; ++r) acc += table[(size_t)r * kBins + d];
+    s_sum[q][d] = acc;
+    __syncthreads();
+    const uint32_t tot = s_sum[0][d] + s_sum[1][d] + s_sum[2][d] + s_sum[3][d];
+    const uint32_t inc = dev::wave_inclusive_sum(tot);   // a wave holds 64 neighbouring digits
+    if (q == 0 && (threadIdx.x & 63u) == 63u) s_w[d >> 6] = inc;
+    __syncthreads();
+    uint32_t run = inc - tot;
+    for (uint32_t w = 0; w < (d >> 6); ++w) run += s_w[w];
+    for (uint32_t w = 0; w < q; ++w) run += s_sum[w][d];
+#pragma unroll 4
+    for (uint32_t r = r0; r < r1; ++r) {
+        const size_t i = (size_t)r * kBins + d;
+        const uint32_t x = table[i];
+        table[i] = run;
+        run += x;
+    }
+}
+
+// IMPLICIT: the value of input element e is e + voff (vin unused). A null
+// table stands for a single tile, whose own digit starts are the offsets.
 template <typename K, int ITEMS, bool IMPLICIT>
 __global__ __launch_bounds__(kBlock, 2) void k_radix_scatter(const K *__restrict__ kin,
                                                           const uint32_t *__restrict__ vin,
@@ -167,7 +198,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_radix_scatter(const K *__restrict
     if (!xcd_tile(tiles, &t)) return;
     const unsigned tid = threadIdx.x, lane = tid & 63u, w = tid >> 6;
     const uint32_t mask = (1u << nbits) - 1u;
-    const uint32_t gbase = table[(size_t)t * kBins + tid];   // output offset of digit tid for this tile
+    const uint32_t gbase = table ? table[(size_t)t * kBins + tid] : 0u;   // output offset of digit tid for this tile
 #pragma unroll
     for (int i = 0; i < W; ++i) {
         s_cnt[i][tid] = 0;
@@ -251,7 +282,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_radix_scatter(const K *__restrict
         s_cnt[i][tid] = run;
         run += c[i];
     }
-    s_delta[tid] = gbase - start;
+    s_delta[tid] = table ? gbase - start : 0u;
     __syncthreads();
 
     uint32_t lp[ITEMS];   // tile slot of each item, TILE when it has none
@@ -381,17 +412,26 @@ lor_status radix_pass_items(const K *ki, const uint32_t *vi, uint32_t voff, K *k
     uint32_t *table = counts;
     uint32_t *csum = counts + (size_t)kBins * div_up(n, kMinTile);
     const double tbytes = 4.0 * kBins * tiles;
-    LOR_LAUNCH("k_radix_count", (double)n * sizeof(K) + tbytes, s,
-               hipLaunchKernelGGL((k_radix_count<K, ITEMS>), dim3(grid), dim3(kBlock), 0, s, ki, n, tiles, shift,
-                                  mask, table));
-    LOR_LAUNCH("k_col_reduce", tbytes, s,
-               hipLaunchKernelGGL(k_col_reduce, dim3(chunks), dim3(kBlock), 0, s, table, tiles, chunks, csum));
-    uint32_t *dtot = csum + (size_t)kBins * kColChunks;
-    LOR_LAUNCH("k_col_scan", 8.0 * kBins * chunks, s,
-               hipLaunchKernelGGL(k_col_scan, dim3(kBins), dim3(kBlock), 0, s, csum, chunks, dtot));
-    LOR_LAUNCH("k_col_down", 2.0 * tbytes, s,
-               hipLaunchKernelGGL(k_col_down, dim3(chunks), dim3(kBlock), 0, s, table, tiles, chunks, csum,
-                                  dtot));
+    if (tiles == 1) {
+        table = nullptr;
+    } else {
+        LOR_LAUNCH("k_radix_count", (double)n * sizeof(K) + tbytes, s,
+                   hipLaunchKernelGGL((k_radix_count<K, ITEMS>), dim3(grid), dim3(kBlock), 0, s, ki, n, tiles, shift,
+                                      mask, table));
+    }
+    if (tiles > 1 && tiles <= kSmallRows) {
+        LOR_LAUNCH("k_col_small", 3.0 * tbytes, s,
+                   hipLaunchKernelGGL(k_col_small, dim3(1), dim3(1024), 0, s, table, tiles));
+    } else if (tiles > 1) {
+        LOR_LAUNCH("k_col_reduce", tbytes, s,
+                   hipLaunchKernelGGL(k_col_reduce, dim3(chunks), dim3(kBlock), 0, s, table, tiles, chunks, csum));
+        uint32_t *dtot = csum + (size_t)kBins * kColChunks;
+        LOR_LAUNCH("k_col_scan", 8.0 * kBins * chunks, s,
+                   hipLaunchKernelGGL(k_col_scan, dim3(kBins), dim3(kBlock), 0, s, csum, chunks, dtot));
+        LOR_LAUNCH("k_col_down", 2.0 * tbytes, s,
+                   hipLaunchKernelGGL(k_col_down, dim3(chunks), dim3(kBlock), 0, s, table, tiles, chunks, csum,
+                                      dtot));
+    }
     const double sbytes = (double)n * ((vi ? 2.0 : 1.0) * (sizeof(K) + 4) + (vi ? 0.0 : sizeof(K))) + tbytes;
     if (vi)
         LOR_LAUNCH("k_radix_scatter", sbytes, s,
