@@ -125,41 +125,6 @@ __global__ __launch_bounds__(kBlock) void k_lcp_window(const CH *__restrict__ t,
     }
 }
 
-struct __attribute__((packed, aligned(1))) Bytes16 {
-    uint32_t x, y, z, w;
-};
-
-// Common-prefix length of suffixes i and j (in symbols), knowing that the
-// first h symbols agree, at most cap.
-template <typename CH>
-__device__ __forceinline__ uint32_t extend(const CH *__restrict__ t, uint32_t n, uint32_t i, uint32_t j, uint32_t h,
-                                           uint32_t cap) {
-    constexpr uint32_t W = 16 / sizeof(CH), B = 8 * sizeof(CH);
-    const uint32_t lim = min(cap, n - max(i, j));
-    uint32_t batch = 1;   // one 16-byte step, then four at a time: their loads wait together
-    while (h < lim && lim - h >= batch * W) {
-        Bytes16 x[4], y[4];
-#pragma unroll
-        for (uint32_t c = 0; c < 4; ++c)
-            if (c < batch) {
-                x[c] = *reinterpret_cast<const Bytes16 *>(t + i + h + c * W);
-                y[c] = *reinterpret_cast<const Bytes16 *>(t + j + h + c * W);
-            }
-#pragma unroll
-        for (uint32_t c = 0; c < 4; ++c)
-            if (c < batch) {
-                const uint64_t d0 = ((uint64_t)(x[c].y ^ y[c].y) << 32) | (x[c].x ^ y[c].x);
-                if (d0) return h + c * W + (uint32_t)__builtin_ctzll(d0) / B;
-                const uint64_t d1 = ((uint64_t)(x[c].w ^ y[c].w) << 32) | (x[c].z ^ y[c].z);
-                if (d1) return h + c * W + W / 2 + (uint32_t)__builtin_ctzll(d1) / B;
-            }
-        h += batch * W;
-        batch = 4;
-    }
-    while (h < lim && t[i + h] == t[j + h]) ++h;
-    return h;
-}
-
 constexpr uint32_t kNoCap = 0xffffffffu;
 
 // PLCP of the unlinked sampled positions, and the links, 64 samples a word.
@@ -174,9 +139,9 @@ __global__ __launch_bounds__(kBlock) void k_plcp(const CH *__restrict__ t, uint3
         const uint32_t next = s + 1 < samples ? phi[s + 1] : kNoCap;
         uint32_t l = 0;
         if (j < n && j != i) {
-            l = extend(t, n, i, j, 0u, step);
+            l = dev::extend<CH, 4>(t, n, i, j, 0u, step);
             linked = l >= step && next < n && next == j + step;
-            if (l >= step && !linked) l = extend(t, n, i, j, step, kNoCap);
+            if (l >= step && !linked) l = dev::extend<CH, 4>(t, n, i, j, step, kNoCap);
         }
         if (!linked) plcp[s] = l;
     }
@@ -246,10 +211,10 @@ __global__ __launch_bounds__(kBlock) void k_lcp_finish(const CH *__restrict__ t,
             h = got - d;                     // same diagonal as the sample before: exact
         } else {
             h = min(max(v[k] & ~kMarked, got > d ? got - d : 0u), n - max(i, j));
-            if (h < to_next) h = extend(t, n, i, j, h, to_next);
+            if (h < to_next) h = dev::extend<CH, 4>(t, n, i, j, h, to_next);
             if (h >= to_next) {
                 if (c + 1 < samples && phi[c + 1] == j + to_next) h = to_next + sampled(c + 1);   // as the one behind
-                else h = extend(t, n, i, j, h, kNoCap);
+                else h = dev::extend<CH, 4>(t, n, i, j, h, kNoCap);
             }
         }
         lcp[r] = (int32_t)h;

@@ -365,5 +365,48 @@ __device__ __forceinline__ uint32_t block_exclusive_sum(uint32_t v, uint32_t *tm
     return base + inc - v;
 }
 
+struct __attribute__((packed, aligned(1))) Bytes16 {
+    uint32_t x, y, z, w;
+};
+
+struct NeverStop {
+    __device__ bool operator()() const { return false; }
+};
+
+// Common-prefix length of suffixes i and j of t[0..n) (in symbols), knowing
+// that the first h agree, at most cap. 16 bytes first, then BATCH times 16 a
+// step, so that a long comparison waits for memory once per step; stop() is
+// asked once per step and ends the comparison early when true.
+template <typename CH, int BATCH, typename Stop = NeverStop>
+__device__ __forceinline__ uint32_t extend(const CH *__restrict__ t, uint32_t n, uint32_t i, uint32_t j, uint32_t h,
+                                           uint32_t cap, Stop stop = Stop()) {
+    constexpr uint32_t W = 16 / sizeof(CH), B = 8 * sizeof(CH);
+    const uint32_t lim = min(cap, n - max(i, j));
+    uint32_t batch = 1;
+    while (h < lim && lim - h >= W) {
+        if (lim - h < batch * W) batch = 1;
+        Bytes16 x[BATCH], y[BATCH];
+#pragma unroll
+        for (uint32_t c = 0; c < (uint32_t)BATCH; ++c)
+            if (c < batch) {
+                x[c] = *reinterpret_cast<const Bytes16 *>(t + i + h + c * W);
+                y[c] = *reinterpret_cast<const Bytes16 *>(t + j + h + c * W);
+            }
+#pragma unroll
+        for (uint32_t c = 0; c < (uint32_t)BATCH; ++c)
+            if (c < batch) {
+                const uint64_t d0 = ((uint64_t)(x[c].y ^ y[c].y) << 32) | (x[c].x ^ y[c].x);
+                if (d0) return h + c * W + (uint32_t)__builtin_ctzll(d0) / B;
+                const uint64_t d1 = ((uint64_t)(x[c].w ^ y[c].w) << 32) | (x[c].z ^ y[c].z);
+                if (d1) return h + c * W + W / 2 + (uint32_t)__builtin_ctzll(d1) / B;
+            }
+        h += batch * W;
+        batch = BATCH;
+        if (stop()) return h;
+    }
+    while (h < lim && t[i + h] == t[j + h]) ++h;
+    return h;
+}
+
 }  // namespace dev
 }  // namespace lor

@@ -63,20 +63,19 @@ constexpr uint32_t kResTile = kBlock * kResItems;
 constexpr uint32_t kResWords = kResTile / 64;
 constexpr uint32_t kDeep = 256;               // symbols that resolve compares
 constexpr uint32_t kSettle = 2048;            // symbols that k_settle compares
-constexpr uint32_t kUnit = 64;                // 16-byte comparison steps per budget unit
+constexpr uint32_t kUnit = 32;                // 32-byte comparison steps per budget unit
 constexpr uint32_t kCodeBits = 15;
 constexpr uint32_t kExtent = (1u << (kCodeBits - 1)) - 1u;   // longest repeat a key describes
+constexpr uint32_t kRepeatSymbols = (64 - kCodeBits) / 3;    // next symbols of resolve's repeat keys
 constexpr uint32_t kKeyTile = 2048;           // positions per workgroup of the key kernels
 constexpr uint32_t kDirectRanks = 1u << 24;   // ranks as plain stores up to here (see kDirectIsa)
 constexpr int kMaxRounds = 4;                 // sorts of large groups before DC3 takes over
 constexpr int kMaxK = 16;
+constexpr int kMaxRefine = 5;                 // slots per thread of refine()
 
 // ------------------------------------------------------------ text access
 
-struct __attribute__((packed, aligned(1))) Bytes16 {
-    uint32_t x, y, z, w;
-};
-
+using dev::Bytes16;
 struct __attribute__((packed, aligned(1))) Bytes8 {
     uint32_t x, y;
 };
@@ -122,52 +121,96 @@ __device__ __forceinline__ uint64_t window8(const CH *__restrict__ t, uint32_t n
     return h;
 }
 
-// A budget for long comparisons: every kUnit steps a lane draws one unit; true
-// when the call should give up.
-__device__ __forceinline__ bool draw(uint32_t *hdr, uint32_t budget) {
-    const uint64_t m = __ballot(1);
-    const int lead = __builtin_ctzll(m);
-    uint32_t got = 0;
-    if ((int)dev::lane_id() == lead) got = atomicAdd(&hdr[kWordSpent], (uint32_t)__popcll(m));
-    got = (uint32_t)__shfl((int)got, lead, kWave);
-    if (got > budget) {
-        hdr[kWordAbort] = 1;
-        return true;
-    }
-    return __hip_atomic_load(&hdr[kWordAbort], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-}
-
-// Length of the common prefix of suffixes p and q, given that the first h
-// symbols agree, at most cap (or the end of the text).
-template <typename CH>
-__device__ __forceinline__ uint32_t common(const CH *__restrict__ t, uint32_t n, uint32_t p, uint32_t q, uint32_t h,
-                                           uint32_t cap, uint32_t *hdr, uint32_t budget) {
-    constexpr uint32_t W = 16 / sizeof(CH), B = 8 * sizeof(CH);
-    const uint32_t lim = min(cap, n - max(p, q));
+// A budget for long comparisons: every kUnit steps a lane draws one unit, and
+// gives up when they are spent (the call then goes to DC3).
+struct Budget {
+    uint32_t *hdr;
+    uint32_t units;
     uint32_t steps = 0;
-    while (h < lim && lim - h >= W) {
-        const Bytes16 x = *reinterpret_cast<const Bytes16 *>(t + p + h);
-        const Bytes16 y = *reinterpret_cast<const Bytes16 *>(t + q + h);
-        const uint64_t d0 = ((uint64_t)(x.y ^ y.y) << 32) | (x.x ^ y.x);
-        if (d0) return h + (uint32_t)__builtin_ctzll(d0) / B;
-        const uint64_t d1 = ((uint64_t)(x.w ^ y.w) << 32) | (x.z ^ y.z);
-        if (d1) return h + W / 2 + (uint32_t)__builtin_ctzll(d1) / B;
-        h += W;
-        if (hdr && (++steps % kUnit) == 0 && draw(hdr, budget)) return h;
+    __device__ bool operator()() {
+        if ((++steps % kUnit) != 0) return false;
+        const uint64_t m = __ballot(1);
+        const int lead = __builtin_ctzll(m);
+        uint32_t got = 0;
+        if ((int)dev::lane_id() == lead) got = atomicAdd(&hdr[kWordSpent], (uint32_t)__popcll(m));
+        got = (uint32_t)__shfl((int)got, lead, kWave);
+        if (got > units) {
+            hdr[kWordAbort] = 1;
+            return true;
+        }
+        return __hip_atomic_load(&hdr[kWordAbort], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
     }
-    while (h < lim && t[p + h] == t[q + h]) ++h;
-    return h;
-}
+};
 
-// Order of suffixes p and q (p != q) as far as `cap` symbols tell: -1, 1, or 0
-// when they share that many.
-template <typename CH>
-__device__ __forceinline__ int order(const CH *__restrict__ t, uint32_t n, uint32_t p, uint32_t q, uint32_t h,
-                                     uint32_t cap) {
-    const uint32_t l = common(t, n, p, q, h, cap, nullptr, 0);
-    if (l >= cap) return 0;
-    if (l >= n - max(p, q)) return p > q ? -1 : 1;
-    return t[p + l] < t[q + l] ? -1 : 1;
+// Refines classes of equal suffixes in LDS. A class lies inside a group of
+// slots [f, f + size) (group(l, &f) gives its size): cls[l] is the first place
+// of the class of slot l, key[l] >> 32 the symbols its members share. In every
+// step the members of a class compare their texts with its first member: a
+// member that differs after L symbols comes before it, the shorter L the
+// earlier, or after it, the shorter L the later; equal (L, direction) form the
+// classes of the next step. One comparison per member and step, instead of one
+// per pair: members of one tandem repeat all part in the first step. A member
+// that shares max(deep, shared + 64) symbols with the first stays in its class
+// for good. All threads of the workgroup call this; `again`: bit r set when
+// slot_of(r) is in a class to refine, r < rounds.
+template <typename CH, typename SlotOf, typename Group>
+__device__ __forceinline__ void refine(const CH *__restrict__ t, uint32_t n, uint32_t deep, int rounds, SlotOf slot_of,
+                                       Group group, const uint32_t *val, uint64_t *key, uint16_t *cls, uint32_t *flag,
+                                       uint32_t again) {
+    constexpr uint32_t kEqual = 0x40000000u, kTop = 0x7fffffffu;
+    for (;;) {
+        if (threadIdx.x == 0) *flag = 0;
+        __syncthreads();
+        if (again) *flag = 1;
+        __syncthreads();
+        if (!*flag) break;
+#pragma unroll 1
+        for (int r = 0; r < rounds; ++r) {
+            if (!((again >> r) & 1u)) continue;
+            const uint32_t l = slot_of(r);
+            uint32_t f;
+            group(l, &f);
+            const uint16_t c = cls[l];
+            uint32_t first = f;
+            while (cls[first] != c) ++first;   // l at the latest
+            uint32_t k = kEqual;
+            if (first != l) {
+                const uint32_t p = val[l], q = val[first], h = (uint32_t)(key[l] >> 32), cap = max(deep, h + 64u);
+                const uint32_t L = dev::extend<CH, 2>(t, n, p, q, h, cap);
+                if (L < cap) {
+                    const bool less = L >= n - max(p, q) ? p > q : t[p + L] < t[q + L];
+                    k = less ? L : kTop - L;
+                }
+            }
+            key[l] = (key[l] & 0xffffffff00000000ull) | k;
+        }
+        __syncthreads();
+        uint32_t next = 0, place[kMaxRefine];
+#pragma unroll
+        for (int r = 0; r < kMaxRefine; ++r) {
+            if (r >= rounds || !((again >> r) & 1u)) continue;
+            const uint32_t l = slot_of(r), mine = (uint32_t)key[l];
+            uint32_t f, less = 0, same = 0;
+            const uint32_t size = group(l, &f);
+            const uint16_t c = cls[l];
+            for (uint32_t q = f; q < f + size; ++q) {
+                if (cls[q] != c) continue;
+                less += (uint32_t)key[q] < mine;
+                same += (uint32_t)key[q] == mine;
+            }
+            place[r] = c + less;
+            if (same > 1 && mine != kEqual) next |= 1u << r;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kMaxRefine; ++r) {
+            if (r >= rounds || !((again >> r) & 1u)) continue;
+            const uint32_t l = slot_of(r), mine = (uint32_t)key[l];
+            cls[l] = (uint16_t)place[r];
+            if (mine != kEqual) key[l] = (uint64_t)(mine < kEqual ? mine : kTop - mine) << 32;
+        }
+        again = next;
+    }
 }
 
 // ------------------------------------------------------------------ texts
@@ -521,9 +564,10 @@ template <> struct StopAtSep<Shared> { static constexpr bool value = false; };
 template <typename X>
 __device__ __forceinline__ uint64_t repeat_key(const X &x, uint32_t q, uint32_t t, uint32_t ns, uint32_t *hdr,
                                                uint32_t budget) {
+    using CH = typename X::CH;
     uint32_t code = kExtent, e = x.n - q;
     if (q + t < x.n) {
-        e = min(e, t + common(x.t, x.n, q, q + t, (uint32_t)x.K - t, kExtent - t, hdr, budget));
+        e = min(e, t + dev::extend<CH, 2>(x.t, x.n, q, q + t, (uint32_t)x.K - t, kExtent - t, Budget{hdr, budget}));
         if (e < kExtent) code = (q + e >= x.n || x.t[q + e] < x.t[q + e - t]) ? e : 2 * kExtent + 1u - e;
     } else {
         code = e;
@@ -558,9 +602,7 @@ struct GroupKey {
 // are looked at by both workgroups. 8 text bytes behind the known prefix are
 // gathered into LDS for every tied rank; a rank's place is the number of
 // smaller ones in its group. Members that agree there too form a class, which
-// goes on with repeat keys (stage 0: a tandem repeat inside one short group
-// would cost a long comparison per pair of members otherwise) and at last
-// with whole texts.
+// goes on with repeat keys (stage 0) and at last with refine().
 // Stage 0 (32-bit keys of the sort) writes places shifted by the near
 // suffixes; stage 1 (64-bit keys of large groups) through `slots`. Larger
 // groups are marked in `large` and counted, with their heads, per tile.
@@ -677,14 +719,50 @@ __global__ __launch_bounds__(kBlock) void k_resolve(X x, GroupKey gk, const KT *
     }
     if (__any(again != 0) && lane == 0) s_again = 1;
     __syncthreads();
-    if (kFirst && s_again) {   // uniform
+    if (s_again) {   // uniform
+        if constexpr (kFirst) {
 #pragma unroll 1
-        for (int r = 0; r <= kResItems; ++r) {
-            if (!((again >> r) & 1u)) continue;
-            const uint32_t l = slot_of(r);
-            s_win[l] = repeat_key(x, s_val[l], period_at(x, s_val[l]), (64u - kCodeBits) / 3u, hdr, budget);
+            for (int r = 0; r <= kResItems; ++r) {
+                if (!((again >> r) & 1u)) continue;
+                const uint32_t l = slot_of(r);
+                s_win[l] = repeat_key(x, s_val[l], period_at(x, s_val[l]), kRepeatSymbols, hdr, budget);
+            }
+            __syncthreads();
+            uint32_t place[kResItems + 1], next = 0;
+            uint64_t mine[kResItems + 1];
+#pragma unroll
+            for (int r = 0; r <= kResItems; ++r) {
+                if (!((again >> r) & 1u)) continue;
+                const uint32_t l = slot_of(r);
+                uint32_t f, same = 0;
+                const uint32_t size = group(l, &f);
+                const uint16_t c = s_cls[l];
+                mine[r] = s_win[l];
+                place[r] = c;
+                for (uint32_t q = f; q < f + size; ++q) {
+                    if (s_cls[q] != c) continue;
+                    place[r] += s_win[q] < mine[r];
+                    same += s_win[q] == mine[r];
+                }
+                next |= (same > 1 ? 1u : 0u) << r;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r <= kResItems; ++r) {
+                if (!((again >> r) & 1u)) continue;
+                const uint32_t l = slot_of(r), c = (uint32_t)(mine[r] >> (3u * kRepeatSymbols));
+                s_cls[l] = (uint16_t)place[r];
+                s_win[l] = (uint64_t)max((uint32_t)x.K, c <= kExtent ? c : 2u * kExtent + 1u - c) << 32;
+            }
+            again = next;
+        } else {
+#pragma unroll
+            for (int r = 0; r <= kResItems; ++r)
+                if ((again >> r) & 1u)
+                    s_win[slot_of(r)] = (uint64_t)max((uint32_t)x.K, gk.reach(keys[rank_of(r)])) << 32;
         }
         __syncthreads();
+        refine(x.t, x.n, kDeep, kResItems + 1, slot_of, group, s_val, s_win, s_cls, &s_again, again);
     }
 
     const uint32_t sh0 = kFirst ? s_shift[0] : 0u, sh1 = kFirst ? s_shift[1] : 0u;
@@ -713,28 +791,10 @@ __global__ __launch_bounds__(kBlock) void k_resolve(X x, GroupKey gk, const KT *
         if (!valid || big) continue;
         uint32_t place = l, same = 0;                       // same: equal ones placed before this rank
         if (size > 1 && !kept) {
-            place = s_cls[l];
-            if ((again >> r) & 1u) {
-                const uint64_t mine = s_win[l];
-                uint32_t h = (uint32_t)x.K;
-                if constexpr (kFirst) {
-                    const uint32_t c = (uint32_t)(mine >> (3u * ((64u - kCodeBits) / 3u)));
-                    h = max(h, c <= kExtent ? c : 2u * kExtent + 1u - c);
-                } else {
-                    h = max(h, gk.reach(keys[e]));
-                }
-                const uint32_t cap = max(kDeep, h + 64u);
-                const uint16_t cls = s_cls[l];
-                for (uint32_t q = f; q < f + size; ++q) {
-                    if (q == l || s_cls[q] != cls) continue;
-                    const uint64_t o = s_win[q];
-                    int c = o < mine ? -1 : 1;
-                    if (o == mine) c = order(x.t, x.n, s_val[q], v, h, cap);
-                    place += c < 0;
-                    same += c == 0 && q < l;
-                }
-                place += same;
-            }
+            const uint16_t cls = s_cls[l];
+            place = cls;
+            for (uint32_t q = f; q < l; ++q) same += s_cls[q] == cls;
+            place += same;
         }
         const uint32_t o = base + place - kSmall;           // place in the sorted order
         if (o >= m) continue;
@@ -987,32 +1047,42 @@ template <typename X>
 __global__ __launch_bounds__(kBlock) void k_settle(X x, const uint32_t *__restrict__ was, uint32_t *__restrict__ open,
                                                    int32_t *__restrict__ sa, uint32_t *__restrict__ left) {
     __shared__ uint32_t s_bits[kRunWords], s_val[kRunTile + kSmall], s_any, s_left;
+    __shared__ uint64_t s_key[kRunTile + kSmall];
+    __shared__ uint16_t s_cls[kRunTile + kSmall];
+    static_assert(kRunItems <= kMaxRefine && kResItems + 1 <= kMaxRefine, "");
     const uint32_t base = blockIdx.x * kRunTile, tid = threadIdx.x;
     if (tid == 0) s_left = 0;
     if (!load_runs(was, x.n, base, s_bits, &s_any)) return;
     const RunTile runs{s_bits};
-    for (uint32_t l = tid; l < kRunTile + kSmall; l += kBlock) {
+    uint32_t again = 0;
+    auto slot_of = [&](int r) { return r * kBlock + tid; };
+    auto group = [&](uint32_t l, uint32_t *first) { return runs.run_of(l, first); };
+#pragma unroll
+    for (int r = 0; r < kRunItems; ++r) {
+        const uint32_t l = slot_of(r);
         uint32_t f;
-        s_val[l] = base + l < x.n && runs.run_of(l, &f) ? min((uint32_t)sa[base + l], x.n - 1u) : 0xffffffffu;
-    }
-    __syncthreads();
-    uint32_t mine_left = 0;
-    for (uint32_t l = tid; l < kRunTile + kSmall; l += kBlock) {
-        const uint32_t v = s_val[l];
-        if (v == 0xffffffffu) continue;
-        uint32_t f;
-        const uint32_t size = runs.run_of(l, &f);
-        uint32_t place = f, same = 0;
-        for (uint32_t q = f; q < f + size; ++q) {
-            if (q == l) continue;
-            const int c = order(x.t, x.n, s_val[q], v, kDeep, kSettle);
-            place += c < 0;
-            same += c == 0 && q < l;
+        if (l < kRunTile + kSmall && base + l < x.n && runs.run_of(l, &f)) {
+            s_val[l] = min((uint32_t)sa[base + l], x.n - 1u);
+            s_key[l] = (uint64_t)kDeep << 32;
+            s_cls[l] = (uint16_t)f;
+            again |= 1u << r;
         }
-        place += same;
-        const uint32_t slot = base + place;
+    }
+    const uint32_t mine = again;
+    __syncthreads();
+    refine(x.t, x.n, kSettle, kRunItems, slot_of, group, s_val, s_key, s_cls, &s_any, again);
+    uint32_t mine_left = 0;
+#pragma unroll
+    for (int r = 0; r < kRunItems; ++r) {
+        if (!((mine >> r) & 1u)) continue;
+        const uint32_t l = slot_of(r);
+        uint32_t f, same = 0;
+        runs.run_of(l, &f);
+        const uint16_t c = s_cls[l];
+        for (uint32_t q = f; q < l; ++q) same += s_cls[q] == c;
+        const uint32_t place = c + same, slot = base + place;
         if (slot >= x.n) continue;
-        sa[slot] = (int32_t)v;
+        sa[slot] = (int32_t)s_val[l];
         if (same) ++mine_left;
         else if (place != f) atomicAnd(&open[slot >> 5], ~(1u << (slot & 31u)));
     }
@@ -1156,7 +1226,7 @@ lor_status prefix_sa(const X &x, int bits, uint32_t near, int32_t *sa, Arena &ar
     *done = false;
     const uint32_t m = x.n - near;
     const uint32_t tiles = div_up(m ? m : 1, kResTile);
-    // 64 steps over two texts read about 32 lines, some 0.7 ns of the chip's
+    // 32 steps over two texts read about 32 lines, some 0.7 ns of the chip's
     // gather rate; DC3 takes 0.25 to 0.4 ns per suffix. At most about a third of
     // a DC3 run is spent before giving up.
     const uint32_t budget = x.n / 8 + 65536u;
