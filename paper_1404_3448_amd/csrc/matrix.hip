@@ -27,6 +27,16 @@
 //                 then (a second launch) of the chunk totals
 //   k_mx_ranks<0> best key of every (sequence, target) pair
 //   k_mx_ranks<1> the rank holding each best key writes its record
+//
+// The walks cost about 3.3 ps per rank and target, but only ranks inside long
+// matches can hold a record. For large inputs the LCPs between neighbouring
+// ranks of different sequences, over an eighth of the tiles, first give every
+// pair a match it certainly has (k_mx_bound), and the shortest of these over
+// all pairs, `bound`, is a length that every record reaches. Two suffixes that
+// share `bound` symbols or more have no smaller LCP between their ranks, so
+// ranks where neither the LCP before nor after reaches `bound` are dropped
+// (k_mx_count, k_mx_keep) and the walks run over the rest, a few per cent of
+// the ranks of a DNA text. 16 x 4M bases: 3.39 -> 0.45 ms.
 #include <climits>
 #include <vector>
 
@@ -450,11 +460,141 @@ __global__ __launch_bounds__(kBlock) void k_mx_init(uint32_t count, unsigned lon
     }
 }
 
+// ------------------------------------------------------------- dropping ranks
+
+constexpr uint32_t kMxSample = 8;                  // k_mx_bound looks at every 8th tile
+constexpr uint32_t kMxPairsLds = 128;              // largest k whose pair table fits LDS (64 KB)
+
+// bound[a * k + b], a < b: a length that sequences a and b share.
+template <bool LDS>
+__global__ __launch_bounds__(kBlock) void k_mx_bound(const int32_t *__restrict__ sa, const int32_t *__restrict__ lcp,
+                                                     uint32_t n, const int32_t *__restrict__ start, uint32_t k,
+                                                     uint32_t *__restrict__ bound) {
+    extern __shared__ uint32_t s_pair[];
+    __shared__ int32_t s_start[kMaxSeqs + 1];
+    load_starts(start, k, s_start);
+    if constexpr (LDS) {
+        for (uint32_t q = threadIdx.x; q < k * k; q += kBlock)
+            s_pair[q] = __hip_atomic_load(&bound[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+    }
+    const uint32_t base = blockIdx.x * kMxSample * kMxTile;
+#pragma unroll 4
+    for (uint32_t i = 0; i < kMxItems; ++i) {
+        const uint32_t r = base + i * kBlock + threadIdx.x;
+        if (r == 0 || r >= n) continue;
+        const uint32_t x = (uint32_t)sa[r - 1], y = (uint32_t)sa[r];
+        const int32_t a = seq_of(s_start, k, x), b = seq_of(s_start, k, y);
+        if (a == b) continue;
+        // an LCP beyond a separator would not count
+        const int32_t m = min(lcp[r], (int32_t)min((uint32_t)s_start[a + 1] - 1u - x, (uint32_t)s_start[b + 1] - 1u - y));
+        if (m <= 0) continue;
+        const uint32_t q = (uint32_t)min(a, b) * k + (uint32_t)max(a, b);
+        if constexpr (LDS) {
+            if ((uint32_t)m > s_pair[q]) atomicMax(&s_pair[q], (uint32_t)m);
+        } else {
+            if ((uint32_t)m > __hip_atomic_load(&bound[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                atomicMax(&bound[q], (uint32_t)m);
+        }
+    }
+    if constexpr (LDS) {
+        __syncthreads();
+        for (uint32_t q = threadIdx.x; q < k * k; q += kBlock)
+            if (s_pair[q] > __hip_atomic_load(&bound[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                atomicMax(&bound[q], s_pair[q]);
+    }
+}
+
+// The smallest bound over all pairs (one workgroup).
+__global__ __launch_bounds__(kBlock) void k_mx_least(const uint32_t *__restrict__ bound, uint32_t k,
+                                                     uint32_t *__restrict__ least) {
+    __shared__ uint32_t s_min;
+    if (threadIdx.x == 0) s_min = 0xffffffffu;
+    __syncthreads();
+    uint32_t m = 0xffffffffu;
+    for (uint32_t q = threadIdx.x; q < k * k; q += kBlock)
+        if (q / k < q % k) m = min(m, bound[q]);
+    atomicMin(&s_min, m);
+    __syncthreads();
+    if (threadIdx.x == 0) *least = s_min;
+}
+
+// Rank r stays when the LCP with the rank before or after it reaches L. Kept
+// ranks per tile; L == 0 keeps all.
+__device__ __forceinline__ bool mx_keeps(const int32_t *__restrict__ lcp, uint32_t n, uint32_t r, int32_t L, int32_t at) {
+    return r < n && (at >= L || (r + 1 < n && lcp[r + 1] >= L));
+}
+
+__global__ __launch_bounds__(kBlock) void k_mx_count(const int32_t *__restrict__ lcp, uint32_t n,
+                                                     const uint32_t *__restrict__ least, uint64_t *__restrict__ kept,
+                                                     uint32_t *__restrict__ count, uint32_t *__restrict__ total) {
+    __shared__ uint32_t s_n;
+    if (threadIdx.x == 0) s_n = 0;
+    __syncthreads();
+    const int32_t L = (int32_t)*least;
+    const uint32_t base = blockIdx.x * kMxTile;
+    uint32_t c = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < kMxItems; ++i) {
+        const uint32_t r = base + i * kBlock + threadIdx.x;
+        const int32_t at = r < n ? lcp[r] : -1;
+        const uint64_t m = __ballot(mx_keeps(lcp, n, r, L, at));
+        if ((threadIdx.x & 63u) == 0) {
+            kept[(base + i * kBlock + threadIdx.x) >> 6] = m;
+            c += (uint32_t)__popcll(m);
+        }
+    }
+    if (c) atomicAdd(&s_n, c);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        count[blockIdx.x] = s_n;
+        if (s_n) atomicAdd(total, s_n);
+    }
+}
+
+// The kept ranks in order; the first of each run of them gets LCP 0, so
+// matches stay inside runs.
+__global__ __launch_bounds__(kBlock) void k_mx_keep(const int32_t *__restrict__ sa, const int32_t *__restrict__ lcp,
+                                                    uint32_t n, const uint32_t *__restrict__ least,
+                                                    const uint64_t *__restrict__ kept,
+                                                    const uint32_t *__restrict__ first, uint32_t total,
+                                                    int32_t *__restrict__ sa_out, int32_t *__restrict__ lcp_out) {
+    constexpr uint32_t kWords = kMxTile / 64;
+    __shared__ uint32_t s_below[kWords];
+    const uint32_t base = blockIdx.x * kMxTile;
+    if (threadIdx.x < kWords) {   // one wave
+        const uint32_t c = (uint32_t)__popcll(kept[base / 64 + threadIdx.x]);
+        s_below[threadIdx.x] = dev::wave_inclusive_sum(c) - c;
+    }
+    static_assert(kWords == kWave, "one lane per word");
+    __syncthreads();
+    const int32_t L = (int32_t)*least;
+    const uint32_t at = first[blockIdx.x];
+    for (uint32_t i = 0; i < kMxItems; ++i) {
+        const uint32_t l = i * kBlock + threadIdx.x, r = base + l;
+        const uint64_t m = kept[r >> 6], bit = 1ull << (r & 63u);
+        if (!(m & bit)) continue;   // bits past n are 0
+        const uint32_t o = at + s_below[l >> 6] + (uint32_t)__popcll(m & (bit - 1ull));
+        if (o >= total) continue;   // never with consistent counts
+        const int32_t v = lcp[r];
+        sa_out[o] = sa[r];
+        lcp_out[o] = v >= L ? v : 0;
+    }
+}
+
+// Dropping pays from here (n x k): its passes and its read-back take about
+// 150 us, the walks 3.3 ps per rank and target.
+constexpr uint64_t kMxDropWork = 100'000'000;
+constexpr uint32_t kMxDropShare = 4;               // and when at most 1/4 of the ranks stay
+
 struct MxLayout {
     int32_t *start;
     unsigned long long *best;
     Up *tu, *cu, *su;
     Dn *td, *cd, *sd;
+    uint32_t *bound, *count, *stmp;   // dropping ranks (null when it cannot pay)
+    uint64_t *kept;
+    int32_t *sa, *lcp;
 };
 
 lor_status mx_carve(Arena &ar, uint64_t n, uint32_t k, MxLayout *L) {
@@ -468,7 +608,50 @@ lor_status mx_carve(Arena &ar, uint64_t n, uint32_t k, MxLayout *L) {
     LOR_TAKE(ar, Dn, (size_t)chunks * k, L->cd);
     LOR_TAKE(ar, Up, k, L->su);
     LOR_TAKE(ar, Dn, k, L->sd);
+    L->bound = nullptr;
+    if (n * k >= kMxDropWork && k > 1) {
+        LOR_TAKE(ar, uint32_t, (size_t)k * k + 2, L->bound);   // then: least bound, kept ranks
+        LOR_TAKE(ar, uint64_t, (size_t)tiles * (kMxTile / 64), L->kept);
+        LOR_TAKE(ar, uint32_t, tiles, L->count);
+        LOR_TAKE(ar, uint32_t, kScanTmpWords, L->stmp);
+        LOR_TAKE(ar, int32_t, n / kMxDropShare, L->sa);
+        LOR_TAKE(ar, int32_t, n / kMxDropShare, L->lcp);
+    }
     if (chunks > kMxChunk) return LOR_EINVAL;   // n < 2^31 keeps chunks <= 512
+    return LOR_OK;
+}
+
+// Replaces (sa, lcp, n) by the ranks that can hold a record, when they are few.
+lor_status mx_drop(const MxLayout &L, uint32_t k, const int32_t **sa, const int32_t **lcp, uint32_t *n,
+                   hipStream_t s) {
+    const uint32_t tiles = div_up(*n, kMxTile), pairs = k * k;
+    uint32_t *words = L.bound + pairs;
+    LOR_TRY(zero_words(L.bound, pairs + 2, s));
+    const dim3 grid(div_up(tiles, kMxSample));
+    if (k <= kMxPairsLds)
+        LOR_LAUNCH("k_mx_bound", 8.0 * *n / kMxSample, s,
+                   hipLaunchKernelGGL(k_mx_bound<true>, grid, dim3(kBlock), pairs * sizeof(uint32_t), s, *sa, *lcp, *n,
+                                      L.start, k, L.bound));
+    else
+        LOR_LAUNCH("k_mx_bound", 8.0 * *n / kMxSample, s,
+                   hipLaunchKernelGGL(k_mx_bound<false>, grid, dim3(kBlock), 0, s, *sa, *lcp, *n, L.start, k, L.bound));
+    LOR_LAUNCH("k_mx_least", 4.0 * pairs, s,
+               hipLaunchKernelGGL(k_mx_least, dim3(1), dim3(kBlock), 0, s, L.bound, k, words));
+    LOR_LAUNCH("k_mx_count", 4.0 * *n, s,
+               hipLaunchKernelGGL(k_mx_count, dim3(tiles), dim3(kBlock), 0, s, *lcp, *n, words, L.kept, L.count,
+                                  words + 1));
+    uint32_t h[2];
+    LOR_HIP(hipMemcpyAsync(h, words, sizeof(h), hipMemcpyDeviceToHost, s));
+    LOR_HIP(hipStreamSynchronize(s));
+    // no pair without a match (records of length 0 need every rank), and few ranks
+    if (h[0] == 0 || h[0] == 0xffffffffu || h[1] == 0 || h[1] > *n / kMxDropShare) return LOR_OK;
+    LOR_TRY(scan_exclusive(L.count, tiles, L.stmp, nullptr, s));
+    LOR_LAUNCH("k_mx_keep", 0.125 * *n + 16.0 * h[1], s,
+               hipLaunchKernelGGL(k_mx_keep, dim3(tiles), dim3(kBlock), 0, s, *sa, *lcp, *n, words, L.kept, L.count,
+                                  h[1], L.sa, L.lcp));
+    *sa = L.sa;
+    *lcp = L.lcp;
+    *n = h[1];
     return LOR_OK;
 }
 
@@ -496,12 +679,12 @@ lor_status overlap_matrix(const int32_t *sa, const int32_t *lcp, uint32_t n, con
     ar.top = kHeaderBytes;
     MxLayout L;
     LOR_TRY(mx_carve(ar, n, k, &L));
-    const uint32_t tiles = div_up(n ? n : 1, kMxTile);
-    const uint32_t chunks = div_up(tiles, kMxChunk);
     LOR_HIP(hipMemcpyAsync(L.start, h_start.data(), (k + 1) * sizeof(int32_t), hipMemcpyHostToDevice, s));
     LOR_LAUNCH("k_mx_init", 40.0 * k * k, s,
                hipLaunchKernelGGL(k_mx_init, dim3(grid_for((uint64_t)k * k)), dim3(kBlock), 0, s, k * k, L.best, out));
     if (n > 0 && k > 1) {
+        if (L.bound) LOR_TRY(mx_drop(L, k, &sa, &lcp, &n, s));
+        const uint32_t tiles = div_up(n, kMxTile), chunks = div_up(tiles, kMxChunk);
         const bool vec = ((reinterpret_cast<uintptr_t>(sa) | reinterpret_cast<uintptr_t>(lcp)) & 15u) == 0;
         LOR_LAUNCH("k_mx_tiles", 8.0 * n, s,
                    hipLaunchKernelGGL(k_mx_tiles, dim3(tiles), dim3(kBlock), 0, s, sa, lcp, n, L.start, k, vec,

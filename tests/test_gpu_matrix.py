@@ -186,3 +186,51 @@ def test_matrix_across_chunks_and_unaligned():
             assert np.array_equal(seqs[a][op:op + L], seqs[b][oq:oq + L]), (a, b)
             assert op == first_shared_window(seqs[a], seqs[b], L), (a, b)
             assert recs[b * k + a][0] == L
+
+
+def mutated_copies(rng, n, k):
+    a = synth.gc40_bases(rng, n)
+    return [synth.mutate(rng, a, 0.02) for _ in range(k)]
+
+
+@pytest.mark.parametrize("kind", ["noncoding", "uniform", "copies", "empty", "ends"])
+def test_matrix_where_ranks_can_be_dropped(kind):
+    """26 sequences of 160,000 bases (k x N above 10^8, where ranks outside long
+    matches are dropped first): texts that drop nearly all ranks, texts that
+    keep too many (copies) or have a pair without a match (empty), and matches
+    at the ends of sequences. Lengths and first offsets equal the plain pair
+    path's for every pair, and both offsets hold the same substring."""
+    k, n = 26, 160_000
+    say("matrix drop", kind)
+    rng = np.random.default_rng(26)
+    if kind == "copies":
+        seqs = mutated_copies(rng, n, k)
+    elif kind == "uniform":
+        seqs = [synth.uniform_bases(rng, n + 7 * j) for j in range(k)]
+    else:
+        seqs = [synth.noncoding_like(rng, n + 7 * j) for j in range(k)]
+    if kind == "empty":
+        seqs[3] = np.zeros(0, np.uint8)
+    if kind == "ends":
+        tail = synth.uniform_bases(rng, 900)
+        for j in range(k):
+            seqs[j][-900 + 10 * j:] = tail[:900 - 10 * j]
+            seqs[j][:400] = tail[:400]
+    M, single = matrix(seqs)
+    step = 1 if kind in ("noncoding", "ends") else 5
+    for a in range(k):
+        for b in range(a + 1, k, step):
+            cat = np.concatenate([seqs[a], seqs[b]])
+            offs = np.array([0, seqs[a].size, seqs[a].size + seqs[b].size], np.int64)
+            L, sp, op, sq, oq = lor.longest_overlap_region(torch.from_numpy(cat).cuda(), offs)["overlap"]
+            rec = M[a][b]
+            assert rec[0] == L and M[b][a][0] == L, (a, b, rec, L)
+            if L == 0:
+                assert rec == (0, -1, -1, -1, -1)
+                continue
+            assert (sp, sq) == (0, 1) and rec[1:4] == (a, op, b), (a, b, rec, op)
+            word = seqs[a][op:op + L]
+            assert np.array_equal(seqs[b][rec[4]:rec[4] + L], word), (a, b)
+            back = M[b][a]
+            assert np.array_equal(seqs[b][back[2]:back[2] + L], seqs[a][back[4]:back[4] + L]), (a, b)
+    assert max(r[0] for row in M for r in row) == single[0]
