@@ -54,12 +54,12 @@ __device__ __forceinline__ uint64_t level_offset_dev(uint64_t n, int level);
 
 constexpr int kStFusedTop = 9;              // levels 1..9 are built from registers (halo < 512 entries)
 constexpr int kStOut = 16;                  // outputs per lane in fused levels (a wave: 64 kStOut entries)
-constexpr int kStIn = kStOut + (1 << (kStFusedTop - 6));   // entries loaded per lane: the outputs plus the halo
-constexpr uint32_t kStWave = kWave * kStOut;
+constexpr int kStOutSmall = 4;              // the same for tables that would leave most of the chip idle
+constexpr uint32_t kStFullWaves = 2048;     // waves from which the large shapes of the level kernels pay
 constexpr uint32_t kRmqBlock = 64;          // LCP entries per block of the compact table
 
 // Levels 1 .. nl (nl <= kStFusedTop) from level 0 (`prev`, prev_count
-// entries), one wave per segment of kStWave outputs, with no LDS and no
+// entries), one wave per segment of 64 OUT outputs, with no LDS and no
 // barriers. Lane l holds entries i0 + 64 m + l (m < kStIn) of the current
 // level in v[m], so the partner of an entry at distance half lies in
 // register m + half / 64 of the same lane when half >= 64, and otherwise in
@@ -71,12 +71,14 @@ constexpr uint32_t kRmqBlock = 64;          // LCP entries per block of the comp
 // levels 1-9, 5.6 ms; levels 1-10 here 7.6 ms (8 outputs per lane: 7.2 ms,
 // 24 or 32: 22-24 ms, fewer waves in flight); levels 1-10 from LDS tiles
 // with two barriers per level 9.5 ms.
+template <int OUT>
 __global__ __launch_bounds__(kBlock) void k_st_fused(const int32_t *__restrict__ prev, uint32_t prev_count,
                                                      uint32_t n, int nl, int32_t *__restrict__ table,
                                                      const uint32_t *__restrict__ hdr) {
+    constexpr int kStIn = OUT + (1 << (kStFusedTop - 6));   // entries loaded per lane: the outputs plus the halo
     const bool narrow = hdr != nullptr && hdr[0] <= 65535u;
     const uint32_t lane = threadIdx.x & 63u;
-    const uint64_t w0 = ((uint64_t)blockIdx.x * (kBlock / kWave) + (threadIdx.x >> 6)) * kStWave;
+    const uint64_t w0 = ((uint64_t)blockIdx.x * (kBlock / kWave) + (threadIdx.x >> 6)) * (uint64_t)(kWave * OUT);
     if (w0 >= n) return;
     const uint64_t i0 = w0 + lane;
     // entries left from this lane's first one: loads and stores test m * 64 against them
@@ -110,12 +112,12 @@ __global__ __launch_bounds__(kBlock) void k_st_fused(const int32_t *__restrict__
         if (narrow) {
             uint16_t *dst = reinterpret_cast<uint16_t *>(table) + at;
 #pragma unroll
-            for (int m = 0; m < kStOut; ++m)
+            for (int m = 0; m < OUT; ++m)
                 if (m * (int64_t)kWave < left) dst[m * kWave] = (uint16_t)v[m];
         } else {
             int32_t *dst = table + at;
 #pragma unroll
-            for (int m = 0; m < kStOut; ++m)
+            for (int m = 0; m < OUT; ++m)
                 if (m * (int64_t)kWave < left) dst[m * kWave] = v[m];
         }
     }
@@ -309,54 +311,83 @@ __device__ __forceinline__ const int32_t *clevel(const Compact &C, int k) {
     return k == 0 ? C.table : C.table + C.nb + level_offset_dev(C.nb, k);
 }
 
-// Smallest value of lcp[a..b] (a <= b) and its leftmost position.
-__device__ __forceinline__ int32_t scan_min(const int32_t *__restrict__ lcp, uint32_t a, uint32_t b, uint32_t *pos) {
-    int32_t best = INT_MAX;
-    uint32_t bp = a;
-    for (uint32_t x = a; x <= b; ++x) {
-        const int32_t y = lcp[x];
-        if (y < best) {
-            best = y;
-            bp = x;
-        }
-    }
-    *pos = bp;
-    return best;
+// kQueryLanes lanes answer one query together: they read the two end blocks of
+// LCP 16 entries at a time with all loads in flight, and find a block in the
+// table 4 levels a step. One lane per query read up to 128 entries and 15
+// table entries one after another (31 us for 10,000 queries of 2.3M entries).
+constexpr uint32_t kQueryLanes = 16;
+constexpr uint32_t kPerLane = kRmqBlock / kQueryLanes;
+
+// (value, position) packed so that the minimum is the leftmost smallest.
+__device__ __forceinline__ uint64_t min_at(int32_t v, uint32_t pos) {
+    return ((uint64_t)((uint32_t)v ^ 0x80000000u) << 32) | pos;
+}
+constexpr uint64_t kNoEntry = ~0ull;
+
+// First lane of the group (0..kQueryLanes) whose predicate holds; kQueryLanes: none.
+__device__ __forceinline__ uint32_t first_lane(bool pred) {
+    const uint32_t base = (threadIdx.x & 63u) & ~(kQueryLanes - 1u);
+    const uint32_t m = (uint32_t)(__ballot(pred) >> base) & ((1u << kQueryLanes) - 1u);
+    return m ? (uint32_t)__builtin_ctz(m) : kQueryLanes;
 }
 
 __device__ int32_t range_min_compact(const Compact &C, uint32_t lo, uint32_t hi, bool want_pos, int32_t *pos) {
-    const uint32_t bl = lo / kRmqBlock, bh = hi / kRmqBlock;
-    uint32_t p;
-    if (bh - bl <= 1) {
-        const int32_t v = scan_min(C.lcp, lo, hi, &p);
-        *pos = (int32_t)p;
+    const uint32_t bl = lo / kRmqBlock, bh = hi / kRmqBlock, sub = threadIdx.x & (kQueryLanes - 1u);
+    int32_t l[kPerLane], r[kPerLane];
+#pragma unroll
+    for (uint32_t j = 0; j < kPerLane; ++j) {
+        const uint32_t x = bl * kRmqBlock + j * kQueryLanes + sub, y = bh * kRmqBlock + j * kQueryLanes + sub;
+        l[j] = x >= lo && x <= hi ? C.lcp[x] : INT_MAX;
+        r[j] = bh > bl && y <= hi ? C.lcp[y] : INT_MAX;
+    }
+    const uint32_t a = bl + 1, c = bh - 1;   // whole blocks in between
+    const bool mid = bh - bl >= 2;
+    const int k = mid ? 31 - __builtin_clz(c - a + 1) : 0;
+    const uint32_t second = c + 1 - (1u << k);
+    const int32_t ml = mid ? clevel(C, k)[a] : INT_MAX, mr = mid ? clevel(C, k)[second] : INT_MAX;
+    uint64_t kl = kNoEntry, kr = kNoEntry;
+#pragma unroll
+    for (uint32_t j = 0; j < kPerLane; ++j) {
+        const uint32_t x = bl * kRmqBlock + j * kQueryLanes + sub, y = bh * kRmqBlock + j * kQueryLanes + sub;
+        if (x >= lo && x <= hi) kl = min(kl, min_at(l[j], x));
+        if (bh > bl && y <= hi) kr = min(kr, min_at(r[j], y));
+    }
+#pragma unroll
+    for (uint32_t o = kQueryLanes / 2; o > 0; o >>= 1) {
+        kl = min(kl, (uint64_t)__shfl_xor((unsigned long long)kl, o, kQueryLanes));
+        kr = min(kr, (uint64_t)__shfl_xor((unsigned long long)kr, o, kQueryLanes));
+    }
+    const int32_t vm = min(ml, mr);
+    const uint64_t ends = min(kl, kr);
+    const int32_t ve = (int32_t)((uint32_t)(ends >> 32) ^ 0x80000000u);
+    const int32_t v = mid ? min(vm, ve) : ve;
+    const int32_t vl = (int32_t)((uint32_t)(kl >> 32) ^ 0x80000000u);   // the left end always holds lo
+    if (!want_pos) return v;
+    if (!mid || vl == v || vm != v) {
+        *pos = (int32_t)(uint32_t)(vl == v ? kl : kr);
         return v;
     }
-    uint32_t pl, pr;
-    const int32_t vl = scan_min(C.lcp, lo, (bl + 1) * kRmqBlock - 1, &pl);
-    const int32_t vr = scan_min(C.lcp, bh * kRmqBlock, hi, &pr);
-    const uint32_t a = bl + 1, c = bh - 1;   // whole blocks in between
-    const int k = 31 - __builtin_clz(c - a + 1);
-    const int32_t *lv = clevel(C, k);
-    const int32_t vm = min(lv[a], lv[c + 1 - (1u << k)]);
-    const int32_t v = min(vl, min(vm, vr));
-    if (want_pos) {
-        if (vl == v) {
-            *pos = (int32_t)pl;
-        } else if (vm == v) {
-            uint32_t b = a;   // leftmost block whose minimum is v
-            for (int kk = k; kk >= 0; --kk) {
-                const uint32_t w = 1u << kk;
-                if (b + w - 1 <= c && clevel(C, kk)[b] > v) b += w;
-            }
-            uint32_t x = b * kRmqBlock;
-            const uint32_t xe = x + kRmqBlock - 1;   // the block holds v; bounded all the same
-            while (x < xe && C.lcp[x] != v) ++x;
-            *pos = (int32_t)x;
-        } else {
-            *pos = (int32_t)pr;
+    // leftmost block whose minimum is v: in the first window when that holds
+    // it, then in the first of its halves, quarters, ... that do
+    uint32_t b = ml == v ? a : second;
+    for (int kk = k; kk > 0;) {
+        const int step = kk < 4 ? kk : 4;
+        kk -= step;
+        const bool in = sub < (1u << step) && clevel(C, kk)[b + (sub << kk)] == v;
+        b += (first_lane(in) & ((1u << step) - 1u)) << kk;
+    }
+    uint32_t at = b * kRmqBlock;
+    bool found = false;
+#pragma unroll
+    for (uint32_t j = 0; j < kPerLane; ++j) {
+        const uint32_t x = b * kRmqBlock + j * kQueryLanes;
+        const uint32_t f = first_lane(C.lcp[x + sub] == v);   // a whole block: inside the array
+        if (!found && f < kQueryLanes) {
+            at = x + f;
+            found = true;
         }
     }
+    *pos = (int32_t)at;
     return v;
 }
 
@@ -375,7 +406,8 @@ __global__ __launch_bounds__(kBlock) void k_query_compact(Compact C, const int32
                                                           const int32_t *__restrict__ qj, uint32_t nq,
                                                           int32_t *__restrict__ out_min,
                                                           int32_t *__restrict__ out_arg) {
-    for (uint32_t q = blockIdx.x * kBlock + threadIdx.x; q < nq; q += gridDim.x * kBlock) {
+    for (uint64_t q = ((uint64_t)blockIdx.x * kBlock + threadIdx.x) / kQueryLanes; q < nq;
+         q += (uint64_t)gridDim.x * (kBlock / kQueryLanes)) {
         const int32_t a = qi[q], b = qj[q];
         int32_t v = -1, pos = -1;
         if (mode == 0) {
@@ -392,8 +424,10 @@ __global__ __launch_bounds__(kBlock) void k_query_compact(Compact C, const int32
                 }
             }
         }
-        out_min[q] = v;
-        if (out_arg) out_arg[q] = pos;
+        if ((threadIdx.x & (kQueryLanes - 1u)) == 0) {
+            out_min[q] = v;
+            if (out_arg) out_arg[q] = pos;
+        }
     }
 }
 
@@ -425,7 +459,7 @@ lor_status rmq_queries_compact(const int32_t *table, uint32_t n, int levels, con
     if (nq == 0) return LOR_OK;
     Compact C{lcp, table, n, (uint32_t)rmq_compact_blocks(n), levels};
     LOR_LAUNCH("k_query_compact", (double)nq * (mode ? 28 : 20), s,
-               hipLaunchKernelGGL(k_query_compact, dim3(grid_for(nq)), dim3(kBlock), 0, s, C, isa, mode, qi, qj, nq,
+               hipLaunchKernelGGL(k_query_compact, dim3(grid_for((uint64_t)nq * kQueryLanes)), dim3(kBlock), 0, s, C, isa, mode, qi, qj, nq,
                                   min_out, argmin_out));
     return LOR_OK;
 }
@@ -462,27 +496,37 @@ lor_status rmq_build_levels(const int32_t *lcp, uint32_t n, int32_t *table, int 
         const int nl = min(levels, kStFusedTop);
         double bytes = 4.0 * n;
         for (int l = 1; l <= nl; ++l) bytes += (double)eb * (n - (1u << l) + 1u);
-        const uint32_t waves = div_up(n, kStWave);
-        LOR_LAUNCH("k_st_fused", bytes, s,
-                   hipLaunchKernelGGL(k_st_fused, dim3(div_up(waves, kBlock / kWave)), dim3(kBlock), 0, s, lcp, n,
-                                      n, nl, table, hdr));
+        // 36,652 block minima: 11 us with 16 outputs per lane (36 waves), 7 us with 4
+        const uint32_t waves = div_up(n, kWave * kStOut), small = div_up(n, kWave * kStOutSmall);
+        if (waves >= kStFullWaves)
+            LOR_LAUNCH("k_st_fused", bytes, s,
+                       hipLaunchKernelGGL(k_st_fused<kStOut>, dim3(div_up(waves, kBlock / kWave)), dim3(kBlock), 0, s,
+                                          lcp, n, n, nl, table, hdr));
+        else
+            LOR_LAUNCH("k_st_fused", bytes, s,
+                       hipLaunchKernelGGL(k_st_fused<kStOutSmall>, dim3(div_up(small, kBlock / kWave)), dim3(kBlock), 0,
+                                          s, lcp, n, n, nl, table, hdr));
         k = nl + 1;
     }
     while (k <= levels) {
         // levels k .. k+nl-1 from level k-1, down columns h = 2^(k-1) apart
         const int nl = min(kColLevels, levels - k + 1);
         const uint64_t h = 1ull << (k - 1);
-        const uint32_t qcols = (uint32_t)(h / (kWave * kColGroups));
         const uint64_t rows = div_up((uint64_t)n - 2 * h + 1, h);   // rows holding level-k outputs
         const uint32_t rblocks = (uint32_t)div_up(rows, (uint64_t)kColRows);
+        // one group of columns per wave while 8 leave most of the chip idle
+        const bool full = h / (kWave * kColGroups) * rblocks >= kStFullWaves;
+        const uint32_t qcols = (uint32_t)(h / (kWave * (full ? kColGroups : 1)));
         const uint64_t waves = (uint64_t)qcols * rblocks;
         const dim3 grid((uint32_t)div_up(waves, (uint64_t)(kBlock / kWave)));
         double bytes = (double)eb * (n - h + 1);
         for (int a = 0; a < nl; ++a) bytes += (double)eb * (n - (1u << (k + a)) + 1u);
 #define LOR_COLS(NL)                                                                                     \
     LOR_LAUNCH("k_st_cols", bytes, s,                                                                    \
-               hipLaunchKernelGGL((k_st_cols<NL, kColRows, kColGroups>), grid, dim3(kBlock), 0, s, table, hdr, n, \
-                                  k, qcols, rblocks))
+               if (full) hipLaunchKernelGGL((k_st_cols<NL, kColRows, kColGroups>), grid, dim3(kBlock), 0, s, table,  \
+                                            hdr, n, k, qcols, rblocks);                                        \
+               else hipLaunchKernelGGL((k_st_cols<NL, kColRows, 1>), grid, dim3(kBlock), 0, s, table, hdr, n, k,     \
+                                       qcols, rblocks))
         static_assert(kColLevels == 3, "one launch form per level count up to kColLevels");
         if (nl == 3) LOR_COLS(3);
         else if (nl == 2) LOR_COLS(2);
