@@ -15,8 +15,8 @@
 //   summarised independently (head = part of a run begun earlier, tail =
 //   last open run, best = best pair of the runs closed inside) and combined
 //   in rank order by an associative rule: a workgroup tree per tile, tiles
-//   in order inside a workgroup, then one workgroup over the workgroup
-//   results. A tile where no LCP reaches L holds only one-suffix runs; its
+//   in order inside a workgroup, then the last workgroup to finish over all
+//   workgroup results. A tile where no LCP reaches L holds only one-suffix runs; its
 //   summary needs the last suffix alone, so such tiles read only LCP.
 #include <climits>
 
@@ -181,6 +181,17 @@ __device__ void block_reduce_chunks(ChunkSum *s, ChunkSum mine) {
     }
 }
 
+// A summary another workgroup wrote, past this XCD's L2.
+__device__ __forceinline__ ChunkSum load_chunk(const ChunkSum *p) {
+    ChunkSum c;
+    const uint32_t *s = reinterpret_cast<const uint32_t *>(p);
+    uint32_t *d = reinterpret_cast<uint32_t *>(&c);
+#pragma unroll
+    for (uint32_t i = 0; i < sizeof(ChunkSum) / 4; ++i)
+        d[i] = __hip_atomic_load(s + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return c;
+}
+
 // One workgroup per group of `per` tiles. First every tile is
 // checked for an LCP >= L with all its loads in flight at once; tiles
 // without one (nearly all) hold only one-suffix runs and are summarised by
@@ -188,11 +199,13 @@ __device__ void block_reduce_chunks(ChunkSum *s, ChunkSum mine) {
 // per-rank path. The tile summaries are then combined in rank order.
 __global__ __launch_bounds__(kBlock) void k_runs(const int32_t *__restrict__ sa, const int32_t *__restrict__ lcp,
                                                  uint32_t n, SeqStarts st, uint32_t per,
-                                                 const uint32_t *__restrict__ Lp, ChunkSum *__restrict__ out) {
+                                                 const uint32_t *__restrict__ Lp, ChunkSum *__restrict__ out,
+                                                 uint32_t *__restrict__ done, uint32_t *__restrict__ result) {
     __shared__ int32_t s_start[kMaxSeqs + 1];
     __shared__ ChunkSum s_sum[kBlock];
     __shared__ ChunkSum s_tile[kTilesPerGroup];
     __shared__ uint32_t s_any[kTilesPerGroup];
+    __shared__ uint32_t s_last;
     for (int i = threadIdx.x; i <= st.k; i += kBlock) s_start[i] = st.start[i];
     if (threadIdx.x < kTilesPerGroup) s_any[threadIdx.x] = 0;
     __syncthreads();
@@ -251,19 +264,20 @@ __global__ __launch_bounds__(kBlock) void k_runs(const int32_t *__restrict__ sa,
         ChunkSum total = chunk_empty();
         for (uint32_t t = t0; t < t1; ++t) total = chunk_combine(total, s_tile[t - t0]);
         out[blockIdx.x] = total;
+        __threadfence();
+        s_last = atomicAdd(done, 1u) == gridDim.x - 1u;
     }
-}
-
-__global__ __launch_bounds__(kBlock) void k_runs_final(const ChunkSum *__restrict__ in, uint32_t count,
-                                                       uint32_t *__restrict__ result) {
-    __shared__ ChunkSum s_sum[kBlock];
-    const uint32_t per = (count + kBlock - 1) / kBlock;
-    const uint32_t b = min(count, threadIdx.x * per), e = min(count, b + per);
+    __syncthreads();
+    if (!s_last) return;
+    // the last workgroup to finish combines all of them in rank order
+    __threadfence();
+    const uint32_t each = (gridDim.x + kBlock - 1) / kBlock;
+    const uint32_t b = min(gridDim.x, threadIdx.x * each), e = min(gridDim.x, b + each);
     ChunkSum c = chunk_empty();
-    for (uint32_t i = b; i < e; ++i) c = chunk_combine(c, in[i]);
+    for (uint32_t i = b; i < e; ++i) c = chunk_combine(c, load_chunk(out + i));
     block_reduce_chunks(s_sum, c);
     if (threadIdx.x == 0) {
-        ChunkSum g = s_sum[0];
+        const ChunkSum g = s_sum[0];
         int32_t bp = g.bp, bq = g.bq;
         if (g.has_b) finalize(g.tail, bp, bq);
         result[0] = (uint32_t)bp;
@@ -292,12 +306,10 @@ lor_status overlap_scan(const int32_t *sa, const int32_t *lcp, uint32_t n, const
                hipLaunchKernelGGL(k_cross_max, dim3(div_up(n - 1, kBlock * kCrossItems)), dim3(kBlock), 0, s, sa, lcp,
                                   n, st, words));
     LOR_LAUNCH("k_runs", (double)n * 4, s,
-               hipLaunchKernelGGL(k_runs, dim3(groups), dim3(kBlock), 0, s, sa, lcp, n, st, group_tiles(n), words, sums));
-    LOR_LAUNCH("k_runs_final", (double)groups * sizeof(ChunkSum), s,
-               hipLaunchKernelGGL(k_runs_final, dim3(1), dim3(kBlock), 0, s, sums, groups, words + 1));
+               hipLaunchKernelGGL(k_runs, dim3(groups), dim3(kBlock), 0, s, sa, lcp, n, st, group_tiles(n), words, sums, words + 3,
+                                  words + 1));
     uint32_t w[3];   // length, positions
-    LOR_HIP(hipMemcpyAsync(w, words, sizeof(w), hipMemcpyDeviceToHost, s));
-    LOR_HIP(hipStreamSynchronize(s));
+    LOR_HIP(hipMemcpyWithStream(w, words, sizeof(w), hipMemcpyDeviceToHost, s));   // waits for the stream
     const uint32_t L = w[0];
     if (L == 0) return LOR_OK;
     const int32_t p = (int32_t)w[1], q = (int32_t)w[2];

@@ -71,6 +71,7 @@ constexpr uint32_t kKeyTile = 2048;           // positions per workgroup of the 
 constexpr uint32_t kDirectRanks = 1u << 24;   // ranks as plain stores up to here (see kDirectIsa)
 constexpr int kMaxRounds = 4;                 // sorts of large groups before DC3 takes over
 constexpr int kMaxK = 16;
+constexpr uint32_t kScan = 4;                 // group members read from LDS together
 constexpr int kMaxRefine = 5;                 // slots per thread of refine()
 
 // ------------------------------------------------------------ text access
@@ -171,8 +172,16 @@ __device__ __forceinline__ void refine(const CH *__restrict__ t, uint32_t n, uin
             uint32_t f;
             group(l, &f);
             const uint16_t c = cls[l];
-            uint32_t first = f;
-            while (cls[first] != c) ++first;   // l at the latest
+            uint32_t first = l;
+            for (uint32_t q = f; q < l; q += kScan) {
+                uint16_t x[kScan];
+#pragma unroll
+                for (uint32_t i = 0; i < kScan; ++i) x[i] = cls[min(q + i, l)];
+#pragma unroll
+                for (uint32_t i = 0; i < kScan; ++i)
+                    if (x[i] == c) first = min(first, min(q + i, l));
+                if (first < l) break;
+            }
             uint32_t k = kEqual;
             if (first != l) {
                 const uint32_t p = val[l], q = val[first], h = (uint32_t)(key[l] >> 32), cap = max(deep, h + 64u);
@@ -193,10 +202,20 @@ __device__ __forceinline__ void refine(const CH *__restrict__ t, uint32_t n, uin
             uint32_t f, less = 0, same = 0;
             const uint32_t size = group(l, &f);
             const uint16_t c = cls[l];
-            for (uint32_t q = f; q < f + size; ++q) {
-                if (cls[q] != c) continue;
-                less += (uint32_t)key[q] < mine;
-                same += (uint32_t)key[q] == mine;
+            for (uint32_t q = f; q < f + size; q += kScan) {
+                uint16_t x[kScan];
+                uint32_t y[kScan];
+#pragma unroll
+                for (uint32_t i = 0; i < kScan; ++i) {
+                    const uint32_t o = min(q + i, f + size - 1u);
+                    x[i] = q + i < f + size ? cls[o] : (uint16_t)0xffffu;
+                    y[i] = (uint32_t)key[o];
+                }
+#pragma unroll
+                for (uint32_t i = 0; i < kScan; ++i) {
+                    less += x[i] == c && y[i] < mine;
+                    same += x[i] == c && y[i] == mine;
+                }
             }
             place[r] = c + less;
             if (same > 1 && mine != kEqual) next |= 1u << r;
@@ -709,9 +728,15 @@ __global__ __launch_bounds__(kBlock) void k_resolve(X x, GroupKey gk, const KT *
         const uint32_t size = tied(r, &f);
         if (size > 1) {
             uint32_t less = f;
-            for (uint32_t q = f; q < f + size; ++q) {
-                less += s_win[q] < win[r];
-                same += s_win[q] == win[r];
+            for (uint32_t q = f; q < f + size; q += kScan) {
+                uint64_t y[kScan];
+#pragma unroll
+                for (uint32_t i = 0; i < kScan; ++i) y[i] = s_win[min(q + i, f + size - 1u)];
+#pragma unroll
+                for (uint32_t i = 0; i < kScan; ++i) {
+                    less += q + i < f + size && y[i] < win[r];
+                    same += q + i < f + size && y[i] == win[r];
+                }
             }
             s_cls[slot_of(r)] = (uint16_t)less;
         }
@@ -739,10 +764,20 @@ __global__ __launch_bounds__(kBlock) void k_resolve(X x, GroupKey gk, const KT *
                 const uint16_t c = s_cls[l];
                 mine[r] = s_win[l];
                 place[r] = c;
-                for (uint32_t q = f; q < f + size; ++q) {
-                    if (s_cls[q] != c) continue;
-                    place[r] += s_win[q] < mine[r];
-                    same += s_win[q] == mine[r];
+                for (uint32_t q = f; q < f + size; q += kScan) {
+                    uint16_t x[kScan];
+                    uint64_t y[kScan];
+#pragma unroll
+                    for (uint32_t i = 0; i < kScan; ++i) {
+                        const uint32_t o = min(q + i, f + size - 1u);
+                        x[i] = q + i < f + size ? s_cls[o] : (uint16_t)0xffffu;
+                        y[i] = s_win[o];
+                    }
+#pragma unroll
+                    for (uint32_t i = 0; i < kScan; ++i) {
+                        place[r] += x[i] == c && y[i] < mine[r];
+                        same += x[i] == c && y[i] == mine[r];
+                    }
                 }
                 next |= (same > 1 ? 1u : 0u) << r;
             }
@@ -793,6 +828,7 @@ __global__ __launch_bounds__(kBlock) void k_resolve(X x, GroupKey gk, const KT *
         if (size > 1 && !kept) {
             const uint16_t cls = s_cls[l];
             place = cls;
+#pragma unroll 4
             for (uint32_t q = f; q < l; ++q) same += s_cls[q] == cls;
             place += same;
         }
@@ -1025,9 +1061,11 @@ __global__ __launch_bounds__(kBlock) void k_double(const uint32_t *__restrict__ 
         uint32_t f;
         const uint32_t size = runs.run_of(l, &f), mine = s_rank[l];
         uint32_t place = f, same = 0;
+#pragma unroll 4
         for (uint32_t q = f; q < f + size; ++q) {
-            place += s_rank[q] < mine;
-            same += s_rank[q] == mine && q < l;
+            const uint32_t o = s_rank[q];
+            place += o < mine;
+            same += o == mine && q < l;
         }
         place += same;
         const uint32_t slot = base + place;
@@ -1079,6 +1117,7 @@ __global__ __launch_bounds__(kBlock) void k_settle(X x, const uint32_t *__restri
         uint32_t f, same = 0;
         runs.run_of(l, &f);
         const uint16_t c = s_cls[l];
+#pragma unroll 4
         for (uint32_t q = f; q < l; ++q) same += s_cls[q] == c;
         const uint32_t place = c + same, slot = base + place;
         if (slot >= x.n) continue;
@@ -1136,8 +1175,7 @@ lor_status launch_near(const Shared &, const uint32_t *, uint32_t, int32_t *, ui
 }
 
 lor_status read_header(uint32_t *hdr, PrefixHdr *h, hipStream_t s) {
-    LOR_HIP(hipMemcpyAsync(h, hdr, sizeof(*h), hipMemcpyDeviceToHost, s));
-    LOR_HIP(hipStreamSynchronize(s));
+    LOR_HIP(hipMemcpyWithStream(h, hdr, sizeof(*h), hipMemcpyDeviceToHost, s));   // waits for the stream
     if (h->word[0]) {
         set_error("input base outside 0..3");
         return LOR_EALPHABET;
