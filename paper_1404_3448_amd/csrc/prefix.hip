@@ -50,17 +50,18 @@ namespace lor {
 
 namespace {
 
-constexpr int kWordAbort = 4;      // header words of this file (see WsHeader)
+constexpr int kWordAbort = 6;      // header words of this file (see WsHeader)
 constexpr int kWordTied = 3;       // suffixes in large groups
-constexpr int kWordHeads = 6;      // large groups
+constexpr int kWordHeads = 4;      // large groups (next to kWordTied: cleared together)
 constexpr int kWordOpen = 7;       // suffixes still equal to their neighbour, after resolve
 constexpr int kWordRound = 8;      // the same after rounds of doubling
 constexpr int kWordSpent = 5;      // comparison budget used, in units of kUnit steps
 
 constexpr uint32_t kSmall = 64;               // largest group resolved in a workgroup
-constexpr int kResItems = 4;                  // ranks per thread of the resolve kernels
-constexpr uint32_t kResTile = kBlock * kResItems;
-constexpr uint32_t kResWords = kResTile / 64;
+// Ranks per thread of the resolve kernels: few per thread for small inputs,
+// whose time is one workgroup's chain of waits (and its instruction fetches).
+constexpr int kResItems = 4, kResItemsSmall = 1;
+constexpr uint32_t kResSmall = 1u << 18;      // inputs up to here count as small
 constexpr uint32_t kDeep = 256;               // symbols that resolve compares
 constexpr uint32_t kSettle = 2048;            // symbols that k_settle compares
 constexpr uint32_t kUnit = 32;                // 32-byte comparison steps per budget unit
@@ -614,8 +615,8 @@ struct GroupKey {
     }
 };
 
-// Groups of equal keys over sorted (key, position) pairs, kResTile ranks per
-// workgroup. Head flags are ballots (a 64-bit word per 64 ranks), with the
+// Groups of equal keys over sorted (key, position) pairs, 256 ITEMS
+// ranks per workgroup. Head flags are ballots (a 64-bit word per 64 ranks), with the
 // words beside the tile's, so every rank of a group of at most kSmall knows
 // its whole group and works out its own place; members just outside the tile
 // are looked at by both workgroups. 8 text bytes behind the known prefix are
@@ -625,7 +626,7 @@ struct GroupKey {
 // Stage 0 (32-bit keys of the sort) writes places shifted by the near
 // suffixes; stage 1 (64-bit keys of large groups) through `slots`. Larger
 // groups are marked in `large` and counted, with their heads, per tile.
-template <typename X, typename KT>
+template <typename X, typename KT, int ITEMS>
 __global__ __launch_bounds__(kBlock) void k_resolve(X x, GroupKey gk, const KT *__restrict__ keys,
                                                     const uint32_t *__restrict__ vals, uint32_t m,
                                                     int32_t *__restrict__ sa, const uint32_t *__restrict__ slots,
@@ -635,7 +636,9 @@ __global__ __launch_bounds__(kBlock) void k_resolve(X x, GroupKey gk, const KT *
                                                     uint32_t *__restrict__ hdr, uint32_t budget) {
     using CH = typename X::CH;
     constexpr bool kFirst = sizeof(KT) == 4;
+    constexpr uint32_t kResTile = kBlock * ITEMS, kResWords = kResTile / 64;
     constexpr uint32_t kSlots = kResTile + 2 * kSmall;
+    static_assert(ITEMS + 1 <= kMaxRefine, "");
     constexpr int kWaves = kBlock / kWave;
     __shared__ uint64_t s_head[kResWords + 2];
     __shared__ uint32_t s_val[kSlots];
@@ -643,15 +646,15 @@ __global__ __launch_bounds__(kBlock) void k_resolve(X x, GroupKey gk, const KT *
     __shared__ uint16_t s_cls[kSlots];
     __shared__ uint32_t s_shift[2], s_large, s_heads, s_again, s_open;
     const uint32_t base = blockIdx.x * kResTile, tid = threadIdx.x, lane = tid & 63u, w = tid >> 6;
-    // Round r < kResItems: slot kSmall + 256 r + tid, rank base + 256 r + tid;
+    // Round r < ITEMS: slot kSmall + 256 r + tid, rank base + 256 r + tid;
     // the last round: the ranks beside the tile, waves 0 (before) and 1 (after).
-    auto slot_of = [&](int r) { return r < kResItems ? kSmall + r * kBlock + tid : (w == 0 ? lane : kResTile + tid); };
+    auto slot_of = [&](int r) { return r < ITEMS ? kSmall + r * kBlock + tid : (w == 0 ? lane : kResTile + tid); };
     auto rank_of = [&](int r) { return base + slot_of(r) - kSmall; };   // wraps before rank 0: not below m then
     // Values are positions; after a bad input base some may be anything, and
     // no text read may leave the text.
 #pragma unroll
-    for (int r = 0; r <= kResItems; ++r) {
-        if (r == kResItems && w >= 2) break;
+    for (int r = 0; r <= ITEMS; ++r) {
+        if (r == ITEMS && w >= 2) break;
         const uint32_t e = rank_of(r);
         const bool ok = e < m;
         const KT key = ok ? keys[e] : KT(0);
@@ -664,7 +667,7 @@ __global__ __launch_bounds__(kBlock) void k_resolve(X x, GroupKey gk, const KT *
             prev = (ok && e > 0) ? keys[e - 1] : KT(0);
         }
         const uint64_t h = __ballot(!ok || e == 0 || prev != key);   // past the end: heads, so groups end there
-        if (lane == 0) s_head[r < kResItems ? 1 + r * kWaves + w : (w == 0 ? 0 : kResWords + 1)] = h;
+        if (lane == 0) s_head[r < ITEMS ? 1 + r * kWaves + w : (w == 0 ? 0 : kResWords + 1)] = h;
         s_val[slot_of(r)] = val;
     }
     if (kFirst && w >= 2) {
@@ -693,7 +696,7 @@ __global__ __launch_bounds__(kBlock) void k_resolve(X x, GroupKey gk, const KT *
     // Size of a slot's group when this workgroup has to look at it: every rank
     // of the tile, and those beside it whose group reaches into it.
     auto tied = [&](int r, uint32_t *first) -> uint32_t {
-        if (r == kResItems) {
+        if (r == ITEMS) {
             if (w >= 2) return 0;
             const uint64_t h = s_head[w == 0 ? 0 : kResWords + 1];
             const bool reach = w == 0 ? (lane == 63 || !(h >> (lane + 1u))) && !(s_head[1] & 1ull)
@@ -704,9 +707,9 @@ __global__ __launch_bounds__(kBlock) void k_resolve(X x, GroupKey gk, const KT *
     };
 
     // 8 text bytes of every tied rank, all gathers of a thread in flight at once
-    uint64_t win[kResItems + 1];
+    uint64_t win[ITEMS + 1];
 #pragma unroll
-    for (int r = 0; r <= kResItems; ++r) {
+    for (int r = 0; r <= ITEMS; ++r) {
         uint32_t f;
         win[r] = 0;
         if (tied(r, &f) > 1) {
@@ -717,13 +720,13 @@ __global__ __launch_bounds__(kBlock) void k_resolve(X x, GroupKey gk, const KT *
         }
     }
 #pragma unroll
-    for (int r = 0; r <= kResItems; ++r)
-        if (r < kResItems || w < 2) s_win[slot_of(r)] = win[r];
+    for (int r = 0; r <= ITEMS; ++r)
+        if (r < ITEMS || w < 2) s_win[slot_of(r)] = win[r];
     __syncthreads();
     // class of every tied rank: first place of those with its window
     uint32_t again = 0;   // bit r: others share it
 #pragma unroll
-    for (int r = 0; r <= kResItems; ++r) {
+    for (int r = 0; r <= ITEMS; ++r) {
         uint32_t f, same = 0;
         const uint32_t size = tied(r, &f);
         if (size > 1) {
@@ -747,16 +750,16 @@ __global__ __launch_bounds__(kBlock) void k_resolve(X x, GroupKey gk, const KT *
     if (s_again) {   // uniform
         if constexpr (kFirst) {
 #pragma unroll 1
-            for (int r = 0; r <= kResItems; ++r) {
+            for (int r = 0; r <= ITEMS; ++r) {
                 if (!((again >> r) & 1u)) continue;
                 const uint32_t l = slot_of(r);
                 s_win[l] = repeat_key(x, s_val[l], period_at(x, s_val[l]), kRepeatSymbols, hdr, budget);
             }
             __syncthreads();
-            uint32_t place[kResItems + 1], next = 0;
-            uint64_t mine[kResItems + 1];
+            uint32_t place[ITEMS + 1], next = 0;
+            uint64_t mine[ITEMS + 1];
 #pragma unroll
-            for (int r = 0; r <= kResItems; ++r) {
+            for (int r = 0; r <= ITEMS; ++r) {
                 if (!((again >> r) & 1u)) continue;
                 const uint32_t l = slot_of(r);
                 uint32_t f, same = 0;
@@ -783,7 +786,7 @@ __global__ __launch_bounds__(kBlock) void k_resolve(X x, GroupKey gk, const KT *
             }
             __syncthreads();
 #pragma unroll
-            for (int r = 0; r <= kResItems; ++r) {
+            for (int r = 0; r <= ITEMS; ++r) {
                 if (!((again >> r) & 1u)) continue;
                 const uint32_t l = slot_of(r), c = (uint32_t)(mine[r] >> (3u * kRepeatSymbols));
                 s_cls[l] = (uint16_t)place[r];
@@ -792,18 +795,18 @@ __global__ __launch_bounds__(kBlock) void k_resolve(X x, GroupKey gk, const KT *
             again = next;
         } else {
 #pragma unroll
-            for (int r = 0; r <= kResItems; ++r)
+            for (int r = 0; r <= ITEMS; ++r)
                 if ((again >> r) & 1u)
                     s_win[slot_of(r)] = (uint64_t)max((uint32_t)x.K, gk.reach(keys[rank_of(r)])) << 32;
         }
         __syncthreads();
-        refine(x.t, x.n, kDeep, kResItems + 1, slot_of, group, s_val, s_win, s_cls, &s_again, again);
+        refine(x.t, x.n, kDeep, ITEMS + 1, slot_of, group, s_val, s_win, s_cls, &s_again, again);
     }
 
     const uint32_t sh0 = kFirst ? s_shift[0] : 0u, sh1 = kFirst ? s_shift[1] : 0u;
     uint32_t lost = 0, heads = 0;
 #pragma unroll 1
-    for (int r = 0; r < kResItems; ++r) {
+    for (int r = 0; r < ITEMS; ++r) {
         const uint32_t l = slot_of(r), e = rank_of(r);
         const bool valid = e < m;
         uint32_t f = 0;
@@ -866,7 +869,7 @@ __global__ __launch_bounds__(kBlock) void k_resolve(X x, GroupKey gk, const KT *
 // (the count of marked heads up to here); a group's head writes how many
 // symbols further into the suffix the group's next keys start, so that the K
 // symbols there end where the known prefix ends.
-template <typename KT>
+template <typename KT, int ITEMS>
 __global__ __launch_bounds__(kBlock) void k_group_collect(GroupKey gk, int K, const KT *__restrict__ keys,
                                                           const uint32_t *__restrict__ vals, uint32_t m,
                                                           const uint64_t *__restrict__ large,
@@ -878,14 +881,15 @@ __global__ __launch_bounds__(kBlock) void k_group_collect(GroupKey gk, int K, co
                                                           uint32_t *__restrict__ tvals, uint32_t *__restrict__ tslots,
                                                           uint32_t *__restrict__ off) {
     constexpr bool kFirst = sizeof(KT) == 4;
+    constexpr uint32_t kResTile = kBlock * ITEMS, kResWords = kResTile / 64;
     __shared__ uint32_t s_below[kResWords], s_hbelow[kResWords];
     __shared__ uint64_t s_bits[kResWords], s_head[kResWords];
     __shared__ uint32_t s_shift[2];
     const uint32_t base = blockIdx.x * kResTile, tid = threadIdx.x, lane = tid & 63u, w = tid >> 6;
     static_assert(kResWords <= 64, "one lane per word");
-    KT key[kResItems];
+    KT key[ITEMS];
 #pragma unroll
-    for (int r = 0; r < kResItems; ++r) {
+    for (int r = 0; r < ITEMS; ++r) {
         const uint32_t e = base + r * kBlock + tid;
         key[r] = e < m ? keys[e] : KT(0);
         const KT prev = (e > 0 && e < m) ? keys[e - 1] : KT(0);
@@ -910,7 +914,7 @@ __global__ __launch_bounds__(kBlock) void k_group_collect(GroupKey gk, int K, co
     __syncthreads();
     const uint32_t at = tbase[blockIdx.x], hat = hbase[blockIdx.x];
 #pragma unroll
-    for (int r = 0; r < kResItems; ++r) {
+    for (int r = 0; r < ITEMS; ++r) {
         const uint32_t l = r * kBlock + tid, e = base + l;
         const uint64_t b = s_bits[l >> 6], bit = 1ull << (l & 63u);
         if (e >= m || !(b & bit)) continue;
@@ -1087,7 +1091,7 @@ __global__ __launch_bounds__(kBlock) void k_settle(X x, const uint32_t *__restri
     __shared__ uint32_t s_bits[kRunWords], s_val[kRunTile + kSmall], s_any, s_left;
     __shared__ uint64_t s_key[kRunTile + kSmall];
     __shared__ uint16_t s_cls[kRunTile + kSmall];
-    static_assert(kRunItems <= kMaxRefine && kResItems + 1 <= kMaxRefine, "");
+    static_assert(kRunItems <= kMaxRefine, "");
     const uint32_t base = blockIdx.x * kRunTile, tid = threadIdx.x;
     if (tid == 0) s_left = 0;
     if (!load_runs(was, x.n, base, s_bits, &s_any)) return;
@@ -1263,7 +1267,8 @@ lor_status prefix_sa(const X &x, int bits, uint32_t near, int32_t *sa, Arena &ar
     constexpr bool kImplicit = !StopAtSep<X>::value;   // every position is sorted: its value is its index
     *done = false;
     const uint32_t m = x.n - near;
-    const uint32_t tiles = div_up(m ? m : 1, kResTile);
+    auto tile_of = [](uint32_t count) { return kBlock * (uint32_t)(count <= kResSmall ? kResItemsSmall : kResItems); };
+    const uint32_t tiles = div_up(m ? m : 1, tile_of(m));
     // 32 steps over two texts read about 32 lines, some 0.7 ns of the chip's
     // gather rate; DC3 takes 0.25 to 0.4 ns per suffix. At most about a third of
     // a DC3 run is spent before giving up.
@@ -1278,8 +1283,10 @@ lor_status prefix_sa(const X &x, int bits, uint32_t near, int32_t *sa, Arena &ar
     uint32_t *open = ar.take<uint32_t>(owords);
     const size_t mark_open = ar.mark();
     uint32_t *ka = ar.take<uint32_t>(m), *va = ar.take<uint32_t>(m), *places = ar.take<uint32_t>(near + 1);
-    uint64_t *large = ar.take<uint64_t>((size_t)tiles * kResWords);
-    uint32_t *tcount = ar.take<uint32_t>(tiles), *hcount = ar.take<uint32_t>(tiles);
+    // sized for every round: the tiles of a smaller count may be smaller, and more
+    const uint32_t most = std::max(tiles, div_up(std::min(m, kResSmall), kBlock * kResItemsSmall)) + 1;
+    uint64_t *large = ar.take<uint64_t>((size_t)div_up(m, 64) + 64);
+    uint32_t *tcount = ar.take<uint32_t>(most), *hcount = ar.take<uint32_t>(most);
     uint32_t *stmp = ar.take<uint32_t>(kScanTmpWords);
     const size_t half = ar.mark();
     uint32_t *kb = ar.take<uint32_t>(m), *counts = ar.take<uint32_t>(radix_counts_words(m));
@@ -1300,10 +1307,13 @@ lor_status prefix_sa(const X &x, int bits, uint32_t near, int32_t *sa, Arena &ar
     }
     if (near) LOR_TRY(launch_near(x, ka, m, sa, places, s));
     GroupKey gk{0, nullptr};
-    if (m > 0)
+    if (m > 0) {
+        auto *resolve = m <= kResSmall ? k_resolve<X, uint32_t, kResItemsSmall> : k_resolve<X, uint32_t, kResItems>;
         LOR_LAUNCH("k_resolve", 12.0 * m, s,
-                   hipLaunchKernelGGL((k_resolve<X, uint32_t>), dim3(tiles), dim3(kBlock), 0, s, x, gk, ka, va, m, sa,
-                                      (const uint32_t *)nullptr, places, near, large, tcount, hcount, open, hdr, budget));
+                   hipLaunchKernelGGL(resolve, dim3(tiles), dim3(kBlock), 0, s, x, gk, ka, va, m, sa,
+                                      (const uint32_t *)nullptr, places, near, large, tcount, hcount, open, hdr,
+                                      budget));
+    }
     PrefixHdr h;
     LOR_TRY(read_header(hdr, &h, s));
     if (trace_on())
@@ -1331,19 +1341,23 @@ lor_status prefix_sa(const X &x, int bits, uint32_t near, int32_t *sa, Arena &ar
         const size_t scratch = ar.mark();
         uint32_t *cnt = ar.take<uint32_t>(radix_counts_words(total));
         if (ar.overflow) return LOR_OK;
-        const uint32_t ct = div_up(cur, kResTile), nt = div_up(total, kResTile);
+        const bool csmall = cur <= kResSmall, tsmall = total <= kResSmall;
+        const uint32_t ct = div_up(cur, tile_of(cur)), nt = div_up(total, tile_of(total));
         LOR_TRY(scan_exclusive(tcount, ct, stmp, nullptr, s));
         LOR_TRY(scan_exclusive(hcount, ct, stmp, nullptr, s));
-        if (round == 0)
+        if (round == 0) {
+            auto *collect = csmall ? k_group_collect<uint32_t, kResItemsSmall> : k_group_collect<uint32_t, kResItems>;
             LOR_LAUNCH("k_group_collect", 4.0 * cur + 20.0 * total, s,
-                       hipLaunchKernelGGL(k_group_collect<uint32_t>, dim3(ct), dim3(kBlock), 0, s, gk, x.K, ka, va,
-                                          cur, large, tcount, hcount, places, near, slots, total, groups, k0, v0, ns,
+                       hipLaunchKernelGGL(collect, dim3(ct), dim3(kBlock), 0, s, gk, x.K, ka, va, cur, large, tcount,
+                                          hcount, places, near, slots, total, groups, k0, v0, ns,
                                           (uint32_t *)nullptr));
-        else
+        } else {
+            auto *collect = csmall ? k_group_collect<uint64_t, kResItemsSmall> : k_group_collect<uint64_t, kResItems>;
             LOR_LAUNCH("k_group_collect", 8.0 * cur + 24.0 * total, s,
-                       hipLaunchKernelGGL(k_group_collect<uint64_t>, dim3(ct), dim3(kBlock), 0, s, gk, x.K, k64, v64,
-                                          cur, large, tcount, hcount, places, near, slots, total, groups, k0, v0, ns,
+                       hipLaunchKernelGGL(collect, dim3(ct), dim3(kBlock), 0, s, gk, x.K, k64, v64, cur, large, tcount,
+                                          hcount, places, near, slots, total, groups, k0, v0, ns,
                                           const_cast<uint32_t *>(ng.off)));
+        }
         gk = ng;
         LOR_LAUNCH("k_group_keys", 20.0 * total, s,
                    hipLaunchKernelGGL(k_group_keys<X>, dim3(div_up(total, kBlock)), dim3(kBlock), 0, s, x, gk, k0, v0,
@@ -1355,11 +1369,11 @@ lor_status prefix_sa(const X &x, int bits, uint32_t near, int32_t *sa, Arena &ar
         slots = ns;
         cur = total;
         ar.release(scratch);
-        LOR_TRY(zero_words(hdr + kWordTied, 1, s));
-        LOR_TRY(zero_words(hdr + kWordHeads, 1, s));
+        LOR_TRY(zero_words(hdr + kWordTied, 2, s));
+        auto *resolve = tsmall ? k_resolve<X, uint64_t, kResItemsSmall> : k_resolve<X, uint64_t, kResItems>;
         LOR_LAUNCH("k_resolve", 20.0 * cur, s,
-                   hipLaunchKernelGGL((k_resolve<X, uint64_t>), dim3(nt), dim3(kBlock), 0, s, x, gk, k64, v64, cur, sa,
-                                      slots, (const uint32_t *)nullptr, 0u, large, tcount, hcount, open, hdr, budget));
+                   hipLaunchKernelGGL(resolve, dim3(nt), dim3(kBlock), 0, s, x, gk, k64, v64, cur, sa, slots,
+                                      (const uint32_t *)nullptr, 0u, large, tcount, hcount, open, hdr, budget));
         LOR_TRY(read_header(hdr, &h, s));
         if (trace_on())
             fprintf(stderr, "[lor] prefix sort: round %d, %u suffixes; left: large groups=%u with %u%s\n", round, total,
