@@ -28,11 +28,13 @@ namespace {
 
 constexpr uint32_t kChunk = 16;                        // ranks per thread in a tile
 constexpr uint32_t kTileRanks = kChunk * kBlock;
-constexpr uint32_t kTilesPerGroup = 16;
+constexpr uint32_t kTilesPerGroup = 4;
 constexpr uint32_t kMinGroups = 2048;                  // workgroups wanted before one takes several tiles
 
 // Tiles per workgroup of the run pass: one while that leaves compute units
-// idle (16 at a time left 64 small pairs to 5 workgroups: 303 us).
+// idle (16 at a time left 64 small pairs to 5 workgroups: 303 us against 25),
+// at most 4 then (700 pairs, 144M ranks: 16 at a time 890 us, 4 640 us with the
+// last combine).
 uint32_t group_tiles(uint64_t n) {
     const uint64_t t = (n + kTileRanks - 1) / kTileRanks / kMinGroups;
     return t < 1 ? 1u : t > kTilesPerGroup ? kTilesPerGroup : (uint32_t)t;
@@ -230,7 +232,9 @@ __global__ __launch_bounds__(kBlock) void k_seg_max(const int32_t *__restrict__ 
     if (w.lds) {
         __syncthreads();
         for (uint32_t j = threadIdx.x; j < w.k; j += kBlock)
-            if (s_best[j] > s_known[j]) atomicMax(&lmax[w.lo + j], s_best[j]);
+            if (s_best[j] > s_known[j] &&
+                s_best[j] > __hip_atomic_load(&lmax[w.lo + j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                atomicMax(&lmax[w.lo + j], s_best[j]);
     }
 }
 
@@ -320,7 +324,7 @@ __global__ __launch_bounds__(kBlock) void k_seg_runs(const int32_t *__restrict__
     __shared__ int32_t s_start[kPairWin + 1];
     __shared__ int32_t s_alen[kPairWin];
     __shared__ uint32_t s_L[kPairWin];
-    __shared__ uint32_t s_sh[2];
+    __shared__ uint32_t s_sh[2], s_least;
     const uint32_t tiles = (n + kTileRanks - 1) / kTileRanks;
     const uint32_t t0 = blockIdx.x * per, t1 = min(tiles, t0 + per);   // per <= kTilesPerGroup
     if (t0 >= t1) return;
@@ -328,9 +332,16 @@ __global__ __launch_bounds__(kBlock) void k_seg_runs(const int32_t *__restrict__
     if (threadIdx.x < kTilesPerGroup) s_any[threadIdx.x] = 0;
     const PairWin w = pair_window(start, alen, P, g0, g1 - 1, s_start, s_alen, s_sh);
     if (w.lds) {
-        for (uint32_t j = threadIdx.x; j < w.k; j += kBlock) s_L[j] = lmax[w.lo + j];
+        if (threadIdx.x == 0) s_least = 0xffffffffu;
+        __syncthreads();
+        for (uint32_t j = threadIdx.x; j < w.k; j += kBlock) {
+            s_L[j] = lmax[w.lo + j];
+            if (s_L[j]) atomicMin(&s_least, s_L[j]);   // pairs that share nothing have no run
+        }
         __syncthreads();
     }
+    // only an LCP that reaches some pair's length can continue a run
+    const int32_t least = w.lds ? (int32_t)min(s_least, 0x7fffffffu) : 1;
     auto pstart = [&](uint32_t q) { return w.lds ? (uint32_t)s_start[q] : (uint32_t)start[w.lo + q]; };
     auto pL = [&](uint32_t q) { return w.lds ? s_L[q] : lmax[w.lo + q]; };
     auto pb = [&](uint32_t q) { return pstart(q) + (w.lds ? (uint32_t)s_alen[q] : (uint32_t)alen[w.lo + q]); };
@@ -349,7 +360,7 @@ __global__ __launch_bounds__(kBlock) void k_seg_runs(const int32_t *__restrict__
 #pragma unroll
         for (uint32_t i = 0; i < kChunk; ++i) {
             const uint32_t j = i * kBlock + threadIdx.x;
-            if (j >= cnt || v[i] <= 0) continue;
+            if (j >= cnt || v[i] < least) continue;
             const uint32_t r = base + j;
             const uint32_t q = pair_at(w, s_start, start, P, r, cur);
             const uint32_t L = pL(q);
@@ -400,8 +411,12 @@ __global__ __launch_bounds__(kBlock) void k_seg_runs(const int32_t *__restrict__
     }
     __syncthreads();
     if (threadIdx.x == 0) {
+        // tiles after the last flagged one only matter through their last suffix
         ChunkSum total = chunk_empty();
-        for (uint32_t t = t0; t < t1; ++t) total = chunk_combine(total, s_tile[t - t0], start, P, best);
+        uint32_t last = t1 - 1;
+        while (last > t0 && !s_any[last - t0] && !s_any[last - 1 - t0]) --last;
+        for (uint32_t t = t0; t <= last; ++t) total = chunk_combine(total, s_tile[t - t0], start, P, best);
+        if (last + 1 < t1) total = chunk_combine(total, s_tile[t1 - 1 - t0], start, P, best);
         out[blockIdx.x] = total;
     }
 }

@@ -13,8 +13,8 @@
 //            sample whose first S symbols agree and whose successor i + S has
 //            Phi[i + S] = Phi[i] + S is linked to it: PLCP[i] = PLCP[i + S] + S;
 //            the others compare their texts;
-//   links  : the end of every chain of links, by a scan over 64-sample words,
-//            so a copy of any length is compared only where it ends;
+//   links  : the end of every chain of links, by scans over 64-sample words and
+//            blocks of 64 of them, so a copy of any length is compared only where it ends;
 //   finish : a marked rank whose Phi lies on the diagonal of the sample before
 //            or behind its position follows from that; others start from
 //            Kasai's bound PLCP[i + d] >= PLCP[i] - d at the sample before, so
@@ -149,33 +149,50 @@ __global__ __launch_bounds__(kBlock) void k_plcp(const CH *__restrict__ t, uint3
     if ((threadIdx.x & 63u) == 0 && s < samples) links[s >> 6] = m;
 }
 
-// ends[w] = the first unlinked sample from 64 w on (one workgroup, each thread
-// a contiguous run of words; the last sample is never linked).
-constexpr int kLinkThreads = 1024;
-__global__ __launch_bounds__(kLinkThreads) void k_plcp_links(const uint64_t *__restrict__ links, uint32_t words,
-                                                             uint32_t samples, uint32_t *__restrict__ ends) {
-    __shared__ uint32_t s_first[kLinkThreads];
-    const uint32_t per = (words + kLinkThreads - 1u) / kLinkThreads;
-    const uint32_t b = min(words, threadIdx.x * per), e = min(words, b + per);
-    auto first_in = [&](uint32_t w) -> uint32_t {
+// ends[w] = the first unlinked sample from 64 w to the end of w's block of 64
+// words (kNoCap: none there), blocks[c] = the first from block c on. A wave per
+// block; one workgroup then completes `blocks` (the last sample is never
+// linked, so the last block has one).
+__global__ __launch_bounds__(kBlock) void k_plcp_links(const uint64_t *__restrict__ links, uint32_t words,
+                                                       uint32_t samples, uint32_t *__restrict__ ends,
+                                                       uint32_t *__restrict__ blocks) {
+    const uint32_t w = blockIdx.x * kBlock + threadIdx.x, lane = threadIdx.x & 63u;
+    uint32_t first = kNoCap;
+    if (w < words) {
         const uint32_t left = samples - 64u * w;
         const uint64_t z = ~links[w] & (left >= 64u ? ~0ull : (1ull << left) - 1ull);
-        return z ? 64u * w + (uint32_t)__builtin_ctzll(z) : kNoCap;
-    };
+        if (z) first = 64u * w + (uint32_t)__builtin_ctzll(z);
+    }
+#pragma unroll
+    for (uint32_t o = 1; o < (uint32_t)kWave; o <<= 1) {
+        const uint32_t x = (uint32_t)__shfl_down((int)first, o, kWave);
+        if (lane + o < (uint32_t)kWave) first = min(first, x);
+    }
+    if (w < words) {
+        ends[w] = first;
+        if (lane == 0) blocks[w >> 6] = first;
+    }
+}
+
+constexpr int kLinkThreads = 1024;
+__global__ __launch_bounds__(kLinkThreads) void k_plcp_blocks(uint32_t *__restrict__ blocks, uint32_t count) {
+    __shared__ uint32_t s_first[kLinkThreads];
+    const uint32_t per = (count + kLinkThreads - 1u) / kLinkThreads;
+    const uint32_t b = min(count, threadIdx.x * per), e = min(count, b + per);
     uint32_t first = kNoCap;
-    for (uint32_t w = b; w < e; ++w) first = min(first, first_in(w));
+    for (uint32_t c = b; c < e; ++c) first = min(first, blocks[c]);
     s_first[threadIdx.x] = first;
     __syncthreads();
-    for (uint32_t o = 1; o < (uint32_t)kLinkThreads; o <<= 1) {   // min over this thread's words and all later ones
+    for (uint32_t o = 1; o < (uint32_t)kLinkThreads; o <<= 1) {   // min over this thread's blocks and all later ones
         const uint32_t x = threadIdx.x + o < (uint32_t)kLinkThreads ? s_first[threadIdx.x + o] : kNoCap;
         __syncthreads();
         s_first[threadIdx.x] = min(s_first[threadIdx.x], x);
         __syncthreads();
     }
     uint32_t after = threadIdx.x + 1 < (uint32_t)kLinkThreads ? s_first[threadIdx.x + 1] : kNoCap;
-    for (uint32_t w = e; w-- > b;) {
-        after = min(after, first_in(w));
-        ends[w] = after;
+    for (uint32_t c = e; c-- > b;) {
+        after = min(after, blocks[c]);
+        blocks[c] = after;
     }
 }
 
@@ -185,7 +202,8 @@ __global__ __launch_bounds__(kBlock) void k_lcp_finish(const CH *__restrict__ t,
                                                        const uint32_t *__restrict__ phi,
                                                        const uint32_t *__restrict__ plcp,
                                                        const uint64_t *__restrict__ links,
-                                                       const uint32_t *__restrict__ ends, uint32_t samples,
+                                                       const uint32_t *__restrict__ ends,
+                                                       const uint32_t *__restrict__ blocks, uint32_t samples,
                                                        uint32_t shift, int32_t *__restrict__ lcp) {
     const uint32_t base = blockIdx.x * (kBlock * kLcpItems);
     uint32_t v[kLcpItems];
@@ -202,7 +220,13 @@ __global__ __launch_bounds__(kBlock) void k_lcp_finish(const CH *__restrict__ t,
         const uint32_t c = i >> shift, d = i & ((1u << shift) - 1u);
         auto sampled = [&](uint32_t q) -> uint32_t {   // PLCP at sample q, through its chain
             const uint64_t z = ~links[q >> 6] >> (q & 63u);
-            const uint32_t end = min(z ? q + (uint32_t)__builtin_ctzll(z) : ends[(q >> 6) + 1u], samples - 1u);
+            uint32_t end = q + (uint32_t)__builtin_ctzll(z | (1ull << 63));
+            if (!z) {   // then word w + 1 exists: the last sample is not linked
+                const uint32_t w = (q >> 6) + 1u;
+                end = ends[w];
+                if (end == kNoCap) end = blocks[(w >> 6) + 1u];
+            }
+            end = min(end, samples - 1u);
             return plcp[end] + ((end - q) << shift);
         };
         const uint32_t got = sampled(c), to_next = (1u << shift) - d;
@@ -233,12 +257,14 @@ lor_status lcp_build_t(const CH *text, uint32_t n, const int32_t *sa, int32_t *l
     const uint32_t shift = (uint32_t)bits_for((uint64_t)plan().plcp_steps) - 2u;
     const uint32_t samples = div_up(n, 1u << shift), words = div_up(samples, 64);
     const uint32_t grid = div_up(n, kBlock * kLcpItems);
-    uint32_t *phi, *plcp, *ends;
+    uint32_t *phi, *plcp, *ends, *blocks;
     uint64_t *links;
     LOR_TAKE(ar, uint32_t, samples, phi);
     LOR_TAKE(ar, uint32_t, samples, plcp);
     LOR_TAKE(ar, uint64_t, words, links);
     LOR_TAKE(ar, uint32_t, (size_t)words + 1, ends);
+    const uint32_t nblocks = div_up(words, 64);
+    LOR_TAKE(ar, uint32_t, (size_t)nblocks + 1, blocks);
     const bool direct = isa && n <= kDirectIsa;
     const double bytes = (double)n * (8 + sizeof(CH) + (direct ? 4 : 0));
     if (direct)
@@ -253,10 +279,14 @@ lor_status lcp_build_t(const CH *text, uint32_t n, const int32_t *sa, int32_t *l
                hipLaunchKernelGGL(k_plcp<CH>, dim3(div_up(samples, kBlock)), dim3(kBlock), 0, s, text, n, phi,
                                   samples, shift, plcp, links));
     LOR_LAUNCH("k_plcp_links", 12.0 * words, s,
-               hipLaunchKernelGGL(k_plcp_links, dim3(1), dim3(kLinkThreads), 0, s, links, words, samples, ends));
+               hipLaunchKernelGGL(k_plcp_links, dim3(div_up(words, kBlock)), dim3(kBlock), 0, s, links, words, samples,
+                                  ends, blocks));
+    if (nblocks > 1)
+        LOR_LAUNCH("k_plcp_blocks", 8.0 * nblocks, s,
+                   hipLaunchKernelGGL(k_plcp_blocks, dim3(1), dim3(kLinkThreads), 0, s, blocks, nblocks));
     LOR_LAUNCH("k_lcp_finish", 4.0 * n, s,
                hipLaunchKernelGGL(k_lcp_finish<CH>, dim3(grid), dim3(kBlock), 0, s, text, n, sa, phi, plcp, links, ends,
-                                  samples, shift, lcp));
+                                  blocks, samples, shift, lcp));
     if (!isa || direct) return LOR_OK;
     uint32_t *tmp[4], *counts;
     for (int i = 0; i < 4; ++i) LOR_TAKE(ar, uint32_t, n, tmp[i]);

@@ -521,35 +521,36 @@ __global__ __launch_bounds__(kBlock) void k_mx_least(const uint32_t *__restrict_
 
 // Rank r stays when the LCP with the rank before or after it reaches L. Kept
 // ranks per tile; L == 0 keeps all.
-__device__ __forceinline__ bool mx_keeps(const int32_t *__restrict__ lcp, uint32_t n, uint32_t r, int32_t L, int32_t at) {
-    return r < n && (at >= L || (r + 1 < n && lcp[r + 1] >= L));
-}
-
 __global__ __launch_bounds__(kBlock) void k_mx_count(const int32_t *__restrict__ lcp, uint32_t n,
                                                      const uint32_t *__restrict__ least, uint64_t *__restrict__ kept,
-                                                     uint32_t *__restrict__ count, uint32_t *__restrict__ total) {
+                                                     uint32_t *__restrict__ count) {
     __shared__ uint32_t s_n;
     if (threadIdx.x == 0) s_n = 0;
     __syncthreads();
     const int32_t L = (int32_t)*least;
     const uint32_t base = blockIdx.x * kMxTile;
+    int32_t at[kMxItems], over[kMxItems];   // over: the LCP behind a wave's last rank
+#pragma unroll
+    for (uint32_t i = 0; i < kMxItems; ++i) {
+        const uint32_t r = base + i * kBlock + threadIdx.x;
+        at[i] = r < n ? lcp[r] : -1;
+        over[i] = (threadIdx.x & 63u) == 63u && r + 1 < n ? lcp[r + 1] : -1;
+    }
     uint32_t c = 0;
 #pragma unroll
     for (uint32_t i = 0; i < kMxItems; ++i) {
         const uint32_t r = base + i * kBlock + threadIdx.x;
-        const int32_t at = r < n ? lcp[r] : -1;
-        const uint64_t m = __ballot(mx_keeps(lcp, n, r, L, at));
+        const int32_t down = __shfl_down(at[i], 1, kWave);
+        const int32_t next = (threadIdx.x & 63u) == 63u ? over[i] : down;   // -1 past the end
+        const uint64_t m = __ballot(r < n && max(at[i], next) >= L);
         if ((threadIdx.x & 63u) == 0) {
-            kept[(base + i * kBlock + threadIdx.x) >> 6] = m;
+            kept[r >> 6] = m;
             c += (uint32_t)__popcll(m);
         }
     }
     if (c) atomicAdd(&s_n, c);
     __syncthreads();
-    if (threadIdx.x == 0) {
-        count[blockIdx.x] = s_n;
-        if (s_n) atomicAdd(total, s_n);
-    }
+    if (threadIdx.x == 0) count[blockIdx.x] = s_n;
 }
 
 // The kept ranks in order; the first of each run of them gets LCP 0, so
@@ -638,14 +639,12 @@ lor_status mx_drop(const MxLayout &L, uint32_t k, const int32_t **sa, const int3
     LOR_LAUNCH("k_mx_least", 4.0 * pairs, s,
                hipLaunchKernelGGL(k_mx_least, dim3(1), dim3(kBlock), 0, s, L.bound, k, words));
     LOR_LAUNCH("k_mx_count", 4.0 * *n, s,
-               hipLaunchKernelGGL(k_mx_count, dim3(tiles), dim3(kBlock), 0, s, *lcp, *n, words, L.kept, L.count,
-                                  words + 1));
+               hipLaunchKernelGGL(k_mx_count, dim3(tiles), dim3(kBlock), 0, s, *lcp, *n, words, L.kept, L.count));
+    LOR_TRY(scan_exclusive(L.count, tiles, L.stmp, words + 1, s));
     uint32_t h[2];
-    LOR_HIP(hipMemcpyAsync(h, words, sizeof(h), hipMemcpyDeviceToHost, s));
-    LOR_HIP(hipStreamSynchronize(s));
+    LOR_HIP(hipMemcpyWithStream(h, words, sizeof(h), hipMemcpyDeviceToHost, s));   // waits for the stream
     // no pair without a match (records of length 0 need every rank), and few ranks
     if (h[0] == 0 || h[0] == 0xffffffffu || h[1] == 0 || h[1] > *n / kMxDropShare) return LOR_OK;
-    LOR_TRY(scan_exclusive(L.count, tiles, L.stmp, nullptr, s));
     LOR_LAUNCH("k_mx_keep", 0.125 * *n + 16.0 * h[1], s,
                hipLaunchKernelGGL(k_mx_keep, dim3(tiles), dim3(kBlock), 0, s, *sa, *lcp, *n, words, L.kept, L.count,
                                   h[1], L.sa, L.lcp));

@@ -15,8 +15,8 @@
 //   summarised independently (head = part of a run begun earlier, tail =
 //   last open run, best = best pair of the runs closed inside) and combined
 //   in rank order by an associative rule: a workgroup tree per tile, tiles
-//   in order inside a workgroup, then the last workgroup to finish over all
-//   workgroup results. A tile where no LCP reaches L holds only one-suffix runs; its
+//   in order inside a workgroup, then one workgroup over all workgroup
+//   results. A tile where no LCP reaches L holds only one-suffix runs; its
 //   summary needs the last suffix alone, so such tiles read only LCP.
 #include <climits>
 
@@ -168,7 +168,10 @@ __global__ __launch_bounds__(kBlock) void k_cross_max(const int32_t *__restrict_
     if (threadIdx.x == 0) {
         int32_t m = s_red[0];
         for (int i = 1; i < kBlock / kWave; ++i) m = max(m, s_red[i]);
-        if (m > known) atomicMax(out_max, (uint32_t)m);
+        // looked at again first: atomics of all workgroups on one word take
+        // their turns (some 30 ns each, 124 us for 4,096 workgroups)
+        if (m > known && (uint32_t)m > __hip_atomic_load(out_max, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicMax(out_max, (uint32_t)m);
     }
 }
 
@@ -191,6 +194,28 @@ __device__ __forceinline__ ChunkSum load_chunk(const ChunkSum *p) {
         d[i] = __hip_atomic_load(s + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return c;
 }
+
+// The summaries of all workgroups in rank order, by one workgroup.
+__device__ __forceinline__ void combine_all(const ChunkSum *__restrict__ in, uint32_t count, ChunkSum *s_sum,
+                                            uint32_t *__restrict__ result) {
+    const uint32_t each = (count + kBlock - 1) / kBlock;
+    const uint32_t b = min(count, threadIdx.x * each), e = min(count, b + each);
+    ChunkSum c = chunk_empty();
+    for (uint32_t i = b; i < e; ++i) c = chunk_combine(c, load_chunk(in + i));
+    block_reduce_chunks(s_sum, c);
+    if (threadIdx.x == 0) {
+        const ChunkSum g = s_sum[0];
+        int32_t bp = g.bp, bq = g.bq;
+        if (g.has_b) finalize(g.tail, bp, bq);
+        result[0] = (uint32_t)bp;
+        result[1] = (uint32_t)bq;
+    }
+}
+
+// With up to this many workgroups the last one to finish combines their
+// summaries (`done` counts them); more take their turns at the counter for
+// longer than another launch takes.
+constexpr uint32_t kFinishGroups = 256;
 
 // One workgroup per group of `per` tiles. First every tile is
 // checked for an LCP >= L with all its loads in flight at once; tiles
@@ -264,25 +289,23 @@ __global__ __launch_bounds__(kBlock) void k_runs(const int32_t *__restrict__ sa,
         ChunkSum total = chunk_empty();
         for (uint32_t t = t0; t < t1; ++t) total = chunk_combine(total, s_tile[t - t0]);
         out[blockIdx.x] = total;
-        __threadfence();
-        s_last = atomicAdd(done, 1u) == gridDim.x - 1u;
+        s_last = 0;
+        if (done) {
+            __threadfence();
+            s_last = atomicAdd(done, 1u) == gridDim.x - 1u;
+        }
     }
     __syncthreads();
     if (!s_last) return;
-    // the last workgroup to finish combines all of them in rank order
     __threadfence();
-    const uint32_t each = (gridDim.x + kBlock - 1) / kBlock;
-    const uint32_t b = min(gridDim.x, threadIdx.x * each), e = min(gridDim.x, b + each);
-    ChunkSum c = chunk_empty();
-    for (uint32_t i = b; i < e; ++i) c = chunk_combine(c, load_chunk(out + i));
-    block_reduce_chunks(s_sum, c);
-    if (threadIdx.x == 0) {
-        const ChunkSum g = s_sum[0];
-        int32_t bp = g.bp, bq = g.bq;
-        if (g.has_b) finalize(g.tail, bp, bq);
-        result[0] = (uint32_t)bp;
-        result[1] = (uint32_t)bq;
-    }
+    combine_all(out, gridDim.x, s_sum, result);
+}
+
+__global__ __launch_bounds__(kBlock) void k_runs_final(const ChunkSum *__restrict__ in, uint32_t count,
+                                                       const uint32_t *__restrict__ Lp, uint32_t *__restrict__ result) {
+    __shared__ ChunkSum s_sum[kBlock];
+    if (*Lp == 0) return;
+    combine_all(in, count, s_sum, result);
 }
 
 }  // namespace
@@ -305,9 +328,13 @@ lor_status overlap_scan(const int32_t *sa, const int32_t *lcp, uint32_t n, const
     LOR_LAUNCH("k_cross_max", (double)n * 4, s,   // LCP; SA only for the few ranks above the running maximum
                hipLaunchKernelGGL(k_cross_max, dim3(div_up(n - 1, kBlock * kCrossItems)), dim3(kBlock), 0, s, sa, lcp,
                                   n, st, words));
+    const bool finish = groups <= kFinishGroups;
     LOR_LAUNCH("k_runs", (double)n * 4, s,
-               hipLaunchKernelGGL(k_runs, dim3(groups), dim3(kBlock), 0, s, sa, lcp, n, st, group_tiles(n), words, sums, words + 3,
-                                  words + 1));
+               hipLaunchKernelGGL(k_runs, dim3(groups), dim3(kBlock), 0, s, sa, lcp, n, st, group_tiles(n), words, sums,
+                                  finish ? words + 3 : nullptr, words + 1));
+    if (!finish)
+        LOR_LAUNCH("k_runs_final", (double)groups * sizeof(ChunkSum), s,
+                   hipLaunchKernelGGL(k_runs_final, dim3(1), dim3(kBlock), 0, s, sums, groups, words, words + 1));
     uint32_t w[3];   // length, positions
     LOR_HIP(hipMemcpyWithStream(w, words, sizeof(w), hipMemcpyDeviceToHost, s));   // waits for the stream
     const uint32_t L = w[0];

@@ -632,7 +632,8 @@ __global__ __launch_bounds__(kBlock) void k_resolve(X x, GroupKey gk, const KT *
                                                     int32_t *__restrict__ sa, const uint32_t *__restrict__ slots,
                                                     const uint32_t *__restrict__ places, uint32_t near,
                                                     uint64_t *__restrict__ large, uint32_t *__restrict__ tcount,
-                                                    uint32_t *__restrict__ hcount, uint32_t *__restrict__ open,
+                                                    uint32_t *__restrict__ hcount, uint32_t *__restrict__ ocount,
+                                                    uint32_t *__restrict__ open,
                                                     uint32_t *__restrict__ hdr, uint32_t budget) {
     using CH = typename X::CH;
     constexpr bool kFirst = sizeof(KT) == 4;
@@ -858,9 +859,32 @@ __global__ __launch_bounds__(kBlock) void k_resolve(X x, GroupKey gk, const KT *
     if (tid == 0) {
         tcount[blockIdx.x] = s_large;
         hcount[blockIdx.x] = s_heads;
-        if (s_large) atomicAdd(&hdr[kWordTied], s_large);
-        if (s_heads) atomicAdd(&hdr[kWordHeads], s_heads);
-        if (s_open) atomicAdd(&hdr[kWordOpen], s_open);
+        ocount[blockIdx.x] = s_open;
+    }
+}
+
+// Sums of the tiles' counts into the header. Atomics from every tile on three
+// words would take their turns, some 30 ns each.
+constexpr uint32_t kSumGroups = 64;
+__global__ __launch_bounds__(kBlock) void k_resolve_totals(const uint32_t *__restrict__ tcount,
+                                                           const uint32_t *__restrict__ hcount,
+                                                           const uint32_t *__restrict__ ocount, uint32_t tiles,
+                                                           uint32_t *__restrict__ hdr) {
+    __shared__ uint32_t s_tmp[kBlock / kWave];
+    uint32_t t = 0, h = 0, o = 0;
+    for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < tiles; i += gridDim.x * kBlock) {
+        t += tcount[i];
+        h += hcount[i];
+        o += ocount[i];
+    }
+    uint32_t st, sh, so;
+    dev::block_exclusive_sum(t, s_tmp, &st);
+    dev::block_exclusive_sum(h, s_tmp, &sh);
+    dev::block_exclusive_sum(o, s_tmp, &so);
+    if (threadIdx.x == 0) {
+        if (st) atomicAdd(&hdr[kWordTied], st);
+        if (sh) atomicAdd(&hdr[kWordHeads], sh);
+        if (so) atomicAdd(&hdr[kWordOpen], so);
     }
 }
 
@@ -1259,6 +1283,14 @@ lor_status double_runs(const X &x, uint32_t count, uint32_t *open, uint32_t owor
     return LOR_OK;
 }
 
+lor_status sum_counts(const uint32_t *tcount, const uint32_t *hcount, const uint32_t *ocount, uint32_t tiles,
+                      uint32_t *hdr, hipStream_t s) {
+    LOR_LAUNCH("k_resolve_totals", 12.0 * tiles, s,
+               hipLaunchKernelGGL(k_resolve_totals, dim3(std::min(div_up(tiles, kBlock), kSumGroups)), dim3(kBlock), 0,
+                                  s, tcount, hcount, ocount, tiles, hdr));
+    return LOR_OK;
+}
+
 // bits: key bits; near: near suffixes (left out of the sort). *done stays
 // false when DC3 has to build the array.
 template <typename X>
@@ -1286,7 +1318,7 @@ lor_status prefix_sa(const X &x, int bits, uint32_t near, int32_t *sa, Arena &ar
     // sized for every round: the tiles of a smaller count may be smaller, and more
     const uint32_t most = std::max(tiles, div_up(std::min(m, kResSmall), kBlock * kResItemsSmall)) + 1;
     uint64_t *large = ar.take<uint64_t>((size_t)div_up(m, 64) + 64);
-    uint32_t *tcount = ar.take<uint32_t>(most), *hcount = ar.take<uint32_t>(most);
+    uint32_t *tcount = ar.take<uint32_t>(most), *hcount = ar.take<uint32_t>(most), *ocount = ar.take<uint32_t>(most);
     uint32_t *stmp = ar.take<uint32_t>(kScanTmpWords);
     const size_t half = ar.mark();
     uint32_t *kb = ar.take<uint32_t>(m), *counts = ar.take<uint32_t>(radix_counts_words(m));
@@ -1311,8 +1343,9 @@ lor_status prefix_sa(const X &x, int bits, uint32_t near, int32_t *sa, Arena &ar
         auto *resolve = m <= kResSmall ? k_resolve<X, uint32_t, kResItemsSmall> : k_resolve<X, uint32_t, kResItems>;
         LOR_LAUNCH("k_resolve", 12.0 * m, s,
                    hipLaunchKernelGGL(resolve, dim3(tiles), dim3(kBlock), 0, s, x, gk, ka, va, m, sa,
-                                      (const uint32_t *)nullptr, places, near, large, tcount, hcount, open, hdr,
+                                      (const uint32_t *)nullptr, places, near, large, tcount, hcount, ocount, open, hdr,
                                       budget));
+        LOR_TRY(sum_counts(tcount, hcount, ocount, tiles, hdr, s));
     }
     PrefixHdr h;
     LOR_TRY(read_header(hdr, &h, s));
@@ -1332,8 +1365,10 @@ lor_status prefix_sa(const X &x, int bits, uint32_t near, int32_t *sa, Arena &ar
             set_error("internal: %u suffixes in %u large groups of %u", total, groups, cur);
             return LOR_EINVAL;
         }
-        // as many symbols as 56 bits hold beside the group number and the repeat code, at least 5
-        const int gb = bits_for(groups - 1), free_bits = std::max(56 - (int)kCodeBits - gb, 15);
+        // as many symbols as 56 bits hold beside the group number and the repeat code (40 for a
+        // small sort, where a pass costs its launches), at least 5
+        const int gb = bits_for(groups - 1);
+        const int free_bits = std::max((total <= kResSmall ? 40 : 56) - (int)kCodeBits - gb, 15);
         const GroupKey ng{(uint32_t)std::min(free_bits / 3, 10), round ? ar.take<uint32_t>(groups) : nullptr};
         if (round == 0) ar.release(half);   // kb and the counts are free
         uint64_t *k0 = ar.take<uint64_t>(total), *k1 = ar.take<uint64_t>(total);
@@ -1373,7 +1408,8 @@ lor_status prefix_sa(const X &x, int bits, uint32_t near, int32_t *sa, Arena &ar
         auto *resolve = tsmall ? k_resolve<X, uint64_t, kResItemsSmall> : k_resolve<X, uint64_t, kResItems>;
         LOR_LAUNCH("k_resolve", 20.0 * cur, s,
                    hipLaunchKernelGGL(resolve, dim3(nt), dim3(kBlock), 0, s, x, gk, k64, v64, cur, sa, slots,
-                                      (const uint32_t *)nullptr, 0u, large, tcount, hcount, open, hdr, budget));
+                                      (const uint32_t *)nullptr, 0u, large, tcount, hcount, ocount, open, hdr, budget));
+        LOR_TRY(sum_counts(tcount, hcount, ocount, nt, hdr, s));
         LOR_TRY(read_header(hdr, &h, s));
         if (trace_on())
             fprintf(stderr, "[lor] prefix sort: round %d, %u suffixes; left: large groups=%u with %u%s\n", round, total,
