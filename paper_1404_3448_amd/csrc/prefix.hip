@@ -55,6 +55,7 @@ constexpr int kWordTied = 3;       // suffixes in large groups
 constexpr int kWordHeads = 4;      // large groups (next to kWordTied: cleared together)
 constexpr int kWordOpen = 7;       // suffixes still equal to their neighbour, after resolve
 constexpr int kWordRound = 8;      // the same after rounds of doubling
+constexpr int kWordItems = 14;     // items of the run list
 constexpr int kWordSpent = 5;      // comparison budget used, in units of kUnit steps
 
 constexpr uint32_t kSmall = 64;               // largest group resolved in a workgroup
@@ -62,18 +63,20 @@ constexpr uint32_t kSmall = 64;               // largest group resolved in a wor
 // whose time is one workgroup's chain of waits (and its instruction fetches).
 constexpr int kResItems = 4, kResItemsSmall = 1;
 constexpr uint32_t kResSmall = 1u << 18;      // inputs up to here count as small
-constexpr uint32_t kDeep = 256;               // symbols that resolve compares
-constexpr uint32_t kSettle = 2048;            // symbols that k_settle compares
+constexpr uint32_t kDeep = 256;               // symbols that k_settle compares: many open suffixes,
+constexpr uint32_t kSettle = 2048;            // and few
 constexpr uint32_t kUnit = 32;                // 32-byte comparison steps per budget unit
 constexpr uint32_t kCodeBits = 15;
 constexpr uint32_t kExtent = (1u << (kCodeBits - 1)) - 1u;   // longest repeat a key describes
 constexpr uint32_t kRepeatSymbols = (64 - kCodeBits) / 3;    // next symbols of resolve's repeat keys
 constexpr uint32_t kKeyTile = 2048;           // positions per workgroup of the key kernels
+// Texts up to here take every slot as an item and settle without waiting to
+// hear whether anything is open.
+constexpr uint32_t kIdentityItems = 1u << 21;
 constexpr uint32_t kDirectRanks = 1u << 24;   // ranks as plain stores up to here (see kDirectIsa)
 constexpr int kMaxRounds = 4;                 // sorts of large groups before DC3 takes over
 constexpr int kMaxK = 16;
 constexpr uint32_t kScan = 4;                 // group members read from LDS together
-constexpr int kMaxRefine = 5;                 // slots per thread of refine()
 
 // ------------------------------------------------------------ text access
 
@@ -144,35 +147,27 @@ struct Budget {
     }
 };
 
-// Refines classes of equal suffixes in LDS. A class lies inside a group of
-// slots [f, f + size) (group(l, &f) gives its size): cls[l] is the first place
-// of the class of slot l, key[l] >> 32 the symbols its members share. In every
-// step the members of a class compare their texts with its first member: a
-// member that differs after L symbols comes before it, the shorter L the
-// earlier, or after it, the shorter L the later; equal (L, direction) form the
-// classes of the next step. One comparison per member and step, instead of one
-// per pair: members of one tandem repeat all part in the first step. A member
-// that shares max(deep, shared + 64) symbols with the first stays in its class
-// for good. All threads of the workgroup call this; `again`: bit r set when
-// slot_of(r) is in a class to refine, r < rounds.
-template <typename CH, typename SlotOf, typename Group>
-__device__ __forceinline__ void refine(const CH *__restrict__ t, uint32_t n, uint32_t deep, int rounds, SlotOf slot_of,
-                                       Group group, const uint32_t *val, uint64_t *key, uint16_t *cls, uint32_t *flag,
-                                       uint32_t again) {
+// Refines classes of equal suffixes in LDS, one slot per thread: thread l has
+// slot l, whose suffix val[l] is in a group of slots [f, f + size). cls[l] is the
+// first place of its class, which lies inside the group, key[l] >> 32 the symbols
+// that the class shares. In every step the members of a class compare their texts
+// with its first member: a member that differs after L symbols comes before it,
+// the shorter L the earlier, or after it, the shorter L the later; equal (L,
+// direction) form the classes of the next step. One comparison per member and
+// step, instead of one per pair: members of one tandem repeat all part in the
+// first step. A member that shares max(deep, shared + 64) symbols with the first
+// stays in its class for good. All threads of the workgroup call this; `again`:
+// whether the thread's slot is in a class to refine.
+template <typename CH>
+__device__ __forceinline__ void refine(const CH *__restrict__ t, uint32_t n, uint32_t deep, uint32_t f, uint32_t size,
+                                       const uint32_t *val, uint64_t *key, uint16_t *cls, bool again) {
     constexpr uint32_t kEqual = 0x40000000u, kTop = 0x7fffffffu;
-    for (;;) {
-        if (threadIdx.x == 0) *flag = 0;
-        __syncthreads();
-        if (again) *flag = 1;
-        __syncthreads();
-        if (!*flag) break;
-#pragma unroll 1
-        for (int r = 0; r < rounds; ++r) {
-            if (!((again >> r) & 1u)) continue;
-            const uint32_t l = slot_of(r);
-            uint32_t f;
-            group(l, &f);
-            const uint16_t c = cls[l];
+    const uint32_t l = threadIdx.x;
+    while (__syncthreads_or(again)) {
+        uint16_t c = 0;
+        uint32_t mine = 0;
+        if (again) {
+            c = cls[l];
             uint32_t first = l;
             for (uint32_t q = f; q < l; q += kScan) {
                 uint16_t x[kScan];
@@ -183,26 +178,20 @@ __device__ __forceinline__ void refine(const CH *__restrict__ t, uint32_t n, uin
                     if (x[i] == c) first = min(first, min(q + i, l));
                 if (first < l) break;
             }
-            uint32_t k = kEqual;
+            mine = kEqual;
             if (first != l) {
                 const uint32_t p = val[l], q = val[first], h = (uint32_t)(key[l] >> 32), cap = max(deep, h + 64u);
                 const uint32_t L = dev::extend<CH, 2>(t, n, p, q, h, cap);
                 if (L < cap) {
                     const bool less = L >= n - max(p, q) ? p > q : t[p + L] < t[q + L];
-                    k = less ? L : kTop - L;
+                    mine = less ? L : kTop - L;
                 }
             }
-            key[l] = (key[l] & 0xffffffff00000000ull) | k;
+            key[l] = (key[l] & 0xffffffff00000000ull) | mine;
         }
         __syncthreads();
-        uint32_t next = 0, place[kMaxRefine];
-#pragma unroll
-        for (int r = 0; r < kMaxRefine; ++r) {
-            if (r >= rounds || !((again >> r) & 1u)) continue;
-            const uint32_t l = slot_of(r), mine = (uint32_t)key[l];
-            uint32_t f, less = 0, same = 0;
-            const uint32_t size = group(l, &f);
-            const uint16_t c = cls[l];
+        uint32_t less = 0, same = 0;
+        if (again) {
             for (uint32_t q = f; q < f + size; q += kScan) {
                 uint16_t x[kScan];
                 uint32_t y[kScan];
@@ -218,18 +207,13 @@ __device__ __forceinline__ void refine(const CH *__restrict__ t, uint32_t n, uin
                     same += x[i] == c && y[i] == mine;
                 }
             }
-            place[r] = c + less;
-            if (same > 1 && mine != kEqual) next |= 1u << r;
         }
         __syncthreads();
-#pragma unroll
-        for (int r = 0; r < kMaxRefine; ++r) {
-            if (r >= rounds || !((again >> r) & 1u)) continue;
-            const uint32_t l = slot_of(r), mine = (uint32_t)key[l];
-            cls[l] = (uint16_t)place[r];
+        if (again) {
+            cls[l] = (uint16_t)(c + less);
             if (mine != kEqual) key[l] = (uint64_t)(mine < kEqual ? mine : kTop - mine) << 32;
+            again = same > 1 && mine != kEqual;
         }
-        again = next;
     }
 }
 
@@ -328,14 +312,19 @@ __device__ __forceinline__ uint32_t seq_of(const int32_t *start, uint32_t count,
     return lo;
 }
 
-// The kernels also clear the tile's words of `open` (see Runs).
-__device__ __forceinline__ void clear_open(uint32_t *open, uint32_t n, uint32_t base) {
+// The kernels also clear the tile's words of the run bits (see RunList).
+struct OpenBits {
+    uint32_t *open, *was;   // was may be null
+};
+__device__ __forceinline__ void clear_open(const OpenBits &o, uint32_t n, uint32_t base) {
     const uint32_t i = base / 32u + threadIdx.x;
-    if (threadIdx.x < kKeyTile / 32u && i < (n + 31u) / 32u) open[i] = 0;
+    if (threadIdx.x >= kKeyTile / 32u || i >= (n + 31u) / 32u) return;
+    o.open[i] = 0;
+    if (o.was) o.was[i] = 0;
 }
 
 __global__ __launch_bounds__(kBlock) void k_prefix_keys(Joined x, uint32_t *__restrict__ keys,
-                                                        uint32_t *__restrict__ vals, uint32_t *__restrict__ open) {
+                                                        uint32_t *__restrict__ vals, OpenBits open) {
     __shared__ uint32_t s_w[kKeyWords];
     __shared__ int32_t s_start[kMaxSeqs + 1];
     __shared__ uint32_t s_below[kMaxSeqs + 1];
@@ -369,8 +358,7 @@ __global__ __launch_bounds__(kBlock) void k_prefix_keys(Joined x, uint32_t *__re
 }
 
 __global__ __launch_bounds__(kBlock) void k_prefix_keys_tagged(Tagged x, uint32_t *__restrict__ keys,
-                                                               uint32_t *__restrict__ vals,
-                                                               uint32_t *__restrict__ open) {
+                                                               uint32_t *__restrict__ vals, OpenBits open) {
     const uint32_t m = x.n - x.near;
     __shared__ uint32_t s_w[kKeyWords];
     const uint32_t base = blockIdx.x * kKeyTile, tid = threadIdx.x;
@@ -401,7 +389,7 @@ __global__ __launch_bounds__(kBlock) void k_prefix_keys_tagged(Tagged x, uint32_
 // key(p) = s_p 5^(K-1) + key(p+1) / 5.
 constexpr int kShareRun = 8;
 __global__ __launch_bounds__(kBlock) void k_prefix_keys_shared(Shared x, uint32_t top, uint32_t *__restrict__ keys,
-                                                               uint32_t *__restrict__ open) {
+                                                               OpenBits open) {
     static_assert(kBlock * kShareRun == kKeyTile, "clear_open covers a workgroup's positions");
     clear_open(open, x.n, blockIdx.x * kKeyTile);
     const uint32_t p0 = (blockIdx.x * kBlock + threadIdx.x) * kShareRun;
@@ -621,8 +609,9 @@ struct GroupKey {
 // its whole group and works out its own place; members just outside the tile
 // are looked at by both workgroups. 8 text bytes behind the known prefix are
 // gathered into LDS for every tied rank; a rank's place is the number of
-// smaller ones in its group. Members that agree there too form a class, which
-// goes on with repeat keys (stage 0) and at last with refine().
+// smaller ones in its group. Members that agree there too stay neighbours in
+// the order they came in and are marked in `open` (see RunList) for k_settle, so
+// that the few of them do not hold up the many.
 // Stage 0 (32-bit keys of the sort) writes places shifted by the near
 // suffixes; stage 1 (64-bit keys of large groups) through `slots`. Larger
 // groups are marked in `large` and counted, with their heads, per tile.
@@ -633,19 +622,17 @@ __global__ __launch_bounds__(kBlock) void k_resolve(X x, GroupKey gk, const KT *
                                                     const uint32_t *__restrict__ places, uint32_t near,
                                                     uint64_t *__restrict__ large, uint32_t *__restrict__ tcount,
                                                     uint32_t *__restrict__ hcount, uint32_t *__restrict__ ocount,
-                                                    uint32_t *__restrict__ open,
-                                                    uint32_t *__restrict__ hdr, uint32_t budget) {
+                                                    uint32_t *__restrict__ open, uint32_t *__restrict__ was) {
     using CH = typename X::CH;
     constexpr bool kFirst = sizeof(KT) == 4;
     constexpr uint32_t kResTile = kBlock * ITEMS, kResWords = kResTile / 64;
     constexpr uint32_t kSlots = kResTile + 2 * kSmall;
-    static_assert(ITEMS + 1 <= kMaxRefine, "");
     constexpr int kWaves = kBlock / kWave;
     __shared__ uint64_t s_head[kResWords + 2];
     __shared__ uint32_t s_val[kSlots];
     __shared__ uint64_t s_win[kSlots];
     __shared__ uint16_t s_cls[kSlots];
-    __shared__ uint32_t s_shift[2], s_large, s_heads, s_again, s_open;
+    __shared__ uint32_t s_shift[2], s_large, s_heads, s_open;
     const uint32_t base = blockIdx.x * kResTile, tid = threadIdx.x, lane = tid & 63u, w = tid >> 6;
     // Round r < ITEMS: slot kSmall + 256 r + tid, rank base + 256 r + tid;
     // the last round: the ranks beside the tile, waves 0 (before) and 1 (after).
@@ -676,7 +663,7 @@ __global__ __launch_bounds__(kBlock) void k_resolve(X x, GroupKey gk, const KT *
                                           w == 2 ? (base > kSmall ? base - kSmall : 0u) : base + kResTile + kSmall);
         if (lane == 0) s_shift[w - 2] = a;
     }
-    if (tid == 0) s_large = s_heads = s_again = s_open = 0;
+    if (tid == 0) s_large = s_heads = s_open = 0;
     __syncthreads();
 
     // Group of a slot: first slot and size; size 0 when it is larger than kSmall.
@@ -725,10 +712,9 @@ __global__ __launch_bounds__(kBlock) void k_resolve(X x, GroupKey gk, const KT *
         if (r < ITEMS || w < 2) s_win[slot_of(r)] = win[r];
     __syncthreads();
     // class of every tied rank: first place of those with its window
-    uint32_t again = 0;   // bit r: others share it
 #pragma unroll
     for (int r = 0; r <= ITEMS; ++r) {
-        uint32_t f, same = 0;
+        uint32_t f;
         const uint32_t size = tied(r, &f);
         if (size > 1) {
             uint32_t less = f;
@@ -737,72 +723,12 @@ __global__ __launch_bounds__(kBlock) void k_resolve(X x, GroupKey gk, const KT *
 #pragma unroll
                 for (uint32_t i = 0; i < kScan; ++i) y[i] = s_win[min(q + i, f + size - 1u)];
 #pragma unroll
-                for (uint32_t i = 0; i < kScan; ++i) {
-                    less += q + i < f + size && y[i] < win[r];
-                    same += q + i < f + size && y[i] == win[r];
-                }
+                for (uint32_t i = 0; i < kScan; ++i) less += q + i < f + size && y[i] < win[r];
             }
             s_cls[slot_of(r)] = (uint16_t)less;
         }
-        again |= (same > 1 ? 1u : 0u) << r;
     }
-    if (__any(again != 0) && lane == 0) s_again = 1;
     __syncthreads();
-    if (s_again) {   // uniform
-        if constexpr (kFirst) {
-#pragma unroll 1
-            for (int r = 0; r <= ITEMS; ++r) {
-                if (!((again >> r) & 1u)) continue;
-                const uint32_t l = slot_of(r);
-                s_win[l] = repeat_key(x, s_val[l], period_at(x, s_val[l]), kRepeatSymbols, hdr, budget);
-            }
-            __syncthreads();
-            uint32_t place[ITEMS + 1], next = 0;
-            uint64_t mine[ITEMS + 1];
-#pragma unroll
-            for (int r = 0; r <= ITEMS; ++r) {
-                if (!((again >> r) & 1u)) continue;
-                const uint32_t l = slot_of(r);
-                uint32_t f, same = 0;
-                const uint32_t size = group(l, &f);
-                const uint16_t c = s_cls[l];
-                mine[r] = s_win[l];
-                place[r] = c;
-                for (uint32_t q = f; q < f + size; q += kScan) {
-                    uint16_t x[kScan];
-                    uint64_t y[kScan];
-#pragma unroll
-                    for (uint32_t i = 0; i < kScan; ++i) {
-                        const uint32_t o = min(q + i, f + size - 1u);
-                        x[i] = q + i < f + size ? s_cls[o] : (uint16_t)0xffffu;
-                        y[i] = s_win[o];
-                    }
-#pragma unroll
-                    for (uint32_t i = 0; i < kScan; ++i) {
-                        place[r] += x[i] == c && y[i] < mine[r];
-                        same += x[i] == c && y[i] == mine[r];
-                    }
-                }
-                next |= (same > 1 ? 1u : 0u) << r;
-            }
-            __syncthreads();
-#pragma unroll
-            for (int r = 0; r <= ITEMS; ++r) {
-                if (!((again >> r) & 1u)) continue;
-                const uint32_t l = slot_of(r), c = (uint32_t)(mine[r] >> (3u * kRepeatSymbols));
-                s_cls[l] = (uint16_t)place[r];
-                s_win[l] = (uint64_t)max((uint32_t)x.K, c <= kExtent ? c : 2u * kExtent + 1u - c) << 32;
-            }
-            again = next;
-        } else {
-#pragma unroll
-            for (int r = 0; r <= ITEMS; ++r)
-                if ((again >> r) & 1u)
-                    s_win[slot_of(r)] = (uint64_t)max((uint32_t)x.K, gk.reach(keys[rank_of(r)])) << 32;
-        }
-        __syncthreads();
-        refine(x.t, x.n, kDeep, ITEMS + 1, slot_of, group, s_val, s_win, s_cls, &s_again, again);
-    }
 
     const uint32_t sh0 = kFirst ? s_shift[0] : 0u, sh1 = kFirst ? s_shift[1] : 0u;
     uint32_t lost = 0, heads = 0;
@@ -848,6 +774,7 @@ __global__ __launch_bounds__(kBlock) void k_resolve(X x, GroupKey gk, const KT *
         sa[slot] = (int32_t)v;
         if (same) {
             atomicOr(&open[slot >> 5], 1u << (slot & 31u));
+            if (was) atomicOr(&was[slot >> 5], 1u << (slot & 31u));
             atomicAdd(&s_open, 1u);
         }
     }
@@ -908,9 +835,18 @@ __global__ __launch_bounds__(kBlock) void k_group_collect(GroupKey gk, int K, co
     constexpr uint32_t kResTile = kBlock * ITEMS, kResWords = kResTile / 64;
     __shared__ uint32_t s_below[kResWords], s_hbelow[kResWords];
     __shared__ uint64_t s_bits[kResWords], s_head[kResWords];
-    __shared__ uint32_t s_shift[2];
+    __shared__ uint32_t s_shift[2], s_none;
     const uint32_t base = blockIdx.x * kResTile, tid = threadIdx.x, lane = tid & 63u, w = tid >> 6;
     static_assert(kResWords <= 64, "one lane per word");
+    // most tiles hold no large group
+    if (w == 0) {
+        const uint64_t b = lane < kResWords ? large[(size_t)blockIdx.x * kResWords + lane] : 0ull;
+        if (lane < kResWords) s_bits[lane] = b;
+        if (lane == 0) s_none = 1;
+        if (b) s_none = 0;
+    }
+    __syncthreads();
+    if (s_none) return;
     KT key[ITEMS];
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {
@@ -926,11 +862,10 @@ __global__ __launch_bounds__(kBlock) void k_group_collect(GroupKey gk, int K, co
     }
     __syncthreads();
     if (w == 0) {
-        const uint64_t b = lane < kResWords ? large[(size_t)blockIdx.x * kResWords + lane] : 0ull;
+        const uint64_t b = lane < kResWords ? s_bits[lane] : 0ull;
         const uint32_t c = (uint32_t)__popcll(b), hc = lane < kResWords ? (uint32_t)__popcll(b & s_head[lane]) : 0u;
         const uint32_t inc = dev::wave_inclusive_sum(c), hinc = dev::wave_inclusive_sum(hc);
         if (lane < kResWords) {
-            s_bits[lane] = b;
             s_below[lane] = inc - c;
             s_hbelow[lane] = hinc - hc;
         }
@@ -969,50 +904,99 @@ __global__ __launch_bounds__(kBlock) void k_group_keys(X x, GroupKey gk, uint64_
     tkeys[i] = (id << gk.shift()) | repeat_key(x, q, period_at(x, q), gk.ns, hdr, budget);
 }
 
-// --------------------------------------------------------------- doubling
-// What direct comparisons leave open: runs of slots (at most kSmall) whose
-// suffixes share at least h = kDeep symbols, marked in `open` (bit s: slot s
-// shares them with slot s - 1). With rank[p] the first slot of p's run, the
-// suffixes of a run are ordered by rank[p + h], after which open runs share
-// 2 h symbols; a few rounds settle long exact or nearly exact copies that a
+// -------------------------------------------------------------- open runs
+// What resolve leaves open: runs of neighbouring slots (at most kSmall) whose
+// suffixes agree as far as it looked. An item is a slot that is in a run, or in
+// small texts any slot (RunList::slots is null then); bit i of `open`: item i
+// agrees with item i - 1. k_settle compares texts; what is left then shares h
+// symbols and is settled by doubling: with rank[p] the first slot of p's run,
+// the suffixes of a run are ordered by rank[p + h], after which open runs share
+// 2 h symbols, so a few rounds settle long exact or nearly exact copies that a
 // comparison would walk through suffix by suffix. A workgroup owns the runs
-// that start in its tile. Ranks only change between the rounds (k_run_ranks):
-// all of a round's lookups see the same ranks.
-struct Runs {
-    const uint32_t *open;
-    uint32_t n;
-    // first slot of the run of slot s (runs span at most kSmall slots)
-    __device__ uint32_t head(uint32_t s) const {
-        uint32_t wd = s >> 5;
-        uint32_t z = ~open[wd] & (0xffffffffu >> (31u - (s & 31u)));
-        while (!z && wd > 0) z = ~open[--wd];
-        return z ? wd * 32u + 31u - (uint32_t)__builtin_clz(z) : 0u;
-    }
-    __device__ bool bit(uint32_t s) const { return s < n && ((open[s >> 5] >> (s & 31u)) & 1u); }
+// that start in its tile of items; `was` holds the bits of before the launch.
+// Ranks only change between the rounds (k_run_ranks): all of a round's lookups
+// see the same ranks.
+struct RunList {
+    const uint32_t *slots;   // slot of every item (null: the item itself)
+    const uint32_t *count;   // device word: the number of items (null: cap)
+    uint32_t cap;
+    __device__ uint32_t items() const { return count ? min(*count, cap) : cap; }
+    __device__ uint32_t slot(uint32_t i) const { return slots ? slots[i] : i; }
 };
 
-// rank of every suffix: to its text position, or in slot order for a scatter.
-template <bool PLACE>
-__global__ __launch_bounds__(kBlock) void k_ranks(Runs runs, const int32_t *__restrict__ sa,
-                                                  uint32_t *__restrict__ rank) {
-    for (uint32_t s = blockIdx.x * kBlock + threadIdx.x; s < runs.n; s += gridDim.x * kBlock) {
-        const uint32_t h = runs.head(s);
-        if constexpr (PLACE) {
-            const uint32_t p = (uint32_t)sa[s];
-            if (p < runs.n) rank[p] = h;
-        } else {
-            rank[s] = h;
+__device__ __forceinline__ bool open_bit(const uint32_t *open, uint32_t i, uint32_t items) {
+    return i < items && ((open[i >> 5] >> (i & 31u)) & 1u);
+}
+
+// Slots in runs: those marked and those before a marked one.
+__device__ __forceinline__ uint32_t run_members(const uint32_t *__restrict__ open, uint32_t words, uint32_t w) {
+    if (w >= words) return 0;
+    const uint32_t b = open[w], next = w + 1 < words ? open[w + 1] & 1u : 0u;
+    return b | (b >> 1) | (next << 31);
+}
+
+// The items of a large text: the slots in runs, in slot order, so that the few
+// of them fill their workgroups (one tile of slots in two holds a run on DNA
+// texts of 16M bases, but few of them: 337 us in k_settle over slots, 60 over the list and 20 to make it).
+constexpr uint32_t kOpenWords = 4 * kBlock;   // bitmap words per workgroup
+__global__ __launch_bounds__(kBlock) void k_open_count(const uint32_t *__restrict__ open, uint32_t words,
+                                                       uint32_t *__restrict__ count) {
+    __shared__ uint32_t s_tmp[kBlock / kWave];
+    uint32_t c = 0, all;
+#pragma unroll
+    for (uint32_t r = 0; r < 4; ++r)
+        c += (uint32_t)__popc(run_members(open, words, blockIdx.x * kOpenWords + r * kBlock + threadIdx.x));
+    dev::block_exclusive_sum(c, s_tmp, &all);
+    if (threadIdx.x == 0) count[blockIdx.x] = all;
+}
+
+__global__ __launch_bounds__(kBlock) void k_open_list(const uint32_t *__restrict__ open, uint32_t words,
+                                                      const uint32_t *__restrict__ first, uint32_t cap,
+                                                      uint32_t *__restrict__ slots, uint32_t *__restrict__ bits) {
+    __shared__ uint32_t s_tmp[kBlock / kWave];
+    uint32_t base = first[blockIdx.x];
+    for (uint32_t r = 0; r < 4; ++r) {
+        const uint32_t w = blockIdx.x * kOpenWords + r * kBlock + threadIdx.x;
+        uint32_t m = run_members(open, words, w), all;
+        uint32_t at = base + dev::block_exclusive_sum((uint32_t)__popc(m), s_tmp, &all);
+        const uint32_t b = m ? open[w] : 0u;
+        for (; m; m &= m - 1u, ++at) {
+            const uint32_t i = (uint32_t)__builtin_ctz(m);
+            if (at >= cap) break;   // never with consistent counts
+            slots[at] = 32u * w + i;
+            if ((b >> i) & 1u) atomicOr(&bits[at >> 5], 1u << (at & 31u));
         }
+        base += all;
     }
 }
 
-// New ranks of the suffixes that were in runs before the round (`was`).
-__global__ __launch_bounds__(kBlock) void k_run_ranks(Runs runs, Runs was, const int32_t *__restrict__ sa,
-                                                      uint32_t *__restrict__ rank) {
-    for (uint32_t s = blockIdx.x * kBlock + threadIdx.x; s < runs.n; s += gridDim.x * kBlock) {
-        if (!was.bit(s) && !was.bit(s + 1)) continue;
+__device__ __forceinline__ uint32_t run_head(const uint32_t *__restrict__ open, uint32_t i) {
+    uint32_t wd = i >> 5;
+    uint32_t z = ~open[wd] & (0xffffffffu >> (31u - (i & 31u)));
+    while (!z && wd > 0) z = ~open[--wd];
+    return z ? wd * 32u + 31u - (uint32_t)__builtin_clz(z) : 0u;
+}
+
+// rank of every suffix: the first slot of its run where the items are the
+// slots, else its slot.
+__global__ __launch_bounds__(kBlock) void k_ranks(uint32_t n, const int32_t *__restrict__ sa,
+                                                  const uint32_t *__restrict__ open, uint32_t *__restrict__ rank) {
+    for (uint32_t s = blockIdx.x * kBlock + threadIdx.x; s < n; s += gridDim.x * kBlock) {
         const uint32_t p = (uint32_t)sa[s];
-        if (p < runs.n) rank[p] = runs.head(s);
+        if (p < n) rank[p] = open ? run_head(open, s) : s;
+    }
+}
+
+// Ranks of the suffixes that were in runs before the round: the slot of their
+// run's first item now.
+__global__ __launch_bounds__(kBlock) void k_run_ranks(RunList list, const uint32_t *__restrict__ open,
+                                                      const uint32_t *__restrict__ was, uint32_t n,
+                                                      const int32_t *__restrict__ sa, uint32_t *__restrict__ rank) {
+    const uint32_t items = list.items();
+    for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < items; i += gridDim.x * kBlock) {
+        if (!open_bit(was, i, items) && !open_bit(was, i + 1, items)) continue;
+        const uint32_t p = (uint32_t)sa[list.slot(i)];
+        if (p < n) rank[p] = list.slot(run_head(open, i));
     }
 }
 
@@ -1021,14 +1005,20 @@ __global__ __launch_bounds__(kBlock) void k_copy_words(const uint32_t *__restric
     for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < count; i += gridDim.x * kBlock) b[i] = a[i];
 }
 
-constexpr uint32_t kRunTile = 1024;
-constexpr uint32_t kRunWords = (kRunTile + 2 * kSmall) / 32;
-constexpr int kRunItems = (kRunTile + kSmall + kBlock - 1) / kBlock;   // slots per thread: the tile's, then kSmall more
+// Items per tile. k_settle: with the kSmall items after them one per thread, so
+// the chains of waits run side by side. k_double, which waits little, has larger ones.
+constexpr uint32_t kSettleTile = kBlock - kSmall, kDoubleTile = 4 * kBlock - kSmall;
+// Workgroups of k_settle and of the (shorter) k_double: each may end in an
+// atomic on the same word, about 30 ns apart.
+constexpr uint32_t kSettleGroups = 8192, kDoubleGroups = 2048;
+constexpr uint32_t kRepeatRun = 5;
 
-// A tile's run bits (and those of the slots after it) in LDS.
+// A tile's run bits (and those of the items after it) in LDS.
+template <uint32_t TILE>
 struct RunTile {
-    const uint32_t *bits;   // kRunWords words
-    // Slot l of the tile or of the kSmall after it: first slot and size of its
+    static constexpr uint32_t kWords = (TILE + 2 * kSmall) / 32;
+    const uint32_t *bits;   // kWords words
+    // Item l of the tile or of the kSmall after it: first item and size of its
     // run, size 0 when the run is one suffix or starts in another tile.
     __device__ uint32_t run_of(uint32_t l, uint32_t *first) const {
         uint32_t wd = l >> 5;
@@ -1038,124 +1028,146 @@ struct RunTile {
         const uint32_t f = wd * 32u + 31u - (uint32_t)__builtin_clz(z);
         uint32_t g = l + 1;
         wd = g >> 5;
-        z = wd < kRunWords ? ~bits[wd] & (0xffffffffu << (g & 31u)) : 1u;
-        while (!z && ++wd < kRunWords) z = ~bits[wd];
-        g = wd < kRunWords ? wd * 32u + (uint32_t)__builtin_ctz(z) : kRunTile + 2 * kSmall;
+        z = wd < kWords ? ~bits[wd] & (0xffffffffu << (g & 31u)) : 1u;
+        while (!z && ++wd < kWords) z = ~bits[wd];
+        g = wd < kWords ? wd * 32u + (uint32_t)__builtin_ctz(z) : TILE + 2 * kSmall;
         *first = f;
-        return f < kRunTile && g - f > 1 && g - f <= kSmall ? g - f : 0u;
+        return f < TILE && g - f > 1 && g - f <= kSmall ? g - f : 0u;
+    }
+    // Loads the bits of the tile that starts at item `base`; false (for the
+    // whole workgroup) when no run is near.
+    static __device__ bool load(const uint32_t *__restrict__ was, uint32_t items, uint32_t base, uint32_t *s_bits) {
+        const uint32_t words = (items + 31u) / 32u, i = threadIdx.x, w = base / 32u + i;
+        const uint32_t b = i < kWords && w < words ? was[w] : 0u;
+        __syncthreads();   // the tile before is done with its bits
+        if (i < kWords) s_bits[i] = b;
+        return __syncthreads_or(b != 0) != 0;
     }
 };
-// Loads the bits; false (for the whole workgroup) when no run is near.
-__device__ __forceinline__ bool load_runs(const uint32_t *__restrict__ was, uint32_t n, uint32_t base,
-                                          uint32_t *s_bits, uint32_t *s_any) {
-    const uint32_t words = (n + 31u) / 32u;
-    if (threadIdx.x == 0) *s_any = 0;
-    __syncthreads();
-    if (threadIdx.x < kRunWords) {
-        const uint32_t b = base / 32u + threadIdx.x < words ? was[base / 32u + threadIdx.x] : 0u;
-        s_bits[threadIdx.x] = b;
-        if (b) *s_any = 1;
-    }
-    __syncthreads();
-    return *s_any != 0;
-}
 
-__global__ __launch_bounds__(kBlock) void k_double(const uint32_t *__restrict__ was, uint32_t *__restrict__ open,
-                                                   uint32_t n, uint32_t h, const uint32_t *__restrict__ rank,
-                                                   int32_t *__restrict__ sa, uint32_t *__restrict__ left) {
-    __shared__ uint32_t s_bits[kRunWords], s_rank[kRunTile + kSmall], s_any, s_left;
-    const uint32_t base = blockIdx.x * kRunTile, tid = threadIdx.x;
+__global__ __launch_bounds__(kBlock) void k_double(RunList list, const uint32_t *__restrict__ was,
+                                                   uint32_t *__restrict__ open, uint32_t n, uint32_t h,
+                                                   const uint32_t *__restrict__ rank, int32_t *__restrict__ sa,
+                                                   uint32_t *__restrict__ left) {
+    using Tile = RunTile<kDoubleTile>;
+    constexpr int kPer = (kDoubleTile + kSmall) / kBlock;
+    static_assert(kPer * kBlock == kDoubleTile + kSmall, "whole items per thread");
+    __shared__ uint32_t s_bits[Tile::kWords], s_rank[kPer * kBlock], s_left;
+    const uint32_t tid = threadIdx.x, items = list.items();
+    const Tile runs{s_bits};
     if (tid == 0) s_left = 0;
-    if (!load_runs(was, n, base, s_bits, &s_any)) return;
-    const RunTile runs{s_bits};
-    uint32_t val[kRunItems];
+    for (uint32_t base = blockIdx.x * kDoubleTile; base < items; base += gridDim.x * kDoubleTile) {
+        if (!Tile::load(was, items, base, s_bits)) continue;
+        uint32_t val[kPer];
 #pragma unroll
-    for (int r = 0; r < kRunItems; ++r) {
-        const uint32_t l = r * kBlock + tid;
-        uint32_t f;
-        val[r] = 0xffffffffu;
-        if (l < kRunTile + kSmall && base + l < n && runs.run_of(l, &f)) {
-            const uint32_t p = (uint32_t)sa[base + l];
-            val[r] = p;
-            s_rank[l] = p < n && h < n - p ? rank[p + h] + 1u : 0u;   // the end of the text comes first
+        for (int r = 0; r < kPer; ++r) {
+            const uint32_t l = r * kBlock + tid;
+            uint32_t f;
+            val[r] = 0xffffffffu;
+            if (base + l < items && runs.run_of(l, &f)) {
+                const uint32_t p = (uint32_t)sa[list.slot(base + l)];
+                val[r] = p;
+                s_rank[l] = p < n && h < n - p ? rank[p + h] + 1u : 0u;   // the end of the text comes first
+            }
         }
-    }
-    __syncthreads();
-    uint32_t mine_left = 0;
+        __syncthreads();
+        uint32_t mine_left = 0;
 #pragma unroll
-    for (int r = 0; r < kRunItems; ++r) {
-        const uint32_t l = r * kBlock + tid;
-        if (val[r] == 0xffffffffu) continue;
-        uint32_t f;
-        const uint32_t size = runs.run_of(l, &f), mine = s_rank[l];
-        uint32_t place = f, same = 0;
+        for (int r = 0; r < kPer; ++r) {
+            const uint32_t l = r * kBlock + tid;
+            if (val[r] == 0xffffffffu) continue;
+            uint32_t f;
+            const uint32_t size = runs.run_of(l, &f), mine = s_rank[l];
+            uint32_t place = f, same = 0;
 #pragma unroll 4
-        for (uint32_t q = f; q < f + size; ++q) {
-            const uint32_t o = s_rank[q];
-            place += o < mine;
-            same += o == mine && q < l;
+            for (uint32_t q = f; q < f + size; ++q) {
+                const uint32_t o = s_rank[q];
+                place += o < mine;
+                same += o == mine && q < l;
+            }
+            place += same;
+            const uint32_t to = base + place;
+            if (to >= items) continue;
+            sa[list.slot(to)] = (int32_t)val[r];
+            if (same) ++mine_left;
+            else if (place != f) atomicAnd(&open[to >> 5], ~(1u << (to & 31u)));
         }
-        place += same;
-        const uint32_t slot = base + place;
-        if (slot >= n) continue;
-        sa[slot] = (int32_t)val[r];
-        if (same) ++mine_left;
-        else if (place != f) atomicAnd(&open[slot >> 5], ~(1u << (slot & 31u)));
+        if (mine_left) atomicAdd(&s_left, mine_left);
     }
-    if (mine_left) atomicAdd(&s_left, mine_left);
     __syncthreads();
     if (tid == 0 && s_left) atomicAdd(left, s_left);
 }
 
-// The same by comparing texts, up to kSettle symbols: when few suffixes are
-// open, ranks of all of them cost more than these comparisons.
+// The same by comparing texts, up to `deep` symbols. Repeat keys come first: a
+// tandem repeat inside one run would cost a long comparison per member and step
+// otherwise. Runs of fewer than kRepeatRun, which have few steps, do without:
+// the keys read as much as a comparison does. Runs share at least the K symbols
+// of their sort key.
 template <typename X>
-__global__ __launch_bounds__(kBlock) void k_settle(X x, const uint32_t *__restrict__ was, uint32_t *__restrict__ open,
-                                                   int32_t *__restrict__ sa, uint32_t *__restrict__ left) {
-    __shared__ uint32_t s_bits[kRunWords], s_val[kRunTile + kSmall], s_any, s_left;
-    __shared__ uint64_t s_key[kRunTile + kSmall];
-    __shared__ uint16_t s_cls[kRunTile + kSmall];
-    static_assert(kRunItems <= kMaxRefine, "");
-    const uint32_t base = blockIdx.x * kRunTile, tid = threadIdx.x;
-    if (tid == 0) s_left = 0;
-    if (!load_runs(was, x.n, base, s_bits, &s_any)) return;
-    const RunTile runs{s_bits};
-    uint32_t again = 0;
-    auto slot_of = [&](int r) { return r * kBlock + tid; };
-    auto group = [&](uint32_t l, uint32_t *first) { return runs.run_of(l, first); };
+__global__ __launch_bounds__(kBlock) void k_settle(X x, RunList list, const uint32_t *__restrict__ was,
+                                                   uint32_t *__restrict__ open, int32_t *__restrict__ sa,
+                                                   uint32_t deep, uint32_t *__restrict__ left,
+                                                   uint32_t *__restrict__ hdr, uint32_t budget) {
+    using Tile = RunTile<kSettleTile>;
+    __shared__ uint32_t s_bits[Tile::kWords], s_val[kBlock], s_left;
+    __shared__ uint64_t s_key[kBlock];
+    __shared__ uint16_t s_cls[kBlock];
+    const uint32_t l = threadIdx.x, items = list.items();
+    const Tile runs{s_bits};
+    if (hdr[kWordTied]) return;   // another round over large groups comes first: all is left as it is
+    if (l == 0) s_left = 0;
+    for (uint32_t base = blockIdx.x * kSettleTile; base < items; base += gridDim.x * kSettleTile) {
+        if (!Tile::load(was, items, base, s_bits)) continue;
+        uint32_t f = 0, place = 0, reach = 0;
+        const uint32_t size = base + l < items ? runs.run_of(l, &f) : 0u;
+        uint64_t k = 0;
+        if (size) {
+            const uint32_t p = min((uint32_t)sa[list.slot(base + l)], x.n - 1u);
+            if (size >= kRepeatRun) k = repeat_key(x, p, period_at(x, p), kRepeatSymbols, hdr, budget);
+            s_val[l] = p;
+            s_key[l] = k;
+        }
+        __syncthreads();
+        bool again = false;
+        if (size) {
+            uint32_t same = 0;
+            place = f;
+            for (uint32_t q = f; q < f + size; q += kScan) {
+                uint64_t y[kScan];
 #pragma unroll
-    for (int r = 0; r < kRunItems; ++r) {
-        const uint32_t l = slot_of(r);
-        uint32_t f;
-        if (l < kRunTile + kSmall && base + l < x.n && runs.run_of(l, &f)) {
-            s_val[l] = min((uint32_t)sa[base + l], x.n - 1u);
-            s_key[l] = (uint64_t)kDeep << 32;
-            s_cls[l] = (uint16_t)f;
-            again |= 1u << r;
+                for (uint32_t i = 0; i < kScan; ++i) y[i] = s_key[min(q + i, f + size - 1u)];
+#pragma unroll
+                for (uint32_t i = 0; i < kScan; ++i) {
+                    place += q + i < f + size && y[i] < k;
+                    same += q + i < f + size && y[i] == k;
+                }
+            }
+            const uint32_t c = (uint32_t)(k >> (3u * kRepeatSymbols));
+            reach = max((uint32_t)x.K, c <= kExtent ? c : 2u * kExtent + 1u - c);
+            again = same > 1;
+        }
+        // where few are open, as around one long copy, a longer comparison here saves a round
+        const bool sparse = __syncthreads_count(again) <= (int)(kSettleTile / 8) && list.slots == nullptr;
+        if (size) {
+            s_cls[l] = (uint16_t)place;
+            s_key[l] = (uint64_t)reach << 32;
+        }
+        refine(x.t, x.n, sparse ? kSettle : deep, f, size, s_val, s_key, s_cls, again);
+        if (size) {
+            uint32_t same = 0;
+            const uint16_t c = s_cls[l];
+#pragma unroll 4
+            for (uint32_t q = f; q < l; ++q) same += s_cls[q] == c;
+            const uint32_t to = base + c + same;
+            if (to < items) {
+                sa[list.slot(to)] = (int32_t)s_val[l];
+                if (same) atomicAdd(&s_left, 1u);
+                else if (to != base + f) atomicAnd(&open[to >> 5], ~(1u << (to & 31u)));
+            }
         }
     }
-    const uint32_t mine = again;
     __syncthreads();
-    refine(x.t, x.n, kSettle, kRunItems, slot_of, group, s_val, s_key, s_cls, &s_any, again);
-    uint32_t mine_left = 0;
-#pragma unroll
-    for (int r = 0; r < kRunItems; ++r) {
-        if (!((mine >> r) & 1u)) continue;
-        const uint32_t l = slot_of(r);
-        uint32_t f, same = 0;
-        runs.run_of(l, &f);
-        const uint16_t c = s_cls[l];
-#pragma unroll 4
-        for (uint32_t q = f; q < l; ++q) same += s_cls[q] == c;
-        const uint32_t place = c + same, slot = base + place;
-        if (slot >= x.n) continue;
-        sa[slot] = (int32_t)s_val[l];
-        if (same) ++mine_left;
-        else if (place != f) atomicAnd(&open[slot >> 5], ~(1u << (slot & 31u)));
-    }
-    if (mine_left) atomicAdd(&s_left, mine_left);
-    __syncthreads();
-    if (tid == 0 && s_left) atomicAdd(left, s_left);
+    if (l == 0 && s_left) atomicAdd(left, s_left);
 }
 
 // ------------------------------------------------------------------ driver
@@ -1164,17 +1176,17 @@ struct PrefixHdr {
     uint32_t word[16];
 };
 
-lor_status launch_keys(const Joined &x, uint32_t *k, uint32_t *v, uint32_t *open, hipStream_t s) {
+lor_status launch_keys(const Joined &x, uint32_t *k, uint32_t *v, OpenBits open, hipStream_t s) {
     LOR_LAUNCH("k_prefix_keys", 9.0 * x.n, s,
                hipLaunchKernelGGL(k_prefix_keys, dim3(div_up(x.n, kKeyTile)), dim3(kBlock), 0, s, x, k, v, open));
     return LOR_OK;
 }
-lor_status launch_keys(const Tagged &x, uint32_t *k, uint32_t *v, uint32_t *open, hipStream_t s) {
+lor_status launch_keys(const Tagged &x, uint32_t *k, uint32_t *v, OpenBits open, hipStream_t s) {
     LOR_LAUNCH("k_prefix_keys", 10.0 * x.n, s,
                hipLaunchKernelGGL(k_prefix_keys_tagged, dim3(div_up(x.n, kKeyTile)), dim3(kBlock), 0, s, x, k, v, open));
     return LOR_OK;
 }
-lor_status launch_keys(const Shared &x, uint32_t *k, uint32_t *, uint32_t *open, hipStream_t s) {
+lor_status launch_keys(const Shared &x, uint32_t *k, uint32_t *, OpenBits open, hipStream_t s) {
     uint32_t top = 1;
     for (int i = 1; i < x.K; ++i) top *= 5u;
     LOR_LAUNCH("k_prefix_keys", 5.0 * x.n, s,
@@ -1211,64 +1223,106 @@ lor_status read_header(uint32_t *hdr, PrefixHdr *h, hipStream_t s) {
     return LOR_OK;
 }
 
-// Rounds of doubling until no run is open. *done stays false when the
-// workspace does not hold the ranks.
+// Compares the texts of open runs, up to `deep` symbols; the number still open
+// is added to *left.
 template <typename X>
-lor_status double_runs(const X &x, uint32_t count, uint32_t *open, uint32_t owords, int32_t *sa, Arena &ar,
-                       uint32_t *hdr, hipStream_t s, bool *done) {
+lor_status launch_settle(const X &x, const RunList &list, const uint32_t *was, uint32_t *open, int32_t *sa,
+                         uint32_t deep, uint32_t *left, uint32_t *hdr, uint32_t budget, hipStream_t s) {
+    LOR_LAUNCH("k_settle", 0.125 * list.cap, s,
+               hipLaunchKernelGGL(k_settle<X>, dim3(std::min(div_up(list.cap, kSettleTile), kSettleGroups)), dim3(kBlock),
+                                  0, s, x, list, was, open, sa, deep, left, hdr, budget));
+    return LOR_OK;
+}
+
+lor_status copy_words(const uint32_t *a, uint32_t *b, uint32_t count, hipStream_t s) {
+    LOR_LAUNCH("k_copy_words", 8.0 * count, s,
+               hipLaunchKernelGGL(k_copy_words, dim3(grid_for(count)), dim3(kBlock), 0, s, a, b, count));
+    return LOR_OK;
+}
+
+// Settles what is open: `count` suffixes, compared up to `from` symbols so far
+// (0: not yet). *done stays false when the workspace does not hold the ranks or
+// the budget is spent.
+template <typename X>
+lor_status settle_runs(const X &x, uint32_t count, uint32_t from, uint32_t *open, int32_t *sa, Arena &ar,
+                       uint32_t *hdr, uint32_t budget, hipStream_t s, bool *done) {
     const uint32_t n = x.n;
-    uint32_t *was = ar.take<uint32_t>(owords);
+    RunList list{nullptr, nullptr, n};
+    uint32_t words = div_up(n, 32);
+    if (n > kIdentityItems) {
+        // every run has at least one marked slot for each unmarked one
+        list.cap = (uint32_t)std::min<uint64_t>(2ull * count, n);
+        const uint32_t groups = div_up(words, kOpenWords), lwords = div_up(list.cap, 32);
+        uint32_t *slots = ar.take<uint32_t>(list.cap), *bits = ar.take<uint32_t>(lwords);
+        uint32_t *counts = ar.take<uint32_t>(groups), *tmp = ar.take<uint32_t>(kScanTmpWords);
+        if (ar.overflow) return LOR_OK;
+        LOR_LAUNCH("k_open_count", 4.0 * words, s,
+                   hipLaunchKernelGGL(k_open_count, dim3(groups), dim3(kBlock), 0, s, open, words, counts));
+        LOR_TRY(scan_exclusive(counts, groups, tmp, hdr + kWordItems, s));
+        LOR_TRY(zero_words(bits, lwords, s));
+        LOR_LAUNCH("k_open_list", 4.0 * words + 4.0 * list.cap, s,
+                   hipLaunchKernelGGL(k_open_list, dim3(groups), dim3(kBlock), 0, s, open, words, counts, list.cap,
+                                      slots, bits));
+        list.slots = slots;
+        list.count = hdr + kWordItems;
+        open = bits;
+        words = lwords;
+    }
+    uint32_t *was = ar.take<uint32_t>(words);
     if (ar.overflow) return LOR_OK;
-    uint32_t from = kDeep;
+    PrefixHdr w;
     // The ranks of all suffixes (a scatter) and the rounds take about 15 ps per
-    // suffix of the text; comparing an open suffix to its neighbour through
-    // kSettle symbols reads some 60 lines, about 1.5 ns.
-    if (count <= n / 256u + 512u) {
-        LOR_LAUNCH("k_copy_words", 8.0 * owords, s,
-                   hipLaunchKernelGGL(k_copy_words, dim3(grid_for(owords)), dim3(kBlock), 0, s, open, was, owords));
-        LOR_LAUNCH("k_settle", 0.125 * n, s,
-                   hipLaunchKernelGGL(k_settle<X>, dim3(div_up(n, kRunTile)), dim3(kBlock), 0, s, x, was, open, sa,
-                                      hdr + kWordRound + 3));
-        PrefixHdr w;
+    // suffix of the text and 80 us; comparing an open suffix to its neighbour
+    // through kSettle symbols reads some 60 lines, about 1.5 ns: for few only.
+    const uint32_t few = n / 128u + 8192u;
+    for (int step = 0; from == 0 || (from == kDeep && count <= few); ++step) {   // at most two steps
+        from = count <= few ? kSettle : kDeep;
+        LOR_TRY(copy_words(open, was, words, s));
+        LOR_TRY(zero_words(hdr + kWordRound, 1, s));
+        LOR_TRY(launch_settle(x, list, was, open, sa, from, hdr + kWordRound, hdr, budget, s));
         LOR_TRY(read_header(hdr, &w, s));
         if (trace_on())
-            fprintf(stderr, "[lor] prefix sort: %u open suffixes compared, %u left\n", count, w.word[kWordRound + 3]);
-        if (w.word[kWordRound + 3] == 0) {
+            fprintf(stderr, "[lor] prefix sort: %u open suffixes compared up to %u symbols, %u left%s\n", count, from,
+                    w.word[kWordRound], w.word[kWordAbort] ? ", given up" : "");
+        if (w.word[kWordAbort]) return LOR_OK;
+        count = w.word[kWordRound];
+        if (count == 0) {
             *done = true;
             return LOR_OK;
         }
-        from = kSettle;
     }
     uint32_t *rank = ar.take<uint32_t>(n);
     if (ar.overflow) return LOR_OK;
     if (n <= kDirectRanks) {
         LOR_LAUNCH("k_ranks", 8.0 * n, s,
-                   hipLaunchKernelGGL(k_ranks<true>, dim3(grid_for(n)), dim3(kBlock), 0, s, Runs{open, n}, sa, rank));
+                   hipLaunchKernelGGL(k_ranks, dim3(grid_for(n)), dim3(kBlock), 0, s, n, sa,
+                                      list.slots ? nullptr : open, rank));
     } else {
-        uint32_t *heads = ar.take<uint32_t>(n), *tmp[4], *counts;
+        uint32_t *tmp[4], *counts;
         for (int i = 0; i < 4; ++i) tmp[i] = ar.take<uint32_t>(n);
         counts = ar.take<uint32_t>(radix_counts_words(n));
         if (ar.overflow) return LOR_OK;
-        LOR_LAUNCH("k_ranks", 4.0 * n, s,
-                   hipLaunchKernelGGL(k_ranks<false>, dim3(grid_for(n)), dim3(kBlock), 0, s, Runs{open, n}, sa, heads));
-        LOR_TRY(bucketed_scatter(reinterpret_cast<int32_t *>(rank), n, reinterpret_cast<const uint32_t *>(sa), heads,
+        LOR_TRY(bucketed_scatter(reinterpret_cast<int32_t *>(rank), n, reinterpret_cast<const uint32_t *>(sa), nullptr,
                                  0, n, tmp, counts, s, true));
     }
+    auto run_ranks = [&](const uint32_t *before) -> lor_status {
+        LOR_LAUNCH("k_run_ranks", 0.25 * list.cap, s,
+                   hipLaunchKernelGGL(k_run_ranks, dim3(grid_for(list.cap)), dim3(kBlock), 0, s, list, open, before, n,
+                                      sa, rank));
+        return LOR_OK;
+    };
+    if (list.slots) LOR_TRY(run_ranks(open));
     constexpr int kPer = 4;   // rounds between read-backs; a round with nothing open is three short launches
     for (uint64_t h = from;;) {
         LOR_TRY(zero_words(hdr + kWordRound, kPer, s));
         for (int r = 0; r < kPer; ++r, h *= 2) {
             const uint32_t step = (uint32_t)std::min<uint64_t>(h, n);
-            LOR_LAUNCH("k_copy_words", 8.0 * owords, s,
-                       hipLaunchKernelGGL(k_copy_words, dim3(grid_for(owords)), dim3(kBlock), 0, s, open, was, owords));
-            LOR_LAUNCH("k_double", 0.125 * n, s,
-                       hipLaunchKernelGGL(k_double, dim3(div_up(n, kRunTile)), dim3(kBlock), 0, s, was, open, n, step,
-                                          rank, sa, hdr + kWordRound + r));
-            LOR_LAUNCH("k_run_ranks", 0.25 * n, s,
-                       hipLaunchKernelGGL(k_run_ranks, dim3(grid_for(n)), dim3(kBlock), 0, s, Runs{open, n},
-                                          Runs{was, n}, sa, rank));
+            LOR_TRY(copy_words(open, was, words, s));
+            LOR_LAUNCH("k_double", 0.125 * list.cap, s,
+                       hipLaunchKernelGGL(k_double, dim3(std::min(div_up(list.cap, kDoubleTile), kDoubleGroups)),
+                                          dim3(kBlock), 0, s, list, was, open, n, step, rank, sa, hdr + kWordRound + r));
+            LOR_TRY(run_ranks(was));
         }
-        PrefixHdr w;
         LOR_TRY(read_header(hdr, &w, s));
         if (trace_on())
             fprintf(stderr, "[lor] prefix sort: doubling up to %llu symbols, open=%u\n", (unsigned long long)h,
@@ -1312,8 +1366,10 @@ lor_status prefix_sa(const X &x, int bits, uint32_t near, int32_t *sa, Arena &ar
         ~Release() { a.release(m); a.overflow = false; }
     } release{ar, mark};
     const uint32_t owords = div_up(x.n, 32);
-    uint32_t *open = ar.take<uint32_t>(owords);
+    const bool identity = x.n <= kIdentityItems;
+    uint32_t *open = ar.take<uint32_t>(owords), *was = identity ? ar.take<uint32_t>(owords) : nullptr;
     const size_t mark_open = ar.mark();
+    const RunList all{nullptr, nullptr, x.n};
     uint32_t *ka = ar.take<uint32_t>(m), *va = ar.take<uint32_t>(m), *places = ar.take<uint32_t>(near + 1);
     // sized for every round: the tiles of a smaller count may be smaller, and more
     const uint32_t most = std::max(tiles, div_up(std::min(m, kResSmall), kBlock * kResItemsSmall)) + 1;
@@ -1329,7 +1385,7 @@ lor_status prefix_sa(const X &x, int bits, uint32_t near, int32_t *sa, Arena &ar
         const int step = plan().digit_bits, passes = radix_passes(0, bits);
         uint32_t *ki = passes % 2 ? kb : ka, *ko = passes % 2 ? ka : kb;
         uint32_t *vi = passes % 2 ? vb : va, *vo = passes % 2 ? va : vb;
-        LOR_TRY(launch_keys(x, ki, vi, open, s));
+        LOR_TRY(launch_keys(x, ki, vi, OpenBits{open, was}, s));
         for (int sh = 0; sh < bits; sh += step) {
             const uint32_t *in = kImplicit && sh == 0 ? nullptr : vi;
             LOR_TRY(radix_pass<uint32_t>(ki, in, 0, ko, vo, m, sh, std::min(step, bits - sh), counts, s));
@@ -1343,9 +1399,9 @@ lor_status prefix_sa(const X &x, int bits, uint32_t near, int32_t *sa, Arena &ar
         auto *resolve = m <= kResSmall ? k_resolve<X, uint32_t, kResItemsSmall> : k_resolve<X, uint32_t, kResItems>;
         LOR_LAUNCH("k_resolve", 12.0 * m, s,
                    hipLaunchKernelGGL(resolve, dim3(tiles), dim3(kBlock), 0, s, x, gk, ka, va, m, sa,
-                                      (const uint32_t *)nullptr, places, near, large, tcount, hcount, ocount, open, hdr,
-                                      budget));
+                                      (const uint32_t *)nullptr, places, near, large, tcount, hcount, ocount, open, was));
         LOR_TRY(sum_counts(tcount, hcount, ocount, tiles, hdr, s));
+        if (identity) LOR_TRY(launch_settle(x, all, was, open, sa, kDeep, hdr + kWordRound, hdr, budget, s));
     }
     PrefixHdr h;
     LOR_TRY(read_header(hdr, &h, s));
@@ -1408,18 +1464,19 @@ lor_status prefix_sa(const X &x, int bits, uint32_t near, int32_t *sa, Arena &ar
         auto *resolve = tsmall ? k_resolve<X, uint64_t, kResItemsSmall> : k_resolve<X, uint64_t, kResItems>;
         LOR_LAUNCH("k_resolve", 20.0 * cur, s,
                    hipLaunchKernelGGL(resolve, dim3(nt), dim3(kBlock), 0, s, x, gk, k64, v64, cur, sa, slots,
-                                      (const uint32_t *)nullptr, 0u, large, tcount, hcount, ocount, open, hdr, budget));
+                                      (const uint32_t *)nullptr, 0u, large, tcount, hcount, ocount, open, was));
         LOR_TRY(sum_counts(tcount, hcount, ocount, nt, hdr, s));
+        if (identity) LOR_TRY(launch_settle(x, all, was, open, sa, kDeep, hdr + kWordRound, hdr, budget, s));
         LOR_TRY(read_header(hdr, &h, s));
         if (trace_on())
             fprintf(stderr, "[lor] prefix sort: round %d, %u suffixes; left: large groups=%u with %u%s\n", round, total,
                     h.word[kWordHeads], h.word[kWordTied], h.word[kWordAbort] ? ", given up" : "");
     }
     if (h.word[kWordAbort]) return LOR_OK;
-    if (h.word[kWordOpen] > 0) {
+    const uint32_t left = h.word[identity ? kWordRound : kWordOpen];
+    if (left > 0) {
         ar.release(mark_open);
-        LOR_TRY(double_runs(x, h.word[kWordOpen], open, owords, sa, ar, hdr, s, done));
-        return LOR_OK;
+        return settle_runs(x, left, identity ? kDeep : 0u, open, sa, ar, hdr, budget, s, done);
     }
     *done = true;
     return LOR_OK;

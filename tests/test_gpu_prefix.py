@@ -194,3 +194,24 @@ def test_bad_bases_leave_every_access_inside():
         with pytest.raises(lor.LorError) as e:
             call(d, offs)
         assert e.value.status == lor.LOR_EALPHABET
+
+
+@pytest.mark.parametrize("n", [(1 << 21) - 1, 1 << 21, (1 << 21) + 1])
+@pytest.mark.parametrize("copies", ["none", "one", "few", "many"])
+def test_open_runs_by_slot_and_by_list(n, copies):
+    """Up to 2^21 suffixes, runs of suffixes that are still equal are settled
+    slot by slot, above from a list of them: no copies, one of 1,500 bases
+    (longer than one comparison, shorter than the second), copies of 9,000
+    bases (doubling), and so many that the list is as long as the text."""
+    say("prefix open runs", n, copies)
+    rng = np.random.default_rng(n)
+    la = n // 2
+    a, b = synth.gc40_bases(rng, la), synth.gc40_bases(rng, n - 2 - la)   # two separators
+    if copies == "one":
+        b[5000:6500] = a[777:2277]
+    elif copies == "few":
+        for k in range(4):
+            b[k * 20_000:k * 20_000 + 9000] = a[1234:10_234]
+    elif copies == "many":
+        b[:] = synth.mutate(rng, a, 0.0004)[:b.size] if la >= b.size else np.resize(a, b.size)
+    check([a, b])
