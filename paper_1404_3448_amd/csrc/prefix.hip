@@ -69,6 +69,7 @@ constexpr uint32_t kUnit = 32;                // 32-byte comparison steps per bu
 constexpr uint32_t kCodeBits = 15;
 constexpr uint32_t kExtent = (1u << (kCodeBits - 1)) - 1u;   // longest repeat a key describes
 constexpr uint32_t kRepeatSymbols = (64 - kCodeBits) / 3;    // next symbols of resolve's repeat keys
+constexpr uint32_t kRepeat = 16;              // symbols of a repeat bit, less one (see mark_runs)
 constexpr uint32_t kKeyTile = 2048;           // positions per workgroup of the key kernels
 // Texts up to here take every slot as an item and settle without waiting to
 // hear whether anything is open.
@@ -235,6 +236,8 @@ struct Joined {
     uint32_t k;                          // sequences
     uint32_t near;                       // near suffixes in total
     int32_t start[kMaxSeqs + 1];         // joined start of every sequence, plus n
+    uint32_t *rep;                       // repeat bits (see mark_runs)
+    static constexpr bool kRepeatBits = true;
 };
 struct Tagged {
     using CH = uint16_t;
@@ -245,12 +248,16 @@ struct Tagged {
     uint32_t near;
     const int32_t *start, *alen;         // joined start of every pair (plus n), |A|
     const uint32_t *below;               // near suffixes in the pairs before
+    uint32_t *rep;
+    static constexpr bool kRepeatBits = true;
 };
 struct Shared {
     using CH = uint8_t;
     const uint8_t *t;
     uint32_t n;
     int K;
+    uint32_t *rep;   // none: its repeats may run through separators
+    static constexpr bool kRepeatBits = false;
 };
 
 __host__ __device__ __forceinline__ uint32_t near_of(uint32_t len, int K) {   // of one sequence and its separator
@@ -272,34 +279,106 @@ __device__ __forceinline__ uint32_t pack4(uint32_t w) {   // 4 byte symbols -> 8
     return ((w & 0x03030303u) * 0x40100401u) >> 24;
 }
 
-__device__ __forceinline__ void pack_tile(const Joined &x, uint32_t base, uint32_t *s_w) {
+// The packed tile, and its symbols' bits apart: symbol i of the tile has bit i
+// of three planes (high bit, low bit, no base), for mark_runs().
+struct KeyTile {
+    uint32_t w[kKeyWords];
+    alignas(8) uint16_t hi[kKeyWords], lo[kKeyWords], no[kKeyWords];
+};
+
+__device__ __forceinline__ uint32_t even_bits(uint32_t v) {   // bits 0, 2, 4.. -> 0, 1, 2..
+    v &= 0x55555555u;
+    v = (v | (v >> 1)) & 0x33333333u;
+    v = (v | (v >> 2)) & 0x0f0f0f0fu;
+    v = (v | (v >> 4)) & 0x00ff00ffu;
+    return (v | (v >> 8)) & 0xffffu;
+}
+
+__device__ __forceinline__ void put_word(KeyTile *s, uint32_t i, uint32_t v, uint32_t no) {
+    s->w[i] = v;
+    const uint32_t r = __builtin_bitreverse32(v);   // the first symbol's high bit lowest
+    s->hi[i] = (uint16_t)even_bits(r);
+    s->lo[i] = (uint16_t)even_bits(r >> 1);
+    s->no[i] = (uint16_t)no;
+}
+
+__device__ __forceinline__ void pack_tile(const Joined &x, uint32_t base, KeyTile *s) {
     for (uint32_t i = threadIdx.x; i < kKeyWords; i += kBlock) {
         const uint32_t p = base + 16 * i;
-        uint32_t v = 0;
+        uint32_t v = 0, no = 0;
         if (p < x.n && x.n - p >= 16) {   // p is a multiple of 16, the text 4-byte aligned
             const uint32_t *w = reinterpret_cast<const uint32_t *>(x.t + p);
             v = (pack4(w[0]) << 24) | (pack4(w[1]) << 16) | (pack4(w[2]) << 8) | pack4(w[3]);
+            if ((w[0] | w[1] | w[2] | w[3]) & 0xfcfcfcfcu)
+                for (uint32_t c = 0; c < 16; ++c) no |= ((w[c >> 2] >> (8 * (c & 3u))) & 0xfcu ? 1u : 0u) << c;
         } else {
-            for (uint32_t c = 0; c < 16; ++c) v = (v << 2) | ((p < x.n && c < x.n - p) ? x.t[p + c] & 3u : 0u);
+            for (uint32_t c = 0; c < 16; ++c) {
+                const uint32_t y = p < x.n && c < x.n - p ? x.t[p + c] : 4u;
+                v = (v << 2) | (y & 3u);
+                no |= (y > 3u ? 1u : 0u) << c;
+            }
         }
-        s_w[i] = v;
+        put_word(s, i, v, no);
     }
 }
 
-__device__ __forceinline__ void pack_tile(const Tagged &x, uint32_t base, uint32_t *s_w) {
+__device__ __forceinline__ void pack_tile(const Tagged &x, uint32_t base, KeyTile *s) {
     for (uint32_t i = threadIdx.x; i < kKeyWords; i += kBlock) {
         const uint32_t p = base + 16 * i;
-        uint32_t v = 0;
+        uint32_t v = 0, no = 0;
         if (p < x.n && x.n - p >= 16) {   // the text is 256-byte aligned
             const uint32_t *w = reinterpret_cast<const uint32_t *>(x.t + p);
 #pragma unroll
-            for (int c = 0; c < 8; ++c) v = (v << 4) | ((((w[c] & 7u) - 1u) & 3u) << 2) | (((w[c] >> 16 & 7u) - 1u) & 3u);
+            for (int c = 0; c < 8; ++c) {
+                const uint32_t y0 = (w[c] & 7u) - 1u, y1 = (w[c] >> 16 & 7u) - 1u;
+                v = (v << 4) | ((y0 & 3u) << 2) | (y1 & 3u);
+                no |= (((y0 >> 2) & 1u) | ((y1 >> 1) & 2u)) << (2 * c);
+            }
         } else {
-            for (uint32_t c = 0; c < 16; ++c)
-                v = (v << 2) | ((p < x.n && c < x.n - p) ? ((x.t[p + c] & 7u) - 1u) & 3u : 0u);
+            for (uint32_t c = 0; c < 16; ++c) {
+                const uint32_t y = p < x.n && c < x.n - p ? (x.t[p + c] & 7u) - 1u : 4u;
+                v = (v << 2) | (y & 3u);
+                no |= ((y >> 2) & 1u) << c;
+            }
         }
-        s_w[i] = v;
+        put_word(s, i, v, no);
     }
+}
+
+// Repeat bits: bit p is set when the M + 1 symbols from p on are bases and have
+// a period of at most M / 2, M = kRepeat. Two such periods of M symbols have
+// their greatest common divisor as a period too (Fine and Wilf, 1965), so along
+// a run of set bits the smallest period stays the same, and a suffix q whose
+// first M symbols have a smallest period t <= M / 2 keeps it for exactly M + r
+// symbols, r the number of set bits from q on. A word of 32 positions per thread
+// and period, over bit planes; the waves take the periods in turn (1.85 -> 2.03 ms
+// for the keys of 1G suffixes).
+__device__ __forceinline__ uint64_t any_of(uint64_t d, uint32_t width) {   // bit i: any of bits i..i + width - 1
+    uint32_t have = 1;
+    for (; 2 * have <= width; have *= 2) d |= d >> have;
+    return d | (d >> (width - have));
+}
+
+__device__ __forceinline__ void mark_runs(const KeyTile &s, uint32_t *s_rep, uint32_t n, uint32_t base,
+                                          uint32_t *__restrict__ rep) {
+    constexpr uint32_t kWords = kKeyTile / 32u, kWaves = kBlock / kWave;
+    static_assert(kWords == kWave, "one lane per word");
+    const uint32_t j = threadIdx.x % kWords;
+    auto plane = [&](const uint16_t *a) {
+        const uint32_t *w = reinterpret_cast<const uint32_t *>(a) + j;
+        return ((uint64_t)w[1] << 32) | w[0];
+    };
+    const uint64_t hi = plane(s.hi), lo = plane(s.lo);
+    uint32_t set = 0;
+    for (uint32_t t = 1 + threadIdx.x / kWords; t <= kRepeat / 2u; t += kWaves)
+        set |= ~(uint32_t)any_of((hi ^ (hi >> t)) | (lo ^ (lo >> t)), kRepeat + 1u - t);
+    if (set) {
+        set &= ~(uint32_t)any_of(plane(s.no), kRepeat + 1u);
+        if (set) atomicOr(&s_rep[j], set);
+    }
+    __syncthreads();
+    const uint32_t w = base / 32u + threadIdx.x;
+    if (threadIdx.x < kWords && w < (n + 31u) / 32u) rep[w] = s_rep[threadIdx.x];
 }
 
 // Largest j in [0, count) with start[j] <= x.
@@ -325,7 +404,8 @@ __device__ __forceinline__ void clear_open(const OpenBits &o, uint32_t n, uint32
 
 __global__ __launch_bounds__(kBlock) void k_prefix_keys(Joined x, uint32_t *__restrict__ keys,
                                                         uint32_t *__restrict__ vals, OpenBits open) {
-    __shared__ uint32_t s_w[kKeyWords];
+    __shared__ KeyTile s_tile;
+    __shared__ uint32_t s_rep[kKeyTile / 32];
     __shared__ int32_t s_start[kMaxSeqs + 1];
     __shared__ uint32_t s_below[kMaxSeqs + 1];
     __shared__ uint32_t s_tmp[kBlock / kWave];
@@ -336,9 +416,11 @@ __global__ __launch_bounds__(kBlock) void k_prefix_keys(Joined x, uint32_t *__re
     if (tid < x.k) mine = near_of((uint32_t)(x.start[tid + 1] - x.start[tid]) - 1u, x.K);
     const uint32_t bel = dev::block_exclusive_sum(mine, s_tmp, &all);
     if (tid < x.k) s_below[tid] = bel;
-    pack_tile(x, base, s_w);
+    pack_tile(x, base, &s_tile);
     clear_open(open, x.n, base);
+    if (tid < kKeyTile / 32) s_rep[tid] = 0;
     __syncthreads();
+    mark_runs(s_tile, s_rep, x.n, base, x.rep);
     const uint32_t drop = 32u - 2u * (uint32_t)x.K;
     const uint32_t j0 = seq_of(s_start, x.k, base);
 #pragma unroll
@@ -349,7 +431,7 @@ __global__ __launch_bounds__(kBlock) void k_prefix_keys(Joined x, uint32_t *__re
         while (p >= (uint32_t)s_start[j + 1]) ++j;        // p < n = start[k]
         if (p + (uint32_t)x.K >= (uint32_t)s_start[j + 1]) continue;   // near: its separator is among its K symbols
         const uint32_t i = l >> 4, sh = (l & 15u) * 2u;
-        const uint64_t ww = ((uint64_t)s_w[i] << 32) | s_w[i + 1];
+        const uint64_t ww = ((uint64_t)s_tile.w[i] << 32) | s_tile.w[i + 1];
         const uint32_t key = (uint32_t)((ww << sh) >> 32) >> drop;
         const uint32_t e = p - s_below[j];
         keys[e] = key;
@@ -360,11 +442,14 @@ __global__ __launch_bounds__(kBlock) void k_prefix_keys(Joined x, uint32_t *__re
 __global__ __launch_bounds__(kBlock) void k_prefix_keys_tagged(Tagged x, uint32_t *__restrict__ keys,
                                                                uint32_t *__restrict__ vals, OpenBits open) {
     const uint32_t m = x.n - x.near;
-    __shared__ uint32_t s_w[kKeyWords];
+    __shared__ KeyTile s_tile;
+    __shared__ uint32_t s_rep[kKeyTile / 32];
     const uint32_t base = blockIdx.x * kKeyTile, tid = threadIdx.x;
-    pack_tile(x, base, s_w);
+    pack_tile(x, base, &s_tile);
     clear_open(open, x.n, base);
+    if (tid < kKeyTile / 32) s_rep[tid] = 0;
     __syncthreads();
+    mark_runs(s_tile, s_rep, x.n, base, x.rep);
     const uint32_t drop = 32u - 2u * (uint32_t)x.K;
 #pragma unroll
     for (int r = 0; r < (int)(kKeyTile / kBlock); ++r) {
@@ -376,7 +461,7 @@ __global__ __launch_bounds__(kBlock) void k_prefix_keys_tagged(Tagged x, uint32_
         const bool inb = p > sep;
         if (p + (uint32_t)x.K >= (inb ? s1 : sep + 1u)) continue;
         const uint32_t i = l >> 4, sh = (l & 15u) * 2u;
-        const uint64_t ww = ((uint64_t)s_w[i] << 32) | s_w[i + 1];
+        const uint64_t ww = ((uint64_t)s_tile.w[i] << 32) | s_tile.w[i + 1];
         const uint32_t key = ((uint32_t)((ww << sh) >> 32) >> drop) | (uint32_t)((uint64_t)pair << (2 * x.K));
         const uint32_t e = p - x.below[pair] - (inb ? near_of(a, x.K) : 0u);
         if (e >= m) continue;   // a bad input base spoils the pair number; the call then fails
@@ -553,29 +638,48 @@ __device__ __forceinline__ uint64_t codes(const CH *__restrict__ t, uint32_t n, 
     return v;
 }
 
-// Smallest period of the K symbols from p on (K when they have none).
-template <typename X>
-__device__ __forceinline__ uint32_t period_at(const X &x, uint32_t p) {
-    const uint32_t K = (uint32_t)x.K;
-    const uint64_t v = codes(x.t, x.n, p, K, false);
-    for (uint32_t t = 1; t < K; ++t)
-        if (((v ^ (v >> (3u * t))) & ((1ull << (3u * (K - t))) - 1ull)) == 0) return t;
-    return K;
-}
 template <typename X> struct StopAtSep { static constexpr bool value = true; };
 template <> struct StopAtSep<Shared> { static constexpr bool value = false; };
 
-// Where and how the suffix at q leaves the period t of its first K symbols
-// (15 bits: e when it breaks downwards, 2 kExtent + 1 - e when upwards,
-// kExtent when it runs at least that far), then its next `ns` symbols at 3
-// bits (0 behind a unique separator, which decides).
+// Set bits of `rep` from bit q on, up to about `cap`; there is a clear one before
+// the end of the text. 128 bits a step.
+__device__ __forceinline__ uint32_t run_ones(const uint32_t *__restrict__ rep, uint32_t q, uint32_t cap) {
+    const uint4 *a = reinterpret_cast<const uint4 *>(rep);
+    uint32_t b = q >> 7;
+    const uint32_t o = q & 127u;
+    uint64_t below0 = o < 64u ? (1ull << o) - 1ull : ~0ull, below1 = o < 64u ? 0ull : (1ull << (o - 64u)) - 1ull;
+    for (;;) {
+        const uint4 v = a[b];
+        const uint64_t z0 = ~(((uint64_t)v.y << 32) | v.x) & ~below0, z1 = ~(((uint64_t)v.w << 32) | v.z) & ~below1;
+        if (z0) return b * 128u + (uint32_t)__builtin_ctzll(z0) - q;
+        if (z1) return b * 128u + 64u + (uint32_t)__builtin_ctzll(z1) - q;
+        ++b;
+        if (b * 128u - q >= cap) return cap;
+        below0 = below1 = 0;
+    }
+}
+
+// Where and how the suffix at q leaves the smallest period t of its first K
+// symbols (K when they have none): 15 bits, e when it breaks downwards,
+// 2 kExtent + 1 - e when upwards, kExtent when it runs at least that far; then
+// its next `ns` symbols at 3 bits (0 behind a unique separator, which decides).
+// The first K symbols hold no unique separator, so symbols that repeat them hold
+// none either. A period that lasts kRepeat symbols is followed over the repeat
+// bits: two or three lines instead of some 30 for the 400 symbols that a tandem
+// repeat has left on average, 3.28 -> 0.15 ms in k_group_keys for 9.2 M suffixes.
 template <typename X>
-__device__ __forceinline__ uint64_t repeat_key(const X &x, uint32_t q, uint32_t t, uint32_t ns, uint32_t *hdr,
-                                               uint32_t budget) {
+__device__ __forceinline__ uint64_t repeat_key(const X &x, uint32_t q, uint32_t ns, uint32_t *hdr, uint32_t budget) {
     using CH = typename X::CH;
+    const uint32_t K = (uint32_t)x.K;
+    const uint64_t v = codes(x.t, x.n, q, kRepeat, false), first = v >> (3u * (kRepeat - K));
+    uint32_t t = 1;
+    while (t < K && ((first ^ (first >> (3u * t))) & ((1ull << (3u * (K - t))) - 1ull))) ++t;
     uint32_t code = kExtent, e = x.n - q;
-    if (q + t < x.n) {
-        e = min(e, t + dev::extend<CH, 2>(x.t, x.n, q, q + t, (uint32_t)x.K - t, kExtent - t, Budget{hdr, budget}));
+    if (X::kRepeatBits && t <= kRepeat / 2u && ((v ^ (v >> (3u * t))) & ((1ull << (3u * (kRepeat - t))) - 1ull)) == 0) {
+        e = min(e, min(kRepeat + run_ones(x.rep, q, kExtent), kExtent));
+        if (e < kExtent) code = (q + e >= x.n || x.t[q + e] < x.t[q + e - t]) ? e : 2 * kExtent + 1u - e;
+    } else if (q + t < x.n) {
+        e = min(e, t + dev::extend<CH, 2>(x.t, x.n, q, q + t, K - t, kExtent - t, Budget{hdr, budget}));
         if (e < kExtent) code = (q + e >= x.n || x.t[q + e] < x.t[q + e - t]) ? e : 2 * kExtent + 1u - e;
     } else {
         code = e;
@@ -901,7 +1005,7 @@ __global__ __launch_bounds__(kBlock) void k_group_keys(X x, GroupKey gk, uint64_
     const uint64_t id = tkeys[i];
     const uint32_t p = min(tvals[i], x.n - 1u);
     const uint32_t q = min(p + (gk.off ? gk.off[id] : 0u), x.n - 1u);
-    tkeys[i] = (id << gk.shift()) | repeat_key(x, q, period_at(x, q), gk.ns, hdr, budget);
+    tkeys[i] = (id << gk.shift()) | repeat_key(x, q, gk.ns, hdr, budget);
 }
 
 // -------------------------------------------------------------- open runs
@@ -1123,7 +1227,7 @@ __global__ __launch_bounds__(kBlock) void k_settle(X x, RunList list, const uint
         uint64_t k = 0;
         if (size) {
             const uint32_t p = min((uint32_t)sa[list.slot(base + l)], x.n - 1u);
-            if (size >= kRepeatRun) k = repeat_key(x, p, period_at(x, p), kRepeatSymbols, hdr, budget);
+            if (size >= kRepeatRun) k = repeat_key(x, p, kRepeatSymbols, hdr, budget);
             s_val[l] = p;
             s_key[l] = k;
         }
@@ -1348,7 +1452,7 @@ lor_status sum_counts(const uint32_t *tcount, const uint32_t *hcount, const uint
 // bits: key bits; near: near suffixes (left out of the sort). *done stays
 // false when DC3 has to build the array.
 template <typename X>
-lor_status prefix_sa(const X &x, int bits, uint32_t near, int32_t *sa, Arena &ar, uint32_t *hdr, hipStream_t s,
+lor_status prefix_sa(X x, int bits, uint32_t near, int32_t *sa, Arena &ar, uint32_t *hdr, hipStream_t s,
                      bool *done) {
     constexpr bool kImplicit = !StopAtSep<X>::value;   // every position is sorted: its value is its index
     *done = false;
@@ -1368,6 +1472,7 @@ lor_status prefix_sa(const X &x, int bits, uint32_t near, int32_t *sa, Arena &ar
     const uint32_t owords = div_up(x.n, 32);
     const bool identity = x.n <= kIdentityItems;
     uint32_t *open = ar.take<uint32_t>(owords), *was = identity ? ar.take<uint32_t>(owords) : nullptr;
+    if (X::kRepeatBits) x.rep = ar.take<uint32_t>(4 * (size_t)div_up(x.n, 128));   // whole 16-byte steps
     const size_t mark_open = ar.mark();
     const RunList all{nullptr, nullptr, x.n};
     uint32_t *ka = ar.take<uint32_t>(m), *va = ar.take<uint32_t>(m), *places = ar.take<uint32_t>(near + 1);
@@ -1538,7 +1643,7 @@ lor_status prefix_sa_tagged(const uint16_t *text, uint32_t n, uint32_t pairs, co
     lor_status st = LOR_OK;
     if (!ar.overflow) {
         LOR_HIP(hipMemcpyAsync(d_below, below.get(), pairs * sizeof(uint32_t), hipMemcpyHostToDevice, s));
-        const Tagged x{text, n, K, pairs, near, start, alen, d_below};
+        const Tagged x{text, n, K, pairs, near, start, alen, d_below, nullptr};
         st = prefix_sa(x, tag + 2 * K, near, sa, ar, hdr, s, done);
     }
     ar.release(mark);

@@ -215,3 +215,31 @@ def test_open_runs_by_slot_and_by_list(n, copies):
     elif copies == "many":
         b[:] = synth.mutate(rng, a, 0.0004)[:b.size] if la >= b.size else np.resize(a, b.size)
     check([a, b])
+
+
+@pytest.mark.parametrize("n", [900, 40_000, 1_000_000])
+@pytest.mark.parametrize("k", [1, 3])
+def test_repeats_at_every_phase(n, k):
+    """Tandem repeats of units 1 to 16 (periods up to and beyond half a key)
+    that start at every offset of the 32- and 128-position words their extents
+    are kept in, end at another repeat, at a separator and at the end, cross
+    tiles of 2,048 positions, and run on past the 16,383 symbols that a sort
+    key describes; n selects the key width."""
+    say("prefix repeats", n, k)
+    rng = np.random.default_rng(n + k)
+    seqs = []
+    for j in range(k):
+        parts, size, long = [], 0, n >= 40_000 and j == 0
+        while size < n // k:
+            unit = rng.integers(0, 4, size=int(rng.integers(1, 17)), dtype=np.uint8)
+            copies = 17_000 // unit.size if long else int(rng.integers(3, 40))
+            part = np.resize(unit, unit.size * copies + int(rng.integers(0, unit.size + 1)))
+            if rng.random() < 0.5:
+                parts.append(rng.integers(0, 4, size=int(rng.integers(1, 200)), dtype=np.uint8))
+            parts.append(part)
+            size += part.size + (parts[-2].size if len(parts) > 1 else 0)
+            long = False
+        seqs.append(np.concatenate(parts))
+    seqs[-1][-60:] = np.resize(np.array([1, 2], np.uint8), 60)
+    seqs.append(np.resize(np.array([1, 2], np.uint8), 61))
+    check(seqs)
