@@ -15,8 +15,9 @@
 // segmented scans over the ranks give both: forward, the minimum LCP since
 // the last reference rank; backward, up to the next one. A query's answer
 // is the largest credited match, the smallest query offset among equals
-// (one 64-bit atomicMax per rank), and a reference offset at which that
+// (a 64-bit atomicMax), and a reference offset at which that
 // match occurs (the neighbour that gave it).
+#include <algorithm>
 #include <climits>
 #include <vector>
 
@@ -109,24 +110,17 @@ __global__ __launch_bounds__(kBlock) void k_rq_join(const uint8_t *__restrict__ 
     if (__any(bad) && dev::lane_id() == 0) atomicOr(err, 1u);
 }
 
-// Forward state over a run of ranks: whether it holds a reference rank, the
-// minimum LCP after the last one (over the whole run if none), that rank.
-struct Fwd {
-    int32_t h, m, last;
-};
-// Backward state: whether the run holds a reference rank, the minimum LCP up
-// to and including the first one (over the whole run if none), that rank.
-struct Bwd {
-    int32_t h, m, first;
+// State of a run of ranks, seen from one end: the reference rank nearest to it
+// (-1: none) and the minimum LCP on the way there (over the whole run if none).
+// Seen from behind the run, that leaves the reference rank's own LCP out; from
+// in front of it, it counts.
+struct Near {
+    int32_t m, at;
 };
 
-__device__ __forceinline__ Fwd f_id() { return Fwd{0, INT_MAX, -1}; }
-__device__ __forceinline__ Bwd b_id() { return Bwd{0, INT_MAX, -1}; }
-// a precedes b
-__device__ __forceinline__ Fwd f_comb(const Fwd &a, const Fwd &b) { return b.h ? b : Fwd{a.h, min(a.m, b.m), a.last}; }
-// near precedes far
-__device__ __forceinline__ Bwd b_comb(const Bwd &nr, const Bwd &fr) {
-    return nr.h ? nr : Bwd{fr.h, min(nr.m, fr.m), fr.first};
+__device__ __forceinline__ Near no_near() { return Near{INT_MAX, -1}; }
+__device__ __forceinline__ Near comb(const Near &far, const Near &near) {
+    return near.at >= 0 ? near : Near{min(far.m, near.m), far.at};
 }
 
 struct RankItem {
@@ -139,152 +133,163 @@ struct Target {
     uint32_t lo, hi, seq;
 };
 
-__device__ __forceinline__ RankItem rank_item(const int32_t *__restrict__ sa, const int32_t *__restrict__ lcp,
-                                              uint32_t n, const Target &tg, uint32_t r) {
-    RankItem it{-1, 0, false};
-    if (r < n) {
-        it.sa = sa[r];
-        it.lcp = lcp[r];
-        it.ref = (uint32_t)it.sa >= tg.lo && (uint32_t)it.sa < tg.hi;
-    }
-    return it;
-}
-
-__device__ __forceinline__ Fwd f_elem(const RankItem &it, uint32_t r) {
-    return it.ref ? Fwd{1, INT_MAX, (int32_t)r} : Fwd{0, it.lcp, -1};
-}
-__device__ __forceinline__ Bwd b_elem(const RankItem &it, uint32_t r) {
-    return it.ref ? Bwd{1, it.lcp, (int32_t)r} : Bwd{0, it.lcp, -1};
-}
-
-// Exclusive scans of per-thread states across a workgroup of NT threads
-// (Hillis-Steele in LDS): forward in thread order, backward from the last
-// thread down.
-template <int NT>
-__device__ Fwd block_fwd_excl(Fwd v, Fwd *s) {
-    const unsigned t = threadIdx.x;
-    s[t] = v;
-    __syncthreads();
-    for (unsigned off = 1; off < NT; off <<= 1) {
-        const Fwd x = t >= off ? s[t - off] : f_id();
-        __syncthreads();
-        s[t] = f_comb(x, s[t]);
-        __syncthreads();
-    }
-    const Fwd r = t ? s[t - 1] : f_id();
-    __syncthreads();
-    return r;
-}
-
-template <int NT>
-__device__ Bwd block_bwd_excl(Bwd v, Bwd *s) {
-    const unsigned u = NT - 1 - threadIdx.x;
-    s[u] = v;
-    __syncthreads();
-    for (unsigned off = 1; off < NT; off <<= 1) {
-        const Bwd x = u >= off ? s[u - off] : b_id();
-        __syncthreads();
-        s[u] = b_comb(s[u], x);
-        __syncthreads();
-    }
-    const Bwd r = u ? s[u - 1] : b_id();
-    __syncthreads();
-    return r;
-}
-
-// Forward and backward states of every tile of kRqTile ranks.
-__global__ __launch_bounds__(kBlock) void k_rq_tiles(const int32_t *__restrict__ sa, const int32_t *__restrict__ lcp,
-                                                     uint32_t n, Target tg, Fwd *__restrict__ tf,
-                                                     Bwd *__restrict__ tb) {
-    __shared__ Fwd s_f[kBlock];
-    __shared__ Bwd s_b[kBlock];
-    const uint32_t c0 = blockIdx.x * kRqTile + threadIdx.x * kRqItems;
-    Fwd f = f_id();
-    Bwd b = b_id();
+// A thread's kRqItems consecutive ranks, from r0 (a multiple of kRqItems) on.
+__device__ __forceinline__ void rank_items(const int32_t *__restrict__ sa, const int32_t *__restrict__ lcp, uint32_t n,
+                                           const Target &tg, uint32_t r0, RankItem *it) {
+    if (r0 < n && n - r0 >= kRqItems) {
 #pragma unroll
-    for (uint32_t k = 0; k < kRqItems; ++k) {
-        const RankItem it = rank_item(sa, lcp, n, tg, c0 + k);
-        if (c0 + k < n) f = f_comb(f, f_elem(it, c0 + k));
+        for (uint32_t k = 0; k < kRqItems; k += 4) {
+            const int4 a = *reinterpret_cast<const int4 *>(sa + r0 + k);
+            const int4 l = *reinterpret_cast<const int4 *>(lcp + r0 + k);
+            it[k].sa = a.x, it[k + 1].sa = a.y, it[k + 2].sa = a.z, it[k + 3].sa = a.w;
+            it[k].lcp = l.x, it[k + 1].lcp = l.y, it[k + 2].lcp = l.z, it[k + 3].lcp = l.w;
+        }
+    } else {
+#pragma unroll
+        for (uint32_t k = 0; k < kRqItems; ++k) {
+            it[k].sa = r0 + k < n ? sa[r0 + k] : -1;
+            it[k].lcp = r0 + k < n ? lcp[r0 + k] : 0;   // behind the last rank: no match
+        }
     }
-    for (int k = (int)kRqItems - 1; k >= 0; --k) {
-        const RankItem it = rank_item(sa, lcp, n, tg, c0 + k);
-        if (c0 + k < n) b = b_comb(b_elem(it, c0 + k), b);
+#pragma unroll
+    for (uint32_t k = 0; k < kRqItems; ++k) it[k].ref = (uint32_t)it[k].sa >= tg.lo && (uint32_t)it[k].sa < tg.hi;
+}
+
+__device__ __forceinline__ Near from_behind(const RankItem &it, uint32_t r) {
+    return it.ref ? Near{INT_MAX, (int32_t)r} : Near{it.lcp, -1};
+}
+__device__ __forceinline__ Near from_front(const RankItem &it, uint32_t r) {
+    return Near{it.lcp, it.ref ? (int32_t)r : -1};
+}
+
+// States of a thread's ranks.
+__device__ __forceinline__ void fold(const RankItem *it, uint32_t r0, Near *f, Near *b) {
+    *f = *b = no_near();
+#pragma unroll
+    for (uint32_t k = 0; k < kRqItems; ++k) *f = comb(*f, from_behind(it[k], r0 + k));
+#pragma unroll
+    for (uint32_t k = kRqItems; k-- > 0;) *b = comb(*b, from_front(it[k], r0 + k));
+}
+
+// Exclusive scan of per-thread states across a workgroup of NT threads, in
+// thread order or (kBack) from the last thread down: shuffles in the waves, LDS
+// between them. s: one entry per wave.
+template <int NT, bool kBack>
+__device__ __forceinline__ Near block_excl(Near v, Near *s) {
+    constexpr uint32_t kWaves = NT / kWave;
+    const uint32_t lane = dev::lane_id(), w = threadIdx.x / kWave;
+#pragma unroll
+    for (uint32_t off = 1; off < (uint32_t)kWave; off <<= 1) {
+        const Near o = kBack ? Near{__shfl_down(v.m, off, kWave), __shfl_down(v.at, off, kWave)}
+                             : Near{__shfl_up(v.m, off, kWave), __shfl_up(v.at, off, kWave)};
+        if (kBack ? lane + off < (uint32_t)kWave : lane >= off) v = comb(o, v);
     }
-    const Fwd fe = block_fwd_excl<kBlock>(f, s_f);
-    const Bwd be = block_bwd_excl<kBlock>(b, s_b);
-    if (threadIdx.x == kBlock - 1) tf[blockIdx.x] = f_comb(fe, f);
-    if (threadIdx.x == 0) tb[blockIdx.x] = b_comb(b, be);
+    if (lane == (kBack ? 0u : (uint32_t)kWave - 1u)) s[w] = v;
+    Near x = kBack ? Near{__shfl_down(v.m, 1, kWave), __shfl_down(v.at, 1, kWave)}
+                   : Near{__shfl_up(v.m, 1, kWave), __shfl_up(v.at, 1, kWave)};
+    if (lane == (kBack ? (uint32_t)kWave - 1u : 0u)) x = no_near();
+    __syncthreads();
+    Near carry = no_near();
+    if (kBack)
+        for (uint32_t i = kWaves; i-- > w + 1;) carry = comb(carry, s[i]);
+    else
+        for (uint32_t i = 0; i < w; ++i) carry = comb(carry, s[i]);
+    return comb(carry, x);
+}
+
+// Forward and backward states of every tile of kRqTile ranks. Reads the ranks
+// once, 16 bytes a load (46M ranks: 558 us with 4-byte loads, each rank twice,
+// and LDS scans).
+__global__ __launch_bounds__(kBlock) void k_rq_tiles(const int32_t *__restrict__ sa, const int32_t *__restrict__ lcp,
+                                                     uint32_t n, Target tg, Near *__restrict__ tf,
+                                                     Near *__restrict__ tb) {
+    __shared__ Near s_f[kBlock / kWave], s_b[kBlock / kWave];
+    const uint32_t r0 = blockIdx.x * kRqTile + threadIdx.x * kRqItems;
+    RankItem it[kRqItems];
+    rank_items(sa, lcp, n, tg, r0, it);
+    Near f, b;
+    fold(it, r0, &f, &b);
+    const Near fe = block_excl<kBlock, false>(f, s_f), be = block_excl<kBlock, true>(b, s_b);
+    if (threadIdx.x == kBlock - 1) tf[blockIdx.x] = comb(fe, f);
+    if (threadIdx.x == 0) tb[blockIdx.x] = comb(be, b);
 }
 
 // Tile states -> the state of everything before (forward) and after
 // (backward) every tile. One workgroup; thread i folds a contiguous run.
-__global__ __launch_bounds__(kRqScanThreads) void k_rq_tile_scan(Fwd *__restrict__ tf, Bwd *__restrict__ tb,
+__global__ __launch_bounds__(kRqScanThreads) void k_rq_tile_scan(Near *__restrict__ tf, Near *__restrict__ tb,
                                                                  uint32_t tiles) {
-    __shared__ Fwd s_f[kRqScanThreads];
-    __shared__ Bwd s_b[kRqScanThreads];
+    __shared__ Near s_f[kRqScanThreads / kWave], s_b[kRqScanThreads / kWave];
     const uint32_t per = (tiles + kRqScanThreads - 1) / kRqScanThreads;
     const uint32_t t0 = min(tiles, threadIdx.x * per), t1 = min(tiles, t0 + per);
-    Fwd f = f_id();
-    Bwd b = b_id();
-    for (uint32_t t = t0; t < t1; ++t) f = f_comb(f, tf[t]);
-    for (uint32_t t = t1; t > t0; --t) b = b_comb(tb[t - 1], b);
-    Fwd run = block_fwd_excl<kRqScanThreads>(f, s_f);
-    Bwd back = block_bwd_excl<kRqScanThreads>(b, s_b);
+    Near f = no_near(), b = no_near();
+#pragma unroll 4
+    for (uint32_t t = t0; t < t1; ++t) f = comb(f, tf[t]);
+#pragma unroll 4
+    for (uint32_t t = t1; t > t0; --t) b = comb(b, tb[t - 1]);
+    f = block_excl<kRqScanThreads, false>(f, s_f);
+    b = block_excl<kRqScanThreads, true>(b, s_b);
     for (uint32_t t = t0; t < t1; ++t) {
-        const Fwd x = tf[t];
-        tf[t] = run;
-        run = f_comb(run, x);
+        const Near x = tf[t];
+        tf[t] = f;
+        f = comb(f, x);
     }
     for (uint32_t t = t1; t > t0; --t) {
-        const Bwd x = tb[t - 1];
-        tb[t - 1] = back;
-        back = b_comb(x, back);
+        const Near x = tb[t - 1];
+        tb[t - 1] = b;
+        b = comb(b, x);
     }
 }
 
-// Per rank: the credited match of every suffix of another sequence j with
-// the target. emit == 0: fold it into best[j * stride + base] =
-// max(m << 32 | ~offset). emit == 1: the rank that holds its slot's best
-// writes the record.
+// Per rank: the credited match of every suffix of another sequence j with the
+// target, folded into best[j * stride + base] = max(m << 32 | ~offset), in three
+// passes, each of which only looks up (a table, two starts, the best so far:
+// random reads, 975 us a pass for 42M query suffixes) what can still matter:
+//   kStrong: the ranks whose match is at least `floor` symbols, some more than
+//     a random text of the target's size shares with a suffix. Most sequences
+//     then have their best, which no shorter match can beat.
+//   kWeak: the other ranks of the sequences left (bits of their positions set
+//     in `pos`); nothing when there are none.
+//   kEmit: the rank that holds a slot's best writes the record: bits of the
+//     winning positions are set in `pos`, and no rank below the smallest best
+//     (word[1] = its complement) can hold one.
+// word[0]: sequences left for kWeak.
+enum RqPass { kStrong, kWeak, kEmit };
+template <RqPass PASS>
 __global__ __launch_bounds__(kBlock) void k_rq_ranks(const int32_t *__restrict__ sa, const int32_t *__restrict__ lcp,
                                                      uint32_t n, Target tg, const int32_t *__restrict__ start,
                                                      const int32_t *__restrict__ tab, uint32_t S,
-                                                     const Fwd *__restrict__ pre,
-                                                     const Bwd *__restrict__ post, int emit, uint32_t stride,
-                                                     int32_t base, unsigned long long *__restrict__ best,
+                                                     const Near *__restrict__ pre, const Near *__restrict__ post,
+                                                     int32_t floor, const uint32_t *__restrict__ word,
+                                                     const uint32_t *__restrict__ pos, uint32_t stride, int32_t base,
+                                                     unsigned long long *__restrict__ best,
                                                      lor_overlap *__restrict__ out) {
-    __shared__ Fwd s_f[kBlock];
-    __shared__ Bwd s_b[kBlock];
-    const uint32_t c0 = blockIdx.x * kRqTile + threadIdx.x * kRqItems;
+    __shared__ Near s_f[kBlock / kWave], s_b[kBlock / kWave];
+    if (PASS == kWeak && word[0] == 0) return;
+    int32_t least = PASS == kEmit ? (int32_t)~word[1] : PASS == kWeak ? 1 : floor;
+    least = max(least, 1);
+    const uint32_t r0 = blockIdx.x * kRqTile + threadIdx.x * kRqItems;
     RankItem it[kRqItems];
-#pragma unroll
-    for (uint32_t k = 0; k < kRqItems; ++k) it[k] = rank_item(sa, lcp, n, tg, c0 + k);
-    Fwd f = f_id();
-    Bwd b = b_id();
-#pragma unroll
-    for (uint32_t k = 0; k < kRqItems; ++k)
-        if (c0 + k < n) f = f_comb(f, f_elem(it[k], c0 + k));
-    for (int k = (int)kRqItems - 1; k >= 0; --k)
-        if (c0 + k < n) b = b_comb(b_elem(it[k], c0 + k), b);
-    Fwd fs = f_comb(pre[blockIdx.x], block_fwd_excl<kBlock>(f, s_f));
-    Bwd bs = b_comb(block_bwd_excl<kBlock>(b, s_b), post[blockIdx.x]);
+    rank_items(sa, lcp, n, tg, r0, it);
+    Near f, b;
+    fold(it, r0, &f, &b);
+    f = comb(pre[blockIdx.x], block_excl<kBlock, false>(f, s_f));
+    b = comb(post[blockIdx.x], block_excl<kBlock, true>(b, s_b));
     int32_t up[kRqItems], up_at[kRqItems];
 #pragma unroll
     for (uint32_t k = 0; k < kRqItems; ++k) {
-        if (c0 + k < n) fs = f_comb(fs, f_elem(it[k], c0 + k));
-        up[k] = fs.h ? fs.m : 0;
-        up_at[k] = fs.last;
+        f = comb(f, from_behind(it[k], r0 + k));
+        up[k] = f.at >= 0 ? f.m : 0;
+        up_at[k] = f.at;
     }
-    for (int k = (int)kRqItems - 1; k >= 0; --k) {
-        const uint32_t r = c0 + (uint32_t)k;
-        if (r >= n) continue;
-        const int32_t down = bs.h ? bs.m : 0;
-        const int32_t down_at = bs.first;
-        bs = b_comb(b_elem(it[k], r), bs);
+#pragma unroll
+    for (uint32_t k = kRqItems; k-- > 0;) {
+        const int32_t down = b.at >= 0 ? b.m : 0, down_at = b.at;
+        b = comb(b, from_front(it[k], r0 + k));
         const uint32_t x = (uint32_t)it[k].sa;
-        if (x >= tg.lo && x <= tg.hi) continue;   // target suffix or its separator
         const int32_t mx = max(up[k], down);
-        if (mx <= 0) continue;
+        if (r0 + k >= n || mx < least || (PASS == kWeak && mx >= floor)) continue;
+        if (x >= tg.lo && x <= tg.hi) continue;   // target suffix or its separator
+        if (x >= n || (PASS != kStrong && !((pos[x >> 5] >> (x & 31u)) & 1u))) continue;
         const uint32_t j = seq_fast(start, tab, x);
         if (j >= S || j == tg.seq) continue;
         const uint32_t d = (uint32_t)start[j + 1] - 1u - x;   // distance to its own separator
@@ -293,7 +298,7 @@ __global__ __launch_bounds__(kBlock) void k_rq_ranks(const int32_t *__restrict__
         const uint32_t off = x - (uint32_t)start[j];
         const unsigned long long key = ((unsigned long long)(uint32_t)m << 32) | (0xffffffffu - off);
         const int64_t slot = (int64_t)j * stride + base;
-        if (!emit) {
+        if (PASS != kEmit) {
             // best only grows: a stale read can only let a redundant atomic through
             if (key > __hip_atomic_load(&best[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
                 atomicMax(&best[slot], key);
@@ -308,6 +313,47 @@ __global__ __launch_bounds__(kBlock) void k_rq_ranks(const int32_t *__restrict__
             out[slot] = rec;
         }
     }
+}
+
+// Sets the positions of every sequence without a match of `floor` symbols, one
+// workgroup per sequence; *left counts them.
+__global__ __launch_bounds__(kBlock) void k_rq_left(const int32_t *__restrict__ start, uint32_t S, Target tg,
+                                                    int32_t floor, uint32_t stride, int32_t base,
+                                                    const unsigned long long *__restrict__ best,
+                                                    uint32_t *__restrict__ pos, uint32_t *__restrict__ left) {
+    uint32_t mine = 0;
+    for (uint32_t j = blockIdx.x; j < S; j += gridDim.x) {
+        if (j == tg.seq || (int32_t)(best[(int64_t)j * stride + base] >> 32) >= floor) continue;
+        const uint32_t lo = (uint32_t)start[j], hi = (uint32_t)start[j + 1];   // lo < hi: the separator is included
+        for (uint32_t w = lo / 32u + threadIdx.x; w <= (hi - 1u) / 32u; w += kBlock) {
+            uint32_t v = 0xffffffffu;
+            if (w == lo / 32u) v &= 0xffffffffu << (lo & 31u);
+            if (w == (hi - 1u) / 32u) v &= 0xffffffffu >> (31u - ((hi - 1u) & 31u));
+            atomicOr(&pos[w], v);
+        }
+        ++mine;
+    }
+    if (threadIdx.x == 0 && mine) atomicAdd(left, mine);
+}
+
+// Sets the position of every slot's best match; *least gets the complement of
+// the smallest of their lengths.
+__global__ __launch_bounds__(kBlock) void k_rq_winners(const int32_t *__restrict__ start, uint32_t S, Target tg,
+                                                       uint32_t stride, int32_t base,
+                                                       const unsigned long long *__restrict__ best, uint32_t n,
+                                                       uint32_t *__restrict__ pos, uint32_t *__restrict__ least) {
+    uint32_t mine = 0;
+    for (uint32_t j = blockIdx.x * kBlock + threadIdx.x; j < S; j += gridDim.x * kBlock) {
+        if (j == tg.seq) continue;
+        const unsigned long long k = best[(int64_t)j * stride + base];
+        if (k == 0) continue;   // no match
+        const uint32_t x = (uint32_t)start[j] + (0xffffffffu - (uint32_t)k);
+        if (x < n) atomicOr(&pos[x >> 5], 1u << (x & 31u));
+        mine = max(mine, ~(uint32_t)(k >> 32));
+    }
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) mine = max(mine, (uint32_t)__shfl_xor((int)mine, off, kWave));
+    if (dev::lane_id() == 0 && mine) atomicMax(least, mine);
 }
 
 __global__ __launch_bounds__(kBlock) void k_rq_init(uint32_t Q, unsigned long long *__restrict__ best,
@@ -328,8 +374,7 @@ struct RqLayout {
     uint8_t *text;
     int32_t *sa, *lcp, *start, *tab;
     unsigned long long *best;
-    Fwd *tf;
-    Bwd *tb;
+    Near *tf, *tb;
 };
 
 lor_status rq_carve(Arena &ar, uint64_t N, uint32_t S, RqLayout *L) {
@@ -340,25 +385,50 @@ lor_status rq_carve(Arena &ar, uint64_t N, uint32_t S, RqLayout *L) {
     LOR_TAKE(ar, int32_t, (size_t)S + 1, L->start);
     LOR_TAKE(ar, int32_t, (size_t)div_up(N ? N : 1, 1u << kRqBucketShift) + 1, L->tab);
     LOR_TAKE(ar, unsigned long long, S, L->best);
-    LOR_TAKE(ar, Fwd, tiles, L->tf);
-    LOR_TAKE(ar, Bwd, tiles, L->tb);
+    LOR_TAKE(ar, Near, tiles, L->tf);
+    LOR_TAKE(ar, Near, tiles, L->tb);
     return LOR_OK;
 }
 
 // Matches of every other sequence's suffixes with one target sequence:
-// tile states, their scan, then the two per-rank passes.
+// tile states, their scan, then the per-rank passes.
 lor_status target_scan(const int32_t *sa, const int32_t *lcp, uint32_t n, Target tg, const int32_t *start,
-                       const int32_t *tab, uint32_t S, uint32_t stride, int32_t base, Fwd *tf, Bwd *tb,
-                       unsigned long long *best, lor_overlap *out, hipStream_t s) {
-    const uint32_t tiles = div_up(n, kRqTile);
+                       const int32_t *tab, uint32_t S, uint32_t stride, int32_t base, Near *tf, Near *tb,
+                       unsigned long long *best, lor_overlap *out, Arena &ar, hipStream_t s) {
+    const uint32_t tiles = div_up(n, kRqTile), words = div_up(n, 32);
+    uint32_t *weak, *won, *word;
+    LOR_TAKE(ar, uint32_t, 2 * (size_t)words + 2, weak);
+    won = weak + words;
+    word = won + words;
+    // A suffix's longest match with a random target of L bases is log4 L or a
+    // symbol less or more: 3% to 12% of the suffixes reach the rounded log4 L and
+    // two more, and of some hundred in a row few have none. (One less: 425 us
+    // strong and 212 weak for 42M suffixes of 64k queries, against 342 and 252.)
+    int32_t floor = 1;
+    for (uint64_t l = 2; 5 * l < 7ull * (tg.hi - tg.lo) && floor < 24; l *= 4) ++floor;   // 7 / 5: root of 2
+    floor += floor > 1;
+    LOR_TRY(zero_words(weak, 2 * words + 2, s));
     LOR_LAUNCH("k_rq_tiles", 8.0 * n, s,
                hipLaunchKernelGGL(k_rq_tiles, dim3(tiles), dim3(kBlock), 0, s, sa, lcp, n, tg, tf, tb));
-    LOR_LAUNCH("k_rq_tile_scan", 48.0 * tiles, s,
+    LOR_LAUNCH("k_rq_tile_scan", 32.0 * tiles, s,
                hipLaunchKernelGGL(k_rq_tile_scan, dim3(1), dim3(kRqScanThreads), 0, s, tf, tb, tiles));
-    for (int emit = 0; emit < 2; ++emit)
+    LOR_LAUNCH("k_rq_ranks", 8.0 * n, s,
+               hipLaunchKernelGGL(k_rq_ranks<kStrong>, dim3(tiles), dim3(kBlock), 0, s, sa, lcp, n, tg, start, tab, S,
+                                  tf, tb, floor, word, weak, stride, base, best, out));
+    if (floor > 1) {
+        LOR_LAUNCH("k_rq_left", 8.0 * S, s,
+                   hipLaunchKernelGGL(k_rq_left, dim3(std::min(S, 8192u)), dim3(kBlock), 0, s, start, S, tg, floor,
+                                      stride, base, best, weak, word));
         LOR_LAUNCH("k_rq_ranks", 8.0 * n, s,
-                   hipLaunchKernelGGL(k_rq_ranks, dim3(tiles), dim3(kBlock), 0, s, sa, lcp, n, tg, start, tab, S, tf,
-                                      tb, emit, stride, base, best, out));
+                   hipLaunchKernelGGL(k_rq_ranks<kWeak>, dim3(tiles), dim3(kBlock), 0, s, sa, lcp, n, tg, start, tab,
+                                      S, tf, tb, floor, word, weak, stride, base, best, out));
+    }
+    LOR_LAUNCH("k_rq_winners", 12.0 * S, s,
+               hipLaunchKernelGGL(k_rq_winners, dim3(grid_for(S)), dim3(kBlock), 0, s, start, S, tg, stride, base, best,
+                                  n, won, word + 1));
+    LOR_LAUNCH("k_rq_ranks", 8.0 * n, s,
+               hipLaunchKernelGGL(k_rq_ranks<kEmit>, dim3(tiles), dim3(kBlock), 0, s, sa, lcp, n, tg, start, tab, S, tf,
+                                  tb, floor, word, won, stride, base, best, out));
     return LOR_OK;
 }
 
@@ -416,7 +486,7 @@ lor_status refq_overlap(const uint8_t *seqs, const int64_t *offsets, uint32_t Q,
     LOR_TRY(lcp_build(L.text, (uint32_t)N, L.sa, L.lcp, nullptr, ar, s));
     ar.release(phase);
     LOR_TRY(target_scan(L.sa, L.lcp, (uint32_t)N, Target{0u, ref_len, 0u}, L.start, L.tab, S, 1u, -1, L.tf, L.tb,
-                        L.best, out, s));
+                        L.best, out, ar, s));
     LOR_HIP(hipStreamSynchronize(s));   // the host table must outlive its copy
     return LOR_OK;
 }

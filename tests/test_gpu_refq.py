@@ -107,3 +107,21 @@ def test_ref_rejects_bad_base():
     with pytest.raises(lor.LorError) as e:
         run(ref, [synth.encode("ACG"), bad])
     assert e.value.status == lor.LOR_EALPHABET
+
+
+@pytest.mark.parametrize("ref_len", [1, 2, 3, 11, 12, 4095, 4097, 70_000])
+def test_ref_strong_and_weak_matches(ref_len):
+    """Matches are looked up from those of about log4 |ref| symbols down: only
+    strong ones, queries that share 1 to 5 symbols with the reference beside
+    them, and queries with none at all; some start or end in the middle of the
+    32-position words, some cover many, and the last rank is a query's."""
+    rng = np.random.default_rng(ref_len)
+    ref = rng.integers(0, 3, size=ref_len, dtype=np.uint8)      # no T
+    few = np.full(300, 3, np.uint8)                             # T, and a few bases 40 apart
+    few[20::40] = rng.integers(0, 3, size=few[20::40].size)
+    queries = [rng.integers(0, 3, size=int(rng.integers(100, 400)), dtype=np.uint8) for _ in range(5)]
+    check(ref, queries, run(ref, queries))
+    queries += [few, np.full(33, 3, np.uint8), few[:31], np.full(1, 3, np.uint8), np.zeros(0, np.uint8),
+                np.concatenate([few[:7], ref[:5], few[:90]]), np.concatenate([ref[-3:], few[:5]]), np.full(200, 3, np.uint8)]
+    check(ref, queries, run(ref, queries))
+    check(ref, queries[5:], run(ref, queries[5:]))
