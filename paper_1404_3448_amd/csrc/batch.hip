@@ -540,7 +540,7 @@ lor_status batch_overlap_run(const uint8_t *seqs, uint32_t P, uint64_t N, const 
     if (!done) LOR_TRY(dc3_u16(text, (uint32_t)N, 8u * (P - 1) + 6u, sa, ar, hdr, s));
     ar.release(phase);
     if (lcp_out) lcp = lcp_out;   // the caller keeps the whole batch's LCP (and ISA)
-    LOR_TRY(lcp_build_u16(text, (uint32_t)N, sa, lcp, isa_out, ar, s));
+    LOR_TRY(lcp_build_u16(text, (uint32_t)N, sa, lcp, isa_out, ar, s, 2u * P));
     ar.release(phase);
 
     const uint32_t groups = group_count(N);

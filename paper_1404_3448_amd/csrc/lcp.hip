@@ -22,12 +22,11 @@
 // LCP is written in rank order throughout. ISA, when wanted, is a scatter of
 // its own.
 //
-// The window kernel is bound by its random reads (1.36 lines of 64 bytes per
-// suffix): 26 ms at 2^30 suffixes, 41 G suffixes/s, near the 45 G/s that
-// random 8-byte reads reach on a table of this size. LCP + ISA against the
-// text-order method it replaces: 1,000 symbols 96 -> 31 us, 100k 296 -> 40 us,
-// 1M 483 -> 69 us, 16M 1.21 -> 0.66 ms, 256M 14.8 -> 10.2 ms; two identical
-// sequences of 2M bases 75 -> 0.15 ms.
+// The window kernels are bound by their random reads: 24 ms at 2^30 suffixes,
+// the 45 G/s that random 8-byte reads reach on such tables. LCP + ISA against the
+// text-order method it replaces: 1,000 symbols 96 -> 36 us, 100k 296 -> 37 us,
+// 1M 483 -> 60 us, 16M 1.21 -> 0.56 ms, 256M 14.8 -> 8.5 ms; two identical
+// sequences of 2M bases 75 -> 0.11 ms.
 #include "lor_internal.hpp"
 
 namespace lor {
@@ -119,6 +118,124 @@ __global__ __launch_bounds__(kBlock) void k_lcp_window(const CH *__restrict__ t,
         } else {
             const uint32_t lim = n - max(i, j);   // a window past the end reads zeros
             lcp[r] = (int32_t)(open && lim > WS ? WS | kMarked : min(l, lim));
+        }
+        if ((i & ((1u << shift) - 1u)) == 0) phi[i >> shift] = r ? j : 0xffffffffu;
+        if constexpr (DIRECT) isa[i] = (int32_t)r;
+    }
+}
+
+// ---------------------------------------------------------- packed windows
+// Large texts are packed to two bits per symbol first, so that a rank's window
+// of kPackWin symbols is 8 bytes of a table a quarter (16-bit text: an eighth)
+// the size: fewer lines, more of them in the caches. Two bits hold bases only: a
+// window that meets anything else, or the end, is flagged, by one bit per
+// 2^shift window starts (the flags stay in L2), and compares the text itself.
+// Packed from 2^21 symbols on, and where sequences (as far as the caller knows)
+// are at least kPackSeq long on average. Window and packing, bytes against
+// packed: two sequences of 1M symbols 46 / 46 us in all of LCP, 4M 102 / 97, 8M
+// 178 / 151, 16M 254 / 173 us, 1G 26.4 / 24.0 ms (then bound by the requests, 45 G/s,
+// not the lines), 700 pairs with 102M symbols 1.27 / 0.86 ms; 65,536 queries of
+// 634 bases, where one window in seven is flagged, 0.82 / 0.85 ms.
+constexpr uint32_t kPackFrom = 1u << 21, kPackSeq = 2048;
+constexpr uint32_t kPackWin = 29;   // 32 symbols in 8 bytes less the up to 3 before the first
+struct PackedText {
+    uint32_t *words;    // symbol p: bits 2 (p % 16) of word p / 16
+    uint32_t *flags;
+    uint32_t shift;
+};
+
+// A base's two bits; 4 and more: no base.
+__device__ __forceinline__ uint32_t pack_code(uint8_t c) { return c; }
+__device__ __forceinline__ uint32_t pack_code(uint16_t c) { return (c & 7u) - 1u; }
+
+template <typename CH>
+__global__ __launch_bounds__(kBlock) void k_lcp_pack(const CH *__restrict__ t, uint32_t n, PackedText pt) {
+    const uint32_t g = blockIdx.x * kBlock + threadIdx.x, p = 16u * g;   // the last thread's group holds position n
+    if (p > n) return;
+    uint32_t v = 0, bad = 0;
+    if (n - p >= 16u) {   // p is a multiple of 16, the text 4-byte aligned where this is used
+        const uint32_t *w = reinterpret_cast<const uint32_t *>(t + p);
+        constexpr uint32_t per = 4 / sizeof(CH);
+        uint32_t x[16 / per];
+#pragma unroll
+        for (uint32_t c = 0; c < 16 / per; ++c) x[c] = w[c];
+#pragma unroll
+        for (uint32_t c = 0; c < 16; ++c) {
+            const uint32_t y = pack_code((CH)(x[c / per] >> (8 * sizeof(CH) * (c % per))));
+            v |= (y & 3u) << (2 * c);
+            bad |= y >> 2;
+        }
+    } else {
+        for (uint32_t c = 0; c < 16; ++c) {
+            const uint32_t y = c < n - p ? pack_code(t[p + c]) : 4u;
+            v |= (y & 3u) << (2 * c);
+            bad |= y >> 2;
+        }
+    }
+    pt.words[g] = v;
+    if (bad) {   // the windows that meet this group start up to kPackWin - 1 before it
+        const uint32_t last = min(p + 15u, n - 1u) >> pt.shift;
+        for (uint32_t b = (p >= kPackWin ? p - kPackWin + 1u : 0u) >> pt.shift; b <= last; ++b)
+            if (!((__hip_atomic_load(&pt.flags[b >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> (b & 31u)) & 1u))
+                atomicOr(&pt.flags[b >> 5], 1u << (b & 31u));
+    }
+}
+
+// The kPackWin symbols from i on, and the flag in bit 63.
+__device__ __forceinline__ uint64_t packed_window(const PackedText &pt, uint32_t i) {
+    const uint64_t v = reinterpret_cast<const Chunk *>(reinterpret_cast<const uint8_t *>(pt.words) + (i >> 2))->w[0];
+    const uint32_t b = i >> pt.shift;
+    const uint64_t f = (pt.flags[b >> 5] >> (b & 31u)) & 1u;
+    return ((v >> (2u * (i & 3u))) & ((1ull << (2u * kPackWin)) - 1ull)) | (f << 63);
+}
+
+// In the batched path's 16-bit text the ranks of a pair are its positions, so
+// the text at the ranks tells neighbours of different pairs apart.
+__device__ __forceinline__ bool same_text(const uint8_t *, uint32_t) { return true; }
+__device__ __forceinline__ bool same_text(const uint16_t *t, uint32_t r) { return (t[r] ^ t[r - 1]) < 8u; }
+
+template <typename CH, bool DIRECT>
+__global__ __launch_bounds__(kBlock) void k_lcp_packed(const CH *__restrict__ t, uint32_t n, PackedText pt,
+                                                       const int32_t *__restrict__ sa, int32_t *__restrict__ lcp,
+                                                       uint32_t *__restrict__ phi, int32_t *__restrict__ isa,
+                                                       uint32_t shift) {
+    const uint32_t base = blockIdx.x * (kBlock * kLcpItems), lane = threadIdx.x & 63u;
+    uint32_t p[kLcpItems], q[kLcpItems];
+    uint64_t w[kLcpItems], e[kLcpItems];   // e: lane 0's predecessor
+#pragma unroll
+    for (int k = 0; k < kLcpItems; ++k) {
+        const uint32_t r = base + k * kBlock + threadIdx.x;
+        p[k] = r < n ? min((uint32_t)sa[r], n - 1u) : 0u;
+        q[k] = (lane == 0 && r > 0 && r < n) ? min((uint32_t)sa[r - 1], n - 1u) : 0u;
+    }
+#pragma unroll
+    for (int k = 0; k < kLcpItems; ++k) w[k] = packed_window(pt, p[k]);
+    if (lane == 0) {
+#pragma unroll
+        for (int k = 0; k < kLcpItems; ++k) e[k] = packed_window(pt, q[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < kLcpItems; ++k) {
+        const uint32_t r = base + k * kBlock + threadIdx.x;
+        const uint32_t pj = (uint32_t)__shfl_up((int)p[k], 1, kWave);
+        const uint64_t up = __shfl_up(w[k], 1, kWave);
+        const uint32_t i = p[k], j = lane == 0 ? q[k] : pj;
+        const uint64_t y = lane == 0 ? e[k] : up, x = (w[k] ^ y) & ~(1ull << 63);
+        if (r >= n) continue;
+        if (r == 0) {
+            lcp[0] = 0;
+        } else {
+            uint32_t l = x ? (uint32_t)__builtin_ctzll(x) / 2u : kPackWin;
+            bool open = x == 0;
+            if ((w[k] | y) >> 63) {
+                l = dev::extend<CH, 2>(t, n, i, j, 0u, kPackWin);
+                open = l >= kPackWin && n - max(i, j) > kPackWin;
+            }
+            if (!same_text(t, r)) {
+                l = 0;
+                open = false;
+            }
+            lcp[r] = (int32_t)(open ? kPackWin | kMarked : l);
         }
         if ((i & ((1u << shift) - 1u)) == 0) phi[i >> shift] = r ? j : 0xffffffffu;
         if constexpr (DIRECT) isa[i] = (int32_t)r;
@@ -251,7 +368,7 @@ size_t lcp_workspace(uint64_t n) { return (size_t)n * 28 + radix_counts_words(n)
 
 template <typename CH>
 lor_status lcp_build_t(const CH *text, uint32_t n, const int32_t *sa, int32_t *lcp, int32_t *isa, Arena &ar,
-                       hipStream_t s) {
+                       hipStream_t s, uint32_t seqs) {
     if (n == 0) return LOR_OK;
     // every 2^shift-th position is sampled: half the plan's steps, 8 to 512
     const uint32_t shift = (uint32_t)bits_for((uint64_t)plan().plcp_steps) - 2u;
@@ -267,7 +384,22 @@ lor_status lcp_build_t(const CH *text, uint32_t n, const int32_t *sa, int32_t *l
     LOR_TAKE(ar, uint32_t, (size_t)nblocks + 1, blocks);
     const bool direct = isa && n <= kDirectIsa;
     const double bytes = (double)n * (8 + sizeof(CH) + (direct ? 4 : 0));
-    if (direct)
+    const size_t before_pack = ar.mark();
+    if (n >= kPackFrom && n / kPackSeq >= seqs && reinterpret_cast<uintptr_t>(text) % 4 == 0) {
+        PackedText pt;
+        pt.shift = n <= 1u << 26 ? 4 : 6;   // flags of at most 512 KB, 2 MB at 2^30
+        const uint32_t fwords = div_up(div_up(n, 1u << pt.shift), 32);
+        LOR_TAKE(ar, uint32_t, (size_t)n / 16 + 4, pt.words);   // the last window reads up to 8 bytes from n / 4 on
+        LOR_TAKE(ar, uint32_t, fwords, pt.flags);
+        LOR_TRY(zero_words(pt.flags, fwords, s));
+        LOR_LAUNCH("k_lcp_pack", (double)n * (sizeof(CH) + 0.25), s,
+                   hipLaunchKernelGGL(k_lcp_pack<CH>, dim3(div_up(n / 16 + 1, kBlock)), dim3(kBlock), 0, s, text, n,
+                                      pt));
+        auto *kernel = direct ? k_lcp_packed<CH, true> : k_lcp_packed<CH, false>;
+        LOR_LAUNCH("k_lcp_packed", bytes, s,
+                   hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBlock), 0, s, text, n, pt, sa, lcp, phi, isa, shift));
+        ar.release(before_pack);
+    } else if (direct)
         LOR_LAUNCH("k_lcp_window", bytes, s,
                    hipLaunchKernelGGL((k_lcp_window<CH, true>), dim3(grid), dim3(kBlock), 0, s, text, n, sa, lcp, phi,
                                       isa, shift));
@@ -295,13 +427,13 @@ lor_status lcp_build_t(const CH *text, uint32_t n, const int32_t *sa, int32_t *l
 }
 
 lor_status lcp_build(const uint8_t *text, uint32_t n, const int32_t *sa, int32_t *lcp, int32_t *isa, Arena &ar,
-                     hipStream_t s) {
-    return lcp_build_t<uint8_t>(text, n, sa, lcp, isa, ar, s);
+                     hipStream_t s, uint32_t seqs) {
+    return lcp_build_t<uint8_t>(text, n, sa, lcp, isa, ar, s, seqs);
 }
 
 lor_status lcp_build_u16(const uint16_t *text, uint32_t n, const int32_t *sa, int32_t *lcp, int32_t *isa, Arena &ar,
-                         hipStream_t s) {
-    return lcp_build_t<uint16_t>(text, n, sa, lcp, isa, ar, s);
+                         hipStream_t s, uint32_t seqs) {
+    return lcp_build_t<uint16_t>(text, n, sa, lcp, isa, ar, s, seqs);
 }
 
 }  // namespace lor

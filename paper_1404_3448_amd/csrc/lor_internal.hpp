@@ -249,9 +249,9 @@ lor_status join_text(const uint8_t *seqs, const int64_t *offsets, int32_t k, uin
 // ------------------------------------------------------------------ LCP
 size_t lcp_workspace(uint64_t n);
 lor_status lcp_build(const uint8_t *text, uint32_t n, const int32_t *sa, int32_t *lcp, int32_t *isa,
-                     Arena &ar, hipStream_t s);
+                     Arena &ar, hipStream_t s, uint32_t seqs = 1);
 lor_status lcp_build_u16(const uint16_t *text, uint32_t n, const int32_t *sa, int32_t *lcp, int32_t *isa,
-                         Arena &ar, hipStream_t s);
+                         Arena &ar, hipStream_t s, uint32_t seqs = 1);
 
 // ------------------------------------------------------------------ RMQ
 // A full table is a header of kRmqHeaderWords words (word 0: the largest LCP

@@ -483,7 +483,7 @@ lor_status refq_overlap(const uint8_t *seqs, const int64_t *offsets, uint32_t Q,
     LOR_TRY(prefix_sa_shared(L.text, (uint32_t)N, L.sa, ar, hdr, s, &done));
     if (!done) LOR_TRY(dc3_u8(L.text, (uint32_t)N, 5u, L.sa, ar, hdr, s));
     ar.release(phase);
-    LOR_TRY(lcp_build(L.text, (uint32_t)N, L.sa, L.lcp, nullptr, ar, s));
+    LOR_TRY(lcp_build(L.text, (uint32_t)N, L.sa, L.lcp, nullptr, ar, s, S));
     ar.release(phase);
     LOR_TRY(target_scan(L.sa, L.lcp, (uint32_t)N, Target{0u, ref_len, 0u}, L.start, L.tab, S, 1u, -1, L.tf, L.tb,
                         L.best, out, ar, s));

@@ -243,3 +243,64 @@ def test_repeats_at_every_phase(n, k):
     seqs[-1][-60:] = np.resize(np.array([1, 2], np.uint8), 60)
     seqs.append(np.resize(np.array([1, 2], np.uint8), 61))
     check(seqs)
+
+
+@pytest.mark.parametrize("n,seqs", [((1 << 21) - 1, 2), (1 << 21, 2), ((1 << 21) + 1, 251), ((1 << 21) + 15, 251),
+                                    ((1 << 26) + 17, 251)])
+def test_lcp_of_packed_text(n, seqs):
+    """LCP on both sides of the sizes from which the text is packed for it and
+    from which a flag covers 64 window starts; ends at, before and behind a
+    multiple of 16; windows that meet separators and the end; copies longer
+    than a window."""
+    say("lcp packed", n, seqs)
+    rng = np.random.default_rng(n)
+    cuts = np.sort(rng.choice(np.arange(100, n - seqs - 1), seqs - 1, replace=False))
+    cuts[1:4] = cuts[0] + np.array([1, 3, 40])[:cuts[1:4].size]            # sequences of 1, 2 and 37 bases
+    cuts = np.sort(cuts)
+    cat = rng.integers(0, 4, size=n - seqs, dtype=np.uint8)
+    cat[-3000:] = cat[5000:8000]
+    offs = np.concatenate([[0], cuts, [cat.size]]).astype(np.int64)
+    sa_d, joined_d = lor.lor_build_sa(torch.from_numpy(cat).cuda(), offs)
+    lcp_d, isa_d = lor.lor_build_lcp(joined_d, sa_d, want_isa=True)
+    lcp2_d, _ = lor.lor_build_lcp(joined_d, sa_d, want_isa=False)
+    assert torch.equal(lcp_d, lcp2_d)
+    sa, lcp, isa, joined = (x.cpu().numpy() for x in (sa_d, lcp_d, isa_d, joined_d))
+    assert joined.size == n and np.array_equal(sa[isa[::977]], np.arange(0, n, 977))
+    bad = np.flatnonzero(lcp != oracle.lcp(joined, sa))
+    assert bad.size == 0, (bad.size, bad[:5], lcp[bad[:5]])
+
+
+@pytest.mark.parametrize("aligned", [True, False])
+def test_lcp_of_other_bytes(aligned):
+    """A text that is not bases: every window is flagged; and one that does not
+    start on a word."""
+    n = (1 << 21) + 5
+    rng = np.random.default_rng(8)
+    text = rng.integers(0, 7, size=n, dtype=np.uint8)
+    text[-1] = 200
+    order = oracle.suffix_array(text)
+    buf = torch.zeros(n + 1, dtype=torch.uint8, device="cuda")
+    t = buf[:n] if aligned else buf[1:]
+    t.copy_(torch.from_numpy(text))
+    lcp, _ = lor.lor_build_lcp(t, torch.from_numpy(order.astype(np.int32)).cuda(), want_isa=False)
+    assert np.array_equal(lcp.cpu().numpy(), oracle.lcp(text, order))
+
+
+def test_batched_lcp_of_packed_text():
+    """A batch large enough to be packed for its LCP: neighbours of different
+    pairs share nothing; pairs of 1 to 400,000 bases."""
+    rng = np.random.default_rng(21)
+    sizes = [(400_000, 390_001), (1, 1), (5, 300_000), (700_000, 3), (64, 64), (250_000, 249_999), (0, 40), (30, 0)]
+    seqs = []
+    for a, b in sizes:
+        x, y = synth.gc40_bases(rng, a), synth.gc40_bases(rng, b)
+        m = min(a, b, 2000) // 2
+        y[:m] = x[:m]
+        seqs += [x, y]
+    cat, d, offs = flat(seqs)
+    rec, lcp, isa = lor.lor_longest_overlap_batched_state(d, offs)
+    rec, lcp, s = lor.records_to_tuples(rec), lcp.cpu().numpy(), lor.pair_starts(offs)
+    for p in range(len(sizes)):
+        joined, sa, want, o = oracle_pair(seqs[2 * p], seqs[2 * p + 1])
+        assert np.array_equal(lcp[s[p]:s[p + 1]], want), p
+        assert rec[p] == oracle.overlap(sa, want, o), p
