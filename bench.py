@@ -1,7 +1,7 @@
 """Benchmark of the longest-overlap-region path on one MI355X.
 
 One step = the whole path over one text already resident in HBM:
-join -> DC3 suffix array -> LCP (+ ISA) -> sparse-table RMQ build ->
+join -> suffix array -> LCP (+ ISA) -> sparse-table RMQ build ->
 10M suffix-pair lcp queries -> longest overlap scan.
 
 Default workload: 16 noncoding-like sequences of 67,108,864 bases (40% GC,

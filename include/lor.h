@@ -2,11 +2,13 @@
  * lor.h -- C-ABI of liblor.so: longest overlap region between DNA sequences
  * on MI355X (gfx950).
  *
- * The library builds the suffix array (SA) of a separator-joined DNA text with
- * DC3 (Section III, Steps 1-3), its LCP array (Section III, Table IV), a range
- * minimum structure over the LCP (Section III, RMQ), and scans the LCP for the
- * longest region shared by two different sequences (Section III, problem
- * statement). Every stage runs as hand-written HIP kernels.
+ * The library builds the suffix array (SA) of a separator-joined DNA text by
+ * sorting its suffixes' first symbols, or with DC3 (Section III, Steps 1-3)
+ * where the text is one repeat for the most part; the array is the same. It
+ * builds the text's LCP array (Section III, Table IV), a range minimum
+ * structure over the LCP (Section III, RMQ), and scans the LCP for the longest
+ * region shared by two different sequences (Section III, problem statement).
+ * Every stage runs as hand-written HIP kernels.
  *
  * Conventions for every entry point:
  *  - Device pointers point to memory of the current HIP device. The library
@@ -16,8 +18,9 @@
  *  - `hip_stream` is a hipStream_t (NULL = the null stream). Work is enqueued
  *    on it in order. Entry points whose result is a host value synchronise the
  *    stream before returning; the others return once work is enqueued, except
- *    lor_build_sa and lor_suffix_array_i32, which read one word back per DC3
- *    level (recursion depth depends on the text) and so return after the work.
+ *    lor_build_sa and the batched calls, which read the counts of every round of
+ *    their sort back (one round for most texts), and lor_suffix_array_i32, which
+ *    reads one word back per DC3 level: these return after the work, or that part.
  *  - Argument errors are detected on the host before any work is enqueued and
  *    leave outputs untouched. No function throws across the ABI.
  *  - Sizes: joined length N = total bases + number of sequences must satisfy
@@ -55,7 +58,7 @@ const char *lor_last_error(void);
 int32_t lor_version(void);
 
 /* ------------------------------------------------------------ suffix array
- * Suffix array of the joined text (Section III, Table I; DC3 Steps 1-3).
+ * Suffix array of the joined text (Section III, Table I).
  *
  * seqs    : device uint8, the sequences concatenated without separators, each
  *           base coded A=0, C=1, G=2, T=3 (the order of Table I).
@@ -113,9 +116,9 @@ lor_status lor_suffix_array_i32(const int32_t *text, int64_t n, int32_t alphabet
 /* ------------------------------------------------------------------- LCP
  * LCP array (Section III, Table IV): lcp_out[0] = 0 and lcp_out[r] = length
  * of the longest common prefix of the suffixes sa[r-1] and sa[r] of
- * text[0..n). Computed with the permuted-LCP method: Phi[sa[r]] = sa[r-1],
- * PLCP[i] = lcp(i, Phi[i]) using PLCP[i] >= PLCP[i-1] - 1 (Kasai et al.),
- * LCP[r] = PLCP[sa[r]].
+ * text[0..n). Neighbours that differ within their first symbols are compared in
+ * rank order; the others start from PLCP[i] = lcp(i, sa[isa[i] - 1]) of sampled
+ * positions, by PLCP[i] >= PLCP[i-1] - 1 (Kasai et al.).
  * text: device uint8[n] (any byte values; the joined text of lor_build_sa);
  * sa: device int32[n], a permutation of 0..n-1 (the suffix array of text);
  * lcp_out: device int32[n]; isa_out: device int32[n] or NULL, receives the
@@ -206,7 +209,7 @@ lor_status lor_longest_overlap(const int32_t *sa, const int32_t *lcp, int64_t n,
 
 /* ------------------------------------------------- batched longest overlap
  * The longest overlap region (as lor_longest_overlap) of every pair in a
- * batch of independent sequence pairs, from one DC3 run over all pairs.
+ * batch of independent sequence pairs, from one suffix array over all pairs.
  * seqs: device uint8 bases (0..3) of all sequences concatenated without
  * separators; offsets: HOST int64[2 * num_pairs + 1], pair p being sequences
  * 2p (A) and 2p+1 (B), offsets[0] = 0 and non-decreasing; empty sequences
@@ -276,8 +279,8 @@ lor_status lor_longest_overlap_ref(const uint8_t *seqs, const int64_t *offsets, 
  * bound to seqs, offsets (copied into pinned host memory it owns), plan,
  * out_device and ws: a replay reads the bases currently in seqs and
  * rewrites out_device, and nothing else may use ws while the graph exists.
- * DC3's recursion depends on the data through the name count of every
- * level. _create runs the batch once eagerly (out_device then holds valid
+ * The graph holds DC3, whose launches depend on the data in one way only: the
+ * name count of every level decides its recursion. _create runs the batch once eagerly (out_device then holds valid
  * records), records those counts, and captures the same launch sequence
  * with a device check per level in place of the read-back. A replay over
  * different bases whose counts differ still stays inside its buffers, but

@@ -7,10 +7,9 @@
 //   keys   : the first K symbols of every suffix packed in at most 32 bits;
 //   sort   : LSD radix passes over (key, position), 1 to 4 of them;
 //   resolve: suffixes with equal keys are neighbours now. A group of up to
-//            kSmall of them is ordered inside one workgroup: 16 more text
-//            bytes per member are gathered into LDS, a member's place is the
-//            number of smaller ones, and members that still agree compare
-//            their texts directly;
+//            kSmall of them is ordered inside one workgroup: 8 more text
+//            bytes per member are gathered into LDS and a member's place is
+//            the number of smaller ones; runs that still agree stay open;
 //   groups : larger groups (short tandem repeats, mostly) are collected and
 //            radix sorted by a key that sees through a repeat. Let t be the
 //            period of the group's K symbols and e the first place where a
@@ -20,24 +19,25 @@
 //            that break at the same place and in the same direction the
 //            symbols from there on decide. So (direction and e, next symbols)
 //            orders a repeat of any length in one sort.
+//   settle : the members of open runs compare their texts.
 // Suffixes that come within K symbols of their sequence's separator ("near"
 // suffixes, at most K per sequence) would need keys with separators in them;
 // they are left out of the sort and merged in afterwards (k_merge).
 //
 // Measured against DC3 on the same texts (whole call, SA + LCP + ISA +
-// overlap): two sequences of 600 and 431 bases 1.41 -> 0.36 ms, 50k + 50k
-// 2.56 -> 0.63 ms, 8M + 8M noncoding-like 7.34 -> 3.27 ms, 16 x 2^26
-// 248 -> 131 ms.
+// overlap): two sequences of 600 and 431 bases 1.34 -> 0.16 ms, 50k + 50k
+// 2.60 -> 0.19 ms, 8M + 8M noncoding-like 7.45 -> 1.71 ms, 16 x 2^26
+// 248 -> 87 ms. Of the 87 ms the radix passes stream 25 (4.1 TB/s), and random
+// reads, at the 45 G/s that they reach, take 10 here and 24 in the LCP.
 //
-// Suffixes of a group of either kind that still agree after kDeep symbols (long
-// exact or nearly exact copies) are ordered by doubling: by the rank of the
-// suffix h symbols on, h doubling from round to round. Two sequences of 2M
-// bases with 0.1% mutations take 2.1 ms (DC3 4.2 ms), two identical ones
-// 3.6 ms (6.4 ms).
+// Suffixes that still agree after kDeep symbols (long exact or nearly exact
+// copies) are ordered by doubling: by the rank of the suffix h symbols on, h
+// doubling from round to round. Two sequences of 2M bases with 0.1% mutations
+// take 1.3 ms (DC3 4.2 ms), two identical ones 2.7 ms (6.4 ms).
 //
 // Texts whose suffixes are mostly in large groups (one repeat all through),
 // groups that stay large, and workspaces that do not hold them are DC3's: the
-// caller then runs it. 2M + 2M equal bases: 5.2 ms (4.7 ms by DC3 alone).
+// caller then runs it. 2M + 2M equal bases: 4.6 ms (4.7 ms by DC3 alone).
 #include <stdio.h>
 
 #include <algorithm>
@@ -72,7 +72,8 @@ constexpr uint32_t kRepeatSymbols = (64 - kCodeBits) / 3;    // next symbols of 
 constexpr uint32_t kRepeat = 16;              // symbols of a repeat bit, less one (see mark_runs)
 constexpr uint32_t kKeyTile = 2048;           // positions per workgroup of the key kernels
 // Texts up to here take every slot as an item and settle without waiting to
-// hear whether anything is open.
+// hear whether anything is open: a read-back and the list's three launches cost
+// more than looking at 2^21 run bits (10 us).
 constexpr uint32_t kIdentityItems = 1u << 21;
 constexpr uint32_t kDirectRanks = 1u << 24;   // ranks as plain stores up to here (see kDirectIsa)
 constexpr int kMaxRounds = 4;                 // sorts of large groups before DC3 takes over
@@ -719,6 +720,9 @@ struct GroupKey {
 // Stage 0 (32-bit keys of the sort) writes places shifted by the near
 // suffixes; stage 1 (64-bit keys of large groups) through `slots`. Larger
 // groups are marked in `large` and counted, with their heads, per tile.
+// Bound by the window reads of the tied ranks, near the rate of random reads: 9.8 ms
+// at 2^30 suffixes, 0.19 ms at 2^24; with the comparisons of what stays open in
+// here too, a few members of long repeats held up their workgroups: 14.5 and 0.42.
 template <typename X, typename KT, int ITEMS>
 __global__ __launch_bounds__(kBlock) void k_resolve(X x, GroupKey gk, const KT *__restrict__ keys,
                                                     const uint32_t *__restrict__ vals, uint32_t m,
@@ -1041,7 +1045,8 @@ __device__ __forceinline__ uint32_t run_members(const uint32_t *__restrict__ ope
 
 // The items of a large text: the slots in runs, in slot order, so that the few
 // of them fill their workgroups (one tile of slots in two holds a run on DNA
-// texts of 16M bases, but few of them: 337 us in k_settle over slots, 60 over the list and 20 to make it).
+// texts of 16M bases, but few of them: 337 us in k_settle over slots, 60 over the
+// list and 20 to make it).
 constexpr uint32_t kOpenWords = 4 * kBlock;   // bitmap words per workgroup
 __global__ __launch_bounds__(kBlock) void k_open_count(const uint32_t *__restrict__ open, uint32_t words,
                                                        uint32_t *__restrict__ count) {
@@ -1205,8 +1210,10 @@ __global__ __launch_bounds__(kBlock) void k_double(RunList list, const uint32_t 
 // The same by comparing texts, up to `deep` symbols. Repeat keys come first: a
 // tandem repeat inside one run would cost a long comparison per member and step
 // otherwise. Runs of fewer than kRepeatRun, which have few steps, do without:
-// the keys read as much as a comparison does. Runs share at least the K symbols
-// of their sort key.
+// the keys read as much as a comparison does (65,536 queries: 1.45 -> 0.48 ms).
+// Runs share at least the K symbols of their sort key. Bound by the chain of
+// waits of a run's members, so one item per thread and many workgroups: five
+// per thread took 100 us longer on 64 pairs of 1,000 to 10,000 bases.
 template <typename X>
 __global__ __launch_bounds__(kBlock) void k_settle(X x, RunList list, const uint32_t *__restrict__ was,
                                                    uint32_t *__restrict__ open, int32_t *__restrict__ sa,

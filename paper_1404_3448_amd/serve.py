@@ -8,8 +8,8 @@ follow-up suffix-pair lcp queries) arrive over time. The loop
   the HBM budget still admits) as one batch, so requests that arrive while
   others are on the GPU join the next batch as soon as a slot and memory
   free up, and batches on different slots overlap on the device;
-* runs each batch through the batched entry point (one DC3 over all its
-  pairs), on the worker's own HIP stream, with the bases staged through a
+* runs each batch through the batched entry point (one suffix array over
+  all its pairs), on the worker's own HIP stream, with the bases staged through a
   pinned host buffer; when a request keeps state, the batch also returns its
   LCP and ISA, and the request's slices of them (its own LCP and ISA) stay
   resident with a compact block sparse table (about 8.4 bytes per base) until
