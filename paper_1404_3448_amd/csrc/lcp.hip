@@ -27,6 +27,8 @@
 // text-order method it replaces: 1,000 symbols 96 -> 36 us, 100k 296 -> 37 us,
 // 1M 483 -> 60 us, 16M 1.21 -> 0.56 ms, 256M 14.8 -> 8.5 ms; two identical
 // sequences of 2M bases 75 -> 0.11 ms.
+#include <algorithm>
+
 #include "lor_internal.hpp"
 
 namespace lor {
@@ -129,7 +131,7 @@ __global__ __launch_bounds__(kBlock) void k_lcp_window(const CH *__restrict__ t,
 // of kPackWin symbols is 8 bytes of a table a quarter (16-bit text: an eighth)
 // the size: fewer lines, more of them in the caches. Two bits hold bases only: a
 // window that meets anything else, or the end, is flagged, by one bit per
-// 2^shift window starts (the flags stay in L2), and compares the text itself.
+// 2^shift window starts (small enough for the L1 caches), and compares the text itself.
 // Packed from 2^21 symbols on, and where sequences (as far as the caller knows)
 // are at least kPackSeq long on average. Window and packing, bytes against
 // packed: two sequences of 1M symbols 46 / 46 us in all of LCP, 4M 102 / 97, 8M
@@ -387,7 +389,10 @@ lor_status lcp_build_t(const CH *text, uint32_t n, const int32_t *sa, int32_t *l
     const size_t before_pack = ar.mark();
     if (n >= kPackFrom && n / kPackSeq >= seqs && reinterpret_cast<uintptr_t>(text) % 4 == 0) {
         PackedText pt;
-        pt.shift = n <= 1u << 26 ? 4 : 6;   // flags of at most 512 KB, 2 MB at 2^30
+        // flags of about 16 KB, which stay in the L1 caches, while the starts that
+        // share one with a separator stay below one in 1,024
+        pt.shift = std::max(bits_for(n) - 17, 4);
+        while (pt.shift > 4 && ((uint64_t)std::max(seqs, 32u) << pt.shift) > n / 1024) --pt.shift;
         const uint32_t fwords = div_up(div_up(n, 1u << pt.shift), 32);
         LOR_TAKE(ar, uint32_t, (size_t)n / 16 + 4, pt.words);   // the last window reads up to 8 bytes from n / 4 on
         LOR_TAKE(ar, uint32_t, fwords, pt.flags);

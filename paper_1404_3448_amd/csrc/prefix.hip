@@ -27,8 +27,8 @@
 // Measured against DC3 on the same texts (whole call, SA + LCP + ISA +
 // overlap): two sequences of 600 and 431 bases 1.34 -> 0.16 ms, 50k + 50k
 // 2.60 -> 0.19 ms, 8M + 8M noncoding-like 7.45 -> 1.71 ms, 16 x 2^26
-// 248 -> 87 ms. Of the 87 ms the key passes stream 20 (4.1 TB/s), and random
-// reads, at the 45 G/s that they reach, take 10 here and 24 in the LCP.
+// 248 -> 83 ms. Of the 83 ms the key passes stream 20 (4.1 TB/s), and random
+// reads, at the 45 to 55 G/s that they reach, take 10 here and 19 in the LCP.
 //
 // Suffixes that still agree after kDeep symbols (long exact or nearly exact
 // copies) are ordered by doubling: by the rank of the suffix h symbols on, h
