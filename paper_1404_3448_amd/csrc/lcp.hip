@@ -22,11 +22,11 @@
 // LCP is written in rank order throughout. ISA, when wanted, is a scatter of
 // its own.
 //
-// The window kernels are bound by their random reads: 24 ms at 2^30 suffixes,
-// the 45 G/s that random 8-byte reads reach on such tables. LCP + ISA against the
-// text-order method it replaces: 1,000 symbols 96 -> 36 us, 100k 296 -> 37 us,
-// 1M 483 -> 60 us, 16M 1.21 -> 0.56 ms, 256M 14.8 -> 8.5 ms; two identical
-// sequences of 2M bases 75 -> 0.11 ms.
+// The window kernels are bound by their random reads: 19.3 ms at 2^30 suffixes, 55
+// G/s, where random 8-byte reads reach 45 to 51 on tables of 256 MB and more.
+// LCP + ISA against the text-order method it replaces: 1,000 symbols 96 -> 36 us,
+// 100k 296 -> 37 us, 1M 483 -> 60 us, 16M 1.21 -> 0.53 ms, 256M 14.8 -> 8.6 ms; two
+// identical sequences of 2M bases 75 -> 0.11 ms.
 #include <algorithm>
 
 #include "lor_internal.hpp"
@@ -135,9 +135,10 @@ __global__ __launch_bounds__(kBlock) void k_lcp_window(const CH *__restrict__ t,
 // Packed from 2^21 symbols on, and where sequences (as far as the caller knows)
 // are at least kPackSeq long on average. Window and packing, bytes against
 // packed: two sequences of 1M symbols 46 / 46 us in all of LCP, 4M 102 / 97, 8M
-// 178 / 151, 16M 254 / 173 us, 1G 26.4 / 24.0 ms (then bound by the requests, 45 G/s,
-// not the lines), 700 pairs with 102M symbols 1.27 / 0.86 ms; 65,536 queries of
-// 634 bases, where one window in seven is flagged, 0.82 / 0.85 ms.
+// 178 / 151, 16M 254 / 139 us, 1G 26.4 / 19.6 ms, 700 pairs with 102M symbols
+// 1.27 / 0.85 ms; 65,536 queries of 634 bases, where one window in seven is
+// flagged, 0.82 / 0.85 ms. With finer flags, 512 KB to 2 MB of them, that miss the L1
+// caches: 16M 173 us, 1G 24.0 ms, as each is one more request to L2 or behind it.
 constexpr uint32_t kPackFrom = 1u << 21, kPackSeq = 2048;
 constexpr uint32_t kPackWin = 29;   // 32 symbols in 8 bytes less the up to 3 before the first
 struct PackedText {
@@ -390,7 +391,8 @@ lor_status lcp_build_t(const CH *text, uint32_t n, const int32_t *sa, int32_t *l
     if (n >= kPackFrom && n / kPackSeq >= seqs && reinterpret_cast<uintptr_t>(text) % 4 == 0) {
         PackedText pt;
         // flags of about 16 KB, which stay in the L1 caches, while the starts that
-        // share one with a separator stay below one in 1,024
+        // share one with a separator stay below one in 1,024 (one in 128: 700 pairs
+        // 811 -> 846 us)
         pt.shift = std::max(bits_for(n) - 17, 4);
         while (pt.shift > 4 && ((uint64_t)std::max(seqs, 32u) << pt.shift) > n / 1024) --pt.shift;
         const uint32_t fwords = div_up(div_up(n, 1u << pt.shift), 32);
