@@ -1636,7 +1636,7 @@ lor_status prefix_sa_tagged(const uint16_t *text, uint32_t n, uint32_t pairs, co
     const int want = tag + bits_for(longest) + 2;
     const int bits = std::min(32, (want + 7) / 8 * 8);
     const int K = std::min((bits - tag) / 2, kMaxK);
-    if (longest >> (2 * K) > 16) return LOR_OK;   // a huge pair among many: too few symbols fit
+    if ((uint64_t)longest >> (2 * K) > 16) return LOR_OK;   // a huge pair among many: too few symbols fit
     const std::unique_ptr<uint32_t[]> below(new (std::nothrow) uint32_t[pairs]);
     if (!below) return LOR_OK;
     uint32_t near = 0;
