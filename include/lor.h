@@ -84,6 +84,13 @@ lor_status lor_build_sa(const uint8_t *seqs, const int64_t *offsets, int32_t num
                         uint8_t *joined_out, int32_t *sa_out,
                         void *ws, size_t ws_bytes, void *hip_stream);
 
+/* The same array by DC3 alone (Section III, Steps 1-3), which lor_build_sa
+ * falls back to where sorting prefixes does not pay. Same arguments, workspace
+ * and result as lor_build_sa; it serves to check and to measure that path. */
+lor_status lor_build_sa_dc3(const uint8_t *seqs, const int64_t *offsets, int32_t num_seqs,
+                            uint8_t *joined_out, int32_t *sa_out,
+                            void *ws, size_t ws_bytes, void *hip_stream);
+
 /* Allocation-free form of lor_build_sa, for callers that cannot allocate
  * device memory or pass a workspace (code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc). Same inputs, outputs and

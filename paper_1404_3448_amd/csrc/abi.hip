@@ -257,6 +257,42 @@ lor_status sort_pairs(K *keys, uint32_t *vals, int64_t n, int32_t bit_lo, int32_
     return LOR_OK;
 }
 
+// lor_build_sa and lor_build_sa_dc3.
+lor_status build_sa(const uint8_t *seqs, const int64_t *offsets, int32_t num_seqs, uint8_t *joined_out,
+                    int32_t *sa_out, void *ws, size_t ws_bytes, void *hip_stream, bool dc3_only) {
+    int64_t N = 0;
+    LOR_TRY(check_offsets(offsets, num_seqs, &N));
+    if (!sa_out || (!seqs && offsets[num_seqs] > 0)) {
+        set_error("NULL seqs or sa_out");
+        return LOR_EINVAL;
+    }
+    if (joined_out && !aligned(joined_out, 4)) {
+        set_error("joined_out must be 4-byte aligned");
+        return LOR_EINVAL;
+    }
+    LOR_TRY(check_ws(ws, ws_bytes, sa_bytes(N, joined_out == nullptr)));
+    hipStream_t s = (hipStream_t)hip_stream;
+    Arena ar = arena_after_header(ws, ws_bytes);
+    uint32_t *hdr = static_cast<uint32_t *>(ws);
+    uint8_t *joined = joined_out;
+    if (!joined) LOR_TAKE(ar, uint8_t, (size_t)N, joined);
+    LOR_TRY(zero_words(hdr, 16, s));
+    LOR_TRY(join_text(seqs, offsets, num_seqs, joined, hdr, s));
+    // symbols are byte + 1: bases 1..4, separators 5..4+num_seqs
+    const uint32_t alphabet = 4u + (uint32_t)num_seqs;
+    if (dc3_only) return dc3_u8(joined, (uint32_t)N, alphabet, sa_out, ar, hdr, s);
+    if (trace_on()) {
+        // For the notes on DC3's levels alone: what builds the result does not depend on the trace.
+        const size_t mark = ar.mark();
+        LOR_TRY(dc3_u8(joined, (uint32_t)N, alphabet, sa_out, ar, hdr, s));
+        ar.release(mark);
+        LOR_TRY(zero_words(hdr + 1, 15, s));
+    }
+    bool done = false;
+    LOR_TRY(prefix_sa_joined(joined, (uint32_t)N, offsets, (uint32_t)num_seqs, sa_out, ar, hdr, s, &done));
+    return done ? LOR_OK : dc3_u8(joined, (uint32_t)N, alphabet, sa_out, ar, hdr, s);
+}
+
 }  // namespace
 
 extern "C" {
@@ -285,30 +321,12 @@ size_t lor_build_sa_workspace(int64_t total_bases, int32_t num_seqs) {
 
 lor_status lor_build_sa(const uint8_t *seqs, const int64_t *offsets, int32_t num_seqs, uint8_t *joined_out,
                         int32_t *sa_out, void *ws, size_t ws_bytes, void *hip_stream) {
-    int64_t N = 0;
-    LOR_TRY(check_offsets(offsets, num_seqs, &N));
-    if (!sa_out || (!seqs && offsets[num_seqs] > 0)) {
-        set_error("NULL seqs or sa_out");
-        return LOR_EINVAL;
-    }
-    if (joined_out && !aligned(joined_out, 4)) {
-        set_error("joined_out must be 4-byte aligned");
-        return LOR_EINVAL;
-    }
-    LOR_TRY(check_ws(ws, ws_bytes, sa_bytes(N, joined_out == nullptr)));
-    hipStream_t s = (hipStream_t)hip_stream;
-    Arena ar = arena_after_header(ws, ws_bytes);
-    uint32_t *hdr = static_cast<uint32_t *>(ws);
-    uint8_t *joined = joined_out;
-    if (!joined) LOR_TAKE(ar, uint8_t, (size_t)N, joined);
-    LOR_TRY(zero_words(hdr, 16, s));
-    LOR_TRY(join_text(seqs, offsets, num_seqs, joined, hdr, s));
-    bool done = false;
-    LOR_TRY(prefix_sa_joined(joined, (uint32_t)N, offsets, (uint32_t)num_seqs, sa_out, ar, hdr, s, &done));
-    if (done && !trace_on()) return LOR_OK;
-    // DC3 (with LOR_TRACE always, for the notes on its levels; the order is the same).
-    // symbols are byte + 1: bases 1..4, separators 5..4+num_seqs
-    return dc3_u8(joined, (uint32_t)N, 4u + (uint32_t)num_seqs, sa_out, ar, hdr, s);
+    return build_sa(seqs, offsets, num_seqs, joined_out, sa_out, ws, ws_bytes, hip_stream, false);
+}
+
+lor_status lor_build_sa_dc3(const uint8_t *seqs, const int64_t *offsets, int32_t num_seqs, uint8_t *joined_out,
+                            int32_t *sa_out, void *ws, size_t ws_bytes, void *hip_stream) {
+    return build_sa(seqs, offsets, num_seqs, joined_out, sa_out, ws, ws_bytes, hip_stream, true);
 }
 
 lor_status lor_build_sa_static(const uint8_t *seqs, const int64_t *offsets, int32_t num_seqs, uint8_t *joined_out,

@@ -87,6 +87,7 @@ def lib():
         "lor_version": ([], I32),
         "lor_build_sa_workspace": ([I64, I32], SZ),
         "lor_build_sa": ([P, P, I32, P, P, P, SZ, P], I32),
+        "lor_build_sa_dc3": ([P, P, I32, P, P, P, SZ, P], I32),
         "lor_build_sa_static": ([P, P, I32, P, P, P], I32),
         "lor_suffix_array_workspace": ([I64], SZ),
         "lor_suffix_array_i32": ([P, I64, I32, P, P, SZ, P], I32),
@@ -202,6 +203,16 @@ def lor_build_sa_workspace(total_bases: int, num_seqs: int) -> int:
 @_on_stream
 def lor_build_sa(seqs, offsets, joined_out=None, sa_out=None, ws=None, stream=None):
     """Suffix array of the separator-joined text. Returns (sa, joined)."""
+    return _build_sa("lor_build_sa", seqs, offsets, joined_out, sa_out, ws, stream)
+
+
+@_on_stream
+def lor_build_sa_dc3(seqs, offsets, joined_out=None, sa_out=None, ws=None, stream=None):
+    """lor_build_sa by DC3 alone. Returns (sa, joined)."""
+    return _build_sa("lor_build_sa_dc3", seqs, offsets, joined_out, sa_out, ws, stream)
+
+
+def _build_sa(fn, seqs, offsets, joined_out, sa_out, ws, stream):
     import torch
     o = _offsets(offsets)
     k = o.size - 1
@@ -216,9 +227,9 @@ def lor_build_sa(seqs, offsets, joined_out=None, sa_out=None, ws=None, stream=No
     _need(sa_out, torch.int32, N, "sa_out")
     nbytes = lor_build_sa_workspace(int(o[-1]), k)
     ws = _workspace(nbytes, dev, ws)
-    st = lib().lor_build_sa(_ptr(seqs), o.ctypes.data_as(ctypes.c_void_p), k, _ptr(joined_out), _ptr(sa_out),
+    st = getattr(lib(), fn)(_ptr(seqs), o.ctypes.data_as(ctypes.c_void_p), k, _ptr(joined_out), _ptr(sa_out),
                             _ptr(ws), ws.numel() * ws.element_size(), _stream(stream))
-    _check("lor_build_sa", st)
+    _check(fn, st)
     return sa_out[:N], joined_out[:N]
 
 
