@@ -35,9 +35,13 @@
 // doubling from round to round. Two sequences of 2M bases with 0.1% mutations
 // take 1.3 ms (DC3 4.2 ms), two identical ones 2.7 ms (6.4 ms).
 //
-// Texts whose suffixes are mostly in large groups (one repeat all through),
-// groups that stay large, and workspaces that do not hold them are DC3's: the
-// caller then runs it. 2M + 2M equal bases: 4.6 ms (4.7 ms by DC3 alone).
+// Groups that stay large (words with more than kSmall copies) are doubled as well,
+// by sorts of (group, rank of the suffix h symbols on).
+//
+// Texts whose suffixes are mostly in large groups (one repeat all through) or
+// would take more sorts than DC3 is worth, and workspaces that do not hold them,
+// are DC3's: the caller then runs it. 2M + 2M equal bases: 4.6 ms (4.7 ms by DC3
+// alone).
 #include <stdio.h>
 
 #include <algorithm>
@@ -76,7 +80,10 @@ constexpr uint32_t kKeyTile = 2048;           // positions per workgroup of the 
 // more than looking at 2^21 run bits (10 us).
 constexpr uint32_t kIdentityItems = 1u << 21;
 constexpr uint32_t kDirectRanks = 1u << 24;   // ranks as plain stores up to here (see kDirectIsa)
-constexpr int kMaxRounds = 4;                 // sorts of large groups before DC3 takes over
+constexpr int kMaxRounds = 4;                 // sorts of large groups by their next symbols, at most
+// What the sorts of large groups may cost before DC3 takes over, counted in sorted
+// suffixes (see Spend): one per member, and kRoundCost for a round's launches.
+constexpr uint64_t kRoundCost = 1u << 19, kLeastSpend = 3u << 23;
 constexpr int kMaxK = 16;
 constexpr uint32_t kScan = 4;                 // group members read from LDS together
 
@@ -1281,6 +1288,106 @@ __global__ __launch_bounds__(kBlock) void k_settle(X x, RunList list, const uint
     if (l == 0 && s_left) atomicAdd(left, s_left);
 }
 
+// ----------------------------------------------------------- larger groups
+// Groups that no workgroup holds and that their next symbols do not tell apart
+// (words with more than kSmall copies) are doubled by sorting: their members (the
+// pool) by (group, rank[p + h]), after which a group's members share 2 h symbols. A
+// suffix alone with its key leaves the pool. Groups are numbered in slot order,
+// so the i-th item of the sorted pool has the slot of the i-th before. Suffix arrays
+// by this against those by DC3 alone: 65 copies of 100 bases in 1M 0.83 / 1.96 ms, in
+// 16M 1.44 / 4.16 ms; 3,000 of 1,000 with 1% mutations in 16M 2.8 / 5.7 ms.
+constexpr uint32_t kPoolItems = 4, kPoolTile = kBlock * kPoolItems;
+
+struct PoolItems {   // the pool after a sort
+    const uint64_t *keys;
+    const uint32_t *vals, *slots;
+    uint32_t m;
+    __device__ bool head(uint32_t i) const { return i == 0 || i >= m || keys[i] != keys[i - 1]; }
+};
+
+// Items of a tile that stay in the pool, and the heads of their groups.
+__global__ __launch_bounds__(kBlock) void k_pool_count(PoolItems x, uint32_t *__restrict__ tcount,
+                                                       uint32_t *__restrict__ hcount) {
+    __shared__ uint32_t s_tmp[kBlock / kWave];
+    uint32_t c = 0, all;   // members, and heads above them
+#pragma unroll
+    for (uint32_t r = 0; r < kPoolItems; ++r) {
+        const uint32_t i = blockIdx.x * kPoolTile + r * kBlock + threadIdx.x;
+        if (i >= x.m) continue;
+        if (!x.head(i)) c += 1u;
+        else if (!x.head(i + 1)) c += 0x10001u;
+    }
+    static_assert(kPoolTile < 0x10000u, "two counts in a word");
+    dev::block_exclusive_sum(c, s_tmp, &all);
+    if (threadIdx.x == 0) {
+        tcount[blockIdx.x] = all & 0xffffu;
+        hcount[blockIdx.x] = all >> 16;
+    }
+}
+
+// SA takes the sorted order, suffixes that leave the pool their ranks; the others
+// go on with their group's new number, and every group with its first slot.
+__global__ __launch_bounds__(kBlock) void k_pool_collect(PoolItems x, const uint32_t *__restrict__ tbase,
+                                                         const uint32_t *__restrict__ hbase, uint32_t cap, uint32_t n,
+                                                         int32_t *__restrict__ sa, uint32_t *__restrict__ rank,
+                                                         uint64_t *__restrict__ keys, uint32_t *__restrict__ vals,
+                                                         uint32_t *__restrict__ slots, uint32_t *__restrict__ first) {
+    __shared__ uint32_t s_tmp[kBlock / kWave];
+    uint32_t at = tbase[blockIdx.x], group = hbase[blockIdx.x];
+    for (uint32_t r = 0; r < kPoolItems; ++r) {
+        const uint32_t i = blockIdx.x * kPoolTile + r * kBlock + threadIdx.x;
+        const bool head = i < x.m && x.head(i), member = i < x.m && !(head && x.head(i + 1));
+        uint32_t all;
+        const uint32_t below = dev::block_exclusive_sum(member ? (head ? 0x10001u : 1u) : 0u, s_tmp, &all);
+        const uint32_t o = at + (below & 0xffffu), id = group + (below >> 16) - (head ? 0u : 1u);
+        at += all & 0xffffu;
+        group += all >> 16;
+        if (i >= x.m) continue;
+        const uint32_t slot = x.slots[i], p = x.vals[i];
+        sa[slot] = (int32_t)p;
+        if (!member) {
+            if (p < n) rank[p] = slot;
+        } else if (o < cap && id <= cap / 2) {   // always with consistent counts
+            keys[o] = id;
+            vals[o] = p;
+            slots[o] = slot;
+            if (head) first[id] = slot;
+        }
+    }
+}
+
+// The pool at its start: SA takes its members in any order (ranks are made from all of
+// SA), every group its first slot.
+__global__ __launch_bounds__(kBlock) void k_pool_start(const uint64_t *__restrict__ keys,
+                                                       const uint32_t *__restrict__ vals,
+                                                       const uint32_t *__restrict__ slots, uint32_t total, uint32_t n,
+                                                       int32_t *__restrict__ sa, uint32_t *__restrict__ first) {
+    const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
+    if (i >= total) return;
+    const uint32_t slot = slots[i];
+    sa[slot] = (int32_t)min(vals[i], n - 1u);
+    if (i == 0 || keys[i] != keys[i - 1]) first[keys[i]] = slot;
+}
+
+// A suffix in the pool ranks as its group's first slot.
+__global__ __launch_bounds__(kBlock) void k_pool_ranks(const uint64_t *__restrict__ keys,
+                                                       const uint32_t *__restrict__ vals,
+                                                       const uint32_t *__restrict__ first, uint32_t total, uint32_t n,
+                                                       uint32_t *__restrict__ rank) {
+    const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
+    if (i < total && vals[i] < n) rank[vals[i]] = first[keys[i]];
+}
+
+__global__ __launch_bounds__(kBlock) void k_pool_keys(uint64_t *__restrict__ keys, const uint32_t *__restrict__ vals,
+                                                      uint32_t total, uint32_t h, uint32_t n, int rank_bits,
+                                                      const uint32_t *__restrict__ rank) {
+    const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
+    if (i >= total) return;
+    const uint32_t p = vals[i];
+    const uint64_t r = p < n && h < n - p ? rank[p + h] + 1u : 0u;   // the end of the text comes first
+    keys[i] = (keys[i] << rank_bits) | r;
+}
+
 // ------------------------------------------------------------------ driver
 
 struct PrefixHdr {
@@ -1351,16 +1458,104 @@ lor_status copy_words(const uint32_t *a, uint32_t *b, uint32_t count, hipStream_
     return LOR_OK;
 }
 
-// Settles what is open: `count` suffixes, compared up to `from` symbols so far
-// (0: not yet). *done stays false when the workspace does not hold the ranks or
-// the budget is spent.
+// What the sorts of large groups may still cost. A sorted suffix of a round takes
+// some 0.13 ns (up to seven passes over 64-bit keys, lookups and scatters), a round's
+// launches 70 us; DC3 0.3 to 0.5 ns per suffix of a text with large groups and 1.3 ms
+// or more. So half of a DC3 run is spent at most before giving up, or 3.3 ms where
+// that is more; mostly a fifth or less, as worth() looks ahead (16M bases with 2,000
+// copies of 3,000: 8.0 ms, 6.6 by DC3 alone, 6.6 by doubling to the end).
+struct Spend {
+    uint64_t left;
+    explicit Spend(uint32_t n) : left(std::max<uint64_t>(n + n / 2ull, kLeastSpend)) {}
+    bool take(uint32_t members) {
+        const uint64_t c = members + kRoundCost;
+        if (c > left) return false;
+        left -= c;
+        return true;
+    }
+    // Of `members` a round is expected to settle `lost`, and every round twice as many
+    // as the one before: a copy's suffixes are told apart where the symbols compared
+    // reach its end.
+    bool worth(uint64_t members, uint64_t lost) const {
+        uint64_t cost = 0;
+        for (lost = std::max<uint64_t>(lost, 1); cost <= left; lost *= 2) {
+            cost += members + kRoundCost;
+            if (lost >= members) return cost <= left;
+            members -= lost;
+        }
+        return false;
+    }
+};
+
+// Members of large groups in slot order: group number, suffix, slot; the first slot
+// of every group; `share` symbols that the members of a group share at least.
+struct Pool {
+    uint64_t *keys;
+    uint32_t *vals, *slots, *first;
+    uint32_t total, groups, share;
+};
+
+// One round: sorts the pool by the rank `h` symbols on, with buffers as large as
+// the pool was first (`cap`). Ranks and *pool are those after the round; `lookups_done`
+// runs once all lookups of ranks have been enqueued, before any rank changes.
+struct PoolRoom {
+    uint64_t *keys;
+    uint32_t *vals, *slots, *radix, *tcount, *hcount, *stmp;
+    uint32_t cap;
+};
+template <typename F>
+lor_status pool_round(Pool *pool, PoolRoom *room, uint32_t h, uint32_t n, int32_t *sa, uint32_t *rank, uint32_t *hdr,
+                      F lookups_done, hipStream_t s) {
+    const uint32_t total = pool->total, tiles = div_up(total, kPoolTile);
+    const int rank_bits = bits_for(n);
+    LOR_LAUNCH("k_pool_keys", 24.0 * total, s,
+               hipLaunchKernelGGL(k_pool_keys, dim3(div_up(total, kBlock)), dim3(kBlock), 0, s, pool->keys, pool->vals,
+                                  total, h, n, rank_bits, rank));
+    LOR_TRY(lookups_done());
+    bool alt;
+    LOR_TRY(radix_sort<uint64_t>(pool->keys, pool->vals, room->keys, room->vals, total, 0,
+                                 rank_bits + bits_for(pool->groups - 1), room->radix, s, &alt));
+    if (!alt) {   // the sorted pool is where the next one is not
+        std::swap(pool->keys, room->keys);
+        std::swap(pool->vals, room->vals);
+    }
+    const PoolItems sorted{room->keys, room->vals, pool->slots, total};
+    LOR_LAUNCH("k_pool_count", 8.0 * total, s,
+               hipLaunchKernelGGL(k_pool_count, dim3(tiles), dim3(kBlock), 0, s, sorted, room->tcount, room->hcount));
+    LOR_TRY(scan_exclusive(room->tcount, tiles, room->stmp, hdr + kWordTied, s));
+    LOR_TRY(scan_exclusive(room->hcount, tiles, room->stmp, hdr + kWordHeads, s));
+    LOR_LAUNCH("k_pool_collect", 44.0 * total, s,
+               hipLaunchKernelGGL(k_pool_collect, dim3(tiles), dim3(kBlock), 0, s, sorted, room->tcount, room->hcount,
+                                  room->cap, n, sa, rank, pool->keys, pool->vals, room->slots, pool->first));
+    std::swap(pool->slots, room->slots);
+    PrefixHdr w;
+    LOR_TRY(read_header(hdr, &w, s));
+    if (trace_on())
+        fprintf(stderr, "[lor] prefix sort: %u suffixes in %u large groups doubled from %u symbols, %u left\n", total,
+                pool->groups, h, w.word[kWordTied]);
+    if (w.word[kWordTied] > total || w.word[kWordHeads] > w.word[kWordTied] / 2) {
+        set_error("internal: %u suffixes in %u large groups of %u", w.word[kWordTied], w.word[kWordHeads], total);
+        return LOR_EINVAL;
+    }
+    pool->total = w.word[kWordTied];
+    pool->groups = w.word[kWordHeads];
+    if (pool->total)
+        LOR_LAUNCH("k_pool_ranks", 16.0 * pool->total, s,
+                   hipLaunchKernelGGL(k_pool_ranks, dim3(div_up(pool->total, kBlock)), dim3(kBlock), 0, s, pool->keys,
+                                      pool->vals, pool->first, pool->total, n, rank));
+    return LOR_OK;
+}
+
+// Settles what is open: `count` suffixes in runs of up to kSmall, compared up to
+// `from` symbols so far (0: not yet), and the pool's. *done stays false when the workspace
+// does not hold the ranks, the budget is spent or the pool costs too much.
 template <typename X>
-lor_status settle_runs(const X &x, uint32_t count, uint32_t from, uint32_t *open, int32_t *sa, Arena &ar,
-                       uint32_t *hdr, uint32_t budget, hipStream_t s, bool *done) {
+lor_status settle_runs(const X &x, uint32_t count, uint32_t from, Pool pool, uint32_t *open, int32_t *sa, Arena &ar,
+                       uint32_t *hdr, uint32_t budget, Spend &spend, hipStream_t s, bool *done) {
     const uint32_t n = x.n;
     RunList list{nullptr, nullptr, n};
     uint32_t words = div_up(n, 32);
-    if (n > kIdentityItems) {
+    if (n > kIdentityItems && count > 0) {
         // every run has at least one marked slot for each unmarked one
         list.cap = (uint32_t)std::min<uint64_t>(2ull * count, n);
         const uint32_t groups = div_up(words, kOpenWords), lwords = div_up(list.cap, 32);
@@ -1386,7 +1581,7 @@ lor_status settle_runs(const X &x, uint32_t count, uint32_t from, uint32_t *open
     // suffix of the text and 80 us; comparing an open suffix to its neighbour
     // through kSettle symbols reads some 60 lines, about 1.5 ns: for few only.
     const uint32_t few = n / 128u + 8192u;
-    for (int step = 0; from == 0 || (from == kDeep && count <= few); ++step) {   // at most two steps
+    while (count > 0 && (from == 0 || (from == kDeep && count <= few))) {   // at most two steps
         from = count <= few ? kSettle : kDeep;
         LOR_TRY(copy_words(open, was, words, s));
         LOR_TRY(zero_words(hdr + kWordRound, 1, s));
@@ -1397,12 +1592,13 @@ lor_status settle_runs(const X &x, uint32_t count, uint32_t from, uint32_t *open
                     w.word[kWordRound], w.word[kWordAbort] ? ", given up" : "");
         if (w.word[kWordAbort]) return LOR_OK;
         count = w.word[kWordRound];
-        if (count == 0) {
-            *done = true;
-            return LOR_OK;
-        }
+    }
+    if (count == 0 && pool.total == 0) {
+        *done = true;
+        return LOR_OK;
     }
     uint32_t *rank = ar.take<uint32_t>(n);
+    const size_t mark = ar.mark();
     if (ar.overflow) return LOR_OK;
     if (n <= kDirectRanks) {
         LOR_LAUNCH("k_ranks", 8.0 * n, s,
@@ -1423,15 +1619,61 @@ lor_status settle_runs(const X &x, uint32_t count, uint32_t from, uint32_t *open
         return LOR_OK;
     };
     if (list.slots) LOR_TRY(run_ranks(open));
+    auto double_runs = [&](uint32_t h, uint32_t *left) -> lor_status {
+        LOR_TRY(copy_words(open, was, words, s));
+        LOR_LAUNCH("k_double", 0.125 * list.cap, s,
+                   hipLaunchKernelGGL(k_double, dim3(std::min(div_up(list.cap, kDoubleTile), kDoubleGroups)),
+                                      dim3(kBlock), 0, s, list, was, open, n, h, rank, sa, left));
+        return LOR_OK;
+    };
+    uint64_t h = from;   // what the open runs share
+    if (pool.total) {
+        ar.release(mark);   // the scatter's buffers
+        const uint32_t most = div_up(pool.total, kPoolTile);
+        PoolRoom room{};
+        room.cap = pool.total;
+        room.keys = ar.take<uint64_t>(room.cap);
+        room.vals = ar.take<uint32_t>(room.cap);
+        room.slots = ar.take<uint32_t>(room.cap);
+        room.radix = ar.take<uint32_t>(radix_counts_words(room.cap));
+        room.tcount = ar.take<uint32_t>(most);
+        room.hcount = ar.take<uint32_t>(most);
+        room.stmp = ar.take<uint32_t>(kScanTmpWords);
+        if (ar.overflow) return LOR_OK;
+        LOR_LAUNCH("k_pool_ranks", 16.0 * pool.total, s,
+                   hipLaunchKernelGGL(k_pool_ranks, dim3(div_up(pool.total, kBlock)), dim3(kBlock), 0, s, pool.keys,
+                                      pool.vals, pool.first, pool.total, n, rank));
+        // The pool's groups share less than the open runs at first; from where they
+        // share as much both are doubled together.
+        for (uint64_t d = pool.share; pool.total > 0; d *= 2) {
+            if (d > 2ull * n) {
+                set_error("internal: %u suffixes of %u left unordered", pool.total, n);
+                return LOR_EINVAL;
+            }
+            const uint32_t total = pool.total;
+            if (!spend.take(total)) return LOR_OK;
+            if (count > 0) d = std::min(d, h);
+            const bool both = count > 0 && d == h;
+            const uint32_t step = (uint32_t)std::min<uint64_t>(d, n);
+            LOR_TRY(zero_words(hdr + kWordRound, 1, s));
+            auto runs = [&]() -> lor_status { return both ? double_runs(step, hdr + kWordRound) : LOR_OK; };
+            LOR_TRY(pool_round(&pool, &room, step, n, sa, rank, hdr, runs, s));
+            if (both) {
+                LOR_TRY(run_ranks(was));
+                h *= 2;
+            }
+            if (pool.total && !spend.worth(pool.total, 2ull * (total - pool.total))) return LOR_OK;
+        }
+        if (count == 0) {
+            *done = true;
+            return LOR_OK;
+        }
+    }
     constexpr int kPer = 4;   // rounds between read-backs; a round with nothing open is three short launches
-    for (uint64_t h = from;;) {
+    for (;;) {
         LOR_TRY(zero_words(hdr + kWordRound, kPer, s));
         for (int r = 0; r < kPer; ++r, h *= 2) {
-            const uint32_t step = (uint32_t)std::min<uint64_t>(h, n);
-            LOR_TRY(copy_words(open, was, words, s));
-            LOR_LAUNCH("k_double", 0.125 * list.cap, s,
-                       hipLaunchKernelGGL(k_double, dim3(std::min(div_up(list.cap, kDoubleTile), kDoubleGroups)),
-                                          dim3(kBlock), 0, s, list, was, open, n, step, rank, sa, hdr + kWordRound + r));
+            LOR_TRY(double_runs((uint32_t)std::min<uint64_t>(h, n), hdr + kWordRound + r));
             LOR_TRY(run_ranks(was));
         }
         LOR_TRY(read_header(hdr, &w, s));
@@ -1467,9 +1709,10 @@ lor_status prefix_sa(X x, int bits, uint32_t near, int32_t *sa, Arena &ar, uint3
     auto tile_of = [](uint32_t count) { return kBlock * (uint32_t)(count <= kResSmall ? kResItemsSmall : kResItems); };
     const uint32_t tiles = div_up(m ? m : 1, tile_of(m));
     // 32 steps over two texts read about 32 lines, some 0.7 ns of the chip's
-    // gather rate; DC3 takes 0.25 to 0.4 ns per suffix. At most about a third of
-    // a DC3 run is spent before giving up.
+    // gather rate; DC3 takes 0.25 to 0.4 ns per suffix. Comparisons cost at most
+    // about a third of a DC3 run before they are given up.
     const uint32_t budget = x.n / 8 + 65536u;
+    Spend spend(x.n);
     const size_t mark = ar.mark();
     struct Release {
         Arena &a;
@@ -1524,10 +1767,20 @@ lor_status prefix_sa(X x, int bits, uint32_t near, int32_t *sa, Arena &ar, uint3
     const uint64_t *k64 = nullptr;
     const uint32_t *v64 = nullptr, *slots = nullptr;
     uint32_t cur = m;
+    Pool pool{};
+    pool.share = (uint32_t)x.K;
     for (int round = 0; h.word[kWordTied] > 0 && !h.word[kWordAbort]; ++round) {
         // Most of the text in large groups (one repeat all through, or of
         // long period): DC3's levels shrink it faster than sorts of all of it.
-        if (round == kMaxRounds || h.word[kWordTied] > x.n / 2) return LOR_OK;
+        if (h.word[kWordTied] > x.n / 2) return LOR_OK;
+        // Words with many copies lose few of their members to a round of a few
+        // symbols; doubling is for them, whose ranks of all suffixes cost as much as a
+        // round over one suffix in 64 of the text.
+        if (round == kMaxRounds || (round > 0 && h.word[kWordTied] > std::max(cur / 2, x.n / 64))) {
+            pool.total = h.word[kWordTied];
+            break;
+        }
+        if (!spend.take(h.word[kWordTied])) return LOR_OK;
         const uint32_t total = h.word[kWordTied], groups = h.word[kWordHeads];
         if (total > cur || groups > total || groups == 0) {
             set_error("internal: %u suffixes in %u large groups of %u", total, groups, cur);
@@ -1562,6 +1815,7 @@ lor_status prefix_sa(X x, int bits, uint32_t near, int32_t *sa, Arena &ar, uint3
                                           const_cast<uint32_t *>(ng.off)));
         }
         gk = ng;
+        pool.share += gk.ns;
         LOR_LAUNCH("k_group_keys", 20.0 * total, s,
                    hipLaunchKernelGGL(k_group_keys<X>, dim3(div_up(total, kBlock)), dim3(kBlock), 0, s, x, gk, k0, v0,
                                       total, hdr, budget));
@@ -1585,10 +1839,39 @@ lor_status prefix_sa(X x, int bits, uint32_t near, int32_t *sa, Arena &ar, uint3
                     h.word[kWordHeads], h.word[kWordTied], h.word[kWordAbort] ? ", given up" : "");
     }
     if (h.word[kWordAbort]) return LOR_OK;
+    if (pool.total) {   // after a round: of its sorted groups, the large ones
+        pool.groups = h.word[kWordHeads];
+        if (pool.total > cur || pool.groups == 0 || pool.groups > pool.total / 2) {
+            set_error("internal: %u suffixes in %u large groups of %u", pool.total, pool.groups, cur);
+            return LOR_EINVAL;
+        }
+        if (!spend.worth(pool.total, (uint64_t)(cur - pool.total) * pool.share / gk.ns)) return LOR_OK;
+        // the pool goes where ka and va were, below all that it is collected from
+        if (18ull * pool.total + 1024u > 8ull * m) return LOR_OK;
+        ar.release(mark_open);
+        pool.keys = ar.take<uint64_t>(pool.total);
+        pool.vals = ar.take<uint32_t>(pool.total);
+        pool.slots = ar.take<uint32_t>(pool.total);
+        pool.first = ar.take<uint32_t>(pool.total / 2 + 1);
+        if (ar.overflow) return LOR_OK;
+        const uint32_t ct = div_up(cur, tile_of(cur));
+        LOR_TRY(scan_exclusive(tcount, ct, stmp, nullptr, s));
+        LOR_TRY(scan_exclusive(hcount, ct, stmp, nullptr, s));
+        auto *collect = cur <= kResSmall ? k_group_collect<uint64_t, kResItemsSmall> : k_group_collect<uint64_t, kResItems>;
+        LOR_LAUNCH("k_group_collect", 8.0 * cur + 24.0 * pool.total, s,
+                   hipLaunchKernelGGL(collect, dim3(ct), dim3(kBlock), 0, s, gk, x.K, k64, v64, cur, large, tcount,
+                                      hcount, places, near, slots, pool.total, pool.groups, pool.keys, pool.vals,
+                                      pool.slots, pool.first));
+        LOR_LAUNCH("k_pool_start", 20.0 * pool.total, s,
+                   hipLaunchKernelGGL(k_pool_start, dim3(div_up(pool.total, kBlock)), dim3(kBlock), 0, s, pool.keys,
+                                      pool.vals, pool.slots, pool.total, x.n, sa, pool.first));
+        LOR_TRY(zero_words(hdr + kWordTied, 2, s));
+        return settle_runs(x, h.word[kWordOpen], 0u, pool, open, sa, ar, hdr, budget, spend, s, done);
+    }
     const uint32_t left = h.word[identity ? kWordRound : kWordOpen];
     if (left > 0) {
         ar.release(mark_open);
-        return settle_runs(x, left, identity ? kDeep : 0u, open, sa, ar, hdr, budget, s, done);
+        return settle_runs(x, left, identity ? kDeep : 0u, pool, open, sa, ar, hdr, budget, spend, s, done);
     }
     *done = true;
     return LOR_OK;
