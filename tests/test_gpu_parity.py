@@ -536,3 +536,28 @@ def test_kernel_timing_registry_and_filter():
         lor.lor_timing_enable(False)
         lor.lor_timing_only(None)
         lor.lor_timing_reset()
+
+
+@pytest.mark.parametrize("nq", [1, 63, 4097, (1 << 16) - 1, 1 << 16, (1 << 18) - 1, 1 << 18, (1 << 20) - 3, (1 << 20) + 5])
+@pytest.mark.parametrize("want_argmin", [True, False])
+def test_rmq_compact_range_lengths(nq, want_argmin):
+    """Compact table: ranges of 1 to 34 entries (up to 32 are read by one lane, the rest by
+    16 lanes), of up to 200 and of any length, mixed in every wave with empty ones, for
+    each number of queries per wave; suffix pairs likewise. Equal to the full table's."""
+    say("rmq compact lengths", nq)
+    rng = np.random.default_rng(nq)
+    n = 300_011
+    lcp = dev(rng.integers(0, 30, size=n).astype(np.int32))
+    isa = dev(rng.permutation(n).astype(np.int32))
+    full, comp = lor.lor_rmq_build(lcp), lor.lor_rmq_compact_build(lcp)
+    kind = rng.integers(0, 4, size=nq)
+    span = np.select([kind == 0, kind == 1, kind == 2], [rng.integers(0, 34, size=nq), rng.integers(0, 200, size=nq),
+                                                         rng.integers(0, n, size=nq)], -1)
+    lo = rng.integers(0, n, size=nq)
+    lo[:2], span[:2] = [n - 1, 0][:nq], [0, 32][:nq]
+    hi = np.minimum(n - 1, lo + span)
+    for mode in (0, 1):
+        a, b = dev(lo.astype(np.int32)), dev(hi.astype(np.int32))
+        mc, ac = lor.lor_rmq_query(comp, lcp, isa, mode, a, b, want_argmin=want_argmin)
+        mf, af = lor.lor_rmq_query(full, lcp, isa, mode, a, b, want_argmin=want_argmin)
+        assert torch.equal(mc, mf) and (not want_argmin or torch.equal(ac, af)), mode
