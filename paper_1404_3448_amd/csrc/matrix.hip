@@ -463,7 +463,7 @@ __global__ __launch_bounds__(kBlock) void k_mx_init(uint32_t count, unsigned lon
 // ------------------------------------------------------------- dropping ranks
 
 constexpr uint32_t kMxSample = 8;                  // k_mx_bound looks at every 8th tile
-constexpr uint32_t kMxPairsLds = 128;              // largest k whose pair table fits LDS (64 KB)
+constexpr uint32_t kMxPairsLds = 128;              // largest k whose pair table is kept in LDS: 64 KB and the starts
 
 // bound[a * k + b], a < b: a length that sequences a and b share.
 template <bool LDS>
@@ -629,10 +629,10 @@ lor_status mx_drop(const MxLayout &L, uint32_t k, const int32_t **sa, const int3
     uint32_t *words = L.bound + pairs;
     LOR_TRY(zero_words(L.bound, pairs + 2, s));
     const dim3 grid(div_up(tiles, kMxSample));
-    if (k <= kMxPairsLds)
+    const size_t table = pairs * sizeof(uint32_t);
+    if (k <= kMxPairsLds && table + (kMaxSeqs + 1) * sizeof(int32_t) <= max_lds_per_block())
         LOR_LAUNCH("k_mx_bound", 8.0 * *n / kMxSample, s,
-                   hipLaunchKernelGGL(k_mx_bound<true>, grid, dim3(kBlock), pairs * sizeof(uint32_t), s, *sa, *lcp, *n,
-                                      L.start, k, L.bound));
+                   hipLaunchKernelGGL(k_mx_bound<true>, grid, dim3(kBlock), table, s, *sa, *lcp, *n, L.start, k, L.bound));
     else
         LOR_LAUNCH("k_mx_bound", 8.0 * *n / kMxSample, s,
                    hipLaunchKernelGGL(k_mx_bound<false>, grid, dim3(kBlock), 0, s, *sa, *lcp, *n, L.start, k, L.bound));

@@ -234,3 +234,46 @@ def test_matrix_where_ranks_can_be_dropped(kind):
             back = M[b][a]
             assert np.array_equal(seqs[b][back[2]:back[2] + L], seqs[a][back[4]:back[4] + L]), (a, b)
     assert max(r[0] for row in M for r in row) == single[0]
+
+
+@pytest.mark.parametrize("k,n", [(127, 97_000), (128, 97_000), (129, 98_000), (251, 191_000)])
+def test_matrix_ranks_dropped_for_many_sequences(k, n):
+    """Sequence counts on both sides of where the table of pairs moves from LDS to global
+    memory, and the most of them, at sizes where ranks are dropped: all share one
+    segment of 90 bases, some pairs longer ones.
+    Sampled pairs equal the plain pair path's."""
+    say("matrix drop, many sequences", k)
+    rng = np.random.default_rng(k)
+    seqs = [synth.uniform_bases(rng, n + j) for j in range(k)]
+    common = synth.uniform_bases(rng, 90)
+    for q in seqs:
+        at = int(rng.integers(0, n - 90))
+        q[at:at + 90] = common
+    planted = []
+    for _ in range(25):
+        a, b = (int(x) for x in rng.choice(k, 2, replace=False))
+        m = int(rng.integers(100, 3000))
+        seqs[a][-m:] = seqs[b][:m]
+        planted.append((min(a, b), max(a, b)))
+    d = torch.from_numpy(np.concatenate(seqs)).cuda()
+    offs = np.concatenate([[0], np.cumsum([s.size for s in seqs])]).astype(np.int64)
+    r = lor.longest_overlap_region(d, offs)
+    try:
+        lor.lor_timing_reset()
+        lor.lor_timing_enable(True)
+        recs = lor.records_to_tuples(lor.lor_overlap_matrix(r["sa"], r["lcp"], offs))
+        torch.cuda.synchronize()
+        kernels = set(lor.lor_timing_read())
+    finally:
+        lor.lor_timing_enable(False)
+        lor.lor_timing_reset()
+    assert {"k_mx_bound", "k_mx_keep"} <= kernels, kernels
+    pairs = planted + [tuple(sorted(int(x) for x in rng.choice(k, 2, replace=False))) for _ in range(15)]
+    for a, b in pairs + [(0, 1), (0, k - 1), (k - 2, k - 1)]:
+        cat = np.concatenate([seqs[a], seqs[b]])
+        o = np.array([0, seqs[a].size, cat.size], np.int64)
+        L, sp, op, sq, oq = lor.longest_overlap_region(torch.from_numpy(cat).cuda(), o)["overlap"]
+        rec, back = recs[a * k + b], recs[b * k + a]
+        assert rec[:4] == (L, a, op, b) and back[0] == L and (back[1], back[3]) == (b, a), (a, b, rec, back, L, op)
+        assert np.array_equal(seqs[a][op:op + L], seqs[b][rec[4]:rec[4] + L]), (a, b)
+        assert np.array_equal(seqs[b][back[2]:back[2] + L], seqs[a][back[4]:back[4] + L]), (a, b)
