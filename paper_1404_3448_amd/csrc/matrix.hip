@@ -583,9 +583,15 @@ __global__ __launch_bounds__(kBlock) void k_mx_keep(const int32_t *__restrict__ 
     }
 }
 
-// Dropping pays from here (n x k): its passes and its read-back take about
-// 150 us, the walks 3.3 ps per rank and target.
-constexpr uint64_t kMxDropWork = 100'000'000;
+// Dropping pays from here (n x k): its passes and its read-back take about 70 us, the
+// walks 3.3 ps per rank and target. Two sequences of n / k bases share some 2 log4(n / k)
+// symbols, so where n is few times k * k a match that every pair has is one that most
+// ranks reach as well: 100 x 20,000 bases 1.69 ms without and 1.77 with, 100 x 52,000 3.04
+// and 3.28, 100 x 60,000 (n = 600 k * k) 3.17 and 1.02, 40 x 70,000 0.67 and 0.43. Where
+// most ranks stay for another reason the passes are lost (40 sequences that differ in one
+// base in 1,000: 0.68 and 0.75 ms).
+constexpr uint64_t kMxDropWork = 100'000'000, kMxDropRanks = 576;
+bool mx_may_drop(uint64_t n, uint32_t k) { return k > 1 && n * k >= kMxDropWork && n >= kMxDropRanks * k * k; }
 constexpr uint32_t kMxDropShare = 4;               // and when at most 1/4 of the ranks stay
 
 struct MxLayout {
@@ -610,7 +616,7 @@ lor_status mx_carve(Arena &ar, uint64_t n, uint32_t k, MxLayout *L) {
     LOR_TAKE(ar, Up, k, L->su);
     LOR_TAKE(ar, Dn, k, L->sd);
     L->bound = nullptr;
-    if (n * k >= kMxDropWork && k > 1) {
+    if (mx_may_drop(n, k)) {
         LOR_TAKE(ar, uint32_t, (size_t)k * k + 2, L->bound);   // then: least bound, kept ranks
         LOR_TAKE(ar, uint64_t, (size_t)tiles * (kMxTile / 64), L->kept);
         LOR_TAKE(ar, uint32_t, tiles, L->count);

@@ -277,3 +277,29 @@ def test_matrix_ranks_dropped_for_many_sequences(k, n):
         assert rec[:4] == (L, a, op, b) and back[0] == L and (back[1], back[3]) == (b, a), (a, b, rec, back, L, op)
         assert np.array_equal(seqs[a][op:op + L], seqs[b][rec[4]:rec[4] + L]), (a, b)
         assert np.array_equal(seqs[b][back[2]:back[2] + L], seqs[a][back[4]:back[4] + L]), (a, b)
+
+
+def test_matrix_of_many_short_sequences_drops_nothing():
+    """100 sequences of 11,000 bases: n x k is above 10^8, but a match that every pair has
+    is one that most ranks reach, so none of the passes that drop ranks are launched."""
+    say("matrix, many short sequences")
+    rng = np.random.default_rng(111)
+    k = 100
+    seqs = [synth.uniform_bases(rng, 11_000 + j) for j in range(k)]
+    d = torch.from_numpy(np.concatenate(seqs)).cuda()
+    offs = np.concatenate([[0], np.cumsum([s.size for s in seqs])]).astype(np.int64)
+    r = lor.longest_overlap_region(d, offs)
+    try:
+        lor.lor_timing_reset()
+        lor.lor_timing_enable(True)
+        recs = lor.records_to_tuples(lor.lor_overlap_matrix(r["sa"], r["lcp"], offs))
+        torch.cuda.synchronize()
+        kernels = set(lor.lor_timing_read())
+    finally:
+        lor.lor_timing_enable(False)
+        lor.lor_timing_reset()
+    assert "k_mx_ranks" in kernels and not {"k_mx_bound", "k_mx_count"} & kernels, kernels
+    for a, b in ((0, 1), (3, 77), (98, 99)):
+        o = np.array([0, seqs[a].size, seqs[a].size + seqs[b].size], np.int64)
+        L, sp, op, sq, oq = lor.longest_overlap_region(torch.from_numpy(np.concatenate([seqs[a], seqs[b]])).cuda(), o)["overlap"]
+        assert recs[a * k + b][:4] == (L, a, op, b) and recs[b * k + a][0] == L
