@@ -201,7 +201,8 @@ lor_status lor_rmq_query(const lor_rmq *rmq, const int32_t *lcp, const int32_t *
  * sa, lcp: device int32[n] of the joined text built from `offsets`
  * (host int64[num_seqs+1], as in lor_build_sa). Result on the host.
  * length == 0 reports -1 for the sequences and offsets.
- * ws: at least lor_longest_overlap_workspace(n, num_seqs) bytes.
+ * ws: lor_longest_overlap_workspace(n, num_seqs) bytes, which grows with n; with less
+ * the scan takes longer, and below about n / 1,365 + 2 KB bytes it returns LOR_EWORKSPACE.
  * Synchronises hip_stream. */
 typedef struct {
     int64_t length;
@@ -256,7 +257,9 @@ lor_status lor_longest_overlap_batched_state(const uint8_t *seqs, const int64_t 
  * matrix is the length lor_longest_overlap reports.
  * sa, lcp: device int32[n]; offsets: host int64[num_seqs + 1] as in
  * lor_build_sa (n must equal offsets[num_seqs] + num_seqs); out_device:
- * device lor_overlap[num_seqs * num_seqs]. Synchronises hip_stream. */
+ * device lor_overlap[num_seqs * num_seqs]. ws: lor_overlap_matrix_workspace(n, num_seqs)
+ * bytes; with less the call may take longer, and below about n * num_seqs / 250 bytes it
+ * returns LOR_EWORKSPACE. Synchronises hip_stream. */
 size_t lor_overlap_matrix_workspace(int64_t n, int32_t num_seqs);
 lor_status lor_overlap_matrix(const int32_t *sa, const int32_t *lcp, int64_t n, const int64_t *offsets,
                               int32_t num_seqs, lor_overlap *out_device, void *ws, size_t ws_bytes,

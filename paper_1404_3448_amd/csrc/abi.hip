@@ -506,7 +506,7 @@ lor_status lor_longest_overlap(const int32_t *sa, const int32_t *lcp, int64_t n,
         set_error("overlap: NULL array/result or n != joined length of offsets");
         return LOR_EINVAL;
     }
-    LOR_TRY(check_ws(ws, ws_bytes, lor_longest_overlap_workspace(n, num_seqs)));
+    LOR_TRY(check_ws(ws, ws_bytes, kHeaderBytes + 512 + overlap_workspace_least((uint64_t)n)));
     SeqStarts st;
     st.k = num_seqs;
     for (int j = 0; j <= num_seqs; ++j) st.start[j] = (int32_t)(offsets[j] + j);
@@ -808,7 +808,7 @@ lor_status lor_overlap_matrix(const int32_t *sa, const int32_t *lcp, int64_t n, 
         set_error("NULL out_device");
         return LOR_EINVAL;
     }
-    LOR_TRY(check_ws(ws, ws_bytes, lor_overlap_matrix_workspace(n, num_seqs)));
+    LOR_TRY(check_ws(ws, ws_bytes, matrix_workspace_least((uint64_t)n, (uint32_t)num_seqs)));
     return overlap_matrix(sa, lcp, (uint32_t)n, offsets, (uint32_t)num_seqs, out_device, ws, ws_bytes,
                           (hipStream_t)hip_stream);
 }

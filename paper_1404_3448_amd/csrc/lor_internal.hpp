@@ -59,6 +59,10 @@ struct Arena {
         if (top > high) high = top;
         return base ? reinterpret_cast<T *>(base + a) : reinterpret_cast<T *>(uintptr_t(256));
     }
+    size_t room() const {   // bytes that one take() can still have
+        const size_t a = (top + 255) & ~size_t(255);
+        return a < cap ? cap - a : 0;
+    }
     size_t mark() const { return top; }
     void release(size_t m) { top = m; }
     bool measuring() const { return base == nullptr; }
@@ -284,7 +288,8 @@ struct SeqStarts {           // joined start of every sequence, plus N
     int32_t start[kMaxSeqs + 1];
     int32_t k;
 };
-size_t overlap_workspace(uint64_t n);
+size_t overlap_workspace(uint64_t n);         // what the scan uses at best
+size_t overlap_workspace_least(uint64_t n);   // and what it can do with
 
 // ------------------------------------------------------------ batched
 constexpr uint32_t kMaxPairs = 8191;   // tags 0..8190: 8 * tag + 6 fits 16 bits
@@ -307,7 +312,8 @@ size_t refq_workspace(uint64_t total_bases, uint32_t num_queries);
 lor_status refq_overlap(const uint8_t *seqs, const int64_t *offsets, uint32_t num_queries, lor_overlap *out,
                         void *ws, size_t ws_bytes, hipStream_t s);
 // All-pairs matrix over an existing SA/LCP of the joined text of k sequences.
-size_t matrix_workspace(uint64_t n, uint32_t k);
+size_t matrix_workspace(uint64_t n, uint32_t k);         // what it uses at best
+size_t matrix_workspace_least(uint64_t n, uint32_t k);   // and what it can do with
 lor_status overlap_matrix(const int32_t *sa, const int32_t *lcp, uint32_t n, const int64_t *offsets, uint32_t k,
                           lor_overlap *out, void *ws, size_t ws_bytes, hipStream_t s);
 

@@ -599,7 +599,7 @@ struct MxLayout {
     unsigned long long *best;
     Up *tu, *cu, *su;
     Dn *td, *cd, *sd;
-    uint32_t *bound, *count, *stmp;   // dropping ranks (null when it cannot pay)
+    uint32_t *bound, *count, *stmp;   // dropping ranks (null: not tried)
     uint64_t *kept;
     int32_t *sa, *lcp;
 };
@@ -616,16 +616,26 @@ lor_status mx_carve(Arena &ar, uint64_t n, uint32_t k, MxLayout *L) {
     LOR_TAKE(ar, Up, k, L->su);
     LOR_TAKE(ar, Dn, k, L->sd);
     L->bound = nullptr;
-    if (mx_may_drop(n, k)) {
-        LOR_TAKE(ar, uint32_t, (size_t)k * k + 2, L->bound);   // then: least bound, kept ranks
-        LOR_TAKE(ar, uint64_t, (size_t)tiles * (kMxTile / 64), L->kept);
-        LOR_TAKE(ar, uint32_t, tiles, L->count);
-        LOR_TAKE(ar, uint32_t, kScanTmpWords, L->stmp);
-        LOR_TAKE(ar, int32_t, n / kMxDropShare, L->sa);
-        LOR_TAKE(ar, int32_t, n / kMxDropShare, L->lcp);
-    }
     if (chunks > kMxChunk) return LOR_EINVAL;   // n < 2^31 keeps chunks <= 512
     return LOR_OK;
+}
+
+// What dropping ranks needs on top; without it where the workspace does not hold that.
+void mx_carve_drop(Arena &ar, uint64_t n, uint32_t k, MxLayout *L) {
+    if (!mx_may_drop(n, k)) return;
+    const uint32_t tiles = div_up(n, kMxTile);
+    const size_t mark = ar.mark();
+    L->bound = ar.take<uint32_t>((size_t)k * k + 2);   // then: least bound, kept ranks
+    L->kept = ar.take<uint64_t>((size_t)tiles * (kMxTile / 64));
+    L->count = ar.take<uint32_t>(tiles);
+    L->stmp = ar.take<uint32_t>(kScanTmpWords);
+    L->sa = ar.take<int32_t>(n / kMxDropShare);
+    L->lcp = ar.take<int32_t>(n / kMxDropShare);
+    if (ar.overflow) {
+        ar.release(mark);
+        ar.overflow = false;
+        L->bound = nullptr;
+    }
 }
 
 // Replaces (sa, lcp, n) by the ranks that can hold a record, when they are few.
@@ -662,11 +672,20 @@ lor_status mx_drop(const MxLayout &L, uint32_t k, const int32_t **sa, const int3
 
 }  // namespace
 
+size_t matrix_workspace_least(uint64_t n, uint32_t k) {
+    Arena ar;   // measuring
+    ar.top = kHeaderBytes;
+    MxLayout L;
+    if (mx_carve(ar, n, k, &L) != LOR_OK) return 0;
+    return ar.top + 1024;
+}
+
 size_t matrix_workspace(uint64_t n, uint32_t k) {
     Arena ar;   // measuring
     ar.top = kHeaderBytes;
     MxLayout L;
     if (mx_carve(ar, n, k, &L) != LOR_OK) return 0;
+    mx_carve_drop(ar, n, k, &L);
     return ar.top + 1024;
 }
 
@@ -684,6 +703,7 @@ lor_status overlap_matrix(const int32_t *sa, const int32_t *lcp, uint32_t n, con
     ar.top = kHeaderBytes;
     MxLayout L;
     LOR_TRY(mx_carve(ar, n, k, &L));
+    mx_carve_drop(ar, n, k, &L);
     LOR_HIP(hipMemcpyAsync(L.start, h_start.data(), (k + 1) * sizeof(int32_t), hipMemcpyHostToDevice, s));
     LOR_LAUNCH("k_mx_init", 40.0 * k * k, s,
                hipLaunchKernelGGL(k_mx_init, dim3(grid_for((uint64_t)k * k)), dim3(kBlock), 0, s, k * k, L.best, out));

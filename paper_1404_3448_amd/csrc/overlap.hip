@@ -18,6 +18,7 @@
 //   in order inside a workgroup, then one workgroup over all workgroup
 //   results. A tile where no LCP reaches L holds only one-suffix runs; its
 //   summary needs the last suffix alone, so such tiles read only LCP.
+#include <algorithm>
 #include <climits>
 
 #include "lor_internal.hpp"
@@ -37,7 +38,6 @@ uint32_t group_tiles(uint64_t n) {
     const uint64_t t = (n + kTileRanks - 1) / kTileRanks / kMinGroups;
     return t < 1 ? 1u : t > kTilesPerGroup ? kTilesPerGroup : (uint32_t)t;
 }
-uint32_t group_count(uint64_t n) { return div_up(n, (uint64_t)kTileRanks * group_tiles(n)); }
 
 struct RunSum {
     int32_t m1, s1, m2, s2;
@@ -46,6 +46,9 @@ struct ChunkSum {
     RunSum head, tail;
     int32_t has_b, bp, bq, pad;
 };
+
+uint32_t group_count(uint64_t n, uint32_t per) { return div_up(n, (uint64_t)kTileRanks * per); }
+size_t sum_bytes(uint64_t groups) { return ((size_t)groups + 1) * sizeof(ChunkSum); }
 
 __device__ __forceinline__ RunSum run_empty() { return RunSum{INT_MAX, -1, INT_MAX, -1}; }
 
@@ -310,15 +313,21 @@ __global__ __launch_bounds__(kBlock) void k_runs_final(const ChunkSum *__restric
 
 }  // namespace
 
+// At most 2 kMinGroups workgroups until every one takes kTilesPerGroup tiles; grows with n,
+// as a workspace that is kept for texts of up to some size expects.
 size_t overlap_workspace(uint64_t n) {
-    return ((size_t)group_count(n) + 1) * sizeof(ChunkSum) + 1024;
+    const uint64_t one = std::min<uint64_t>(group_count(n, 1), 2ull * kMinGroups);
+    return sum_bytes(std::max<uint64_t>(one, group_count(n, kTilesPerGroup))) + 1024;
 }
+size_t overlap_workspace_least(uint64_t n) { return sum_bytes(group_count(n, kTilesPerGroup)) + 1024; }
 
 lor_status overlap_scan(const int32_t *sa, const int32_t *lcp, uint32_t n, const SeqStarts &st, Arena &ar,
                         hipStream_t s, int64_t result[5]) {
     uint32_t *words;
     LOR_TAKE(ar, uint32_t, 64, words);
-    const uint32_t groups = group_count(n);
+    uint32_t per = group_tiles(n);   // fewer workgroups where the workspace holds no more summaries
+    while (per < kTilesPerGroup && sum_bytes(group_count(n, per)) > ar.room()) per = std::min(2 * per, kTilesPerGroup);
+    const uint32_t groups = group_count(n, per);
     ChunkSum *sums;
     LOR_TAKE(ar, ChunkSum, (size_t)groups + 1, sums);
     for (int x = 0; x < 5; ++x) result[x] = -1;
@@ -330,7 +339,7 @@ lor_status overlap_scan(const int32_t *sa, const int32_t *lcp, uint32_t n, const
                                   n, st, words));
     const bool finish = groups <= kFinishGroups;
     LOR_LAUNCH("k_runs", (double)n * 4, s,
-               hipLaunchKernelGGL(k_runs, dim3(groups), dim3(kBlock), 0, s, sa, lcp, n, st, group_tiles(n), words, sums,
+               hipLaunchKernelGGL(k_runs, dim3(groups), dim3(kBlock), 0, s, sa, lcp, n, st, per, words, sums,
                                   finish ? words + 3 : nullptr, words + 1));
     if (!finish)
         LOR_LAUNCH("k_runs_final", (double)groups * sizeof(ChunkSum), s,

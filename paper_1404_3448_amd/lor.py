@@ -181,6 +181,13 @@ def _workspace(nbytes: int, device, ws=None):
     return torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
 
 
+def _check_scratch(fn: str, status: int, ws):
+    """_check for calls that can do with less than their size query gives."""
+    if status == LOR_EWORKSPACE:
+        raise ValueError(f"workspace holds {ws.numel() * ws.element_size()} bytes: {lib().lor_last_error().decode()}")
+    _check(fn, status)
+
+
 def _need(t, dtype, n, name):
     import torch
     if t.dtype != dtype or not t.is_cuda or not t.is_contiguous() or t.numel() < n:
@@ -393,12 +400,12 @@ def lor_longest_overlap(sa, lcp, offsets, ws=None, stream=None) -> tuple:
     o = _offsets(offsets)
     k = o.size - 1
     n = int(o[-1]) + k
-    nbytes = lor_longest_overlap_workspace(n, k)
-    ws = _workspace(nbytes, sa.device, ws)
+    if ws is None:
+        ws = _workspace(lor_longest_overlap_workspace(n, k), sa.device)
     out = lor_overlap()
     st = lib().lor_longest_overlap(_ptr(sa), _ptr(lcp), n, o.ctypes.data_as(ctypes.c_void_p), k, ctypes.byref(out),
                                    _ptr(ws), ws.numel() * ws.element_size(), _stream(stream))
-    _check("lor_longest_overlap", st)
+    _check_scratch("lor_longest_overlap", st, ws)
     return (int(out.length), int(out.seq_p), int(out.off_p), int(out.seq_q), int(out.off_q))
 
 
@@ -512,10 +519,11 @@ def lor_overlap_matrix(sa, lcp, offsets, out=None, ws=None, stream=None):
     _need(lcp, torch.int32, n, "lcp")
     if out is None:
         out = torch.empty(k * k * ctypes.sizeof(lor_overlap), dtype=torch.uint8, device=sa.device)
-    ws = _workspace(lor_overlap_matrix_workspace(n, k), sa.device, ws)
+    if ws is None:
+        ws = _workspace(lor_overlap_matrix_workspace(n, k), sa.device)
     st = lib().lor_overlap_matrix(_ptr(sa), _ptr(lcp), n, o.ctypes.data_as(ctypes.c_void_p), k, _ptr(out), _ptr(ws),
                                   ws.numel() * ws.element_size(), _stream(stream))
-    _check("lor_overlap_matrix", st)
+    _check_scratch("lor_overlap_matrix", st, ws)
     return out
 
 

@@ -219,3 +219,10 @@ def test_lor_check_argument_errors(L):
     assert L.lor_check(None, None) == lor.LOR_EINVAL
     assert L.lor_check(ctypes.c_void_p((1 << 20) + 8), None) == lor.LOR_EINVAL
     assert L.lor_status_string(lor.LOR_ESTALE).startswith(b"stale")
+
+
+def test_overlap_workspace_grows_with_the_text():
+    """A workspace sized for one text serves every smaller one."""
+    sizes = sorted([*range(1, 40_000_000, 65_521), *range(16_700_000, 16_900_000, 1021), 1 << 30, (1 << 31) - 1])
+    need = [lor.lor_longest_overlap_workspace(n, 2) for n in sizes]
+    assert all(a <= b for a, b in zip(need, need[1:]))
