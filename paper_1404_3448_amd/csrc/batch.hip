@@ -567,7 +567,6 @@ lor_status batch_overlap(const uint8_t *seqs, const int64_t *offsets, uint32_t P
     std::vector<int32_t> h_start(P + 1), h_alen(P);
     std::vector<int64_t> h_src(2 * (size_t)P);
     const uint64_t N = batch_tables(offsets, P, h_start.data(), h_alen.data(), h_src.data());
-    // DC3 reads back one word per level, which also orders the host copies
     LOR_TRY(batch_overlap_run(seqs, P, N, h_start.data(), h_alen.data(), h_src.data(), out, ws, ws_bytes, s, lcp_out,
                               isa_out));
     LOR_HIP(hipStreamSynchronize(s));   // the host tables must outlive their copies

@@ -1935,6 +1935,9 @@ lor_status prefix_sa_tagged(const uint16_t *text, uint32_t n, uint32_t pairs, co
         LOR_HIP(hipMemcpyAsync(d_below, below.get(), pairs * sizeof(uint32_t), hipMemcpyHostToDevice, s));
         const Tagged x{text, n, K, pairs, near, start, alen, d_below, nullptr};
         st = prefix_sa(x, tag + 2 * K, near, sa, ar, hdr, s, done);
+        // a finished sort has waited for the stream; others may leave before that, with
+        // the copy from `below` still to come
+        if (!*done) (void)hipStreamSynchronize(s);
     }
     ar.release(mark);
     ar.overflow = false;
