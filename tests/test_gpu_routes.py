@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 
 import oracle
+import test_gpu_prefix as prefix
 from paper_1404_3448_amd import lor, synth
 
 pytestmark = pytest.mark.gpu
@@ -222,3 +223,56 @@ def test_doubling_is_given_up_in_time():
     assert used_dc3(k) and 1 <= k["k_pool_keys"] <= 2, k
     want, _ = lor.lor_build_sa_dc3(d, offs)
     assert torch.equal(sa, want)
+
+
+# ------------------------------------- the prefix sort's own tests take its paths
+
+def check_route(call, with_, without=()):
+    _, k = launches(call)
+    assert set(with_) <= set(k) and not set(without) & set(k), k
+    if "k_records" not in with_:
+        assert not used_dc3(k), k
+
+
+@pytest.mark.parametrize("text,with_", [("zeros", ["k_records"]), ("threes", ["k_records"]), ("pairs", ["k_records"]),
+                                        ("unit40", ["k_records"]), ("identical", ["k_double", "k_ranks"]),
+                                        ("close", ["k_double", "k_ranks"]), ("copies", ["k_double", "k_group_keys"]),
+                                        ("related", ["k_settle"])])
+def test_route_of_repetitive_texts(text, with_):
+    check_route(lambda: prefix.test_repetitive_texts(text), with_)
+
+
+@pytest.mark.parametrize("copies", [2, 31, 62, 63, 64, 65, 66, 130])
+def test_route_of_group_sizes(copies):
+    check_route(lambda: prefix.test_group_sizes(copies), ["k_settle"] if copies <= 64 else ["k_group_keys", *POOL])
+
+
+def test_route_of_doubling_above_the_plain_store_limit():
+    check_route(prefix.test_doubling_above_the_plain_store_limit, ["k_open_list", "k_double", "k_scatter_window"],
+                ["k_ranks"])
+
+
+@pytest.mark.parametrize("n", [(1 << 21) - 1, 1 << 21, (1 << 21) + 1])
+@pytest.mark.parametrize("copies", ["none", "one", "few", "many"])
+def test_route_of_open_runs(n, copies):
+    listed, doubled = n > 1 << 21, copies in ("few", "many")
+    check_route(lambda: prefix.test_open_runs_by_slot_and_by_list(n, copies),
+                ["k_settle"] + ["k_open_list"] * listed + ["k_double", "k_run_ranks"] * doubled,
+                ["k_open_list"] * (not listed) + ["k_double"] * (not doubled))
+
+
+@pytest.mark.parametrize("k", [1, 3])
+def test_route_of_repeats_at_every_phase(k):
+    check_route(lambda: prefix.test_repeats_at_every_phase(1_000_000, k), ["k_group_keys", "k_double"])
+
+
+@pytest.mark.parametrize("pairs", [1, 2, 40, 300])
+def test_route_of_batched_state(pairs):
+    check_route(lambda: prefix.test_batched_state(pairs), ["k_resolve", "k_settle"])
+
+
+@pytest.mark.parametrize("n,seqs", [((1 << 21) - 1, 2), (1 << 21, 2), ((1 << 21) + 1, 251)])
+def test_route_of_packed_lcp(n, seqs):
+    packed = n >= 1 << 21
+    check_route(lambda: prefix.test_lcp_of_packed_text(n, seqs), ["k_lcp_packed" if packed else "k_lcp_window"],
+                ["k_lcp_window" if packed else "k_lcp_packed"])
