@@ -4,7 +4,8 @@
  *
  * The library builds the suffix array (SA) of a separator-joined DNA text by
  * sorting its suffixes' first symbols, or with DC3 (Section III, Steps 1-3)
- * where the text is one repeat for the most part; the array is the same. It
+ * where the text is one repeat for the most part or long words have so many
+ * copies that DC3 is the cheaper way; the array is the same. It
  * builds the text's LCP array (Section III, Table IV), a range minimum
  * structure over the LCP (Section III, RMQ), and scans the LCP for the longest
  * region shared by two different sequences (Section III, problem statement).

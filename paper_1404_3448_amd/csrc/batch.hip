@@ -382,7 +382,8 @@ __global__ __launch_bounds__(kBlock) void k_seg_runs(const int32_t *__restrict__
     }
     for (uint32_t t = t0; t < t1; ++t) {
         if (!s_any[t - t0]) continue;   // uniform: s_any is final after the barrier above
-        // rare (tiles inside a run of its pair's length): each thread reads its ranks directly
+        // each thread reads its ranks directly (the tandem repeats of one sequence have LCPs above
+        // their pair's length, too)
         const uint32_t base = t * kTileRanks;
         const uint32_t cnt = min(kTileRanks, n - base);
         ChunkSum c = chunk_empty();

@@ -114,7 +114,7 @@ struct Plan {
     int items_u32;      // radix items per thread, 32-bit keys: 8, 12, 16, 24
     int items_u64;      // radix items per thread, 64-bit keys: 4, 8, 12, 16
     int merge_items;    // merge outputs per thread: 4, 8, 12
-    int plcp_steps;     // PLCP positions per lane: 32..512
+    int plcp_steps;     // 16..1024: the LCP samples every 8th to 512th position (half of it, a power of two)
 };
 const Plan &plan();                 // the calling thread's plan
 bool plan_valid(const Plan &p);
@@ -232,8 +232,9 @@ size_t dc3_workspace_bound(uint64_t n);
 
 // ------------------------------------------------------- prefix sorting
 // The same suffix arrays by sorting prefixes (prefix.hip). *done stays false,
-// with sa unspecified, when the text needs DC3 (long exact repeats) or the
-// workspace left in `ar` does not suffice; header words 3..5 are used.
+// with sa unspecified, when DC3 is the better way (most of the text in one
+// repeat, or more sorts than DC3 is worth) or the workspace left in `ar` does not
+// suffice; header words 3..11 and 14 are used, and have to be 0 at first.
 lor_status prefix_sa_joined(const uint8_t *text, uint32_t n, const int64_t *offsets, uint32_t k, int32_t *sa,
                             Arena &ar, uint32_t *hdr, hipStream_t s, bool *done);
 lor_status prefix_sa_tagged(const uint16_t *text, uint32_t n, uint32_t pairs, const int32_t *start,

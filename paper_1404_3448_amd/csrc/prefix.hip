@@ -600,11 +600,7 @@ __global__ __launch_bounds__(kBlock) void k_merge_tagged(Tagged x, const uint32_
     places[rank] = at;
 }
 
-// Number of the `count` sorted entries not above x, by one lane and by a wave.
-__device__ __forceinline__ uint32_t places_not_above(const uint32_t *__restrict__ a, uint32_t count, uint32_t x) {
-    return keys_not_above(a, count, x);
-}
-
+// keys_not_above() for the `count` sorted entries of a, by a wave.
 __device__ __forceinline__ uint32_t wave_not_above(const uint32_t *__restrict__ a, uint32_t count, uint32_t x) {
     const uint32_t lane = threadIdx.x & 63u;
     uint32_t lo = 0, len = count;
@@ -882,7 +878,7 @@ __global__ __launch_bounds__(kBlock) void k_resolve(X x, GroupKey gk, const KT *
         uint32_t slot;
         if constexpr (kFirst) {
             slot = o + sh0;
-            if (sh0 != sh1) slot += places_not_above(places + sh0, sh1 - sh0, o);
+            if (sh0 != sh1) slot += keys_not_above(places + sh0, sh1 - sh0, o);
         } else {
             slot = slots[o];
         }
@@ -997,7 +993,7 @@ __global__ __launch_bounds__(kBlock) void k_group_collect(GroupKey gk, int K, co
         const uint32_t id = hat + s_hbelow[l >> 6] + (uint32_t)__popcll(heads & (bit | (bit - 1ull))) - 1u;
         if (i >= total || id >= groups) continue;   // never with consistent counts
         if constexpr (kFirst) {
-            tslots[i] = e + s_shift[0] + places_not_above(places + s_shift[0], s_shift[1] - s_shift[0], e);
+            tslots[i] = e + s_shift[0] + keys_not_above(places + s_shift[0], s_shift[1] - s_shift[0], e);
         } else {
             tslots[i] = slots[e];
             if (heads & bit) off[id] = gk.reach(key[r]) + gk.ns - (uint32_t)K;
